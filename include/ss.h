@@ -127,7 +127,10 @@ typedef struct ss_weights ss_weights; /* opaque; owns packed bf16 weights and a 
  * IEEE half: the same number for 2^-17 <= |w| <= 65504, rounded to a multiple of 2^-24 below that, saturated
  * above.  An activation that feeds a projection is rounded to IEEE half once (11 significand bits); accumulation,
  * softmax, normalisation and the residual stream are fp32; key/value cache slots are IEEE half (2 bytes per
- * element).  Everything stored as half saturates at +-65504.  Source values must be finite: they are not checked.
+ * element).  Everything stored as half saturates at +-65504.  A matrix whose values are all below 0.25 in magnitude is
+ * kept a second time in a 12-bit form of the same values, which small decode batches stream instead (three quarters of
+ * the packed bytes once more, only while all such copies take at most an eighth of the free device memory; a call that
+ * runs out of device memory gives them back and is run again without them).  Source values must be finite: they are not checked.
  * A row whose logits are all NaN or -inf yields token id 0, never an id outside the vocabulary.
  * Errors: SS_EINVAL (shape), SS_EDEVICE (no usable GPU / HIP error), SS_ENOMEM.
  */

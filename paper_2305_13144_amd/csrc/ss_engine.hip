@@ -157,6 +157,12 @@ struct ss_weights {
     std::atomic<int> busy{0};
     void* scratch_ptr = nullptr;   // device address of this device's static scratch array
     int in_flight = SS_IN_FLIGHT_DEFAULT;       // micro-batches a group pass keeps in flight (1 to kLanes)
+    bool has_narrow() const
+    {
+        for (const Layer& L : layers)
+            if (L.wqkv.pn || L.wo.pn || L.wgu.pn || L.wd.pn) return true;
+        return lm_head.pn != nullptr;
+    }
 };
 
 namespace {
@@ -217,6 +223,79 @@ int alloc_packed(ss_weights* w, PackedMat* m, int n, int k)
     if (int rc = dev_alloc(w, &p, (size_t)n * m->Kp * 2, m->Kp != k)) return rc;
     m->p = (f16_t*)p;
     return SS_OK;
+}
+
+std::vector<PackedMat*> all_matrices(ss_weights* w)
+{
+    std::vector<PackedMat*> m;
+    for (Layer& L : w->layers) m.insert(m.end(), {&L.wqkv, &L.wo, &L.wgu, &L.wd});
+    m.push_back(&w->lm_head);
+    return m;
+}
+
+void drop_narrow(ss_weights* w)
+{
+    for (PackedMat* m : all_matrices(w)) {
+        if (m->pn) (void)hipFree(m->pn);
+        m->pn = nullptr;
+    }
+}
+
+// Adds the 12-bit copies that decode batches stream (see k_narrow_weight): three quarters of the packed weights' bytes
+// once more.  Only when they take at most an eighth of the device memory that is free now, so that they do not stand in
+// the way of key/value caches (and a call that runs out of memory all the same drops them, see with_memory); a matrix
+// that has a value without a 12-bit form, or whose K is no multiple of a group, goes without.
+int make_narrow(ss_weights* w)
+{
+    const std::vector<PackedMat*> mats = all_matrices(w);
+    auto fits = [](const PackedMat* m) { return m->Kp % 128 == 0; };
+    auto groups = [](const PackedMat* m) { return (size_t)(m->N / 16) * (m->Kp / 128); };
+    size_t need = 0, free_b = 0, total_b = 0;
+    for (const PackedMat* m : mats)
+        if (fits(m)) need += groups(m) * 3072;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need == 0 || need > free_b / 8) return SS_OK;
+    struct Flags {
+        Buf b;
+        ~Flags() { b.release(); }
+    } flags;
+    if (int rc = flags.b.ensure(mats.size() * 4, true)) return rc;
+    hipStream_t s = w->lane[0].stream;
+    for (size_t i = 0; i < mats.size(); ++i) {
+        PackedMat* m = mats[i];
+        if (!fits(m)) continue;
+        if (hipMalloc(&m->pn, groups(m) * 3072) != hipSuccess) {   // no room after all: none of them
+            (void)hipGetLastError();
+            m->pn = nullptr;
+            HIPCHK(hipStreamSynchronize(s));
+            drop_narrow(w);
+            return SS_OK;
+        }
+        ss::launch_narrow_weight(m->p, m->pn, groups(m), flags.b.as<int32_t>() + i, s);
+    }
+    std::vector<int32_t> unfit(mats.size());
+    HIPCHK(hipStreamSynchronize(s));
+    HIPCHK(hipMemcpy(unfit.data(), flags.b.p, mats.size() * 4, hipMemcpyDeviceToHost));
+    for (size_t i = 0; i < mats.size(); ++i)
+        if (unfit[i] && mats[i]->pn) {
+            (void)hipFree(mats[i]->pn);
+            mats[i]->pn = nullptr;
+        }
+    return SS_OK;
+}
+
+// Runs a call's body; if it runs out of device memory while the handle holds 12-bit weight copies, gives those back
+// and runs it once more (from the start: a body writes its outputs from scratch).  Nothing else is in flight on the
+// handle: the caller holds its busy flag, and a body's lanes have ended when it returns.
+template <class F>
+int with_memory(ss_weights* w, F body)
+{
+    int rc = ss::no_throw(body);
+    if (rc != SS_ENOMEM || !w->has_narrow()) return rc;
+    for (Lane& ln : w->lane) (void)hipStreamSynchronize(ln.stream);
+    drop_narrow(w);
+    (void)hipGetLastError();
+    ss::clear_error();
+    return ss::no_throw(body);
 }
 
 int check_cfg(const ss_model_cfg* c)
@@ -321,11 +400,13 @@ Plans make_plans(const ss_weights* w, int n, int n_sel)
     return p;
 }
 
-GemmArgs gemm_args(const ss_weights* w, const f16_t* W, const f16_t* X, float* out, f16_t* outp, int N, int Kp, int rows,
-                   int kp_out, const ss::GemmPlan& p)
+GemmArgs gemm_args(const ss_weights* w, const PackedMat& W, const f16_t* X, float* out, f16_t* outp, int rows, int kp_out,
+                   const ss::GemmPlan& p)
 {
     GemmArgs g{};
-    g.W = W; g.X = X; g.out = out; g.out_packed = outp; g.N = N; g.Kp = Kp;
+    g.W = W.p; g.Wn = W.pn; g.X = X; g.out = out; g.out_packed = outp; g.N = W.N; g.Kp = W.Kp;
+    g.narrow = W.pn ? p.narrow : 0;
+    g.group4 = p.narrow;
     g.m_rows = rows; g.m_stride = rows; g.kp_out = kp_out; g.ksplit = p.ksplit; g.nb = p.nb; g.kd = p.kd;
     g.kp = p.kp; g.tms = p.tms; g.sweep_p = p.sweep_p; g.sweep_gn = p.sweep_gn; g.sweep_kh = p.sweep_kh; g.zero_blk = w->zero_blk;
     return g;
@@ -353,8 +434,9 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
     const ss::GemmPlan &p_qkv = pl.qkv, &p_o = pl.o, &p_gu = pl.gu, &p_d = pl.down, &p_lm = pl.lm;
     const int ks_qkv = p_qkv.ksplit, ks_o = p_o.ksplit, ks_d = p_d.ksplit;
     const size_t st_qkv = (size_t)n * 3 * d, st_d = (size_t)n * d;
-    auto mk = [w](const f16_t* W, const f16_t* X, float* out, f16_t* outp, int N, int Kp, int rows, int kp_out,
-                  const ss::GemmPlan& p) { return gemm_args(w, W, X, out, outp, N, Kp, rows, kp_out, p); };
+    auto mk = [w](const PackedMat& W, const f16_t* X, float* out, f16_t* outp, int rows, int kp_out, const ss::GemmPlan& p) {
+        return gemm_args(w, W, X, out, outp, rows, kp_out, p);
+    };
 
     ss::launch_embed(st, w->embed, x, d, n, s);
     for (int l = 0; l < c.n_layers; ++l) {
@@ -362,26 +444,26 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
         ss::kv_t* kc = ws.kv.as<ss::kv_t>() + (size_t)l * 2 * ln.kv_layer_stride;
         ss::kv_t* vc = kc + ln.kv_layer_stride;
         ss::launch_rmsnorm(st, x, l ? pd : nullptr, ks_d, st_d, L.attn_norm, c.rms_eps, nullptr, nullptr, h, d, n, s);
-        ss::launch_gemm(mk(L.wqkv.p, h, pqkv, nullptr, 3 * d, d, n, 0, p_qkv), ss::EPI_PARTIAL, s);
+        ss::launch_gemm(mk(L.wqkv, h, pqkv, nullptr, n, 0, p_qkv), ss::EPI_PARTIAL, s);
         if (decode) {   // one token-row per row: rotation and append are fused into the attention kernel
             ss::launch_attention_decode(st, pqkv, ks_qkv, st_qkv, kc, vc, w->rope_cos, w->rope_sin, ao, d, H, hd, n, s);
         } else {        // prompt: every key of a row must be in place before any of its queries attends
             ss::launch_rope_append(st, pqkv, ks_qkv, st_qkv, qrot, kc, vc, w->rope_cos, w->rope_sin, d, H, hd, n, s);
             ss::launch_attention_prompt(st, qrot, kc, vc, ao, d, H, hd, ln.prompt_rows, ln.prompt_max_len, s);
         }
-        ss::launch_gemm(mk(L.wo.p, ao, pd, nullptr, d, d, n, 0, p_o), ss::EPI_PARTIAL, s);
+        ss::launch_gemm(mk(L.wo, ao, pd, nullptr, n, 0, p_o), ss::EPI_PARTIAL, s);
         ss::launch_rmsnorm(st, x, pd, ks_o, st_d, L.mlp_norm, c.rms_eps, nullptr, nullptr, h, d, n, s);
         if (p_gu.ksplit == 1) {
-            ss::launch_gemm(mk(L.wgu.p, h, nullptr, act, 2 * F, d, n, Fp, p_gu), ss::EPI_SWIGLU, s);
+            ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
         } else {   // k-sliced: partial sums, then one small kernel adds them and applies SwiGLU
-            ss::launch_gemm(mk(L.wgu.p, h, ws.pgu.as<float>(), nullptr, 2 * F, d, n, 0, p_gu), ss::EPI_PARTIAL, s);
+            ss::launch_gemm(mk(L.wgu, h, ws.pgu.as<float>(), nullptr, n, 0, p_gu), ss::EPI_PARTIAL, s);
             ss::launch_swiglu_reduce(ws.pgu.as<float>(), p_gu.ksplit, (size_t)n * 2 * F, n, F, Fp, act, s);
         }
-        ss::launch_gemm(mk(L.wd.p, act, pd, nullptr, d, Fp, n, 0, p_d), ss::EPI_PARTIAL, s);
+        ss::launch_gemm(mk(L.wd, act, pd, nullptr, n, 0, p_d), ss::EPI_PARTIAL, s);
     }
     f16_t* hsel = ws.hsel.as<f16_t>();
     ss::launch_rmsnorm(st, x, pd, ks_d, st_d, w->final_norm, c.rms_eps, d_sel, d_nsel, hsel, d, n_sel, s);
-    ss::launch_gemm(mk(w->lm_head.p, hsel, ws.logits.as<float>(), nullptr, V, d, n_sel, 0, p_lm), ss::EPI_PARTIAL, s);
+    ss::launch_gemm(mk(w->lm_head, hsel, ws.logits.as<float>(), nullptr, n_sel, 0, p_lm), ss::EPI_PARTIAL, s);
     if (ln.cur_inv_temp > 0.f)
         ss::launch_sample(ws.logits.as<float>(), V, d_nsel ? d_nsel : st.d_n, st, ln.cur_draws, ln.cur_ids, ln.cur_seed,
                           ln.cur_inv_temp, n_sel, s);
@@ -703,8 +785,9 @@ int weights_create_impl(ss_weights* w, const void* const* tensors, int32_t src_d
         }
     }
     void* p = nullptr;
-    if ((rc = dev_alloc(w, &p, 1024, true))) return rc;
+    if ((rc = dev_alloc(w, &p, ss::kZeroBlkBytes, true))) return rc;
     w->zero_blk = (f16_t*)p;
+    if ((rc = make_narrow(w))) return rc;
     hipDeviceProp_t prop;
     if (hipGetDeviceProperties(&prop, w->device) != hipSuccess || prop.multiProcessorCount <= 0)
         return ss::fail(SS_EDEVICE, "cannot read the device's compute unit count");
@@ -779,6 +862,7 @@ extern "C" void ss_weights_destroy(ss_weights* w)
         for (auto& e : ln.ev)
             if (e) (void)hipEventDestroy(e);
     }
+    drop_narrow(w);
     for (void* p : w->allocs) (void)hipFree(p);
     delete w;
 }
@@ -794,7 +878,7 @@ extern "C" int ss_decode_microbatch(ss_weights* w, const int32_t* prompt_tokens,
     if (!guard.ok) return ss::fail(SS_ESTATE, "another call is in flight on this handle");
     Lane& ln = w->lane[0];
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : ln.stream;
-    return ss::no_throw([&] {
+    return with_memory(w, [&] {
         return decode_microbatch_impl(w, ln, prompt_tokens, prompt_offsets, B, max_new, target_lens, nullptr, flags,
                                       out_tokens, out_lens, out_failed, stats, s);
     });
@@ -840,7 +924,7 @@ extern "C" int ss_decode_microbatch_static(ss_weights* w, const int32_t* prompt_
     view.ws.arena = (char*)w->scratch_ptr;
     view.ws.arena_bytes = kStaticScratchBytes;
     view.in();
-    return ss::no_throw([&] {
+    return ss::no_throw([&] {   // (no with_memory: this call frees no device memory)
         return decode_microbatch_impl(w, ln, prompt_tokens, prompt_offsets, B, max_new, target_lens, nullptr, flags,
                                       out_tokens, out_lens, out_failed, stats, s);
     });
@@ -860,7 +944,7 @@ extern "C" int ss_generate_microbatch(ss_weights* w, const int32_t* prompt_token
     if (!guard.ok) return ss::fail(SS_ESTATE, "another call is in flight on this handle");
     Lane& ln = w->lane[0];
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : ln.stream;
-    return ss::no_throw([&] {
+    return with_memory(w, [&] {
         return decode_microbatch_impl(w, ln, prompt_tokens, prompt_offsets, B, max_new, nullptr, opts, flags, out_tokens,
                                       out_lens, out_failed, stats, s);
     });
@@ -955,8 +1039,8 @@ extern "C" int ss_forward_logits(ss_weights* w, const int32_t* tokens, const int
     if (!guard.ok) return ss::fail(SS_ESTATE, "another call is in flight on this handle");
     Lane& ln = w->lane[0];
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : ln.stream;
-    return ss::no_throw(
-        [&] { return forward_logits_impl(w, ln, s, tokens, offsets, B, n_prompt, all_prompt_logits, logits_out); });
+    return with_memory(
+        w, [&] { return forward_logits_impl(w, ln, s, tokens, offsets, B, n_prompt, all_prompt_logits, logits_out); });
 }
 
 namespace {
@@ -1164,7 +1248,7 @@ extern "C" int ss_run_group(ss_weights* w, const int32_t* prompt_tokens, const i
     for (int i = 0; i < n; ++i)
         if (target_lens[i] < 1 || target_lens[i] > policy->base_len)
             return ss::fail(SS_EINVAL, "target_lens[%d] outside [1, base_len]", i);
-    return ss::no_throw([&] {
+    return with_memory(w, [&] {
         return run_group_impl(w, prompt_tokens, prompt_offsets, n, target_lens, pred_lens, bin, policy, nullptr,
                               out_tokens, out_lens, stats, s);
     });
@@ -1185,7 +1269,7 @@ extern "C" int ss_run_group_generate(ss_weights* w, const int32_t* prompt_tokens
     if (!guard.ok) return ss::fail(SS_ESTATE, "another call is in flight on this handle");
     Lane& ln = w->lane[0];
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : ln.stream;
-    return ss::no_throw([&] {
+    return with_memory(w, [&] {
         return run_group_impl(w, prompt_tokens, prompt_offsets, n, nullptr, pred_lens, bin, policy, opts, out_tokens,
                               out_lens, stats, s);
     });
@@ -1264,8 +1348,8 @@ extern "C" int ss_bench_decode_step(ss_weights* w, const int32_t* prompt_tokens,
     if (!guard.ok) return ss::fail(SS_ESTATE, "another call is in flight on this handle");
     Lane& ln = w->lane[0];
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : ln.stream;
-    return ss::no_throw(
-        [&] { return bench_decode_step_lane(w, ln, s, prompt_tokens, B, ctx, iters, ms_out, nullptr, 0); });
+    return with_memory(
+        w, [&] { return bench_decode_step_lane(w, ln, s, prompt_tokens, B, ctx, iters, ms_out, nullptr, 0); });
 }
 
 extern "C" int ss_bench_decode_steps_in_flight(ss_weights* w, const int32_t* prompt_tokens, int32_t B, int32_t ctx,
@@ -1318,12 +1402,13 @@ int bench_weight_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32
     HIPCHK(hipSetDevice(w->device));
     if (int rc = ensure_workspace(w, ln, B, B, B, (size_t)B, 1, s)) return rc;
     const ss_model_cfg& c = w->cfg;
-    const int d = c.d_model, F = c.d_ffn, V = c.vocab, Fp = ss::padded_k(F), n = B;
+    const int Fp = ss::padded_k(c.d_ffn), n = B;
     Workspace& ws = ln.ws;
     const Plans pl = make_plans(w, n, n);
     const ss::GemmPlan &p_qkv = pl.qkv, &p_o = pl.o, &p_gu = pl.gu, &p_d = pl.down, &p_lm = pl.lm;
-    auto mk = [w](const f16_t* W, const f16_t* X, float* out, f16_t* outp, int N, int Kp, int rows, int kp_out,
-                  const ss::GemmPlan& p) { return gemm_args(w, W, X, out, outp, N, Kp, rows, kp_out, p); };
+    auto mk = [w](const PackedMat& W, const f16_t* X, float* out, f16_t* outp, int rows, int kp_out, const ss::GemmPlan& p) {
+        return gemm_args(w, W, X, out, outp, rows, kp_out, p);
+    };
     f16_t *h = ws.h.as<f16_t>(), *ao = ws.ao.as<f16_t>(), *act = ws.act.as<f16_t>();
     float *pqkv = ws.pqkv.as<float>(), *pd = ws.pd.as<float>();
     EventList evl;
@@ -1335,16 +1420,16 @@ int bench_weight_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32
         launches = 0;
         for (int l = 0; l < c.n_layers; ++l) {
             const Layer& L = w->layers[l];
-            ss::launch_gemm(mk(L.wqkv.p, h, pqkv, nullptr, 3 * d, d, n, 0, p_qkv), ss::EPI_PARTIAL, s);
-            ss::launch_gemm(mk(L.wo.p, ao, pd, nullptr, d, d, n, 0, p_o), ss::EPI_PARTIAL, s);
+            ss::launch_gemm(mk(L.wqkv, h, pqkv, nullptr, n, 0, p_qkv), ss::EPI_PARTIAL, s);
+            ss::launch_gemm(mk(L.wo, ao, pd, nullptr, n, 0, p_o), ss::EPI_PARTIAL, s);
             if (p_gu.ksplit == 1)
-                ss::launch_gemm(mk(L.wgu.p, h, nullptr, act, 2 * F, d, n, Fp, p_gu), ss::EPI_SWIGLU, s);
+                ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
             else
-                ss::launch_gemm(mk(L.wgu.p, h, ws.pgu.as<float>(), nullptr, 2 * F, d, n, 0, p_gu), ss::EPI_PARTIAL, s);
-            ss::launch_gemm(mk(L.wd.p, act, pd, nullptr, d, Fp, n, 0, p_d), ss::EPI_PARTIAL, s);
+                ss::launch_gemm(mk(L.wgu, h, ws.pgu.as<float>(), nullptr, n, 0, p_gu), ss::EPI_PARTIAL, s);
+            ss::launch_gemm(mk(L.wd, act, pd, nullptr, n, 0, p_d), ss::EPI_PARTIAL, s);
             launches += 4;
         }
-        ss::launch_gemm(mk(w->lm_head.p, ws.hsel.as<f16_t>(), ws.logits.as<float>(), nullptr, V, d, n, 0, p_lm),
+        ss::launch_gemm(mk(w->lm_head, ws.hsel.as<f16_t>(), ws.logits.as<float>(), nullptr, n, 0, p_lm),
                         ss::EPI_PARTIAL, s);
         launches += 1;
         HIPCHK(hipEventRecord(ev[it + 1], s));
@@ -1406,7 +1491,7 @@ extern "C" int ss_bench_weight_stream(ss_weights* w, int32_t B, int32_t iters, d
     if (!guard.ok) return ss::fail(SS_ESTATE, "another call is in flight on this handle");
     Lane& ln = w->lane[0];
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : ln.stream;
-    return ss::no_throw([&] { return bench_weight_stream_impl(w, ln, s, B, iters, ms_out, launches_out); });
+    return with_memory(w, [&] { return bench_weight_stream_impl(w, ln, s, B, iters, ms_out, launches_out); });
 }
 
 extern "C" int ss_bench_read_stream(ss_weights* w, int32_t iters, double* ms_out, int64_t* bytes_out, void* hip_stream)
@@ -1418,5 +1503,5 @@ extern "C" int ss_bench_read_stream(ss_weights* w, int32_t iters, double* ms_out
     if (!guard.ok) return ss::fail(SS_ESTATE, "another call is in flight on this handle");
     Lane& ln = w->lane[0];
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : ln.stream;
-    return ss::no_throw([&] { return bench_read_stream_impl(w, ln, s, iters, ms_out, bytes_out); });
+    return with_memory(w, [&] { return bench_read_stream_impl(w, ln, s, iters, ms_out, bytes_out); });
 }

@@ -17,6 +17,7 @@ typedef uint16_t kv_t;    // key/value cache slot: IEEE half bit pattern
 // Packed weight matrix: N output rows (multiple of 16), K inputs padded to Kp (multiple of 64).
 struct PackedMat {
     f16_t* p = nullptr;
+    void* pn = nullptr;   // the same values in the 12-bit form, or null (see k_narrow_weight)
     int N = 0, K = 0, Kp = 0;
 };
 
@@ -41,8 +42,11 @@ struct MbState {
     int32_t max_new;
 };
 
+constexpr size_t kZeroBlkBytes = 4096;   // a 12-bit group (3 KiB) or an operand block (1 KiB)
+
 struct GemmArgs {
     const f16_t* W;      // packed [N, Kp]
+    const void* Wn;      // the same matrix in the 12-bit form; read instead of W when `narrow`
     const f16_t* X;      // packed [rows, Kp] activations
     float* out;          // EPI_PARTIAL: [ksplit][m_stride][N] fp32
     f16_t* out_packed;   // EPI_SWIGLU: packed [rows, kp_out], column f = silu(gate_f) * up_f
@@ -55,12 +59,16 @@ struct GemmArgs {
     int tms;             //      row strips per tile, 4 or 8 (gemm_plan)
     int sweep_p;         // > 0: sweep kernel with this many waves per workgroup (gemm_plan)
     int sweep_gn;        //      its workgroups per k-slice
+    int group4;          // sweep and skinny kernels: k-slices are whole groups of 4 k-blocks (gemm_plan: narrow)
+    int narrow;          // sweep and skinny kernels: read Wn (the plan allows it and the matrix has one)
     int sweep_kh;        //      2: two waves per unit, each half of every chunk's k-blocks (gemm_plan)
-    const f16_t* zero_blk;   // 1 KiB of zeros: operand block read in place of weights beyond a range (sweep kernel)
+    const f16_t* zero_blk;   // kZeroBlkBytes of zeros: read in place of weights beyond a range (sweep kernel)
 };
 
 void launch_pack_weight(const void* src, int src_f32, f16_t* dst, int n_src, int k, int kp, int blk_stride,
                         int blk_off, hipStream_t s);
+// Writes the 12-bit form of n_groups groups of 4 packed k-blocks (3 KiB each); sets *unfit if a value has no such form.
+void launch_narrow_weight(const f16_t* src, void* dst, size_t n_groups, int32_t* unfit, hipStream_t s);
 void launch_cast_rows(const void* src, int src_f32, bf16_t* dst, size_t count, hipStream_t s);
 void launch_embed(const MbState& st, const bf16_t* embed, float* x, int d, int n_max, hipStream_t s);
 void launch_rmsnorm(const MbState& st, float* x, const float* part, int ksplit, size_t part_stride,

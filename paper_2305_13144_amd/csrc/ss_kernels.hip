@@ -101,6 +101,77 @@ __global__ void k_pack_weight(const void* __restrict__ src, int src_f32, f16_t* 
     }
 }
 
+// ------------------------------------------------------------------------------------------ 12-bit weights
+// A second copy of a weight matrix for the kernels that are bound by streaming it (decode batches), at 12 bits per
+// weight instead of 16 and with exactly the same values.  A packed weight is a bf16 value written as IEEE half; below
+// 0.25 in magnitude that is sign, 4 exponent bits (2^-17 .. 2^-3, code 0 = multiples of 2^-24 below) and 7 mantissa bits:
+// eight times the weight, as a half, has bit 14 and bits 2..0 clear.  The kernels multiply with eight times the weight
+// and scale their sums by 1/8, both exactly; sums of products round alike, but for the last bit of some that contain
+// weights which are subnormal as halves.  A matrix with a value of 0.25 or more (or a NaN) has no such copy and is
+// streamed as halves.
+// Layout: [strip][group of 4 k-blocks][3 planes][lane] of 16 bytes: a lane's 4 operand fragments (4 dwords each) take
+// 12 dwords, 3 per fragment, read as three fully coalesced 1 KiB loads.  Of a fragment's 4 dwords the first three are
+// stored as they are, and the 8 clear bits of each hold a third of the fourth.
+// Why: a decode step of few rows is a weight stream and its bytes are its time; the 15 vector instructions that open a
+// fragment run beside it.  Measured alone, halves / 12 bits, 16 rows, 7B: q|k|v 18.7 / 14.3 us, gate|up 31.0 / 25.8, down
+// 16.7 / 14.6, o 8.2 / 7.1, LM head 43.4 / 32.1; 13B gate|up 47.8 / 36.4.  With more row strips LDS reads and matrix work
+// take over (64 rows: gate|up 32.0 / 30.5, 96 rows 37.3 / 36.4), so the copies are read up to kNarrowMaxRows rows.
+constexpr unsigned kNarrowMask = 0xBFF8BFF8u;   // sign, exponent and mantissa bits of two halves
+constexpr float kNarrowScale = 0.125f;
+
+__global__ __launch_bounds__(256) void k_narrow_weight(const u32x4* __restrict__ src, u32x4* __restrict__ dst,
+                                                       size_t n_groups, int32_t* __restrict__ unfit)
+{
+    const size_t total = n_groups * 64;   // one thread per group of 4 k-blocks and lane
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
+        const size_t g = i >> 6;
+        const int lane = (int)(i & 63);
+        unsigned o[12];
+        bool bad = false;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const u32x4 w = src[(g * 4 + q) * 64 + lane];
+            unsigned f[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const unsigned lo = w[e] & 0xffffu, hi = w[e] >> 16;
+                bad = bad || (lo & 0x7fffu) >= 0x3400u || (hi & 0x7fffu) >= 0x3400u;
+                const _Float16 a = __builtin_bit_cast(_Float16, (unsigned short)lo) * (_Float16)8.f;
+                const _Float16 b = __builtin_bit_cast(_Float16, (unsigned short)hi) * (_Float16)8.f;
+                f[e] = (unsigned)__builtin_bit_cast(unsigned short, a) | ((unsigned)__builtin_bit_cast(unsigned short, b) << 16);
+                bad = bad || (f[e] & ~kNarrowMask) != 0u;
+            }
+            // the fourth dword's bits 5..3, 8..6, 11..9 and 15, 13, 12 of each half: see narrow_frag
+            o[3 * q] = f[0] | ((f[3] >> 3) & 0x00070007u) | ((f[3] >> 1) & 0x40004000u);
+            o[3 * q + 1] = f[1] | ((f[3] >> 6) & 0x00070007u) | ((f[3] << 1) & 0x40004000u);
+            o[3 * q + 2] = f[2] | ((f[3] >> 9) & 0x00070007u) | ((f[3] << 2) & 0x40004000u);
+        }
+        if (bad) *unfit = 1;
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+            dst[(g * 3 + p) * 64 + lane] = (u32x4){o[4 * p], o[4 * p + 1], o[4 * p + 2], o[4 * p + 3]};
+    }
+}
+
+// Three stored dwords -> the four dwords of an operand fragment (eight times the weights).  15 vector instructions.
+__device__ __forceinline__ u32x4 narrow_frag(unsigned a, unsigned b, unsigned c)
+{
+    unsigned d = (a << 3) & 0x00380038u;
+    d |= (b << 6) & 0x01C001C0u;
+    d |= (c << 9) & 0x0E000E00u;
+    d |= (a << 1) & 0x80008000u;
+    d |= (b >> 1) & 0x20002000u;
+    d |= (c >> 2) & 0x10001000u;
+    return (u32x4){a & kNarrowMask, b & kNarrowMask, c & kNarrowMask, d};
+}
+
+// Fragment q (0..3) of a lane's three 16-byte pieces of a group.
+template <int Q>
+__device__ __forceinline__ u32x4 narrow_group_frag(const u32x4 (&p)[3])
+{
+    return narrow_frag(p[(3 * Q) / 4][(3 * Q) % 4], p[(3 * Q + 1) / 4][(3 * Q + 1) % 4], p[(3 * Q + 2) / 4][(3 * Q + 2) % 4]);
+}
+
 __global__ void k_cast_rows(const void* __restrict__ src, int src_f32, bf16_t* __restrict__ dst, size_t count)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (size_t)gridDim.x * blockDim.x)
@@ -215,35 +286,62 @@ __global__ __launch_bounds__(T) void k_rmsnorm(const int32_t* __restrict__ d_cou
 // At the end waves 1..3 hand their accumulators to wave 0 through LDS; wave 0 runs the epilogue.
 __device__ __forceinline__ float silu_f(float z) { return z / (1.f + __expf(-z)); }
 
-template <int MT, int NB, int KD>
+// WN: weights in the 12-bit form (KD = 4, one group per load; k-ranges are whole groups).
+template <int MT, int NB, int KD, int WN>
 struct SkinnyFrags {
-    u32x4 w[NB][KD];
+    static_assert(!WN || KD == 4, "a 12-bit load covers 4 k-blocks");
+    u32x4 w[NB][WN ? 3 : KD];
     u32x4 x[MT][KD];
 };
 
 // Loads for k-blocks kb..kb+KD-1; k-blocks at or beyond kend are clamped re-reads whose activation
 // operands are zeroed in skinny_mma, so they add 0.
-template <int MT, int NB, int KD>
-__device__ __forceinline__ void skinny_load(SkinnyFrags<MT, NB, KD>& f, const u32x4* __restrict__ Wl,
+template <int MT, int NB, int KD, int WN>
+__device__ __forceinline__ void skinny_load(SkinnyFrags<MT, NB, KD, WN>& f, const u32x4* __restrict__ Wl,
                                             const u32x4* __restrict__ Xl, int KB, int nb0, int nvalid, int kb,
                                             int kend)
 {
-#pragma unroll
-    for (int q = 0; q < KD; ++q) {
-        const int kk = min(kb + q, kend - 1);
+    if (WN) {
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             const int nb = nb0 + (i < nvalid ? i : 0);
-            f.w[i][q] = __builtin_nontemporal_load(Wl + ((size_t)nb * KB + kk) * 64);
+            const u32x4* g = Wl + ((size_t)nb * (KB >> 2) + (kb >> 2)) * 192;
+#pragma unroll
+            for (int p = 0; p < 3; ++p) f.w[i][p] = __builtin_nontemporal_load(g + p * 64);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < KD; ++q) {
+        const int kk = min(kb + q, kend - 1);
+        if (!WN) {
+#pragma unroll
+            for (int i = 0; i < NB; ++i) {
+                const int nb = nb0 + (i < nvalid ? i : 0);
+                f.w[i][q] = __builtin_nontemporal_load(Wl + ((size_t)nb * KB + kk) * 64);
+            }
         }
 #pragma unroll
         for (int m = 0; m < MT; ++m) f.x[m][q] = Xl[((size_t)m * KB + kk) * 64];
     }
 }
 
-template <int MT, int NB, int KD>
-__device__ __forceinline__ void skinny_mma(const SkinnyFrags<MT, NB, KD>& f, f32x4 (&acc)[NB][MT], int kb, int kend)
+template <int MT, int NB, int KD, int WN>
+__device__ __forceinline__ void skinny_mma(const SkinnyFrags<MT, NB, KD, WN>& f, f32x4 (&acc)[NB][MT], int kb, int kend)
 {
+    if constexpr (WN) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const u32x4 w[4] = {narrow_group_frag<0>(f.w[i]), narrow_group_frag<1>(f.w[i]), narrow_group_frag<2>(f.w[i]),
+                                narrow_group_frag<3>(f.w[i])};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+                    acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[q]),
+                                                                       __builtin_bit_cast(f16x8, f.x[m][q]), acc[i][m], 0, 0, 0);
+        }
+        return;
+    } else {
     const u32x4 zero = {0u, 0u, 0u, 0u};
 #pragma unroll
     for (int q = 0; q < KD; ++q) {
@@ -257,9 +355,10 @@ __device__ __forceinline__ void skinny_mma(const SkinnyFrags<MT, NB, KD>& f, f32
                                                                    __builtin_bit_cast(f16x8, xv), acc[i][m], 0, 0, 0);
         }
     }
+    }
 }
 
-template <int MT, int NB, int KD, int EPI>
+template <int MT, int NB, int KD, int EPI, int WN>
 __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a, int n_groups, int kb_per_slice)
 {
     __shared__ f32x4 red[3][NB][MT][64];
@@ -267,7 +366,8 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a, int n_groups, i
     const int ng = blockIdx.x % n_groups, ks = blockIdx.x / n_groups;
     const int KB = a.Kp >> 5, NBT = a.N >> 4;
     const int s0 = ks * kb_per_slice, s1 = min(KB, s0 + kb_per_slice);
-    const int per_wave = (max(s1 - s0, 0) + 3) >> 2;
+    int per_wave = (max(s1 - s0, 0) + 3) >> 2;
+    if (WN) per_wave = (per_wave + 3) & ~3;   // whole groups of 4 k-blocks (the slices are, too)
     const int kbeg = min(s1, s0 + wave * per_wave), kend = min(s1, kbeg + per_wave);
     const int nb0 = ng * NB;
     const int nvalid = min(NB, NBT - nb0);  // block-uniform
@@ -278,10 +378,10 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a, int n_groups, i
 #pragma unroll
         for (int m = 0; m < MT; ++m) acc[i][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    const u32x4* Wl = (const u32x4*)a.W + lane;
+    const u32x4* Wl = (const u32x4*)(WN ? a.Wn : a.W) + lane;
     const u32x4* Xl = (const u32x4*)a.X + lane;
     if (kbeg < kend) {
-        SkinnyFrags<MT, NB, KD> fa, fb;
+        SkinnyFrags<MT, NB, KD, WN> fa, fb;
         skinny_load(fa, Wl, Xl, KB, nb0, nvalid, kbeg, kend);
         // Loads past the wave's k-range are skipped rather than clamped: measured, the wasted re-reads of an
         // unconditional tail cost more (k-ranges are only 4-40 blocks) than the conservative load-counter waits
@@ -307,6 +407,12 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a, int n_groups, i
         for (int i = 0; i < NB; ++i)
 #pragma unroll
             for (int m = 0; m < MT; ++m) acc[i][m] += red[w][i][m][lane];
+    if (WN) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[i][m] *= kNarrowScale;
+    }
 
     const int col4 = (lane >> 4) * 4;  // first of this lane's 4 consecutive output columns inside a strip
 #pragma unroll
@@ -354,17 +460,33 @@ __global__ __launch_bounds__(256) void k_gemm_skinny(GemmArgs a, int n_groups, i
 // accumulators to the even one through LDS at the end.  Used above 96 rows when a workgroup owns at most 4 units:
 // there the matrix-core and LDS work per weight byte grows with the row strips, and 3 or 4 waves (one per SIMD,
 // nothing to overlap their waits with) no longer keep up with the weight stream.
-template <int NBW, int KQ>
+// With WN = 1 the weights come in the 12-bit form, one group of 4 k-blocks per wave and chunk.  A workgroup with at most
+// 4 units then always runs two waves per unit on chunks of 8 k-blocks: 4 waves have too few of the shorter loads in
+// flight (16 rows, one / two waves per unit: down 16.4 / 14.6 us, gate|up 26.7 / 25.8, o at 24 rows 8.5 / 7.4).
+template <int NBW, int KQ, int WN>
 struct SweepSlot {
-    u32x4 w[NBW][KQ];   // KQ = k-blocks of a chunk this wave handles
+    static_assert(!WN || KQ == 4, "a 12-bit group covers 4 k-blocks");
+    u32x4 w[NBW][WN ? 3 : KQ];   // KQ = k-blocks of a chunk this wave handles
 };
 
-template <int NBW, int KQ>
-__device__ __forceinline__ void sweep_load_w(SweepSlot<NBW, KQ>& f, const u32x4* __restrict__ Wl,
+template <int NBW, int KQ, int WN>
+__device__ __forceinline__ void sweep_load_w(SweepSlot<NBW, KQ, WN>& f, const u32x4* __restrict__ Wl,
                                              const u32x4* __restrict__ Zl, int KB, int nb0, int nvalid, int kb, int kend)
 {
+    if (WN) {   // slices are whole groups: a chunk is either inside or beyond
+        const int kg = min(kb, kend - 4) >> 2;
 #pragma unroll
-    for (int q = 0; q < KQ; ++q) {
+        for (int i = 0; i < NBW; ++i) {
+            const uintptr_t wp = (uintptr_t)(Wl + ((size_t)(nb0 + i) * (KB >> 2) + kg) * 192), zp = (uintptr_t)Zl;
+            const uintptr_t mask = (kb < kend && i < nvalid) ? ~(uintptr_t)0 : (uintptr_t)0;
+            const u32x4* g = (const u32x4*)(zp ^ ((wp ^ zp) & mask));
+#pragma unroll
+            for (int p = 0; p < 3; ++p) f.w[i][p] = __builtin_nontemporal_load(g + p * 64);
+        }
+        return;
+    }
+#pragma unroll
+    for (int q = 0; q < (WN ? 0 : KQ); ++q) {
         const bool live = kb + q < kend;
         const int kk = min(kb + q, kend - 1);
 #pragma unroll
@@ -411,10 +533,20 @@ __device__ __forceinline__ void sweep_store_x(const SweepStage<P, MT, KC>& xs, u
 }
 
 // q0: first k-block of the chunk this wave handles (0, or KC/2 for the second wave of a pair).
-template <int MT, int NBW, int KC, int KQ>
-__device__ __forceinline__ void sweep_mma(const SweepSlot<NBW, KQ>& f, const u32x4* buf, int lane, int q0,
+template <int MT, int NBW, int KC, int KQ, int WN>
+__device__ __forceinline__ void sweep_mma(const SweepSlot<NBW, KQ, WN>& f, const u32x4* buf, int lane, int q0,
                                           f32x4 (&acc)[NBW][MT])
 {
+    u32x4 wn[NBW][WN ? 4 : 1];
+    if constexpr (WN) {
+#pragma unroll
+        for (int i = 0; i < NBW; ++i) {
+            wn[i][0] = narrow_group_frag<0>(f.w[i]);
+            wn[i][1] = narrow_group_frag<1>(f.w[i]);
+            wn[i][2] = narrow_group_frag<2>(f.w[i]);
+            wn[i][3] = narrow_group_frag<3>(f.w[i]);
+        }
+    }
 #pragma unroll
     for (int q = 0; q < KQ; ++q) {
         u32x4 xv[MT];
@@ -424,8 +556,9 @@ __device__ __forceinline__ void sweep_mma(const SweepSlot<NBW, KQ>& f, const u32
         for (int m = 0; m < MT; ++m)
 #pragma unroll
             for (int i = 0; i < NBW; ++i)
-                acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, f.w[i][q]),
-                                                                   __builtin_bit_cast(f16x8, xv[m]), acc[i][m], 0, 0, 0);
+                acc[i][m] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(f16x8, WN ? wn[i][WN ? q : 0] : f.w[i][WN ? 0 : q]),
+                    __builtin_bit_cast(f16x8, xv[m]), acc[i][m], 0, 0, 0);
     }
 }
 
@@ -434,22 +567,22 @@ __device__ __forceinline__ void sweep_mma(const SweepSlot<NBW, KQ>& f, const u32
 // block, would take their share of the compute unit's memory requests.  The two variants are separate
 // straight-line loops, chosen once per wave, because a load under a branch inside the loop would make
 // every wait there cover all loads in flight.
-template <bool ACTIVE, int P, int MT, int NBW, int KC, int KH>
+template <bool ACTIVE, int P, int MT, int NBW, int KC, int KH, int WN>
 __device__ __forceinline__ void sweep_run(u32x4* xl0, u32x4* xl1, f32x4 (&acc)[NBW][MT],
                                           const u32x4* __restrict__ Wl, const u32x4* __restrict__ Zl,
                                           const u32x4* __restrict__ X, int KB, int nb0, int nvalid, int s0, int s1,
                                           int C, int lane, int q0)
 {
     constexpr int KQ = KC / KH;
-    SweepSlot<NBW, KQ> fa, fb;
+    SweepSlot<NBW, KQ, WN> fa, fb;
     SweepStage<P, MT, KC> xs;
     sweep_load_x<P, MT, KC>(xs, X, KB, s0, s1);
-    if (ACTIVE) sweep_load_w<NBW, KQ>(fa, Wl, Zl, KB, nb0, nvalid, s0 + q0, s1);
+    if (ACTIVE) sweep_load_w<NBW, KQ, WN>(fa, Wl, Zl, KB, nb0, nvalid, s0 + q0, s1);
     __builtin_amdgcn_sched_barrier(0);
     sweep_store_x<P, MT, KC>(xs, xl0);
     __builtin_amdgcn_sched_barrier(0);
     sweep_load_x<P, MT, KC>(xs, X, KB, s0 + KC, s1);
-    if (ACTIVE) sweep_load_w<NBW, KQ>(fb, Wl, Zl, KB, nb0, nvalid, s0 + KC + q0, s1);
+    if (ACTIVE) sweep_load_w<NBW, KQ, WN>(fb, Wl, Zl, KB, nb0, nvalid, s0 + KC + q0, s1);
     __builtin_amdgcn_sched_barrier(0);
     __syncthreads();
     // Two chunks per trip (slot fa with LDS buffer 0, slot fb with buffer 1).  Within a chunk: contract it,
@@ -457,20 +590,20 @@ __device__ __forceinline__ void sweep_run(u32x4* xl0, u32x4* xl1, f32x4 (&acc)[N
     // the chunk after that, barrier.  A buffer is rewritten one barrier after its last read.
     for (int c = 0; c < C; c += 2) {
         const int k2 = s0 + (c + 2) * KC, k3 = k2 + KC;
-        if (ACTIVE) sweep_mma<MT, NBW, KC, KQ>(fa, xl0, lane, q0, acc);
+        if (ACTIVE) sweep_mma<MT, NBW, KC, KQ, WN>(fa, xl0, lane, q0, acc);
         __builtin_amdgcn_sched_barrier(0);
         sweep_store_x<P, MT, KC>(xs, xl1);
         __builtin_amdgcn_sched_barrier(0);
         sweep_load_x<P, MT, KC>(xs, X, KB, k2, s1);
-        if (ACTIVE) sweep_load_w<NBW, KQ>(fa, Wl, Zl, KB, nb0, nvalid, k2 + q0, s1);
+        if (ACTIVE) sweep_load_w<NBW, KQ, WN>(fa, Wl, Zl, KB, nb0, nvalid, k2 + q0, s1);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
-        if (ACTIVE) sweep_mma<MT, NBW, KC, KQ>(fb, xl1, lane, q0, acc);
+        if (ACTIVE) sweep_mma<MT, NBW, KC, KQ, WN>(fb, xl1, lane, q0, acc);
         __builtin_amdgcn_sched_barrier(0);
         sweep_store_x<P, MT, KC>(xs, xl0);
         __builtin_amdgcn_sched_barrier(0);
         sweep_load_x<P, MT, KC>(xs, X, KB, k3, s1);
-        if (ACTIVE) sweep_load_w<NBW, KQ>(fb, Wl, Zl, KB, nb0, nvalid, k3 + q0, s1);
+        if (ACTIVE) sweep_load_w<NBW, KQ, WN>(fb, Wl, Zl, KB, nb0, nvalid, k3 + q0, s1);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
     }
@@ -479,13 +612,13 @@ __device__ __forceinline__ void sweep_run(u32x4* xl0, u32x4* xl1, f32x4 (&acc)[N
 // Grid: n_gn workgroups per k-slice x ksplit; workgroup gn of a slice owns units [gn*n_units/n_gn,
 // (gn+1)*n_units/n_gn) (a unit = NBW consecutive strips; at most P/KH of them, checked by the launcher), one per
 // wave, or with KH = 2 one per pair of waves.
-template <int P, int MT, int NBW, int EPI, int KH>
+template <int P, int MT, int NBW, int EPI, int KH, int WN>
 __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, int n_gn, int kb_per_slice)
 {
     // k-blocks per chunk: 4 up to 12 row strips (both staging buffers: 8 KiB per row strip, at most 96 KiB), 2 above.
     // Measured: one strip 4 against 2 and 8, 5-8 strips 4 against 2: 4 is the fastest; 9-12 strips 4 against 2: 4 % faster;
     // 13-15 strips: equal; 16 strips: 2 is 10 % faster (128 KiB of LDS and the registers of the widest instantiation).
-    constexpr int KC = MT > 12 ? 2 : 4;
+    constexpr int KC = WN ? 4 * KH : (MT > 12 ? 2 : 4);
     static_assert(KC % KH == 0, "a chunk's k-blocks split evenly between the waves of a unit");
     constexpr int STAGE = SweepStage<P, MT, KC>::PIECES;
     // two staging buffers; after the sweep the same memory carries the odd waves' accumulators (KH = 2)
@@ -511,15 +644,15 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
 #pragma unroll
         for (int m = 0; m < MT; ++m) acc[i][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    const u32x4* Wl = (const u32x4*)a.W + lane;
+    const u32x4* Wl = (const u32x4*)(WN ? a.Wn : a.W) + lane;
     const u32x4* Zl = (const u32x4*)a.zero_blk + lane;
     const u32x4* X = (const u32x4*)a.X;
     const int C = (s1 - s0 + KC - 1) / KC;   // chunks of this slice: the same for every wave of the workgroup
     if (C > 0) {
         if (active)
-            sweep_run<true, P, MT, NBW, KC, KH>(xl0, xl1, acc, Wl, Zl, X, KB, nb0, nvalid, s0, s1, C, lane, q0);
+            sweep_run<true, P, MT, NBW, KC, KH, WN>(xl0, xl1, acc, Wl, Zl, X, KB, nb0, nvalid, s0, s1, C, lane, q0);
         else
-            sweep_run<false, P, MT, NBW, KC, KH>(xl0, xl1, acc, Wl, Zl, X, KB, nb0, nvalid, s0, s1, C, lane, q0);
+            sweep_run<false, P, MT, NBW, KC, KH, WN>(xl0, xl1, acc, Wl, Zl, X, KB, nb0, nvalid, s0, s1, C, lane, q0);
     }
     if (KH == 2) {
         // the odd wave of a pair hands its sums to the even one (the staging buffers are free after the last barrier
@@ -541,6 +674,12 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
         }
     }
     if (!active) return;
+    if (WN) {
+#pragma unroll
+        for (int i = 0; i < NBW; ++i)
+#pragma unroll
+            for (int m = 0; m < MT; ++m) acc[i][m] *= kNarrowScale;
+    }
 
     const int col4 = (lane >> 4) * 4;
 #pragma unroll
@@ -1384,6 +1523,12 @@ void launch_pack_weight(const void* src, int src_f32, f16_t* dst, int n_src, int
                        blk_stride, blk_off);
 }
 
+void launch_narrow_weight(const f16_t* src, void* dst, size_t n_groups, int32_t* unfit, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_narrow_weight, dim3(grid_for(n_groups * 64, 256)), dim3(256), 0, s, (const u32x4*)src, (u32x4*)dst,
+                       n_groups, unfit);
+}
+
 void launch_cast_rows(const void* src, int src_f32, bf16_t* dst, size_t count, hipStream_t s)
 {
     hipLaunchKernelGGL(k_cast_rows, dim3(grid_for(count, 256)), dim3(256), 0, s, src, src_f32, dst, count);
@@ -1424,18 +1569,29 @@ void launch_swiglu_reduce(const float* part, int ksplit, size_t part_stride, int
                        m_rows, F, kp_out, out);
 }
 
-template <int MT, int NB, int KD, int EPI>
+// k-blocks per slice; whole groups of 4 wherever a matrix with 12-bit weights would be read in that form, so that a
+// matrix without them adds up in the same order.
+static inline int slice_kb(const GemmArgs& a)
+{
+    const int kbs = (a.Kp / 32 + a.ksplit - 1) / a.ksplit;
+    return a.group4 ? (kbs + 3) & ~3 : kbs;
+}
+
+template <int MT, int NB, int KD, int EPI, int WN = 0>
 static void launch_skinny_inst(const GemmArgs& a, hipStream_t s)
 {
-    const int KB = a.Kp / 32;
     const int groups = (a.N / 16 + NB - 1) / NB;
-    const int kbs = (KB + a.ksplit - 1) / a.ksplit;
-    hipLaunchKernelGGL((k_gemm_skinny<MT, NB, KD, EPI>), dim3(groups * a.ksplit), dim3(256), 0, s, a, groups, kbs);
+    hipLaunchKernelGGL((k_gemm_skinny<MT, NB, KD, EPI, WN>), dim3(groups * a.ksplit), dim3(256), 0, s, a, groups, slice_kb(a));
 }
 
 template <int MT, int EPI>
 static void launch_skinny_mt(const GemmArgs& a, hipStream_t s)
 {
+    if constexpr (MT == 1)
+        if (a.narrow) {   // gemm_plan: one row strip, 4 k-blocks per load
+            if (a.nb == 2) return launch_skinny_inst<MT, 2, 4, EPI, 1>(a, s);
+            return launch_skinny_inst<MT, 4, 4, EPI, 1>(a, s);
+        }
     if (a.nb == 2) {
         if (a.kd == 2) launch_skinny_inst<MT, 2, 2, EPI>(a, s);
         else launch_skinny_inst<MT, 2, 4, EPI>(a, s);
@@ -1445,27 +1601,25 @@ static void launch_skinny_mt(const GemmArgs& a, hipStream_t s)
     }
 }
 
-template <int P, int MT, int NBW, int EPI, int KH>
-static void launch_sweep_inst(const GemmArgs& a, int units, hipStream_t s)
-{
-    const int KB = a.Kp / 32;
-    const int kbs = (KB + a.ksplit - 1) / a.ksplit;
-    hipLaunchKernelGGL((k_gemm_sweep<P, MT, NBW, EPI, KH>), dim3(a.sweep_gn * a.ksplit), dim3(64 * P), 0, s, a, units,
-                       a.sweep_gn, kbs);
-}
-
 template <int P, int MT, int EPI, int KH>
 static void launch_sweep_mt(const GemmArgs& a, int units, hipStream_t s)
 {
     // strips per wave (sweep_nbw): a gate/up pair with the SwiGLU epilogue, otherwise one
-    launch_sweep_inst<P, MT, EPI == EPI_SWIGLU ? 2 : 1, EPI, KH>(a, units, s);
+    constexpr int NBW = EPI == EPI_SWIGLU ? 2 : 1;
+    const dim3 grid(a.sweep_gn * a.ksplit), block(64 * P);
+    if constexpr (MT <= kNarrowMaxRows / 16)
+        if (a.narrow) {
+            hipLaunchKernelGGL((k_gemm_sweep<P, MT, NBW, EPI, KH, 1>), grid, block, 0, s, a, units, a.sweep_gn, slice_kb(a));
+            return;
+        }
+    hipLaunchKernelGGL((k_gemm_sweep<P, MT, NBW, EPI, KH, 0>), grid, block, 0, s, a, units, a.sweep_gn, slice_kb(a));
 }
 
 template <int P, int EPI, int KH>
 static void launch_sweep_p(const GemmArgs& a, int units, hipStream_t s)
 {
     switch ((a.m_rows + 15) / 16) {
-        case 1: launch_sweep_mt<P, 1, EPI, 1>(a, units, s); break;   // one row strip: never split
+        case 1: launch_sweep_mt<P, 1, EPI, KH>(a, units, s); break;
         case 2: launch_sweep_mt<P, 2, EPI, KH>(a, units, s); break;
         case 3: launch_sweep_mt<P, 3, EPI, KH>(a, units, s); break;
         case 4: launch_sweep_mt<P, 4, EPI, KH>(a, units, s); break;
@@ -1502,8 +1656,8 @@ static void launch_gemm_epi(const GemmArgs& a, hipStream_t s)
         const int units = (a.N / 16 + nbw - 1) / nbw;
         const int per = (units + a.sweep_gn - 1) / a.sweep_gn;   // most units any workgroup owns
         if (a.sweep_p == 4 && per <= 4) {
-            // where the plan asks for it (above 96 rows): 8 waves, two per unit (see SweepSlot)
-            if (a.m_rows > 16 && a.sweep_kh == 2) return launch_sweep_p<8, EPI, 2>(a, units, s);
+            // where the plan asks for it (above 96 rows; with 12-bit weights everywhere): 8 waves, two per unit (see SweepSlot)
+            if ((a.narrow ? a.narrow : a.sweep_kh) == 2) return launch_sweep_p<8, EPI, 2>(a, units, s);
             return launch_sweep_p<4, EPI, 1>(a, units, s);
         }
         if (per <= 8) return launch_sweep_p<8, EPI, 1>(a, units, s);

@@ -48,7 +48,7 @@ int sweep_nbw(int epilogue, int /*m_rows*/) { return epilogue == EPI_SWIGLU ? 2 
 
 GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ksplit)
 {
-    GemmPlan p{1, 2, 4, 1, 0, 0, 1, 4};
+    GemmPlan p{1, 2, 4, 1, 0, 0, 1, 0, 4};
     const int KB = Kp / 32;
     const int mode = gemm_mode();
     if (m_rows <= kSweepMaxRows) {
@@ -69,6 +69,8 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
             // grows with the row strips and 4 waves (one per SIMD) stop keeping up with the weight stream (same GPU,
             // split / not split: 104 rows 5.09 / 5.18 ms per step, 112 rows 5.21 / 5.28, 128 rows 5.59 / 5.81; up to
             // 96 rows the two are equal to within 0.1 %)
+            if (Kp % 128 == 0 && m_rows <= kNarrowMaxRows)
+                p.narrow = (p.sweep_p == 4 && g_sweep_split.load(std::memory_order_relaxed)) ? 2 : 1;
             p.sweep_kh = (p.sweep_p == 4 && m_rows > 96 && g_sweep_split.load(std::memory_order_relaxed)) ? 2 : 1;
             return p;
         }
@@ -77,6 +79,7 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
         if (epilogue == EPI_SWIGLU) max_ksplit = 1;   // fused epilogue: no k-slices
         const int mt = (m_rows + 15) / 16;
         p.kd = mt == 1 ? 4 : 2;
+        p.narrow = Kp % 128 == 0 && mt == 1;   // the kernel reads 12-bit weights 4 k-blocks at a time
         if (max_ksplit == 1 && epilogue == EPI_SWIGLU) return p;
         p.nb = (mt == 1 && KB > 256) ? 2 : 4;   // with several row strips the activation re-reads dominate: 4 strips
         if (max_ksplit == 1 && mt == 1) p.nb = 2;

@@ -15,8 +15,12 @@ struct GemmPlan {
     int ksplit, nb, kd, kp;
     int sweep_p, sweep_gn;
     int sweep_kh;   // sweep kernel: waves per unit (1 or 2)
+    int narrow;     // sweep and skinny kernels: > 0 if the 12-bit form of the weights is read where the matrix has one;
+                    // sweep kernel: then this many waves per unit
     int tms;        // tiled kernel: row strips per tile (4 = 64 rows, 8 = 128 rows)
 };
+
+constexpr int kNarrowMaxRows = 96;   // most token-rows for which the 12-bit weights are read
 
 constexpr int kTiledTallFrom = 896;   // token-rows from which the tiled kernel uses 128-row tiles
 

@@ -1,0 +1,50 @@
+"""The 12-bit copies of the weights (what decode batches stream) hold the same values as the halves they replace: two
+models whose heads differ in one value of one row, so that one has such a copy and the other (0.5 has no 12-bit form) has
+not, give the same numbers in every other column.  The copy carries eight times the weight, so weights that are subnormal
+as halves are normal there, and the matrix unit may round a sum that contains one differently in its last bit: fewer than
+one column in a thousand, by no more than an fp32 rounding of the largest partial sum.  A wrong weight changes every row
+of its column by far more than that."""
+import numpy as np
+import pytest
+
+from paper_2305_13144_amd import binding as ss
+from paper_2305_13144_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _wide_head(shape, rng):
+    """bf16 patterns over everything the 12-bit form covers: both zeros, all exponents below 2^-2, all mantissas, and the
+    values below 2^-17 that are held as multiples of 2^-24."""
+    v, d = shape.vocab, shape.d_model
+    exp = rng.integers(0, 125, (v, d))                   # biased exponent 124 = [2^-3, 2^-2)
+    exp = np.where(rng.random((v, d)) < 0.7, rng.integers(105, 125, (v, d)), exp)
+    return ((rng.integers(0, 2, (v, d)) << 15) | (exp << 7) | rng.integers(0, 128, (v, d))).astype(np.uint16)
+
+
+@pytest.mark.parametrize("mode", [5, 6])                 # skinny kernel; sweep kernel, one wave per unit in both forms
+@pytest.mark.parametrize("rows", [1, 16, 17, 48, 96, 97])
+def test_logits_are_the_same_with_and_without_the_12_bit_copy(mode, rows):
+    shape = synth.ModelShape("narrow", 1, 512, 4, 128, 640, 1040)
+    rng = np.random.default_rng(rows)
+    W = synth.make_weights(shape, seed=3, threads=1)
+    W[-1] = _wide_head(shape, rng)
+    other = list(W)
+    other[-1] = W[-1].copy()
+    other[-1][1039, 5] = synth.f32_to_bf16_bits(np.array([0.5], np.float32))[0]
+    toks = rng.integers(0, shape.vocab, rows * 3).astype(np.int32)
+    offs = np.arange(rows + 1, dtype=np.int32) * 3
+    ss.ss_set_gemm_mode(mode)
+    try:
+        out = []
+        for weights in (W, other):
+            gw = ss.Weights(shape, weights)
+            out.append(ss.ss_forward_logits(gw, toks, offs, np.full(rows, 1, np.int32)))   # a prompt forward, two steps
+            gw.close()
+    finally:
+        ss.ss_set_gemm_mode(0)
+    assert np.isfinite(out[0]).all()
+    a, b = out[0][:, :1039], out[1][:, :1039]
+    assert (a != b).mean() < 1e-3
+    assert np.abs(a - b).max() <= 2.0 ** -22 * np.abs(a).max()
+    assert not np.array_equal(out[0][:, 1039], out[1][:, 1039])
