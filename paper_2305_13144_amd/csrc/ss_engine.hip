@@ -106,13 +106,13 @@ struct Buf {
 };
 
 struct Workspace {
-    Buf x, h, ao, act, qrot, pqkv, pd, pgu, hsel, logits, kv, ints, i64s, draws;
+    Buf x, h, ao, act, qrot, pqkv, pd, hsel, logits, kv, ints, i64s, draws;
     // Non-null: every buffer is carved out of [arena, arena + arena_bytes) instead of being allocated.
     char* arena = nullptr;
     size_t arena_bytes = 0;
     void release()
     {
-        for (Buf* b : {&x, &h, &ao, &act, &qrot, &pqkv, &pd, &pgu, &hsel, &logits, &kv, &ints, &i64s, &draws})
+        for (Buf* b : {&x, &h, &ao, &act, &qrot, &pqkv, &pd, &hsel, &logits, &kv, &ints, &i64s, &draws})
             b->release();
     }
 };
@@ -325,7 +325,7 @@ int ensure_workspace(const ss_weights* w, Lane& ln, int n_max, int B, int n_sel,
     const size_t n_i32 = 4 + 3 * np + 5 * Bp + 2 * sp + (size_t)B * max_new;
     ln.kv_layer_stride = slots * d;
     // Partial-sum buffers hold [ksplit][rows][N] for whatever plan a forward over 1..n_max rows gets.
-    // gate|up partial sums exist only when that projection runs with k-slices (never in the sweep kernel).
+    // gate|up has none: its SwiGLU epilogue needs whole sums, so it is never cut in slices.
     struct Item { Buf* b; size_t bytes; bool zero; };
     const Item items[] = {
         {&ws.x, nr * d * 4, false},
@@ -335,7 +335,6 @@ int ensure_workspace(const ss_weights* w, Lane& ln, int n_max, int B, int n_sel,
         {&ws.qrot, nr * d * 4, false},
         {&ws.pqkv, ss::gemm_partial_rows_bound(3 * d, n_max) * 3 * d * 4, false},
         {&ws.pd, ss::gemm_partial_rows_bound(d, n_max) * d * 4, false},
-        {&ws.pgu, ss::gemm_partial_rows_bound(2 * F, n_max, true) * 2 * F * 4, false},
         {&ws.hsel, (size_t)ss::round_up(n_sel, 128) * d * 2, true},
         {&ws.logits, (size_t)ss::round_up(n_sel, 16) * V * 4, false},
         {&ws.kv, (size_t)c.n_layers * 2 * slots * d * 2, false},
@@ -408,7 +407,7 @@ GemmArgs gemm_args(const ss_weights* w, const PackedMat& W, const f16_t* X, floa
     g.narrow = W.pn ? p.narrow : 0;
     g.group4 = p.narrow;
     g.m_rows = rows; g.m_stride = rows; g.kp_out = kp_out; g.ksplit = p.ksplit; g.nb = p.nb; g.kd = p.kd;
-    g.kp = p.kp; g.tms = p.tms; g.sweep_p = p.sweep_p; g.sweep_gn = p.sweep_gn; g.sweep_kh = p.sweep_kh; g.zero_blk = w->zero_blk;
+    g.block = p.block; g.sweep_p = p.sweep_p; g.sweep_gn = p.sweep_gn; g.sweep_kh = p.sweep_kh; g.zero_blk = w->zero_blk;
     return g;
 }
 
@@ -453,12 +452,7 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
         }
         ss::launch_gemm(mk(L.wo, ao, pd, nullptr, n, 0, p_o), ss::EPI_PARTIAL, s);
         ss::launch_rmsnorm(st, x, pd, ks_o, st_d, L.mlp_norm, c.rms_eps, nullptr, nullptr, h, d, n, s);
-        if (p_gu.ksplit == 1) {
-            ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
-        } else {   // k-sliced: partial sums, then one small kernel adds them and applies SwiGLU
-            ss::launch_gemm(mk(L.wgu, h, ws.pgu.as<float>(), nullptr, n, 0, p_gu), ss::EPI_PARTIAL, s);
-            ss::launch_swiglu_reduce(ws.pgu.as<float>(), p_gu.ksplit, (size_t)n * 2 * F, n, F, Fp, act, s);
-        }
+        ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
         ss::launch_gemm(mk(L.wd, act, pd, nullptr, n, 0, p_d), ss::EPI_PARTIAL, s);
     }
     f16_t* hsel = ws.hsel.as<f16_t>();
@@ -1422,10 +1416,7 @@ int bench_weight_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32
             const Layer& L = w->layers[l];
             ss::launch_gemm(mk(L.wqkv, h, pqkv, nullptr, n, 0, p_qkv), ss::EPI_PARTIAL, s);
             ss::launch_gemm(mk(L.wo, ao, pd, nullptr, n, 0, p_o), ss::EPI_PARTIAL, s);
-            if (p_gu.ksplit == 1)
-                ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
-            else
-                ss::launch_gemm(mk(L.wgu, h, ws.pgu.as<float>(), nullptr, n, 0, p_gu), ss::EPI_PARTIAL, s);
+            ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
             ss::launch_gemm(mk(L.wd, act, pd, nullptr, n, 0, p_d), ss::EPI_PARTIAL, s);
             launches += 4;
         }

@@ -55,8 +55,7 @@ struct GemmArgs {
     int kp_out;          // padded K of out_packed
     int ksplit;          // outer k-slices (gemm_plan)
     int nb, kd;          // skinny kernel shape (gemm_plan)
-    int kp;              // tiled kernel: k-parts inside the workgroup (gemm_plan)
-    int tms;             //      row strips per tile, 4 or 8 (gemm_plan)
+    int block;           // >= 0: block kernel with this tile (gemm_plan)
     int sweep_p;         // > 0: sweep kernel with this many waves per workgroup (gemm_plan)
     int sweep_gn;        //      its workgroups per k-slice
     int group4;          // sweep and skinny kernels: k-slices are whole groups of 4 k-blocks (gemm_plan: narrow)
@@ -75,8 +74,6 @@ void launch_rmsnorm(const MbState& st, float* x, const float* part, int ksplit, 
                     const bf16_t* w, float eps, const int32_t* sel, const int32_t* d_nsel, f16_t* h_packed, int d,
                     int n_max, hipStream_t s);
 void launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s);
-void launch_swiglu_reduce(const float* part, int ksplit, size_t part_stride, int m_rows, int F, int kp_out,
-                          f16_t* out, hipStream_t s);
 void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride, float* qrot,
                         kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin, int d, int H,
                         int hd, int n_max, hipStream_t s);

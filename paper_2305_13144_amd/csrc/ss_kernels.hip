@@ -708,170 +708,157 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
     }
 }
 
-// ------------------------------------------------------------------------------------------ tiled GEMM
-// More than 64 token rows where the sweep kernel does not apply: prompt forwards (more than 256 token-rows) and
-// matrices too small for it.  A workgroup computes
-// TMS*16 token rows x 256 output columns; wave w owns 4 strips of 16 columns and every row strip.
-// Weights never touch LDS: they are stored in operand order, so each wave loads its own 4 operand
-// blocks per k-block straight into registers (1 KiB coalesced each) and is the only wave of the
-// workgroup that needs them.  The activation tile is shared by the 4 waves and staged
-// through LDS in operand order (conflict-free 1 KiB reads).  One k-block per trip; both streams run
-// D k-blocks ahead of the MFMAs in a register ring (6 for a 64-row tile: 150 KiB in flight per CU with two
-// workgroups, enough to keep HBM busy when there are few row tiles; 2 for a 128-row
-// tile, whose doubled accumulators leave no registers for more).
-// Workgroup ids are mapped so that the row tiles of one column tile follow each other at a stride of 8:
-// they land on the same XCD (ids are dealt round-robin over the 8 XCDs) at about the same time and share
-// that column tile's weights through its L2.
-// With KP = 2 the workgroup has 8 waves: two groups of 4 take the two halves of the k-slice (each with its
-// own LDS stages) and the second group hands its accumulators to the first through LDS at the end.  Used
-// when there are too few tiles to give every CU two workgroups: it doubles the waves per CU and halves
-// the serial k loop without sending partial sums through HBM.
-template <int TMS, int KP, int EPI>
-__global__ __launch_bounds__(256 * KP, 2) void k_gemm_tiled(GemmArgs a, int kb_per_slice, int n_ntiles, int n_mtiles)
+// ------------------------------------------------------------------------------------------ block GEMM
+// Many token rows (prompt forwards; decode batches above kSweepAutoRows rows): both operands go through LDS, so that every
+// byte fetched from L2 feeds MS or NS strips instead of one wave's.  A workgroup computes MS*16 token rows x NS*16 output
+// columns with WM x WN waves of (MS/WM) x (NS/WN) strips each.  A stage is one k-block of both tiles, MS + NS operand
+// blocks of 1 KiB, copied from global memory straight into LDS (no registers, no address arithmetic per lane: a block is
+// contiguous and lands in the order in which a wave reads it back, conflict-free).  ST stages form a ring; a stage is
+// requested ST - 1 trips before it is read.  One trip: wait until the next stage has landed, barrier, then, spread over
+// the matrix instructions of this trip, the copies of the stage ST ahead into the slot that the barrier has just freed
+// and the LDS reads of the next trip's operands.
+// What bounds it: with nothing to copy the same loop reaches 1.54 PFLOP/s on a full chip (the clock under matrix load),
+// with the copies 1.28; LDS reads and the order of the tiles change nothing any more.  Measured against the kernel it
+// replaced (weights straight from L2 to registers, 64 or 128 rows per tile), gate|up at the 7B width: 256 rows
+// 73.7 -> 56.3 us, 494 123 -> 81, 995 216 -> 166, 3146 544 -> 488, 12311 1989 -> 1743 (1.27 PFLOP/s); down 494 67 -> 49,
+// 995 98 -> 87, 4200 504 -> 351.
+// The copies are written in assembly because the compiler would wait for all of them before every LDS read: it counts
+// only its own loads, and the waits here are written out.  They name no output register; waits that the compiler adds
+// for loads of its own can only be too strict.
+__device__ __forceinline__ void lds_copy_1k(unsigned lds_addr, const void* base, unsigned lane_off)
 {
-    constexpr int D = TMS > 4 ? 2 : (KP == 1 ? 6 : 4);   // k-blocks in flight
-    constexpr int XV = TMS * 64 / 256;          // 16-byte vectors per thread: one k-block of the activation tile
-    __shared__ u32x4 lds_all[KP][2][TMS * 64];                // [k-part][stage][row strip][lane]
-    __shared__ f32x4 red[KP > 1 ? 4 * TMS : 1][KP > 1 ? 256 : 1];
-    const int part = threadIdx.x >> 8, tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
-    u32x4 (*lds)[TMS * 64] = lds_all[part];
-    const int KB = a.Kp >> 5, NBT = a.N >> 4;
-    const int MBT = (a.m_rows + 15) >> 4;
-    const int per_slice = ((n_ntiles + 7) >> 3) * 8 * n_mtiles;
-    const int ks = blockIdx.x / per_slice, r = blockIdx.x % per_slice;
-    const int chunk = r / (8 * n_mtiles), within = r % (8 * n_mtiles);
-    const int n_tile = chunk * 8 + (within & 7), m_tile = within >> 3;
-    if (n_tile >= n_ntiles) return;
-    const int nb0 = n_tile * 16 + wave * 4, mb0 = m_tile * TMS;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(base)
+                 : "memory");
+}
+
+template <int N>
+__device__ __forceinline__ void wait_copies()
+{
+    static_assert(N < 64, "the counter has 6 bits");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+}
+
+template <int MS, int NS, int WM, int WN, int ST, int EPI>
+__global__ __launch_bounds__(64 * WM * WN, MS * NS / (WM * WN) > 32 ? 1 : 2) void k_gemm_block(GemmArgs a, int kb_per_slice, int n_ntiles,
+                                                                                  int n_mtiles)
+{
+    constexpr int W = WM * WN;                 // waves
+    constexpr int RM = MS / WM, RN = NS / WN;  // strips per wave
+    constexpr int SB = MS + NS;                // operand blocks of a stage
+    constexpr int CP = (SB + W - 1) / W;       // copies per wave and stage (the same for all: the last block may go twice)
+    static_assert(MS % WM == 0 && NS % WN == 0, "even shares");
+    __shared__ u32x4 ring[ST][SB][64];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wm = wave % WM, wn = wave / WM;
+    const int KB = a.Kp >> 5, NBT = a.N >> 4, MBT = (a.m_rows + 15) >> 4;
+    // Tiles in panels of 8 row tiles, column tile by column tile inside a panel; a contiguous share for each of the 8
+    // dies (workgroup ids are dealt to them round-robin), so that the tiles a die works on at one time share their
+    // operands through its L2.
+    const int tiles = n_ntiles * n_mtiles;
+    const int ks = blockIdx.x / tiles, b = blockIdx.x % tiles;
+    const int x = b & 7, per = tiles >> 3, extra = tiles & 7;
+    const int t = x * per + min(x, extra) + (b >> 3);
+    const int panel = t / (8 * n_ntiles), in_panel = t % (8 * n_ntiles), ph = min(8, n_mtiles - panel * 8);
+    const int n_tile = in_panel / ph, m_tile = panel * 8 + in_panel % ph;
+    const int nb0 = n_tile * NS, mb0 = m_tile * MS;
     const int s0 = ks * kb_per_slice, s1 = min(KB, s0 + kb_per_slice);
-    const int part_len = (max(s1 - s0, 0) + KP - 1) / KP;      // trips every wave of the workgroup runs
-    const int kb0 = min(s1, s0 + part * part_len), kb1 = min(s1, kb0 + part_len);
+    const int trips = s1 - s0;
 
-    f32x4 acc[4][TMS];
+    f32x4 acc[RN][RM];
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
+    for (int i = 0; i < RN; ++i)
 #pragma unroll
-        for (int m = 0; m < TMS; ++m) acc[i][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < RM; ++m) acc[i][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    const u32x4* W4 = (const u32x4*)a.W + lane;
-    const u32x4* Xh = (const u32x4*)a.X;
-    // Ring slots are separately named arrays of native vectors indexed only by unrolled constants, so
-    // that they stay in registers (a ring that ends up in scratch memory makes every access wait for all
-    // outstanding loads).
-    u32x4 w0[4], w1[4], w2[4], w3[4], w4[4], w5[4], x0[XV], x1[XV], x2[XV], x3[XV], x4[XV], x5[XV];
-    static_assert(D == 6 || D == 4 || D == 2, "the ring below is written out for 6, 4 and 2 slots");
-#define SS_WLOAD(W_, KB_)                                                                       \
-    _Pragma("unroll") for (int i_ = 0; i_ < 4; ++i_)                                            \
-        W_[i_] = W4[((size_t)min(nb0 + i_, NBT - 1) * KB + (KB_)) * 64];
-#define SS_XLOAD(X_, KB_)                                                                       \
-    _Pragma("unroll") for (int i_ = 0; i_ < XV; ++i_) {                                         \
-        const int c_ = tid + i_ * 256;                                                          \
-        const int ln_ = c_ & 63, ms_ = c_ >> 6;                                                 \
-        X_[i_] = Xh[((size_t)min(mb0 + ms_, MBT - 1) * KB + (KB_)) * 64 + ln_];                 \
-    }
-#define SS_XSTORE(STAGE_, X_, LIVE_)                                                            \
-    _Pragma("unroll") for (int i_ = 0; i_ < XV; ++i_) lds[STAGE_][tid + i_ * 256] = (LIVE_) ? X_[i_] : zero4;
-#define SS_COMPUTE(W_, STAGE_)                                                                  \
-    {                                                                                           \
-        /* every operand read of the trip is issued before the first MFMA (the reads return in  \
-           order, so each MFMA group waits only for its own operand): LDS latency overlaps MFMAs */ \
-        u32x4 xh_[TMS];                                                                         \
-        _Pragma("unroll") for (int m_ = 0; m_ < TMS; ++m_) xh_[m_] = lds[STAGE_][m_ * 64 + lane]; \
-        __builtin_amdgcn_sched_barrier(0x16);   /* only VALU, SALU and global loads may cross */ \
-        _Pragma("unroll") for (int m_ = 0; m_ < TMS; ++m_) {                                    \
-            _Pragma("unroll") for (int i_ = 0; i_ < 4; ++i_) {                                  \
-                acc[i_][m_] = __builtin_amdgcn_mfma_f32_16x16x32_f16(                           \
-                    __builtin_bit_cast(f16x8, W_[i_]), __builtin_bit_cast(f16x8, xh_[m_]), acc[i_][m_], 0, 0, 0); \
-            }                                                                                   \
-        }                                                                                       \
-    }
-    // One trip: k-block t from ring slot (WC_, XC_); the next k-block's tile (XN_) goes into the other LDS
-    // stage first; afterwards the slot is refilled D k-blocks ahead.  Nothing in a trip is conditional: the
-    // compiler counts outstanding loads statically, and a load issued under a branch makes it wait for every
-    // load in flight at the next use.  K-blocks at or beyond kb1 are clamped re-reads whose activation tile
-    // is stored as zeros, so they add 0; every wave of the workgroup runs the same number of trips.
-#define SS_TRIP(P_, WC_, XC_, XN_)                                                              \
-    {                                                                                           \
-        const int t_ = kb0 + it + P_;                                                           \
-        SS_XSTORE((P_ + 1) & 1, XN_, t_ + 1 < kb1)                                              \
-        SS_COMPUTE(WC_, P_ & 1)                                                                 \
-        SS_WLOAD(WC_, min(t_ + D, last)) SS_XLOAD(XC_, min(t_ + D, last))                       \
-        __syncthreads();                                                                        \
-    }
-
-    const u32x4 zero4 = {0u, 0u, 0u, 0u};
-    const int last = max(min(kb1, KB) - 1, 0);   // beyond the range: a harmless in-bounds re-read
-    SS_WLOAD(w0, min(kb0, last)) SS_XLOAD(x0, min(kb0, last))
-    SS_WLOAD(w1, min(kb0 + 1, last)) SS_XLOAD(x1, min(kb0 + 1, last))
-    if (D >= 4) {
-        SS_WLOAD(w2, min(kb0 + 2, last)) SS_XLOAD(x2, min(kb0 + 2, last))
-        SS_WLOAD(w3, min(kb0 + 3, last)) SS_XLOAD(x3, min(kb0 + 3, last))
-    }
-    if (D == 6) {
-        SS_WLOAD(w4, min(kb0 + 4, last)) SS_XLOAD(x4, min(kb0 + 4, last))
-        SS_WLOAD(w5, min(kb0 + 5, last)) SS_XLOAD(x5, min(kb0 + 5, last))
-    }
-    SS_XSTORE(0, x0, kb0 < kb1)
-    __syncthreads();
-    if (D == 6) {
-        for (int it = 0; it < part_len; it += 6) {
-            SS_TRIP(0, w0, x0, x1)
-            SS_TRIP(1, w1, x1, x2)
-            SS_TRIP(2, w2, x2, x3)
-            SS_TRIP(3, w3, x3, x4)
-            SS_TRIP(4, w4, x4, x5)
-            SS_TRIP(5, w5, x5, x0)
-        }
-    } else if (D == 4) {
-        for (int it = 0; it < part_len; it += 4) {
-            SS_TRIP(0, w0, x0, x1)
-            SS_TRIP(1, w1, x1, x2)
-            SS_TRIP(2, w2, x2, x3)
-            SS_TRIP(3, w3, x3, x0)
-        }
-    } else {
-        for (int it = 0; it < part_len; it += 2) {
-            SS_TRIP(0, w0, x0, x1)
-            SS_TRIP(1, w1, x1, x0)
-        }
-    }
-#undef SS_WLOAD
-#undef SS_XLOAD
-#undef SS_XSTORE
-#undef SS_COMPUTE
-#undef SS_TRIP
-
-    if (KP > 1) {
-        if (part == 1) {
+    // this wave copies blocks wave*CP .. +CP-1 of a stage: the first MS are activation strips, the others weight strips
+    const char* src[CP];
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+    for (int c = 0; c < CP; ++c) {
+        const int blk = min(wave * CP + c, SB - 1);
+        const char* p = blk < MS ? (const char*)a.X + (size_t)min(mb0 + blk, MBT - 1) * KB * 1024
+                                 : (const char*)a.W + (size_t)min(nb0 + blk - MS, NBT - 1) * KB * 1024;
+        src[c] = p + (size_t)s0 * 1024;
+    }
+    const unsigned lane_off = lane * 16;
+    const unsigned ring0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)&ring[0][0][0];
+    auto request = [&](int trip, int slot) {   // k-blocks beyond the slice: the last one once more, never used
+        const size_t at = (size_t)min(trip, trips - 1) * 1024;
 #pragma unroll
-                for (int m = 0; m < TMS; ++m) red[i * TMS + m][tid] = acc[i][m];
+        for (int c = 0; c < CP; ++c) lds_copy_1k(ring0 + (unsigned)((slot * SB + min(wave * CP + c, SB - 1)) * 1024), src[c] + at, lane_off);
+    };
+    u32x4 xf[2][RM], wf[2][RN];
+    auto read = [&](int slot, u32x4 (&xv)[RM], u32x4 (&wv)[RN]) {
+#pragma unroll
+        for (int i = 0; i < RN; ++i) wv[i] = ring[slot][MS + wn * RN + i][lane];
+#pragma unroll
+        for (int m = 0; m < RM; ++m) xv[m] = ring[slot][wm * RM + m][lane];
+    };
+    if (trips > 0) {
+#pragma unroll
+        for (int q = 0; q < ST; ++q) request(q, q);
+        wait_copies<(ST - 1) * CP>();
+        __builtin_amdgcn_s_barrier();
+        read(0, xf[0], wf[0]);
+        int slot = 0;
+        auto trip = [&](int it, u32x4 (&xc)[RM], u32x4 (&wc)[RN], u32x4 (&xn)[RM], u32x4 (&wn_)[RN]) {
+            // the operands of this trip are in registers (the wait covers their LDS reads); the next stage has landed
+            wait_copies<(ST - 2) * CP>();
+            __builtin_amdgcn_s_barrier();
+            const size_t at = (size_t)min(it + ST, trips - 1) * 1024;
+            const int free_slot = slot;
+            slot = slot + 1 == ST ? 0 : slot + 1;
+            const u32x4* st = &ring[slot][0][0] + lane;
+            // CP parts: one copy, a share of the operand reads, a share of the products.  (All copies at once hold up
+            // every wave of the workgroup behind the address unit at the start of the trip.)
+#pragma unroll
+            for (int c = 0; c < CP; ++c) {
+                lds_copy_1k(ring0 + (unsigned)((free_slot * SB + min(wave * CP + c, SB - 1)) * 1024), src[c] + at, lane_off);
+                constexpr int R = RM + RN, E = RM * RN;
+#pragma unroll
+                for (int q = c * R / CP; q < (c + 1) * R / CP; ++q) {
+                    if (q < RN) wn_[q < RN ? q : 0] = st[(MS + wn * RN + q) * 64];
+                    else xn[q >= RN ? q - RN : 0] = st[(wm * RM + q - RN) * 64];
+                }
+#pragma unroll
+                for (int e = c * E / CP; e < (c + 1) * E / CP; ++e)
+                    acc[e % RN][e / RN] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wc[e % RN]),
+                                                                                 __builtin_bit_cast(f16x8, xc[e / RN]),
+                                                                                 acc[e % RN][e / RN], 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < R / CP; ++q) {
+                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x008, E / R, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        int it = 0;
+        for (; it + 2 <= trips; it += 2) {
+            trip(it, xf[0], wf[0], xf[1], wf[1]);
+            trip(it + 1, xf[1], wf[1], xf[0], wf[0]);
         }
-        __syncthreads();
-        if (part == 1) return;
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int m = 0; m < TMS; ++m) acc[i][m] += red[i * TMS + m][tid];
+        if (it < trips) trip(it, xf[0], wf[0], xf[1], wf[1]);
+        wait_copies<0>();   // nothing may still be on its way into LDS when the workgroup ends
     }
 
     const int col4 = (lane >> 4) * 4;
+    const int c0 = nb0 + wn * RN, r0 = mb0 + wm * RM;
 #pragma unroll
-    for (int m = 0; m < TMS; ++m) {
-        const int row = (mb0 + m) * 16 + (lane & 15);
+    for (int m = 0; m < RM; ++m) {
+        const int row = (r0 + m) * 16 + (lane & 15);
         if (row >= a.m_rows) continue;
         if (EPI == EPI_PARTIAL) {
             float* o = a.out + ((size_t)ks * a.m_stride + row) * a.N;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (nb0 + i < NBT)
-                    *(float4*)(o + (nb0 + i) * 16 + col4) = make_float4(acc[i][m][0], acc[i][m][1], acc[i][m][2], acc[i][m][3]);
+            for (int i = 0; i < RN; ++i)
+                if (c0 + i < NBT)
+                    *(float4*)(o + (c0 + i) * 16 + col4) = make_float4(acc[i][m][0], acc[i][m][1], acc[i][m][2], acc[i][m][3]);
         } else {
 #pragma unroll
-            for (int i = 0; i < 4; i += 2)
-                if (nb0 + i + 1 < NBT) {
-                    const int f = ((nb0 + i) >> 1) * 16 + col4;
+            for (int i = 0; i + 1 < RN; i += 2)
+                if (c0 + i + 1 < NBT) {
+                    const int f = ((c0 + i) >> 1) * 16 + col4;
                     f16_t o[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = f2h(silu_f(acc[i][m][e]) * acc[i + 1][m][e]);
@@ -880,28 +867,6 @@ __global__ __launch_bounds__(256 * KP, 2) void k_gemm_tiled(GemmArgs a, int kb_p
                 }
         }
     }
-}
-
-// SwiGLU over k-sliced partial sums: the gate|up projection was run with k-slices (its output columns are
-// in strip order: strip 2j = gate columns 16j.., strip 2j+1 = the matching up columns); this adds the
-// slices and writes silu(gate)*up as packed activations.  One thread per 4 MLP columns of a row.
-__global__ __launch_bounds__(256) void k_swiglu_reduce(const float* __restrict__ part, int ksplit, size_t part_stride,
-                                                       int m_rows, int F, int kp_out, f16_t* __restrict__ out)
-{
-    const int row = blockIdx.y;
-    const int f = (blockIdx.x * 256 + threadIdx.x) * 4;
-    if (row >= m_rows || f >= F) return;
-    const size_t g_at = (size_t)row * 2 * F + (size_t)(f >> 4) * 32 + (f & 15);
-    float4 g = make_float4(0.f, 0.f, 0.f, 0.f), u = g;
-    for (int s = 0; s < ksplit; ++s) {
-        const float4 a = *(const float4*)(part + (size_t)s * part_stride + g_at);
-        const float4 b = *(const float4*)(part + (size_t)s * part_stride + g_at + 16);
-        g.x += a.x; g.y += a.y; g.z += a.z; g.w += a.w;
-        u.x += b.x; u.y += b.y; u.z += b.z; u.w += b.w;
-    }
-    const f16_t o[4] = {f2h(silu_f(g.x) * u.x), f2h(silu_f(g.y) * u.y), f2h(silu_f(g.z) * u.z), f2h(silu_f(g.w) * u.w)};
-    const size_t at = pk_index(row, f, kp_out);
-    *(uint2*)(out + at) = *(const uint2*)o;
 }
 
 // ------------------------------------------------------------------------------------------ RoPE + KV append
@@ -1562,13 +1527,6 @@ void launch_rmsnorm(const MbState& st, float* x, const float* part, int ksplit, 
                            part ? ksplit : 0, part_stride, w, eps, sel, h_packed, d);
 }
 
-void launch_swiglu_reduce(const float* part, int ksplit, size_t part_stride, int m_rows, int F, int kp_out,
-                          f16_t* out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_swiglu_reduce, dim3((F / 4 + 255) / 256, m_rows), dim3(256), 0, s, part, ksplit, part_stride,
-                       m_rows, F, kp_out, out);
-}
-
 // k-blocks per slice; whole groups of 4 wherever a matrix with 12-bit weights would be read in that form, so that a
 // matrix without them adds up in the same order.
 static inline int slice_kb(const GemmArgs& a)
@@ -1638,20 +1596,18 @@ static void launch_sweep_p(const GemmArgs& a, int units, hipStream_t s)
     }
 }
 
-template <int TMS, int KP, int EPI>
-static void launch_tiled(const GemmArgs& a, hipStream_t s)
+template <int MS, int NS, int WM, int WN, int ST, int EPI>
+static void launch_block(const GemmArgs& a, hipStream_t s)
 {
-    const int KB = a.Kp / 32;
-    const int kbs = (KB + a.ksplit - 1) / a.ksplit;
-    const int n_ntiles = (a.N + 255) / 256, n_mtiles = (a.m_rows + TMS * 16 - 1) / (TMS * 16);
-    const int grid = (n_ntiles + 7) / 8 * 8 * n_mtiles * a.ksplit;
-    hipLaunchKernelGGL((k_gemm_tiled<TMS, KP, EPI>), dim3(grid), dim3(256 * KP), 0, s, a, kbs, n_ntiles, n_mtiles);
+    const int n_ntiles = (a.N / 16 + NS - 1) / NS, n_mtiles = ((a.m_rows + 15) / 16 + MS - 1) / MS;
+    hipLaunchKernelGGL((k_gemm_block<MS, NS, WM, WN, ST, EPI>), dim3(n_ntiles * n_mtiles * a.ksplit), dim3(64 * WM * WN), 0, s,
+                       a, (a.Kp / 32 + a.ksplit - 1) / a.ksplit, n_ntiles, n_mtiles);
 }
 
 template <int EPI>
 static void launch_gemm_epi(const GemmArgs& a, hipStream_t s)
 {
-    if (a.m_rows <= kSweepMaxRows && a.sweep_p > 0 && a.sweep_gn > 0 && a.zero_blk) {
+    if (a.block < 0 && a.m_rows <= kSweepMaxRows && a.sweep_p > 0 && a.sweep_gn > 0 && a.zero_blk) {
         const int nbw = sweep_nbw(EPI, a.m_rows);
         const int units = (a.N / 16 + nbw - 1) / nbw;
         const int per = (units + a.sweep_gn - 1) / a.sweep_gn;   // most units any workgroup owns
@@ -1663,7 +1619,7 @@ static void launch_gemm_epi(const GemmArgs& a, hipStream_t s)
         if (per <= 8) return launch_sweep_p<8, EPI, 1>(a, units, s);
         // a plan this kernel cannot run falls through to the other kernels
     }
-    if (a.m_rows <= 64) {
+    if (a.block < 0 && a.m_rows <= 64) {
         const int mt = (a.m_rows + 15) / 16;
         switch (mt) {
             case 1: launch_skinny_mt<1, EPI>(a, s); break;
@@ -1673,9 +1629,14 @@ static void launch_gemm_epi(const GemmArgs& a, hipStream_t s)
         }
         return;
     }
-    if (a.tms == 8 && a.kp != 2) return launch_tiled<8, 1, EPI>(a, s);
-    if (a.kp == 2) return launch_tiled<4, 2, EPI>(a, s);
-    launch_tiled<4, 1, EPI>(a, s);
+    // waves, strips per wave and stages of each tile of kBlockTiles
+    switch (a.block) {
+        case 0: return launch_block<16, 16, 2, 4, 4, EPI>(a, s);   // 8 waves of 8 x 4 strips, 128 KiB of LDS: one per unit
+        case 1: return launch_block<16, 12, 4, 2, 4, EPI>(a, s);   // 8 waves of 4 x 6, 112 KiB
+        case 2: return launch_block<8, 16, 2, 2, 3, EPI>(a, s);    // 4 waves of 4 x 8, 72 KiB: two per unit
+        case 3: return launch_block<8, 12, 2, 2, 4, EPI>(a, s);    // 4 waves of 4 x 6, 80 KiB
+        default: return launch_block<8, 8, 2, 2, 4, EPI>(a, s);    // 4 waves of 4 x 4, 64 KiB
+    }
 }
 
 void launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s)

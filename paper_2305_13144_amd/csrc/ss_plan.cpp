@@ -11,16 +11,44 @@ std::atomic<int> g_gemm_mode{0};
 std::atomic<int> g_sweep_split{1};
 std::atomic<int> g_tall_tiles{1};
 constexpr int kSmallMaxKsplit = 8;   // sweep and skinny kernels: at most 8 k-slices
-constexpr int kTiledMaxKsplit = 4;   // tiled kernel: at most 4
-constexpr int kTiledNoSliceTiles = 256;  // from this many tiles on (one per compute unit) the tiled kernel runs unsliced
-constexpr int kTiledFullGroups = 320;    // below that, k-slices double until it has this many workgroups
+// Block kernel: rows up to which k may be cut in 4 and in 2 (more rows fill the chip without, and the partial sums of
+// every slice are written and read again)
+constexpr int kBlockRows4 = 512, kBlockRows2 = 2048;
+constexpr double kBlockStart = 3300.0;        // ns: launch, first stage, epilogue
+constexpr double kBlockWrite = 3.84;          // bytes per ns at which results are written
+constexpr double kBlockStream = 3.64;         // bytes per ns at which the weights arrive at best
+constexpr double kPartialRead = 4.5;          // bytes per ns at which the consumer adds further slices
+
+}
+
+// Trip times fitted to 300 timings of the five tiles at the 7B shapes, 100 to 12311 rows, 1 to 4 slices (8 % off in the
+// root mean square; the plan taken is 0.7 % slower than the best of them on average, 10 % at worst).
+const BlockTile block_tiles[kBlockTiles] = {{16, 16, 1, 615.0, 740.0}, {16, 12, 1, 485.0, 613.0}, {8, 16, 2, 412.0, 772.0},
+                                            {8, 12, 2, 313.0, 619.0}, {8, 8, 2, 239.0, 475.0}};
+
+namespace {
+// Time of a projection in the block kernel, in nanoseconds: rounds of workgroups over the chip times the k-blocks of a
+// slice, the results, and what adding up the slices costs the consumer.
+double block_ns(const BlockTile& t, int ks, int N, int Kp, int m_rows, int epilogue, int n_cu)
+{
+    const long long strips_m = (m_rows + 15) / 16, strips_n = N / 16;
+    const long long wgs = ((strips_m + t.ms - 1) / t.ms) * ((strips_n + t.ns - 1) / t.ns) * ks;
+    const long long full = wgs / ((long long)n_cu * t.per_cu), rest = wgs % ((long long)n_cu * t.per_cu);
+    const double trip = (double)full * t.trip_full + (rest > n_cu ? t.trip_full : rest > 0 ? t.trip_one : 0.0);
+    const double cells = (double)m_rows * N;
+    const double work = kBlockStart + trip * ((Kp / 32 + ks - 1) / ks) +
+                        cells * (epilogue == EPI_SWIGLU ? 1.0 : 4.0 * ks) / (kBlockWrite * 1000.0);
+    const double stream = kBlockStart + (double)N * Kp * 2 / (kBlockStream * 1000.0);
+    const double ns = work > stream ? work : stream;
+    return epilogue == EPI_SWIGLU ? ns : ns + cells * 4.0 * (ks - 1) / (kPartialRead * 1000.0);
+}
 }
 
 void set_gemm_mode(int mode)
 {
     // bit 2 (value 4) added to a mode: the sweep kernel never splits a unit between two waves (A/B measurements)
     g_sweep_split.store((mode & 4) ? 0 : 1, std::memory_order_relaxed);
-    // bit 3 (value 8): the tiled kernel never uses 128-row tiles (A/B measurements)
+    // bit 3 (value 8): the block kernel never uses its largest tile (A/B measurements)
     g_tall_tiles.store((mode & 8) ? 0 : 1, std::memory_order_relaxed);
     g_gemm_mode.store(mode & 3, std::memory_order_relaxed);
 }
@@ -36,8 +64,8 @@ int gemm_mode() { return g_gemm_mode.load(std::memory_order_relaxed); }
 // Skinny kernel (<= 64 rows otherwise), from sweeps on the 7B shapes: aim at 512+ workgroups; 4 strips per
 // workgroup halve the activation re-reads and win when k is short, 2 strips when k is long or when the
 // epilogue forbids k-slices (SwiGLU, logits); k-slices double until there are 512 workgroups, at most 8,
-// never leaving a wave fewer than 4 k-blocks.  Tiled kernel: ksplit fills the chip when there are few
-// 64x256 tiles.
+// never leaving a wave fewer than 4 k-blocks.  Block kernel (everything else): the tile and the number of k-slices
+// with the smallest estimated time.
 
 // Strips per wave of the sweep kernel: a gate/up pair for the SwiGLU epilogue, otherwise one.  One strip per wave gives
 // twice the units of two, so half the k-slices (longer sweeps, half the partial sums).  Two strips per wave halve the LDS
@@ -48,13 +76,13 @@ int sweep_nbw(int epilogue, int /*m_rows*/) { return epilogue == EPI_SWIGLU ? 2 
 
 GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ksplit)
 {
-    GemmPlan p{1, 2, 4, 1, 0, 0, 1, 0, 4};
+    GemmPlan p{1, 2, 4, 1, 0, 0, 1, 0, -1, 4};
     const int KB = Kp / 32;
     const int mode = gemm_mode();
     if (m_rows <= kSweepMaxRows) {
         const size_t w_per_cu = (size_t)N * (size_t)Kp * 2 / (size_t)n_cu;
         const size_t mt_rows = (size_t)(m_rows + 15) / 16;   // activation re-reads grow with the row strips: sweep earlier
-        if (mode == 2 || (mode == 0 && w_per_cu * mt_rows >= ((size_t)160 << 10))) {
+        if (mode == 2 || (mode == 0 && m_rows <= kSweepAutoRows && w_per_cu * mt_rows >= ((size_t)160 << 10))) {
             if (epilogue == EPI_SWIGLU) max_ksplit = 1;   // fused epilogue: no k-slices
             const int nbw = sweep_nbw(epilogue, m_rows);
             const int units = (N / 16 + nbw - 1) / nbw;
@@ -89,38 +117,32 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
             p.ksplit *= 2;
         return p;
     }
-    // Tiled kernel.  Many tiles (prompt forwards): 4-wave workgroups, two per CU, no slicing.  Few tiles
-    // (short prompt forwards; decode batches of 65-256 rows on matrices too small for the sweep kernel): measured on the 7B shapes, outer k-slices up to 4 (partial sums
-    // through HBM are small while rows are few) beat everything else; where slicing is impossible an
-    // 8-wave workgroup halves the k range inside the workgroup instead.
-    // Tile height: 64 token-rows, or 128 from kTiledTallFrom rows on.  A 64 x 256 tile asks L2 for 20 KiB per 16
-    // matrix-core instructions of every wave, which is more than a compute unit can take in while its matrix cores
-    // run; a 128 x 256 tile asks for 24 KiB per 32.  Below that row count tall tiles leave too many rows idle.
-    p.tms = (m_rows >= kTiledTallFrom && g_tall_tiles.load(std::memory_order_relaxed)) ? 8 : 4;
-    const int tiles = ((N + 255) / 256) * ((m_rows + p.tms * 16 - 1) / (p.tms * 16));
-    // Measured at the 7B shape, same GPU, against slicing up to 512 workgroups whenever there are fewer than 512 tiles:
-    // prompt forward of 640 token-rows 12.6 against 13.8 ms (q|k|v, 480 tiles, now unsliced; o and down, 160 tiles, two
-    // slices instead of four), 1280 token-rows 19.6 against 21.9, decode steps of 129-256 rows (run by this kernel at the time) 3-4 % shorter; stopping at
-    // 256 workgroups instead of 320 costs 4 % at 1024 token-rows, going on to 384 costs 5 % at 640 and 1280.
-    if (tiles >= kTiledNoSliceTiles) return p;
-    while (tiles * p.ksplit < kTiledFullGroups && p.ksplit * 2 <= max_ksplit && p.ksplit < kTiledMaxKsplit &&
-           KB / (p.ksplit * 2) >= 16)
-        p.ksplit *= 2;
-    if (p.ksplit == 1) p.kp = 2;
+    if (epilogue == EPI_SWIGLU) max_ksplit = 1;   // fused epilogue: no k-slices
+    const bool tall = m_rows >= kTiledTallFrom && g_tall_tiles.load(std::memory_order_relaxed);
+    const int most = m_rows <= kBlockRows4 ? 4 : m_rows <= kBlockRows2 ? 2 : 1;
+    double best = 0.0;
+    for (int t = tall ? 0 : 1; t < kBlockTiles; ++t)
+        for (int ks = 1; ks <= std::min(most, max_ksplit) && (ks == 1 || KB / ks >= 16); ks *= 2) {
+            const double ns = block_ns(block_tiles[t], ks, N, Kp, m_rows, epilogue, n_cu);
+            if (p.block < 0 || ns < best) {
+                best = ns;
+                p.block = t;
+                p.ksplit = ks;
+            }
+        }
+    p.tms = p.block == 0 ? 8 : 4;
     return p;
 }
 
 size_t gemm_partial_rows_bound(int N, int n_max, bool sliced_only)
 {
-    // up to kSweepMaxRows rows: at most kSmallMaxKsplit slices; above: the tiled kernel slices only while it
-    // has fewer than kTiledNoSliceTiles tiles, i.e. up to 128 * floor((kTiledNoSliceTiles - 1) / column tiles) rows
-    // (its tallest tile)
+    // up to kSweepMaxRows rows: at most kSmallMaxKsplit slices; the block kernel: 4 up to kBlockRows4 rows, 2 up to
+    // kBlockRows2.  sliced_only: plans with slices exist only without the SwiGLU epilogue, whatever the rows.
     const size_t n = (size_t)std::max(n_max, 1);
-    const size_t col_tiles = (size_t)(N + 255) / 256;
-    const size_t tiled_rows = 128 * ((size_t)(kTiledNoSliceTiles - 1) / std::max<size_t>(col_tiles, 1));
     size_t need = sliced_only ? 1 : n;
     need = std::max(need, (size_t)kSmallMaxKsplit * std::min<size_t>(n, (size_t)kSweepMaxRows));
-    need = std::max(need, (size_t)kTiledMaxKsplit * std::min(n, tiled_rows));
+    need = std::max(need, (size_t)4 * std::min<size_t>(n, (size_t)kBlockRows4));
+    need = std::max(need, (size_t)2 * std::min<size_t>(n, (size_t)kBlockRows2));
     return need;
 }
 

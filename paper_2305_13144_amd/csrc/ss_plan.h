@@ -10,19 +10,32 @@ namespace ss {
 enum Epilogue { EPI_PARTIAL = 0, EPI_SWIGLU = 1 };
 
 constexpr int kSweepMaxRows = 256;   // 16 row strips: accumulators and the LDS chunk of the sweep kernel still fit
+// Rows up to which it is chosen: 9 row strips.  Per step of the sweep / block kernel, 7B, microseconds: 130 rows q|k|v
+// 28.5 / 30.6, gate|up 44.6 / 48.4, down 28.3 / 29.2, o 14.7 / 14.1; 163 rows 36.7 / 31.3, 58.9 / 51.3, 33.0 / 29.9, 16.6 / 14.5.
+constexpr int kSweepAutoRows = 144;
+
+constexpr int kNarrowMaxRows = 96;   // most token-rows for which the 12-bit weights are read
+
+// Block kernel: tiles in 16-row strips, workgroups that share a compute unit, and the time of one k-block in
+// nanoseconds while a unit holds one workgroup and while it holds per_cu of them.
+struct BlockTile {
+    int ms, ns, per_cu;
+    double trip_one, trip_full;
+};
+constexpr int kBlockTiles = 5;
+extern const BlockTile block_tiles[kBlockTiles];
 
 struct GemmPlan {
-    int ksplit, nb, kd, kp;
+    int ksplit, nb, kd, kp;   // kp: k-parts inside a workgroup (1: no kernel splits k there)
     int sweep_p, sweep_gn;
     int sweep_kh;   // sweep kernel: waves per unit (1 or 2)
     int narrow;     // sweep and skinny kernels: > 0 if the 12-bit form of the weights is read where the matrix has one;
                     // sweep kernel: then this many waves per unit
-    int tms;        // tiled kernel: row strips per tile (4 = 64 rows, 8 = 128 rows)
+    int block;      // block kernel: index into block_tiles; -1: one of the others
+    int tms;        // block kernel: row strips per wave, 8 with the largest tile, else 4
 };
 
-constexpr int kNarrowMaxRows = 96;   // most token-rows for which the 12-bit weights are read
-
-constexpr int kTiledTallFrom = 896;   // token-rows from which the tiled kernel uses 128-row tiles
+constexpr int kTiledTallFrom = 896;   // token-rows from which the block kernel may use its largest tile
 
 // n_cu: compute units of the device (the sweep kernel runs one workgroup per unit).
 // max_ksplit: 1 when the consumer reads the output directly (logits).

@@ -1,0 +1,49 @@
+"""The projections of prompt forwards at the edges of the block kernel's tiles, through whole forwards, against the
+oracle: row counts around 16, 64, 128 and 256, widths that are no multiple of a tile (gate|up of 344 strips, a head of 65),
+an odd number of k-blocks per slice, the largest tile (from 896 token-rows on) and the others forced in its place."""
+import numpy as np
+import pytest
+
+from oracle.model_oracle import OracleModel
+from paper_2305_13144_amd import binding as ss
+from paper_2305_13144_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SHAPE = synth.ModelShape("block", 1, 512, 4, 128, 2752, 1040)
+# fp32 sums of products of halves: the oracle has exact weights and unrounded activations; one layer stays within 2e-3
+# (a projection input is rounded once to 11 bits: 2^-12 relative per rounding, six of them and the cache's two)
+TOL = 2e-3
+
+
+@pytest.fixture(scope="module")
+def model(oracle_built):
+    W = synth.make_weights(SHAPE, seed=9, norm_jitter=0.1, threads=1)
+    gw = ss.Weights(SHAPE, W)
+    yield gw, OracleModel(SHAPE, W, "f32")
+    gw.close()
+
+
+@pytest.mark.parametrize("mode", [0, 1, 8])
+@pytest.mark.parametrize("rows", [65, 127, 129, 145, 256, 257, 513, 895, 897, 1025])
+def test_prompt_logits_match_the_oracle(model, rows, mode):
+    gw, om = model
+    rng = np.random.default_rng(rows)
+    lens, left = [], rows
+    while left > 0:
+        n = int(min(left, rng.integers(20, 60)))
+        lens.append(n)
+        left -= n
+    toks = rng.integers(0, SHAPE.vocab, rows).astype(np.int32)
+    offs = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ss.ss_set_gemm_mode(mode)
+    try:
+        got = ss.ss_forward_logits(gw, toks, offs, np.array(lens, np.int32), all_prompt_logits=True)
+    finally:
+        ss.ss_set_gemm_mode(0)
+    for i in sorted({0, 1, len(lens) // 2, len(lens) - 1} & set(range(len(lens)))):
+        ref = om.teacher_forced(toks[offs[i]:offs[i + 1]], first=0)
+        err = np.abs(got[offs[i]:offs[i + 1]] - ref).max() / np.abs(ref).max()
+        assert err <= TOL, (rows, mode, i, err)
+    # every row is an independent sequence of sums: the same prompts alone give the same logits within rounding
+    assert np.isfinite(got).all()
