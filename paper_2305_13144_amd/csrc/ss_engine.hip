@@ -2,13 +2,17 @@
 // forward over a list of token-rows, and the C-ABI entry points built on it (Sec. 4.1 of the paper:
 // micro-batch generation with a cap, failure collection and recomputation after the group).
 #include <hip/hip_runtime.h>
+#include <sys/mman.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <atomic>
 #include <chrono>
 #include <cmath>
+#include <condition_variable>
 #include <cstdio>
 #include <cstring>
+#include <deque>
 #include <mutex>
 #include <numeric>
 #include <thread>
@@ -107,12 +111,13 @@ struct Buf {
 
 struct Workspace {
     Buf x, h, ao, act, qrot, pqkv, pd, hsel, logits, kv, ints, i64s, draws;
+    Buf logits2, steps;   // ss_forward_logits: the other logits buffer, the tables of every decode step
     // Non-null: every buffer is carved out of [arena, arena + arena_bytes) instead of being allocated.
     char* arena = nullptr;
     size_t arena_bytes = 0;
     void release()
     {
-        for (Buf* b : {&x, &h, &ao, &act, &qrot, &pqkv, &pd, &hsel, &logits, &kv, &ints, &i64s, &draws})
+        for (Buf* b : {&x, &h, &ao, &act, &qrot, &pqkv, &pd, &hsel, &logits, &kv, &ints, &i64s, &draws, &logits2, &steps})
             b->release();
     }
 };
@@ -124,8 +129,49 @@ struct Workspace {
 // on the other lanes at the same time (the weights are shared and only read).
 namespace {
 constexpr int kLanes = SS_IN_FLIGHT_MAX;
+// What ss_forward_logits moves its results with: a stream of its own, so that the logits of one forward leave while the
+// next one runs, and a small ring of pinned pieces.  Made on the first such call, kept with the handle.
+struct LogitPipe {
+    static constexpr int kSlots = 4;
+    static constexpr size_t kSlotBytes = (size_t)4 << 20;
+    hipStream_t copy = nullptr;
+    hipEvent_t forward_done[2] = {nullptr, nullptr}, left[2] = {nullptr, nullptr}, landed[kSlots] = {};
+    char* pin[kSlots] = {};
+    size_t slot_bytes = 0;
+    int ensure(size_t row_bytes)
+    {
+        if (!copy) HIPCHK(hipStreamCreateWithFlags(&copy, hipStreamNonBlocking));
+        for (hipEvent_t* e : {&forward_done[0], &forward_done[1], &left[0], &left[1], &landed[0], &landed[1], &landed[2], &landed[3]})
+            if (!*e) HIPCHK(hipEventCreateWithFlags(e, hipEventDisableTiming));
+        const size_t want = std::max(kSlotBytes, row_bytes);   // at least a row
+        if (want <= slot_bytes) return SS_OK;
+        slot_bytes = 0;
+        for (char*& p : pin) {
+            if (p) (void)hipHostFree(p);
+            p = nullptr;
+            HIPCHK(hipHostMalloc((void**)&p, want, hipHostMallocDefault));
+        }
+        slot_bytes = want;
+        return SS_OK;
+    }
+    void release()
+    {
+        if (copy) (void)hipStreamSynchronize(copy);
+        for (char*& p : pin) {
+            if (p) (void)hipHostFree(p);
+            p = nullptr;
+        }
+        for (hipEvent_t e : {forward_done[0], forward_done[1], left[0], left[1], landed[0], landed[1], landed[2], landed[3]})
+            if (e) (void)hipEventDestroy(e);
+        if (copy) (void)hipStreamDestroy(copy);
+    }
+};
+
 struct Lane {
     hipStream_t stream = nullptr;
+    LogitPipe pipe;
+    float* cur_logits = nullptr;   // where the forward in flight writes its logits (null: ws.logits)
+    bool cur_choose = true;        // whether it ends with the token choice
     Workspace ws;
     int32_t* d_sel = nullptr;  // carved from ws.ints
     MbState st{};
@@ -457,12 +503,14 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
     }
     f16_t* hsel = ws.hsel.as<f16_t>();
     ss::launch_rmsnorm(st, x, pd, ks_d, st_d, w->final_norm, c.rms_eps, d_sel, d_nsel, hsel, d, n_sel, s);
-    ss::launch_gemm(mk(w->lm_head, hsel, ws.logits.as<float>(), nullptr, n_sel, 0, p_lm), ss::EPI_PARTIAL, s);
+    float* logits = ln.cur_logits ? ln.cur_logits : ws.logits.as<float>();
+    ss::launch_gemm(mk(w->lm_head, hsel, logits, nullptr, n_sel, 0, p_lm), ss::EPI_PARTIAL, s);
+    if (!ln.cur_choose) return;
     if (ln.cur_inv_temp > 0.f)
-        ss::launch_sample(ws.logits.as<float>(), V, d_nsel ? d_nsel : st.d_n, st, ln.cur_draws, ln.cur_ids, ln.cur_seed,
+        ss::launch_sample(logits, V, d_nsel ? d_nsel : st.d_n, st, ln.cur_draws, ln.cur_ids, ln.cur_seed,
                           ln.cur_inv_temp, n_sel, s);
     else
-        ss::launch_argmax(ws.logits.as<float>(), V, d_nsel ? d_nsel : st.d_n, st.am, n_sel, s);
+        ss::launch_argmax(logits, V, d_nsel ? d_nsel : st.d_n, st.am, n_sel, s);
 }
 
 int check_prompts(const ss_weights* w, const int32_t* toks, const int32_t* offs, int B)
@@ -479,27 +527,27 @@ int check_prompts(const ss_weights* w, const int32_t* toks, const int32_t* offs,
     return SS_OK;
 }
 
-struct Upload {
-    std::vector<int32_t> v;
-    hipStream_t s;
-    int put(int32_t* dst, const int32_t* src, size_t n)
-    {
-        HIPCHK(hipMemcpyAsync(dst, src, n * 4, hipMemcpyHostToDevice, s));
-        return SS_OK;
-    }
-};
-
 // Uploads the state of a prompt forward: token-rows are the concatenated prompt positions.
 //   lens[i]   tokens of row i processed by this forward (positions 0..lens[i]-1)
 //   slab[i]   key/value slots reserved for row i
+//   n_live    rows that the forward's logits are wanted for
+// The tables are neighbours in one array: they are laid out here as there and uploaded in one copy (twelve small ones
+// took about 0.1 ms of a call).
 int upload_prompt_state(Lane& ln, const int32_t* toks, const int32_t* offs, const int32_t* lens, int B,
-                        const int32_t* slab, const int32_t* limit, const std::vector<int32_t>& sel, hipStream_t s)
+                        const int32_t* slab, const int32_t* limit, const std::vector<int32_t>& sel, int n_live, hipStream_t s)
 {
     const MbState& st = ln.st;
     int n = 0;
     for (int i = 0; i < B; ++i) n += lens[i];
-    std::vector<int32_t> tok(n), row(n), pos(n), live(B), plen(B), first(B);
+    int32_t* const base = st.d_n;
+    std::vector<int32_t> tab((size_t)(ln.d_sel - base) + sel.size(), 0);
     std::vector<int64_t> so(B);
+    auto at_host = [&](const int32_t* dev) { return tab.data() + (dev - base); };
+    int32_t *tok = at_host(st.tr_tok), *row = at_host(st.tr_row), *pos = at_host(st.tr_pos), *live = at_host(st.live_row),
+            *plen = at_host(st.row_plen), *first = at_host(st.row_j0);
+    *at_host(st.d_n) = n;
+    *at_host(st.d_nlive) = n_live;
+    *at_host(st.d_active) = B;
     int at = 0;
     int64_t slot = 0;
     for (int i = 0; i < B; ++i) {
@@ -514,20 +562,13 @@ int upload_prompt_state(Lane& ln, const int32_t* toks, const int32_t* offs, cons
         so[i] = slot;
         slot += slab[i];
     }
-    const int32_t hdr[4] = {n, 0, B, B};
-    HIPCHK(hipMemcpyAsync(st.d_n, hdr, 16, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(st.tr_tok, tok.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(st.tr_row, row.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(st.tr_pos, pos.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(st.live_row, live.data(), (size_t)B * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(st.row_plen, plen.data(), (size_t)B * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(st.row_j0, first.data(), (size_t)B * 4, hipMemcpyHostToDevice, s));
+    std::copy(limit, limit + B, at_host(st.row_limit));
+    std::copy(slab, slab + B, at_host(st.row_cap));
+    std::copy(sel.begin(), sel.end(), at_host(ln.d_sel));
     ln.prompt_rows = B;
-    ln.prompt_max_len = *std::max_element(plen.begin(), plen.end());
-    HIPCHK(hipMemcpyAsync(st.row_limit, limit, (size_t)B * 4, hipMemcpyHostToDevice, s));
-    HIPCHK(hipMemcpyAsync(st.row_cap, slab, (size_t)B * 4, hipMemcpyHostToDevice, s));
+    ln.prompt_max_len = *std::max_element(lens, lens + B);
+    HIPCHK(hipMemcpyAsync(base, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(st.row_so, so.data(), (size_t)B * 8, hipMemcpyHostToDevice, s));
-    if (!sel.empty()) HIPCHK(hipMemcpyAsync(ln.d_sel, sel.data(), sel.size() * 4, hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));   // the host vectors above die with this frame
     return SS_OK;
 }
@@ -619,7 +660,7 @@ int decode_microbatch_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_
     const int compact = (flags & SS_COMPACT) ? 1 : 0;
     const int eos_id = gen ? gen->eos_id : -1;
 
-    if (int rc = upload_prompt_state(ln, prompt_tokens, prompt_offsets, lens.data(), B, slab.data(), limit.data(), sel, s))
+    if (int rc = upload_prompt_state(ln, prompt_tokens, prompt_offsets, lens.data(), B, slab.data(), limit.data(), sel, B, s))
         return rc;
     ChoiceGuard choice{ln};
     if (gen && gen->temperature > 0.f) {
@@ -850,6 +891,7 @@ extern "C" void ss_weights_destroy(ss_weights* w)
     (void)hipSetDevice(w->device);
     for (Lane& ln : w->lane) {
         if (ln.stream) (void)hipStreamSynchronize(ln.stream);
+        ln.pipe.release();
         ln.ws.release();
         if (ln.stream) (void)hipStreamDestroy(ln.stream);
         if (ln.h_poll) (void)hipHostFree(ln.h_poll);
@@ -946,6 +988,93 @@ extern "C" int ss_generate_microbatch(ss_weights* w, const int32_t* prompt_token
 
 namespace {
 
+// Host threads that copy finished rows to the caller's array (and first have its pages mapped, while the GPU still works
+// on the first forward).  Without threads (few bytes, or none to be had) the caller copies itself.
+class RowCopier {
+public:
+    explicit RowCopier(int n_threads)
+    {
+        for (int i = 0; i < n_threads; ++i) {
+            try {
+                threads_.emplace_back([this] { run(); });
+            } catch (...) {
+                break;
+            }
+        }
+    }
+    ~RowCopier()   // finishes what was handed in: the caller's array is written by nobody afterwards
+    {
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            stop_ = true;
+        }
+        work_.notify_all();
+        for (std::thread& t : threads_) t.join();
+    }
+    // dst <- src, `busy` being counted down when it is done; src == nullptr: map dst's pages
+    void add(char* dst, const char* src, size_t bytes, int* busy)
+    {
+        if (threads_.empty()) {
+            if (src) std::memcpy(dst, src, bytes);
+            return;
+        }
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            jobs_.push_back({dst, src, bytes, busy});
+            if (busy) ++*busy;
+        }
+        work_.notify_one();
+    }
+    void wait(const int& busy)
+    {
+        std::unique_lock<std::mutex> lock(mu_);
+        idle_.wait(lock, [&] { return busy == 0; });
+    }
+    size_t threads() const { return threads_.size(); }
+
+private:
+    struct Job {
+        char* dst;
+        const char* src;
+        size_t bytes;
+        int* busy;
+    };
+    void run()
+    {
+        std::unique_lock<std::mutex> lock(mu_);
+        for (;;) {
+            work_.wait(lock, [&] { return stop_ || !jobs_.empty(); });
+            if (jobs_.empty()) return;
+            const Job j = jobs_.front();
+            jobs_.pop_front();
+            lock.unlock();
+            if (j.src) {
+                std::memcpy(j.dst, j.src, j.bytes);
+            } else {
+#ifdef MADV_POPULATE_WRITE
+                const uintptr_t page = (uintptr_t)sysconf(_SC_PAGESIZE);
+                const uintptr_t p0 = ((uintptr_t)j.dst + page - 1) / page * page, p1 = ((uintptr_t)j.dst + j.bytes) / page * page;
+                if (p1 > p0) (void)madvise((void*)p0, p1 - p0, MADV_POPULATE_WRITE);   // contents stay; not known: no harm
+#endif
+            }
+            lock.lock();
+            if (j.busy && --*j.busy == 0) idle_.notify_all();
+        }
+    }
+    std::mutex mu_;
+    std::condition_variable work_, idle_;
+    std::deque<Job> jobs_;
+    std::vector<std::thread> threads_;
+    bool stop_ = false;
+};
+
+constexpr size_t kCopyThreadsFrom = (size_t)8 << 20;   // bytes of logits from which host threads copy them
+constexpr int kCopyThreads = 4;
+
+// One forward per position, its logits copied out while the next forward runs: forwards alternate between two logits
+// buffers, the copies go through a ring of pinned pieces on a stream of their own, and the tables of all steps (the
+// tokens are given, so they are known) are uploaded once.  163 rows, 7B: 100 ms with a copy to pageable memory, a host
+// copy and four uploads between any two forwards.
 int forward_logits_impl(const ss_weights* w, Lane& ln, hipStream_t s, const int32_t* tokens, const int32_t* offsets,
                         int32_t B, const int32_t* n_prompt, int32_t all_prompt_logits, float* logits_out)
 {
@@ -973,49 +1102,130 @@ int forward_logits_impl(const ss_weights* w, Lane& ln, hipStream_t s, const int3
         max_extra = std::max(max_extra, len[i] - np[i]);
     }
     const int n_sel = (int)sel.size();
+    const size_t row_bytes = (size_t)V * 4;
     HIPCHK(hipSetDevice(w->device));
     if (int rc = ensure_workspace(w, ln, std::max(n_p, B), B, std::max(n_sel, B), slots, 1, s)) return rc;
-    const MbState& st = ln.st;
+    const MbState st = ln.st;
+    // decode steps: rows that still have a forced token feed it at their next position.  Step g's tables lie at
+    // table_at[g] of one array: the row count, then tokens, rows and positions
+    std::vector<int32_t> tables;
+    std::vector<size_t> table_at(max_extra + 1, 0);
+    std::vector<int> step_n(max_extra + 1, n_sel);
+    for (int g = 1; g <= max_extra; ++g) {
+        table_at[g] = tables.size();
+        int n = 0;
+        for (int i = 0; i < B; ++i) n += len[i] - np[i] >= g;
+        step_n[g] = n;
+        tables.resize(table_at[g] + (size_t)ss::round_up(4 + 3 * n, 4));
+        int32_t* t = tables.data() + table_at[g];
+        t[0] = n;
+        int j = 0;
+        for (int i = 0; i < B; ++i)
+            if (len[i] - np[i] >= g) {
+                t[4 + j] = tokens[offsets[i] + np[i] + g - 1];
+                t[4 + n + j] = i;
+                t[4 + 2 * n + j] = np[i] + g - 1;
+                ++j;
+            }
+    }
+    if (max_extra > 0) {
+        if (int rc = ln.ws.steps.ensure(tables.size() * 4, false)) return rc;
+        if (int rc = ln.ws.logits2.ensure((size_t)ss::round_up(B, 16) * row_bytes, false)) return rc;
+    }
+    if (int rc = ln.pipe.ensure(row_bytes)) return rc;
     // prompt forward over the first n_prompt[i] tokens of every row
     std::vector<int32_t> ptoks, poffs(B + 1, 0);
     for (int i = 0; i < B; ++i) {
         ptoks.insert(ptoks.end(), tokens + offsets[i], tokens + offsets[i] + np[i]);
         poffs[i + 1] = (int32_t)ptoks.size();
     }
-    if (int rc = upload_prompt_state(ln, ptoks.data(), poffs.data(), np.data(), B, slab.data(), limit.data(), sel, s))
+    if (!tables.empty())
+        HIPCHK(hipMemcpyAsync(ln.ws.steps.p, tables.data(), tables.size() * 4, hipMemcpyHostToDevice, s));
+    if (int rc = upload_prompt_state(ln, ptoks.data(), poffs.data(), np.data(), B, slab.data(), limit.data(), sel, n_sel, s))
         return rc;
-    const int32_t nsel32 = n_sel;
-    HIPCHK(hipMemcpyAsync(st.d_nlive, &nsel32, 4, hipMemcpyHostToDevice, s));
-    forward(w, ln, n_p, n_sel, ln.d_sel, st.d_nlive, false, s);
-    std::vector<float> lg((size_t)std::max(n_sel, B) * V);
-    HIPCHK(hipMemcpyAsync(lg.data(), ln.ws.logits.p, (size_t)n_sel * V * 4, hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    if (all_prompt_logits) {
-        std::memcpy(logits_out, lg.data(), (size_t)n_sel * V * 4);
-    } else {
-        for (int i = 0; i < B; ++i) std::memcpy(logits_out + out_base[i] * V, lg.data() + (size_t)i * V, (size_t)V * 4);
+
+    LogitPipe& pipe = ln.pipe;
+    const hipStream_t cs = max_extra > 0 ? pipe.copy : s;   // one forward: nothing to overlap its copy with
+    int busy[LogitPipe::kSlots] = {};
+    struct Quiet {   // however the call ends: nothing of it still runs on the device, the lane is as it was
+        Lane& ln;
+        hipStream_t s;
+        MbState st;
+        ~Quiet()
+        {
+            (void)hipStreamSynchronize(s);
+            (void)hipStreamSynchronize(ln.pipe.copy);
+            ln.st = st;
+            ln.cur_logits = nullptr;
+            ln.cur_choose = true;
+        }
+    } quiet{ln, s, st};
+    RowCopier copier(out_rows * row_bytes >= kCopyThreadsFrom ? kCopyThreads : 0);
+    if (copier.threads()) {
+        const size_t total = out_rows * row_bytes, part = (size_t)2 << 20;
+        for (size_t at = 0; at < total; at += part) copier.add((char*)logits_out + at, nullptr, std::min(part, total - at), nullptr);
     }
-    // decode steps: rows that still have a forced token feed it at their next position
-    for (int g = 1; g <= max_extra; ++g) {
-        std::vector<int32_t> tok, row, pos;
-        for (int i = 0; i < B; ++i)
-            if (len[i] - np[i] >= g) {
-                tok.push_back(tokens[offsets[i] + np[i] + g - 1]);
-                row.push_back(i);
-                pos.push_back(np[i] + g - 1);
+    ln.cur_choose = false;
+    float* const bufs[2] = {ln.ws.logits.as<float>(), ln.ws.logits2.as<float>()};
+    auto launch = [&](int g) -> int {
+        const int b = g & 1;
+        if (g >= 2) HIPCHK(hipStreamWaitEvent(s, pipe.left[b], 0));   // the buffer's last logits have been copied out
+        ln.cur_logits = bufs[b];
+        if (g == 0) {
+            forward(w, ln, n_p, n_sel, ln.d_sel, st.d_nlive, false, s);
+        } else {
+            int32_t* t = ln.ws.steps.as<int32_t>() + table_at[g];
+            ln.st.d_n = t;
+            ln.st.tr_tok = t + 4;
+            ln.st.tr_row = t + 4 + step_n[g];
+            ln.st.tr_pos = t + 4 + 2 * step_n[g];
+            forward(w, ln, step_n[g], step_n[g], nullptr, nullptr, true, s);
+        }
+        if (cs != s) HIPCHK(hipEventRecord(pipe.forward_done[b], s));
+        return SS_OK;
+    };
+    std::vector<float*> dst;
+    auto drain = [&](int g) -> int {
+        const int b = g & 1;
+        dst.clear();
+        if (g == 0 && all_prompt_logits) {
+            for (int r = 0; r < n_sel; ++r) dst.push_back(logits_out + (size_t)r * V);
+        } else {
+            for (int i = 0; i < B; ++i)
+                if (g == 0 || len[i] - np[i] >= g) dst.push_back(logits_out + (out_base[i] + g) * V);
+        }
+        if (cs != s) HIPCHK(hipStreamWaitEvent(cs, pipe.forward_done[b], 0));
+        const size_t rows = dst.size(), per = pipe.slot_bytes / row_bytes, pieces = (rows + per - 1) / per;
+        auto send = [&](size_t k) -> int {
+            const int slot = (int)(k % LogitPipe::kSlots);
+            copier.wait(busy[slot]);
+            HIPCHK(hipMemcpyAsync(pipe.pin[slot], bufs[b] + k * per * V, std::min(per, rows - k * per) * row_bytes,
+                                  hipMemcpyDeviceToHost, cs));
+            HIPCHK(hipEventRecord(pipe.landed[slot], cs));
+            return SS_OK;
+        };
+        for (size_t k = 0; k < std::min<size_t>(pieces, LogitPipe::kSlots); ++k)
+            if (int rc = send(k)) return rc;
+        if (pieces <= (size_t)LogitPipe::kSlots) HIPCHK(hipEventRecord(pipe.left[b], cs));
+        for (size_t k = 0; k < pieces; ++k) {
+            const int slot = (int)(k % LogitPipe::kSlots);
+            HIPCHK(hipEventSynchronize(pipe.landed[slot]));
+            for (size_t r = k * per; r < std::min(rows, (k + 1) * per); ++r)
+                copier.add((char*)dst[r], pipe.pin[slot] + (r - k * per) * row_bytes, row_bytes, &busy[slot]);
+            if (k + LogitPipe::kSlots < pieces) {
+                if (int rc = send(k + LogitPipe::kSlots)) return rc;
+                if (k + LogitPipe::kSlots + 1 == pieces) HIPCHK(hipEventRecord(pipe.left[b], cs));
             }
-        const int n = (int)tok.size();
-        const int32_t n32 = n;
-        HIPCHK(hipMemcpyAsync(st.d_n, &n32, 4, hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(st.tr_tok, tok.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(st.tr_row, row.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-        HIPCHK(hipMemcpyAsync(st.tr_pos, pos.data(), (size_t)n * 4, hipMemcpyHostToDevice, s));
-        forward(w, ln, n, n, nullptr, nullptr, true, s);
-        HIPCHK(hipMemcpyAsync(lg.data(), ln.ws.logits.p, (size_t)n * V * 4, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
-        for (int j = 0; j < n; ++j)
-            std::memcpy(logits_out + (out_base[row[j]] + g) * V, lg.data() + (size_t)j * V, (size_t)V * 4);
+        }
+        return SS_OK;
+    };
+    if (int rc = launch(0)) return rc;
+    for (int g = 0; g <= max_extra; ++g) {
+        if (g < max_extra)
+            if (int rc = launch(g + 1)) return rc;
+        if (int rc = drain(g)) return rc;
     }
+    HIPCHK(hipStreamSynchronize(s));
     HIPCHK(hipGetLastError());
     return SS_OK;
 }
@@ -1293,7 +1503,7 @@ int bench_decode_step_lane(const ss_weights* w, Lane& ln, hipStream_t s, const i
     HIPCHK(hipSetDevice(w->device));
     if (int rc = ensure_workspace(w, ln, B * ctx, B, B, (size_t)B * (ctx + 1), 2, s)) return rc;
     const MbState& st = ln.st;
-    if (int rc = upload_prompt_state(ln, prompt_tokens, offs.data(), lens.data(), B, slab.data(), limit.data(), sel, s))
+    if (int rc = upload_prompt_state(ln, prompt_tokens, offs.data(), lens.data(), B, slab.data(), limit.data(), sel, B, s))
         return rc;
     forward(w, ln, B * ctx, B, ln.d_sel, st.d_nlive, false, s);
     ss::launch_step_update(st, 0, -1, s);   // token-rows of the decode step: every row at position ctx
