@@ -237,12 +237,13 @@ int dev_alloc(ss_weights* w, void** out, size_t bytes, bool zero)
 // Uploads a row-major host matrix through a staging buffer and packs it into dst (Sec. of ss_internal.h
 // on the operand layout).  Source row r -> packed row (r/16*blk_stride + blk_off)*16 + r%16.
 int upload_pack(ss_weights* w, Buf& staging, const void* host, int src_f32, int n_src, int k, f16_t* dst, int kp,
-                int blk_stride, int blk_off)
+                int blk_stride, int blk_off, int head_strips = 0)
 {
     const size_t bytes = (size_t)n_src * k * (src_f32 ? 4 : 2);
     if (int rc = staging.ensure(bytes, false)) return rc;
     HIPCHK(hipMemcpy(staging.p, host, bytes, hipMemcpyHostToDevice));
-    ss::launch_pack_weight(staging.p, src_f32, dst, n_src, k, kp, blk_stride, blk_off, w->lane[0].stream);
+    ss::launch_pack_weight(staging.p, src_f32, dst, n_src, k, kp, blk_stride, blk_off, head_strips,
+                           w->lane[0].stream);
     HIPCHK(hipStreamSynchronize(w->lane[0].stream));
     return SS_OK;
 }
@@ -483,26 +484,38 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
         return gemm_args(w, W, X, out, outp, rows, kp_out, p);
     };
 
+    // an unsliced launch of the block kernel adds its sums to the residual stream itself, and in a prompt forward rotates
+    // and stores q, k and v (every key of a row must be in place before any of its queries attends)
+    const bool whole_qkv = !decode && p_qkv.block >= 0 && ks_qkv == 1;
+    const bool whole_o = p_o.block >= 0 && ks_o == 1, whole_d = p_d.block >= 0 && ks_d == 1;
+    float* const add_d = whole_d ? nullptr : pd;   // what the next norm adds to the residual stream
+
     ss::launch_embed(st, w->embed, x, d, n, s);
     for (int l = 0; l < c.n_layers; ++l) {
         const Layer& L = w->layers[l];
         ss::kv_t* kc = ws.kv.as<ss::kv_t>() + (size_t)l * 2 * ln.kv_layer_stride;
         ss::kv_t* vc = kc + ln.kv_layer_stride;
-        ss::launch_rmsnorm(st, x, l ? pd : nullptr, ks_d, st_d, L.attn_norm, c.rms_eps, nullptr, nullptr, h, d, n, s);
-        ss::launch_gemm(mk(L.wqkv, h, pqkv, nullptr, n, 0, p_qkv), ss::EPI_PARTIAL, s);
+        ss::launch_rmsnorm(st, x, l ? add_d : nullptr, ks_d, st_d, L.attn_norm, c.rms_eps, nullptr, nullptr, h, d, n, s);
+        if (whole_qkv) {
+            const ss::QkvOut qo{st, qrot, kc, vc, w->rope_cos, w->rope_sin, hd};
+            ss::launch_gemm(mk(L.wqkv, h, nullptr, nullptr, n, 0, p_qkv), ss::EPI_QKV, s, &qo);
+        } else {
+            ss::launch_gemm(mk(L.wqkv, h, pqkv, nullptr, n, 0, p_qkv), ss::EPI_PARTIAL, s);
+        }
         if (decode) {   // one token-row per row: rotation and append are fused into the attention kernel
             ss::launch_attention_decode(st, pqkv, ks_qkv, st_qkv, kc, vc, w->rope_cos, w->rope_sin, ao, d, H, hd, n, s);
-        } else {        // prompt: every key of a row must be in place before any of its queries attends
-            ss::launch_rope_append(st, pqkv, ks_qkv, st_qkv, qrot, kc, vc, w->rope_cos, w->rope_sin, d, H, hd, n, s);
+        } else {
+            if (!whole_qkv)
+                ss::launch_rope_append(st, pqkv, ks_qkv, st_qkv, qrot, kc, vc, w->rope_cos, w->rope_sin, d, H, hd, n, s);
             ss::launch_attention_prompt(st, qrot, kc, vc, ao, d, H, hd, ln.prompt_rows, ln.prompt_max_len, s);
         }
-        ss::launch_gemm(mk(L.wo, ao, pd, nullptr, n, 0, p_o), ss::EPI_PARTIAL, s);
-        ss::launch_rmsnorm(st, x, pd, ks_o, st_d, L.mlp_norm, c.rms_eps, nullptr, nullptr, h, d, n, s);
+        ss::launch_gemm(mk(L.wo, ao, whole_o ? x : pd, nullptr, n, 0, p_o), whole_o ? ss::EPI_RESIDUAL : ss::EPI_PARTIAL, s);
+        ss::launch_rmsnorm(st, x, whole_o ? nullptr : pd, ks_o, st_d, L.mlp_norm, c.rms_eps, nullptr, nullptr, h, d, n, s);
         ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
-        ss::launch_gemm(mk(L.wd, act, pd, nullptr, n, 0, p_d), ss::EPI_PARTIAL, s);
+        ss::launch_gemm(mk(L.wd, act, whole_d ? x : pd, nullptr, n, 0, p_d), whole_d ? ss::EPI_RESIDUAL : ss::EPI_PARTIAL, s);
     }
     f16_t* hsel = ws.hsel.as<f16_t>();
-    ss::launch_rmsnorm(st, x, pd, ks_d, st_d, w->final_norm, c.rms_eps, d_sel, d_nsel, hsel, d, n_sel, s);
+    ss::launch_rmsnorm(st, x, add_d, ks_d, st_d, w->final_norm, c.rms_eps, d_sel, d_nsel, hsel, d, n_sel, s);
     float* logits = ln.cur_logits ? ln.cur_logits : ws.logits.as<float>();
     ss::launch_gemm(mk(w->lm_head, hsel, logits, nullptr, n_sel, 0, p_lm), ss::EPI_PARTIAL, s);
     if (!ln.cur_choose) return;
@@ -794,7 +807,8 @@ int weights_create_impl(ss_weights* w, const void* const* tensors, int32_t src_d
         if ((rc = upload_vec(w, staging, tensors[ti++], f32, d, &L.attn_norm))) return rc;
         if ((rc = alloc_packed(w, &L.wqkv, 3 * d, d))) return rc;
         for (int part = 0; part < 3; ++part)   // q, k, v stacked along the output dimension
-            if ((rc = upload_pack(w, staging, tensors[ti++], f32, d, d, L.wqkv.p, L.wqkv.Kp, 1, part * d / 16)))
+            if ((rc = upload_pack(w, staging, tensors[ti++], f32, d, d, L.wqkv.p, L.wqkv.Kp, 1, part * d / 16,
+                                  cfg->head_dim / 16)))
                 return rc;
         if ((rc = alloc_packed(w, &L.wo, d, d))) return rc;
         if ((rc = upload_pack(w, staging, tensors[ti++], f32, d, d, L.wo.p, L.wo.Kp, 1, 0))) return rc;

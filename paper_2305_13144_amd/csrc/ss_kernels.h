@@ -65,7 +65,7 @@ struct GemmArgs {
 };
 
 void launch_pack_weight(const void* src, int src_f32, f16_t* dst, int n_src, int k, int kp, int blk_stride,
-                        int blk_off, hipStream_t s);
+                        int blk_off, int head_strips, hipStream_t s);
 // Writes the 12-bit form of n_groups groups of 4 packed k-blocks (3 KiB each); sets *unfit if a value has no such form.
 void launch_narrow_weight(const f16_t* src, void* dst, size_t n_groups, int32_t* unfit, hipStream_t s);
 void launch_cast_rows(const void* src, int src_f32, bf16_t* dst, size_t count, hipStream_t s);
@@ -73,7 +73,17 @@ void launch_embed(const MbState& st, const bf16_t* embed, float* x, int d, int n
 void launch_rmsnorm(const MbState& st, float* x, const float* part, int ksplit, size_t part_stride,
                     const bf16_t* w, float eps, const int32_t* sel, const int32_t* d_nsel, f16_t* h_packed, int d,
                     int n_max, hipStream_t s);
-void launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s);
+// Where an EPI_QKV launch puts its results: q rotated, fp32 [rows, d]; k rotated and v into the rows' slabs.
+struct QkvOut {
+    MbState st;
+    float* qrot;
+    kv_t *kc, *vc;
+    const float *rcos, *rsin;
+    int hd;
+};
+
+// EPI_QKV and EPI_RESIDUAL (out += sums) need a plan for the block kernel without k-slices; EPI_QKV needs `qkv`.
+void launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s, const QkvOut* qkv = nullptr);
 void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride, float* qrot,
                         kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin, int d, int H,
                         int hd, int n_max, hipStream_t s);

@@ -7,7 +7,8 @@
 
 namespace ss {
 
-enum Epilogue { EPI_PARTIAL = 0, EPI_SWIGLU = 1 };
+// EPI_RESIDUAL and EPI_QKV: block kernel without k-slices only; planned as EPI_PARTIAL.
+enum Epilogue { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_RESIDUAL = 2, EPI_QKV = 3 };
 
 constexpr int kSweepMaxRows = 256;   // 16 row strips: accumulators and the LDS chunk of the sweep kernel still fit
 // Rows up to which it is chosen: 9 row strips.  Per step of the sweep / block kernel, 7B, microseconds: 130 rows q|k|v
