@@ -10,12 +10,14 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "ss_internal.h"
 
 namespace ss {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));  // one 16-byte operand fragment
@@ -1092,38 +1094,53 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     }
 }
 
-// Prompt forwards: q was rotated and K, V appended for every token-row by k_rope_append before this runs.
-// Causal attention of one (row, head, tile of 64 queries) per workgroup; each of its 4 waves owns 16 queries.
-// The row's keys and values are visited in tiles of 32 slots that are staged once in LDS for all 64 queries
+// Prompt forwards: q was rotated and K, V put into their slots for every token-row before this runs.
+// Causal attention of one (row, head, tile of 64 * QT queries) per workgroup; each of its 4 waves owns QT tiles of 16
+// queries.  The row's keys and values are visited in tiles of 64 slots that are staged once in LDS for all queries
 // (K as stored, V transposed), the next tile's global loads in flight while the current one is used.
 // Both contractions run on the matrix cores in half precision, the cache's own format:
-//   S^T = K Q^T   A = K tile (16 keys x 32 head elements), B = Q^T; q is carried as the sum of two halves
-//                 (hi + lo), so the scores see q to ~22 bits like the decode kernel's fp32 dot product;
+//   S^T = K Q^T   A = K tile (16 keys x 32 head elements), B = Q^T; q, times log2(e) / sqrt(hd), is carried as the sum of
+//                 two halves (hi + lo), so the scores see q to ~22 bits like the decode kernel's fp32 dot product;
 //                 D: lane holds, for query lane%16, keys 4*(lane/16)..+3 of a 16-key tile.
 //   O^T = V^T P^T two score tiles (32 keys) form one B operand as they lie in the registers: contraction slot
 //                 8*(lane/16) + j is key 4*(lane/16) + j of the first tile for j < 4, of the second for j >= 4;
-//                 the A operand reads V^T in the same slot order (two 8-byte LDS reads);
+//                 V^T is staged in that slot order (vt_pos), so the A operand is one 16-byte LDS read;
 //                 D: lane holds, for query lane%16, output elements 16t + 4*(lane/16)..+3.
 // So a query's running maximum, sum and rescale factor stay in its own lanes: fp32 online softmax with no
-// transposition of the probabilities.  Slots above a query's position are masked before the exponential.
-template <int HD>
-__global__ __launch_bounds__(256) void k_attention_prompt(MbState st, const float* __restrict__ qrot,
-                                                          const kv_t* __restrict__ kc, const kv_t* __restrict__ vc,
-                                                          f16_t* __restrict__ out, int d)
+// transposition of the probabilities.  Slots above a query's position are masked before the exponential; only tiles that
+// reach past the wave's first query test for it, and the accumulators are rescaled only when some maximum has moved.
+// What bounds it: matrix instructions and, as many cycles again, the vector work of the softmax.  With two query tiles a
+// wave reads every staged operand for 32 queries; the loads of short rows are latency, and there one tile with
+// one buffer leaves room for three workgroups per compute unit instead of two.
+// Per layer, 7B, against 32-slot tiles with one query tile per wave and V transposed by 2-byte LDS writes: three prompts of
+// about 2400 slots 945 -> 416 us, 256 prompts of 8 to 256 slots 301 -> 139 us, 16 of about 45 12.1 -> 10.0 us.
+constexpr int kAttnTile = 64;        // slots per staged tile
+constexpr int kAttnTallFrom = 256;   // longest row of the forward from which a wave owns two query tiles
+// Place of a tile's slot in the staged V^T rows.
+__device__ __forceinline__ int vt_pos(int k) { return (k & 32) + ((k >> 2) & 3) * 8 + ((k >> 4) & 1) * 4 + (k & 3); }
+
+template <int HD, int QT, int NBUF>
+__global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbState st, const float* __restrict__ qrot,
+                                                                          const kv_t* __restrict__ kc,
+                                                                          const kv_t* __restrict__ vc,
+                                                                          f16_t* __restrict__ out, int d)
 {
+    constexpr int KT = kAttnTile;
     constexpr int KS = HD / 32;          // steps of the score contraction
     constexpr int ET = HD / 16;          // 16-element tiles of the output
     constexpr int OCT = HD / 8;          // 16-byte pieces per key
     constexpr int KROW = HD + 8;         // halves per staged key row (16 bytes of padding: conflict-free operand reads)
-    constexpr int VROW = 32 + 4;         // halves per row of the transposed value tile (8 bytes of padding)
-    constexpr int PIECES = 32 * OCT;     // 16-byte pieces of a tile
-    constexpr int PPT = PIECES / 256;    // pieces per thread
-    static_assert(PIECES % 256 == 0, "tile pieces per thread");
-    __shared__ __attribute__((aligned(16))) _Float16 k_lds[32 * KROW];
-    __shared__ __attribute__((aligned(16))) _Float16 v_lds[HD * VROW];
-    const int qt = blockIdx.x, h = blockIdx.y, row = blockIdx.z;
+    constexpr int VROW = KT + 8;         // halves per row of the transposed value tile (likewise)
+    constexpr int PPT = KT * OCT / 256;  // pieces per thread: PPT keys rows apart, and PPT neighbouring keys' values
+    constexpr int NKG = KT / PPT;        // groups of neighbouring keys
+    static_assert(PPT == 4 || PPT == 2, "head_dim 128 or 64");
+    __shared__ __attribute__((aligned(16))) _Float16 k_lds[NBUF][KT * KROW];
+    __shared__ __attribute__((aligned(16))) _Float16 v_lds[NBUF][HD * VROW];
+    // heads are the fastest index: a multiple of 8 of them keeps each head's keys and values on one die; tiles of late
+    // queries, which visit the most slots, come first
+    const int h = blockIdx.x, row = blockIdx.y, qt = gridDim.z - 1 - blockIdx.z;
     const int p = st.row_plen[row];      // tokens of this row in the forward: positions 0..p-1
-    const int q0 = qt * 64;
+    const int q0 = qt * 64 * QT;
     if (q0 >= p) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int ql = lane & 15, g = lane >> 4;
@@ -1131,33 +1148,11 @@ __global__ __launch_bounds__(256) void k_attention_prompt(MbState st, const floa
     const size_t base = (size_t)st.row_so[row] * d + (size_t)h * st.row_cap[row] * HD;
     const u32x4* Kg = (const u32x4*)(kc + base);
     const u32x4* Vg = (const u32x4*)(vc + base);
-    const int qpos = min(q0 + wave * 16 + ql, p - 1);   // queries past the row's end repeat its last one (never stored)
-    const bool q_valid = q0 + wave * 16 + ql < p;
-    const int wave_last = min(q0 + wave * 16 + 15, p - 1);
-    const int n_keys = min(p, q0 + 64);
-    const int n_tiles = (n_keys + 31) >> 5;
-    const float scale = rsqrtf((float)HD);
-
-    // this lane's query: head elements 32*ks + 8*g .. +7 for every step, split into two halves
-    f16x8 qh[KS], qlo[KS];
-    {
-        const float* qp = qrot + (size_t)(j0 + qpos) * d + h * HD + 8 * g;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const float4 a = *(const float4*)(qp + 32 * ks), b = *(const float4*)(qp + 32 * ks + 4);
-            const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const _Float16 hi = (_Float16)v[e];
-                qh[ks][e] = hi;
-                qlo[ks][e] = (_Float16)(v[e] - (float)hi);
-            }
-        }
-    }
-    f32x4 o[ET];
-#pragma unroll
-    for (int t = 0; t < ET; ++t) o[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    float m_run = -3.0e38f, l_run = 0.f;
+    const int wave_first = q0 + wave * 16 * QT;
+    const int wave_last = wave_first < p ? min(wave_first + 16 * QT - 1, p - 1) : -1;   // -1: no query, nothing to visit
+    const int n_keys = min(p, q0 + 64 * QT);
+    const int n_tiles = (n_keys + KT - 1) / KT;
+    const float scale = rsqrtf((float)HD) * 1.44269504088896341f;   // scores in units of log2: exp2 below
 
     u32x4 kreg[PPT], vreg[PPT];
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
@@ -1165,86 +1160,159 @@ __global__ __launch_bounds__(256) void k_attention_prompt(MbState st, const floa
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
             const int c = tid + i * 256;
-            const int key = t * 32 + c / OCT, oct = c % OCT;
-            const bool live = key < n_keys;
-            const size_t at = (size_t)min(key, n_keys - 1) * OCT + oct;
-            const u32x4 kv = Kg[at], vv = Vg[at];
-            kreg[i] = live ? kv : zero4;
-            vreg[i] = live ? vv : zero4;
+            const int key = t * KT + c / OCT;
+            const u32x4 kv = Kg[(size_t)min(key, n_keys - 1) * OCT + c % OCT];
+            kreg[i] = key < n_keys ? kv : zero4;
+        }
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) {
+            const int key = t * KT + (tid % NKG) * PPT + i;
+            const u32x4 vv = Vg[(size_t)min(key, n_keys - 1) * OCT + tid / NKG];
+            vreg[i] = key < n_keys ? vv : zero4;
         }
     };
-    load_tile(0);
-    for (int t = 0; t < n_tiles; ++t) {
-        // stage tile t: K rows as stored, V transposed
+    auto stage_tile = [&](int b) {   // K rows as stored, V transposed
 #pragma unroll
         for (int i = 0; i < PPT; ++i) {
             const int c = tid + i * 256;
-            const int key = c / OCT, oct = c % OCT;
-            *(u32x4*)&k_lds[key * KROW + oct * 8] = kreg[i];
-            const f16x8 vv = __builtin_bit_cast(f16x8, vreg[i]);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v_lds[(oct * 8 + e) * VROW + key] = vv[e];
+            *(u32x4*)&k_lds[b][(c / OCT) * KROW + (c % OCT) * 8] = kreg[i];
         }
-        __syncthreads();
-        if (t + 1 < n_tiles) load_tile(t + 1);
-        const int k0 = t * 32;
-        if (k0 <= wave_last) {   // wave-uniform: tiles wholly above this wave's queries are skipped
-            f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+        _Float16* vt = &v_lds[b][(tid / NKG) * 8 * VROW + vt_pos((tid % NKG) * PPT)];
+        f16x8 v[PPT];
+#pragma unroll
+        for (int i = 0; i < PPT; ++i) v[i] = __builtin_bit_cast(f16x8, vreg[i]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if constexpr (PPT == 4) {
+                const f16x4 o = {v[0][e], v[1][e], v[PPT - 2][e], v[PPT - 1][e]};
+                *(f16x4*)(vt + e * VROW) = o;
+            } else {
+                const f16x2 o = {v[0][e], v[1][e]};
+                *(f16x2*)(vt + e * VROW) = o;
+            }
+        }
+    };
+    load_tile(0);
+
+    // this lane's queries: head elements 32*ks + 8*g .. +7 for every step, split into two halves (queries past the row's
+    // end repeat its last one, and are never stored)
+    f16x8 qh[QT][KS], qlo[QT][KS];
+    int qpos[QT];
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+        qpos[u] = min(wave_first + u * 16 + ql, p - 1);
+        const float* qp = qrot + (size_t)(j0 + qpos[u]) * d + h * HD + 8 * g;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            const float4 a = *(const float4*)(qp + 32 * ks), b = *(const float4*)(qp + 32 * ks + 4);
+            const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float sv = v[e] * scale;
+                const _Float16 hi = (_Float16)sv;
+                qh[u][ks][e] = hi;
+                qlo[u][ks][e] = (_Float16)(sv - (float)hi);
+            }
+        }
+    }
+    f32x4 o[QT][ET];
+    float m_run[QT], l_run[QT];   // l_run: this lane's share of the sum, over its own slots
+#pragma unroll
+    for (int u = 0; u < QT; ++u) {
+#pragma unroll
+        for (int t = 0; t < ET; ++t) o[u][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        m_run[u] = -3.0e38f;
+        l_run[u] = 0.f;
+    }
+
+    auto use_tile = [&](int b, int k0, auto masked) {
+        constexpr bool MASKED = decltype(masked)::value;
+        f32x4 s[QT][4];
+#pragma unroll
+        for (int kt = 0; kt < 4; ++kt) {
+#pragma unroll
+            for (int u = 0; u < QT; ++u) s[u][kt] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            if (MASKED && k0 + kt * 16 > wave_last) continue;   // wave-uniform
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
-                const f16x8 a0 = *(const f16x8*)&k_lds[ql * KROW + ks * 32 + 8 * g];
-                const f16x8 a1 = *(const f16x8*)&k_lds[(16 + ql) * KROW + ks * 32 + 8 * g];
-                s0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, qlo[ks], s0, 0, 0, 0);
-                s0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, qh[ks], s0, 0, 0, 0);
-                s1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, qlo[ks], s1, 0, 0, 0);
-                s1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, qh[ks], s1, 0, 0, 0);
-            }
-            float sc[8];
-            float mt = -3.0e38f;
+                const f16x8 a = *(const f16x8*)&k_lds[b][(kt * 16 + ql) * KROW + ks * 32 + 8 * g];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                sc[i] = (k0 + 4 * g + i <= qpos) ? s0[i] * scale : -3.0e38f;
-                sc[4 + i] = (k0 + 16 + 4 * g + i <= qpos) ? s1[i] * scale : -3.0e38f;
-            }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) mt = fmaxf(mt, sc[i]);
-            mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
-            mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-            const float m_new = fmaxf(m_run, mt);
-            const float alpha = __expf(m_run - m_new);
-            float ps = 0.f;
-            f16x8 pb;
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const float pv = sc[i] > -1.0e38f ? __expf(sc[i] - m_new) : 0.f;
-                ps += pv;
-                pb[i] = (_Float16)pv;
-            }
-            ps += __shfl_xor(ps, 16, 64);
-            ps += __shfl_xor(ps, 32, 64);
-            l_run = l_run * alpha + ps;
-            m_run = m_new;
-#pragma unroll
-            for (int tt = 0; tt < ET; ++tt) {
-                const _Float16* vr = &v_lds[(tt * 16 + ql) * VROW];
-                const f16x4 lo4 = *(const f16x4*)(vr + 4 * g), hi4 = *(const f16x4*)(vr + 16 + 4 * g);
-                const f16x8 av = {lo4[0], lo4[1], lo4[2], lo4[3], hi4[0], hi4[1], hi4[2], hi4[3]};
-                o[tt] *= alpha;
-                o[tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, pb, o[tt], 0, 0, 0);
+                for (int u = 0; u < QT; ++u) {
+                    s[u][kt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, qlo[u][ks], s[u][kt], 0, 0, 0);
+                    s[u][kt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, qh[u][ks], s[u][kt], 0, 0, 0);
+                }
             }
         }
-        __syncthreads();   // the tile is rewritten next trip
+        f16x8 pb[QT][2];
+#pragma unroll
+        for (int u = 0; u < QT; ++u) {
+            float mt = -3.0e38f;
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (MASKED && k0 + kt * 16 + 4 * g + i > qpos[u]) s[u][kt][i] = -3.0e38f;
+                    mt = fmaxf(mt, s[u][kt][i]);
+                }
+            mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
+            mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+            if (__any(mt > m_run[u])) {
+                const float m_new = fmaxf(m_run[u], mt);
+                const float alpha = __builtin_amdgcn_exp2f(m_run[u] - m_new);
+                m_run[u] = m_new;
+                l_run[u] *= alpha;
+#pragma unroll
+                for (int tt = 0; tt < ET; ++tt) o[u][tt] *= alpha;
+            }
+#pragma unroll
+            for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const float pv = __builtin_amdgcn_exp2f(s[u][kt][i] - m_run[u]);   // masked: 0, some slot is not
+                    l_run[u] += pv;
+                    pb[u][kt >> 1][(kt & 1) * 4 + i] = (_Float16)pv;
+                }
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            if (MASKED && k0 + c * 32 > wave_last) continue;
+#pragma unroll
+            for (int tt = 0; tt < ET; ++tt) {
+                const f16x8 av = *(const f16x8*)&v_lds[b][(tt * 16 + ql) * VROW + c * 32 + 8 * g];
+#pragma unroll
+                for (int u = 0; u < QT; ++u) o[u][tt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, pb[u][c], o[u][tt], 0, 0, 0);
+            }
+        }
+    };
+    stage_tile(0);
+    for (int t = 0; t < n_tiles; ++t) {
+        const int b = NBUF == 2 ? t & 1 : 0;
+        __syncthreads();
+        if (t + 1 < n_tiles) load_tile(t + 1);
+        const int k0 = t * KT;
+        if (k0 <= wave_last) {   // wave-uniform: tiles wholly above this wave's queries are skipped
+            if (k0 + KT - 1 <= wave_first) use_tile(b, k0, std::false_type{});
+            else use_tile(b, k0, std::true_type{});
+        }
+        if (NBUF == 1) __syncthreads();   // with two buffers the next one was last read before this trip's barrier
+        if (t + 1 < n_tiles) stage_tile(NBUF == 2 ? b ^ 1 : 0);
     }
-    if (!q_valid) return;
-    const float inv = 1.f / l_run;
-    const int j = j0 + qpos;
 #pragma unroll
-    for (int tt = 0; tt < ET; ++tt) {
-        f16_t r[4];
+    for (int u = 0; u < QT; ++u) {
+        float l = l_run[u];
+        l += __shfl_xor(l, 16, 64);
+        l += __shfl_xor(l, 32, 64);
+        if (wave_first + u * 16 + ql >= p) continue;
+        const float inv = 1.f / l;
+        const int j = j0 + qpos[u];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) r[e] = f2h(o[tt][e] * inv);
-        const size_t at = pk_index(j, h * HD + tt * 16 + 4 * g, d);
-        *(uint2*)(out + at) = *(const uint2*)r;
+        for (int tt = 0; tt < ET; ++tt) {
+            f16_t r[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) r[e] = f2h(o[u][tt][e] * inv);
+            const size_t at = pk_index(j, h * HD + tt * 16 + 4 * g, d);
+            *(uint2*)(out + at) = *(const uint2*)r;
+        }
     }
 }
 
@@ -1759,11 +1827,18 @@ void launch_attention_decode(const MbState& st, const float* qkv_part, int kspli
 void launch_attention_prompt(const MbState& st, const float* qrot, const kv_t* kcache, const kv_t* vcache,
                              f16_t* out_packed, int d, int H, int hd, int B, int max_len, hipStream_t s)
 {
-    const dim3 grid((max_len + 63) / 64, H, B);
-    if (hd == 128)
-        hipLaunchKernelGGL((k_attention_prompt<128>), grid, dim3(256), 0, s, st, qrot, kcache, vcache, out_packed, d);
-    else
-        hipLaunchKernelGGL((k_attention_prompt<64>), grid, dim3(256), 0, s, st, qrot, kcache, vcache, out_packed, d);
+    // two query tiles per wave from kAttnTallFrom positions on, see k_attention_prompt
+    const int per = max_len >= kAttnTallFrom ? 128 : 64;
+    const dim3 grid(H, B, (max_len + per - 1) / per);
+#define SS_ATTN_ARGS grid, dim3(256), 0, s, st, qrot, kcache, vcache, out_packed, d
+    if (hd == 128) {
+        if (per == 128) hipLaunchKernelGGL((k_attention_prompt<128, 2, 2>), SS_ATTN_ARGS);
+        else hipLaunchKernelGGL((k_attention_prompt<128, 1, 1>), SS_ATTN_ARGS);
+    } else {
+        if (per == 128) hipLaunchKernelGGL((k_attention_prompt<64, 2, 2>), SS_ATTN_ARGS);
+        else hipLaunchKernelGGL((k_attention_prompt<64, 1, 1>), SS_ATTN_ARGS);
+    }
+#undef SS_ATTN_ARGS
 }
 
 void launch_argmax(const float* logits, int vocab, const int32_t* d_nsel, int32_t* am, int n_max, hipStream_t s)
