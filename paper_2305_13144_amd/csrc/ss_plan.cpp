@@ -107,7 +107,9 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
         if (epilogue == EPI_SWIGLU) max_ksplit = 1;   // fused epilogue: no k-slices
         const int mt = (m_rows + 15) / 16;
         p.kd = mt == 1 ? 4 : 2;
-        p.narrow = Kp % 128 == 0 && mt == 1;   // the kernel reads 12-bit weights 4 k-blocks at a time
+        // the kernel reads 12-bit weights 4 k-blocks at a time, and its 4 waves take whole groups: below 16 k-blocks some
+        // would have none (such matrices are small enough to stay in L2, where their bytes are not what takes time)
+        p.narrow = Kp % 128 == 0 && mt == 1 && KB >= 16;
         if (max_ksplit == 1 && epilogue == EPI_SWIGLU) return p;
         p.nb = (mt == 1 && KB > 256) ? 2 : 4;   // with several row strips the activation re-reads dominate: 4 strips
         if (max_ksplit == 1 && mt == 1) p.nb = 2;
