@@ -229,9 +229,16 @@ template <int T, int ITER>
 __global__ __launch_bounds__(T) void k_rmsnorm(const int32_t* __restrict__ d_count, float* __restrict__ x,
                                                   const float* __restrict__ part, int ksplit, size_t part_stride,
                                                   const bf16_t* __restrict__ w, float eps,
-                                                  const int32_t* __restrict__ sel, f16_t* __restrict__ h, int d)
+                                                  const int32_t* __restrict__ sel, f16_t* __restrict__ h, int d,
+                                                  int n_rows)
 {
-    const int j = blockIdx.x;
+    // A packed row is pieces of 16 bytes, and 16 rows together fill whole lines.  With many rows the 16 rows of a strip
+    // therefore go to workgroups of one die (ids are dealt to the 8 dies round-robin), whose L2 puts the lines
+    // together; few rows gain nothing, their lines are read by all dies at once.  Per launch, 7B: 7200
+    // token-rows 72 -> 52 us, 3000 28 -> 21.
+    const int b = blockIdx.x;
+    const int j = T == 1024 ? b : ((b >> 7) * 8 + (b & 7)) * 16 + ((b >> 3) & 15);
+    if (T != 1024 && j >= n_rows) return;   // the grid is whole groups of 8 strips
     // The row count, the row, its partial sums and the norm weights are all requested before anything waits:
     // the kernel is a chain of dependent round trips otherwise (count, then the row, then the weights), and its
     // whole cost is latency.  Rows at or beyond the count are loaded as well (the buffers are sized for the grid)
@@ -1654,11 +1661,11 @@ void launch_rmsnorm(const MbState& st, float* x, const float* part, int ksplit, 
     // threads per row, whose norm launches took 47 us each there; up to 256 rows the wide form is the faster one:
     // 24 rows 3.29 against 3.37 ms per decode step, 256 rows equal).
     if (n_max >= kNormNarrowFrom)
-        hipLaunchKernelGGL((k_rmsnorm<256, 8>), dim3(n_max), dim3(256), 0, s, d_nsel ? d_nsel : st.d_n, x, part,
-                           part ? ksplit : 0, part_stride, w, eps, sel, h_packed, d);
+        hipLaunchKernelGGL((k_rmsnorm<256, 8>), dim3(round_up(n_max, 128)), dim3(256), 0, s, d_nsel ? d_nsel : st.d_n, x, part,
+                           part ? ksplit : 0, part_stride, w, eps, sel, h_packed, d, n_max);
     else
         hipLaunchKernelGGL((k_rmsnorm<1024, 2>), dim3(n_max), dim3(1024), 0, s, d_nsel ? d_nsel : st.d_n, x, part,
-                           part ? ksplit : 0, part_stride, w, eps, sel, h_packed, d);
+                           part ? ksplit : 0, part_stride, w, eps, sel, h_packed, d, n_max);
 }
 
 // k-blocks per slice; whole groups of 4 wherever a matrix with 12-bit weights would be read in that form, so that a
