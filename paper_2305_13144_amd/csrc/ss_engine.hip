@@ -185,6 +185,7 @@ struct Lane {
     int32_t* h_poll = nullptr;   // pinned host copy of the 4-int device header (d_n, d_step, d_nlive, d_active)
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};   // start, end of the prompt forward, end of a micro-batch
     int prompt_rows = 0, prompt_max_len = 0;   // shape of the prompt forward whose state was uploaded last
+    int max_slots = 0;                         // largest slab of its rows
 };
 }  // namespace
 
@@ -503,7 +504,8 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
             ss::launch_gemm(mk(L.wqkv, h, pqkv, nullptr, n, 0, p_qkv), ss::EPI_PARTIAL, s);
         }
         if (decode) {   // one token-row per row: rotation and append are fused into the attention kernel
-            ss::launch_attention_decode(st, pqkv, ks_qkv, st_qkv, kc, vc, w->rope_cos, w->rope_sin, ao, d, H, hd, n, s);
+            ss::launch_attention_decode(st, pqkv, ks_qkv, st_qkv, kc, vc, w->rope_cos, w->rope_sin, ao, d, H, hd, n,
+                                        ln.max_slots, s);
         } else {
             if (!whole_qkv)
                 ss::launch_rope_append(st, pqkv, ks_qkv, st_qkv, qrot, kc, vc, w->rope_cos, w->rope_sin, d, H, hd, n, s);
@@ -580,6 +582,7 @@ int upload_prompt_state(Lane& ln, const int32_t* toks, const int32_t* offs, cons
     std::copy(sel.begin(), sel.end(), at_host(ln.d_sel));
     ln.prompt_rows = B;
     ln.prompt_max_len = *std::max_element(lens, lens + B);
+    ln.max_slots = *std::max_element(slab, slab + B);
     HIPCHK(hipMemcpyAsync(base, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(st.row_so, so.data(), (size_t)B * 8, hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));   // the host vectors above die with this frame

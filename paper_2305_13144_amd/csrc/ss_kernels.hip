@@ -988,8 +988,12 @@ __global__ __launch_bounds__(256) void k_rope_append(MbState st, const float* __
 // sum of V.  A wave's load covers 64/LPK consecutive keys (LPK = hd/8 lanes of 16 bytes per key), so K
 // and V are each streamed once, fully coalesced; a wave issues AU such loads before it consumes them, so
 // a context of a few hundred slots costs two or three memory round trips, not one per load.
+// Short contexts are bound by vector instructions (a load's share of the dot products and of the sums is some 60), so the
+// loads of a group that lie beyond the context are left out of both passes.  Per layer, 7B: 163 rows
+// 31.4 -> 27.1 us, 51 rows 15.7 -> 14.1, one row 8.1 -> 6.8 (contexts of 16 to 70).
 constexpr int kAttnUnroll = 8;
 constexpr int kAttnWideMaxGroups = 512;   // decode attention: (row, head) workgroups up to which 8 waves each are used
+constexpr int kAttnWidestMaxGroups = 192; //   ... and 16 waves each, if some context is long enough
 
 template <int HD, int NW>
 __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __restrict__ sc, float* __restrict__ red,
@@ -1000,7 +1004,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     constexpr int LPK = HD / 8;       // lanes per key
     constexpr int KPW = 64 / LPK;     // keys per wave load
     constexpr int AU = kAttnUnroll;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = lane % LPK, kin = lane / LPK;
     const float scale = rsqrtf((float)HD);
     float q[8];
@@ -1017,6 +1021,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
         }
 #pragma unroll
         for (int u = 0; u < AU; ++u) {
+            if (c0 + u * NW * KPW >= ctx) break;   // wave-uniform: nothing of this load is inside the context
             const int s = c0 + u * NW * KPW + kin;
             const kv_t* kv = (const kv_t*)&raw[u];
             float part = 0.f;
@@ -1071,6 +1076,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
         }
 #pragma unroll
         for (int u = 0; u < AU; ++u) {
+            if (c0 + u * NW * KPW >= ctx) break;
             const int s = c0 + u * NW * KPW + kin;
             const float p = s < ctx ? sc[s] : 0.f;
             const kv_t* vv = (const kv_t*)&raw[u];
@@ -1327,7 +1333,9 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
 // (sums the k-slices, rotates q and k at the row's position, appends k and v to the row's slab), then
 // attends.  Saves a launch and the round trip of q through HBM for every layer of every step.
 // NW waves per workgroup: 8 (256 cache slots per round trip) when the grid is small enough for every workgroup to
-// be resident with room to spare, 4 (128 slots) for larger batches, whose many workgroups already fill the chip.
+// be resident with room to spare, 4 (128 slots) for larger batches, whose many workgroups already fill the chip, and 16
+// (512 slots) when there is less than one workgroup per compute unit and a context exceeds 256 slots: what a unit has in
+// flight is then all that counts.
 template <int HD, int NW>
 __global__ __launch_bounds__(64 * NW) void k_attention_decode(MbState st, const float* __restrict__ part, int ksplit,
                                                           size_t part_stride, kv_t* __restrict__ kc,
@@ -1815,17 +1823,23 @@ static void launch_attention_decode_inst(const MbState& st, const float* qkv_par
 
 void launch_attention_decode(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
-                             f16_t* out_packed, int d, int H, int hd, int n_max, hipStream_t s)
+                             f16_t* out_packed, int d, int H, int hd, int n_max, int max_slots, hipStream_t s)
 {
     // measured at the 7B shape: 8 waves win at 16 rows (512 workgroups: 14.1 against 14.9 us per layer at context
     // 200), 4 waves win at 64 rows (2048 workgroups: 25.7 against 36.1 us at context 100)
-    const bool wide = n_max * H <= kAttnWideMaxGroups;
+    const int groups = n_max * H;
+    // 16 waves where 8 would need a second round trip (3 rows at context 2400: 47.5 -> 38 us); shorter contexts leave some
+    // of them without a slot (tiny model, context 40: 6 us with 8 waves, 7.3 with 16)
+    const bool wide = groups <= kAttnWideMaxGroups;
+    const bool widest = groups <= kAttnWidestMaxGroups && max_slots > 8 * kAttnUnroll * (512 / hd);
 #define SS_ATTN_ARGS st, qkv_part, ksplit, part_stride, kcache, vcache, rope_cos, rope_sin, out_packed, d, H, n_max, s
     if (hd == 128) {
-        if (wide) launch_attention_decode_inst<128, 8>(SS_ATTN_ARGS);
+        if (widest) launch_attention_decode_inst<128, 16>(SS_ATTN_ARGS);
+        else if (wide) launch_attention_decode_inst<128, 8>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<128, 4>(SS_ATTN_ARGS);
     } else {
-        if (wide) launch_attention_decode_inst<64, 8>(SS_ATTN_ARGS);
+        if (widest) launch_attention_decode_inst<64, 16>(SS_ATTN_ARGS);
+        else if (wide) launch_attention_decode_inst<64, 8>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<64, 4>(SS_ATTN_ARGS);
     }
 #undef SS_ATTN_ARGS
