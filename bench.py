@@ -488,9 +488,12 @@ def main() -> int:
                     achieved=ach, peak=HBM_PEAK_GBS, unit="GB/s", frac=ach / HBM_PEAK_GBS, traffic=traffic,
                     traffic_source=traffic_source, ms=float(ms_s.mean()), ms_min=float(ms_s.min()),
                     algorithmic_bytes=sbytes, launches_per_step=step_launches,
+                    bytes_note="algorithmic bytes count 2 per weight; the small-batch projections stream a 12-bit form of the same "
+                               "values, so the step moves about a fifth less than that",
                     steps_in_flight=two,
                     projection_launches=dict(
-                        what="the projection kernels of that step alone (k_gemm_sweep + k_gemm_skinny), back to back",
+                        what="the projection kernels of that step alone (k_gemm_sweep + k_gemm_skinny), back to back; bytes at 2 per "
+                             "weight, of which the kernels read the 12-bit form of the same values (three quarters)",
                         ms=float(ms_w.mean()), achieved=ach_w, unit="GB/s", frac=ach_w / HBM_PEAK_GBS, launches=launches,
                         avg_launch_us=ms_w.mean() * 1e3 / launches, bytes_per_launch=wbytes / launches),
                     plain_read_stream=dict(
