@@ -58,7 +58,9 @@ def profile_traffic(shape_name: str, rows: int, ctx: int, gemm_mode: int):
     want = dict(shape=shape_name, rows=str(rows), ctx=str(ctx), gemm_mode=str(gemm_mode))
     if any(kv.get(k) != v for k, v in want.items()) or "decode_step_hbm_bytes" not in kv:
         return None, f"{TRAFFIC_PROFILE} was taken at another shape or launch configuration"
-    return float(kv["decode_step_hbm_bytes"]), f"{TRAFFIC_PROFILE} (rocprofv3 counters of an earlier run, not live)"
+    narrow = kv.get("decode_step_hbm_bytes_12bit")
+    note = f"; weights as halves, with the 12-bit copies in use {narrow} bytes" if narrow else ""
+    return float(kv["decode_step_hbm_bytes"]), f"{TRAFFIC_PROFILE} (rocprofv3 counters of an earlier run, not live{note})"
 
 
 def ablation(a, ss, gw, wl, shape) -> int:
