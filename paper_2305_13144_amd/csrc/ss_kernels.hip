@@ -1112,8 +1112,10 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
 // queries.  The row's keys and values are visited in tiles of 64 slots that are staged once in LDS for all queries
 // (K as stored, V transposed), the next tile's global loads in flight while the current one is used.
 // Both contractions run on the matrix cores in half precision, the cache's own format:
-//   S^T = K Q^T   A = K tile (16 keys x 32 head elements), B = Q^T; q, times log2(e) / sqrt(hd), is carried as the sum of
-//                 two halves (hi + lo), so the scores see q to ~22 bits like the decode kernel's fp32 dot product;
+//   S^T = K Q^T   A = K tile (16 keys x 32 head elements), B = Q^T; q is carried as the sum of two halves (hi + lo), so
+//                 the scores see q to ~22 bits (to 2^-25 where an element is below 1/8) like the decode kernel's fp32
+//                 dot product.  The factor log2(e) / sqrt(hd) comes after the product, in the exponent's multiply-add:
+//                 a q made smaller by it first would keep fewer bits;
 //                 D: lane holds, for query lane%16, keys 4*(lane/16)..+3 of a 16-key tile.
 //   O^T = V^T P^T two score tiles (32 keys) form one B operand as they lie in the registers: contraction slot
 //                 8*(lane/16) + j is key 4*(lane/16) + j of the first tile for j < 4, of the second for j >= 4;
@@ -1165,7 +1167,7 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
     const int wave_last = wave_first < p ? min(wave_first + 16 * QT - 1, p - 1) : -1;   // -1: no query, nothing to visit
     const int n_keys = min(p, q0 + 64 * QT);
     const int n_tiles = (n_keys + KT - 1) / KT;
-    const float scale = rsqrtf((float)HD) * 1.44269504088896341f;   // scores in units of log2: exp2 below
+    const float scale = rsqrtf((float)HD) * 1.44269504088896341f;   // of the scores, in units of log2: exp2 below
 
     u32x4 kreg[PPT], vreg[PPT];
     const u32x4 zero4 = {0u, 0u, 0u, 0u};
@@ -1221,15 +1223,14 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
             const float v[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float sv = v[e] * scale;
-                const _Float16 hi = (_Float16)sv;
+                const _Float16 hi = (_Float16)v[e];
                 qh[u][ks][e] = hi;
-                qlo[u][ks][e] = (_Float16)(sv - (float)hi);
+                qlo[u][ks][e] = (_Float16)(v[e] - (float)hi);
             }
         }
     }
     f32x4 o[QT][ET];
-    float m_run[QT], l_run[QT];   // l_run: this lane's share of the sum, over its own slots
+    float m_run[QT], l_run[QT];   // m_run: before the factor; l_run: this lane's share of the sum, over its own slots
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
 #pragma unroll
@@ -1271,17 +1272,18 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
             mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
             if (__any(mt > m_run[u])) {
                 const float m_new = fmaxf(m_run[u], mt);
-                const float alpha = __builtin_amdgcn_exp2f(m_run[u] - m_new);
+                const float alpha = __builtin_amdgcn_exp2f((m_run[u] - m_new) * scale);
                 m_run[u] = m_new;
                 l_run[u] *= alpha;
 #pragma unroll
                 for (int tt = 0; tt < ET; ++tt) o[u][tt] *= alpha;
             }
+            const float m_scaled = m_run[u] * scale;   // its rounding is a factor common to all of a query's slots
 #pragma unroll
             for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float pv = __builtin_amdgcn_exp2f(s[u][kt][i] - m_run[u]);   // masked: 0, some slot is not
+                    const float pv = __builtin_amdgcn_exp2f(fmaf(s[u][kt][i], scale, -m_scaled));   // masked: 0, some slot is not
                     l_run[u] += pv;
                     pb[u][kt >> 1][(kt & 1) * 4 + i] = (_Float16)pv;
                 }
