@@ -185,7 +185,7 @@ struct Lane {
     int32_t* h_poll = nullptr;   // pinned host copy of the 4-int device header (d_n, d_step, d_nlive, d_active)
     hipEvent_t ev[3] = {nullptr, nullptr, nullptr};   // start, end of the prompt forward, end of a micro-batch
     int prompt_rows = 0, prompt_max_len = 0;   // shape of the prompt forward whose state was uploaded last
-    int max_slots = 0;                         // largest slab of its rows
+    int max_ctx = 0;                           // decode forward in flight: the longest context of any row, were all alive
 };
 }  // namespace
 
@@ -505,7 +505,7 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
         }
         if (decode) {   // one token-row per row: rotation and append are fused into the attention kernel
             ss::launch_attention_decode(st, pqkv, ks_qkv, st_qkv, kc, vc, w->rope_cos, w->rope_sin, ao, d, H, hd, n,
-                                        ln.max_slots, s);
+                                        ln.prompt_rows, ln.max_ctx, s);
         } else {
             if (!whole_qkv)
                 ss::launch_rope_append(st, pqkv, ks_qkv, st_qkv, qrot, kc, vc, w->rope_cos, w->rope_sin, d, H, hd, n, s);
@@ -582,7 +582,7 @@ int upload_prompt_state(Lane& ln, const int32_t* toks, const int32_t* offs, cons
     std::copy(sel.begin(), sel.end(), at_host(ln.d_sel));
     ln.prompt_rows = B;
     ln.prompt_max_len = *std::max_element(lens, lens + B);
-    ln.max_slots = *std::max_element(slab, slab + B);
+    ln.max_ctx = ln.prompt_max_len;
     HIPCHK(hipMemcpyAsync(base, tab.data(), tab.size() * 4, hipMemcpyHostToDevice, s));
     HIPCHK(hipMemcpyAsync(st.row_so, so.data(), (size_t)B * 8, hipMemcpyHostToDevice, s));
     HIPCHK(hipStreamSynchronize(s));   // the host vectors above die with this frame
@@ -715,6 +715,7 @@ int decode_microbatch_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_
             int n_live = B;
             if (compact)
                 n_live = (int)(sorted_limit.end() - std::upper_bound(sorted_limit.begin(), sorted_limit.end(), g));
+            ln.max_ctx = ln.prompt_max_len + g;
             forward(w, ln, n_live, n_live, nullptr, nullptr, true, s);
             ss::launch_step_update(st, compact, eos_id, s);
             row_steps += n_live;
@@ -735,6 +736,7 @@ int decode_microbatch_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_
         int n_live = B, active = B;
         if (int rc = poll(&n_live, &active)) return rc;
         for (int g = 1; g < max_new && active > 0; ++g) {
+            ln.max_ctx = ln.prompt_max_len + g;
             forward(w, ln, n_live, n_live, nullptr, nullptr, true, s);
             ss::launch_step_update(st, compact, eos_id, s);
             row_steps += n_live;
@@ -1196,6 +1198,7 @@ int forward_logits_impl(const ss_weights* w, Lane& ln, hipStream_t s, const int3
             ln.st.tr_tok = t + 4;
             ln.st.tr_row = t + 4 + step_n[g];
             ln.st.tr_pos = t + 4 + 2 * step_n[g];
+            ln.max_ctx = ln.prompt_max_len + g;
             forward(w, ln, step_n[g], step_n[g], nullptr, nullptr, true, s);
         }
         if (cs != s) HIPCHK(hipEventRecord(pipe.forward_done[b], s));
@@ -1524,6 +1527,7 @@ int bench_decode_step_lane(const ss_weights* w, Lane& ln, hipStream_t s, const i
         return rc;
     forward(w, ln, B * ctx, B, ln.d_sel, st.d_nlive, false, s);
     ss::launch_step_update(st, 0, -1, s);   // token-rows of the decode step: every row at position ctx
+    ln.max_ctx = ctx + 1;
     EventList evl;
     if (int rc = evl.create(iters + 1)) return rc;
     const std::vector<hipEvent_t>& ev = evl.e;

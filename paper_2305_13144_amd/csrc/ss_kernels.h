@@ -91,10 +91,12 @@ void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, si
 // st.row_j0[i]; max_len = the longest row (sizes the grid).
 void launch_attention_prompt(const MbState& st, const float* qrot, const kv_t* kcache, const kv_t* vcache,
                              f16_t* out_packed, int d, int H, int hd, int B, int max_len, hipStream_t s);
-// max_slots: an upper bound of every row's context (chooses the launch shape).
+// n_max: rows of this launch; mb_rows, max_ctx: rows of the micro-batch, finished ones included, and an upper bound of its
+// contexts in this forward (they choose the launch shape).
 void launch_attention_decode(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
-                             f16_t* out_packed, int d, int H, int hd, int n_max, int max_slots, hipStream_t s);
+                             f16_t* out_packed, int d, int H, int hd, int n_max, int mb_rows, int max_ctx,
+                             hipStream_t s);
 void launch_argmax(const float* logits, int vocab, const int32_t* d_nsel, int32_t* am, int n_max, hipStream_t s);
 // Temperature sampling in place of the argmax: st.am[j] for the first *d_nsel selected rows.  The draw of slot j
 // (row r = st.live_row[j], token number t = *st.d_step) is draws[r * st.max_new + t], or with draws == nullptr

@@ -993,7 +993,7 @@ __global__ __launch_bounds__(256) void k_rope_append(MbState st, const float* __
 // 31.4 -> 27.1 us, 51 rows 15.7 -> 14.1, one row 8.1 -> 6.8 (contexts of 16 to 70).
 constexpr int kAttnUnroll = 8;
 constexpr int kAttnWideMaxGroups = 512;   // decode attention: (row, head) workgroups up to which 8 waves each are used
-constexpr int kAttnWidestMaxGroups = 192; //   ... and 16 waves each, if some context is long enough
+constexpr int kAttnWidestMaxGroups = 192; //   ... and, of the whole micro-batch, 16 waves each, if some context is long enough
 
 template <int HD, int NW>
 __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __restrict__ sc, float* __restrict__ red,
@@ -1336,8 +1336,8 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
 // attends.  Saves a launch and the round trip of q through HBM for every layer of every step.
 // NW waves per workgroup: 8 (256 cache slots per round trip) when the grid is small enough for every workgroup to
 // be resident with room to spare, 4 (128 slots) for larger batches, whose many workgroups already fill the chip, and 16
-// (512 slots) when there is less than one workgroup per compute unit and a context exceeds 256 slots: what a unit has in
-// flight is then all that counts.
+// (512 slots) when the micro-batch has less than one workgroup per compute unit and a context exceeds 256 slots: what a
+// unit has in flight is then all that counts.
 template <int HD, int NW>
 __global__ __launch_bounds__(64 * NW) void k_attention_decode(MbState st, const float* __restrict__ part, int ksplit,
                                                           size_t part_stride, kv_t* __restrict__ kc,
@@ -1825,15 +1825,17 @@ static void launch_attention_decode_inst(const MbState& st, const float* qkv_par
 
 void launch_attention_decode(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
-                             f16_t* out_packed, int d, int H, int hd, int n_max, int max_slots, hipStream_t s)
+                             f16_t* out_packed, int d, int H, int hd, int n_max, int mb_rows, int max_ctx, hipStream_t s)
 {
     // measured at the 7B shape: 8 waves win at 16 rows (512 workgroups: 14.1 against 14.9 us per layer at context
     // 200), 4 waves win at 64 rows (2048 workgroups: 25.7 against 36.1 us at context 100)
     const int groups = n_max * H;
     // 16 waves where 8 would need a second round trip (3 rows at context 2400: 47.5 -> 38 us); shorter contexts leave some
-    // of them without a slot (tiny model, context 40: 6 us with 8 waves, 7.3 with 16)
+    // of them without a slot (tiny model, context 40: 6 us with 8 waves, 7.3 with 16).  Their sums add up in another order,
+    // so the choice depends on the micro-batch and on how far it has come, not on how many of its rows are still alive: a
+    // row's numbers are to be the same whether or when the others leave.
     const bool wide = groups <= kAttnWideMaxGroups;
-    const bool widest = groups <= kAttnWidestMaxGroups && max_slots > 8 * kAttnUnroll * (512 / hd);
+    const bool widest = mb_rows * H <= kAttnWidestMaxGroups && max_ctx > 8 * kAttnUnroll * (512 / hd);
 #define SS_ATTN_ARGS st, qkv_part, ksplit, part_stride, kcache, vcache, rope_cos, rope_sin, out_packed, d, H, n_max, s
     if (hd == 128) {
         if (widest) launch_attention_decode_inst<128, 16>(SS_ATTN_ARGS);

@@ -1,0 +1,37 @@
+"""A row's numbers do not depend on when the other rows of its micro-batch leave: within one 16-row strip the same launches
+run, whatever is still alive.  Bit for bit: the sums are the same sums in the same order."""
+import numpy as np
+import pytest
+
+from paper_2305_13144_amd import binding as ss
+from paper_2305_13144_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+# 16 heads: 16 rows are 256 (row, head) pairs, 3 rows 48; 32 heads: 512 and 96.  Contexts on both sides of what 8 waves have
+# in flight (256 slots of 128 elements, 512 of 64).
+@pytest.mark.parametrize("heads,head_dim,longest", [(16, 64, 600), (16, 64, 505), (32, 128, 300), (32, 128, 250)])
+def test_rows_that_leave_do_not_change_the_others(heads, head_dim, longest):
+    shape = synth.ModelShape("leave", 1, heads * head_dim, heads, head_dim, 256, 272)
+    gw = ss.Weights(shape, synth.make_weights(shape, seed=8, std=0.04, threads=4))
+    rng = np.random.default_rng(longest)
+    rows, steps, stay = 16, 10, (0, 7, 15)
+    plens = rng.integers(3, 30, rows)
+    plens[0] = longest
+    seqs = [rng.integers(0, shape.vocab, p + steps).astype(np.int32) for p in plens]
+
+    def call(cut):
+        s = [q if i in stay else q[:len(q) - cut] for i, q in enumerate(seqs)]
+        offs = np.concatenate([[0], np.cumsum([len(q) for q in s])]).astype(np.int32)
+        out = ss.ss_forward_logits(gw, np.concatenate(s), offs, plens.astype(np.int32))
+        at = np.concatenate([[0], np.cumsum([len(q) - p + 1 for q, p in zip(s, plens)])])
+        return [out[at[i]:at[i + 1]] for i in stay]
+
+    try:
+        all_stay = call(0)
+        for cut in (9, 4):
+            for i, a, b in zip(stay, all_stay, call(cut)):
+                assert np.array_equal(a, b), (cut, i, np.abs(a - b).max())
+    finally:
+        gw.close()
