@@ -1670,7 +1670,7 @@ void launch_rmsnorm(const MbState& st, float* x, const float* part, int ksplit, 
     // start-up (measured at the 7B width: a prompt forward of 640 token-rows takes 13.8 ms, against 15.8 with 1024
     // threads per row, whose norm launches took 47 us each there; up to 256 rows the wide form is the faster one:
     // 24 rows 3.29 against 3.37 ms per decode step, 256 rows equal).
-    if (n_max >= kNormNarrowFrom)
+    if (round_up(n_max, 16) >= kNormNarrowFrom)   // by whole strips, like the projections
         hipLaunchKernelGGL((k_rmsnorm<256, 8>), dim3(round_up(n_max, 128)), dim3(256), 0, s, d_nsel ? d_nsel : st.d_n, x, part,
                            part ? ksplit : 0, part_stride, w, eps, sel, h_packed, d, n_max);
     else

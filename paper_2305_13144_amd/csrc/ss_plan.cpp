@@ -77,6 +77,8 @@ int sweep_nbw(int epilogue, int /*m_rows*/) { return epilogue == EPI_SWIGLU ? 2 
 GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ksplit)
 {
     GemmPlan p{1, 2, 4, 1, 0, 0, 1, 0, -1, 4};
+    // whole strips: a micro-batch keeps its launch shapes, and its rows their last bits, while it shrinks inside a strip
+    m_rows = (m_rows + 15) / 16 * 16;
     const int KB = Kp / 32;
     const int mode = gemm_mode();
     if (m_rows <= kSweepMaxRows) {
