@@ -35,10 +35,10 @@ void ss_set_verbose(int32_t level);
 
 /* Testing aid: which kernel runs the projections of small batches.  0 (default): chosen per shape and row
  * count; 1: never the kernel that stages activations once per workgroup (then: the k-splitting kernel up to 64
- * token-rows, the block kernel, which stages both operands, above); 2: that kernel for every projection of at most 256
+ * token-rows, the block kernel, which stages both operands, above); 2: that kernel for every projection of at most 192
  * token-rows.
  * Adding 4 to a mode (4, 5, 6) keeps that kernel from sharing a strip's k-blocks between two wavefronts; adding 8 keeps
- * the block kernel from its largest tile (256 x 256, prompt forwards of 896 token-rows and more); both for A/B
+ * the block kernel from its largest tile (256 x 256, prompt forwards of more than 880 token-rows); both for A/B
  * measurements.
  * Results agree to the rounding differences between launch shapes (about 1e-3 of the largest logit).  Process-wide (atomic integers, read when a forward is planned: set it
  * between calls, not during one); other values are ignored. */

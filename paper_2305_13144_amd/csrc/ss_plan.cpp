@@ -55,7 +55,7 @@ void set_gemm_mode(int mode)
 int gemm_mode() { return g_gemm_mode.load(std::memory_order_relaxed); }
 
 // Launch shape of a projection.
-// Sweep kernel (<= 256 rows, at least 160 KiB of weights per compute unit and row strip; below that the launch is
+// Sweep kernel (up to sweep_rows rows, at least 160 KiB of weights per compute unit and row strip; below that the launch is
 // too short to amortise its start-up and the skinny kernel's finer split wins: measured at 16 rows, the 7B o
 // projection, 131 KiB per unit, is 12 % faster in the skinny kernel, the 13B one, 205 KiB, 30 % faster here): one workgroup per compute unit and
 // k-slice, a wave per output strip (per gate/up strip pair with the SwiGLU epilogue).  k-slices double
@@ -74,6 +74,19 @@ int gemm_mode() { return g_gemm_mode.load(std::memory_order_relaxed); }
 // 64 rows 3.99 / 4.27 ms, 80 rows 4.36 / 4.58, 96 rows 4.82 / 5.04, 128 rows 5.59 / 5.81.
 int sweep_nbw(int epilogue, int /*m_rows*/) { return epilogue == EPI_SWIGLU ? 2 : 1; }
 
+// Rows up to which the sweep kernel is chosen before the block kernel (the sweep's cost grows with every strip, the block
+// kernel computes whole tiles of 128 rows but streams nothing twice).  The more weights a compute unit has to stream, and
+// the fewer k-slices it takes to occupy them all, the longer the sweep stays ahead.  Microseconds, sweep / block:
+//   little weight   d 1024 gate|up 160 rows 13.1 / 11.3; d 2048 gate|up 160 rows 21.4 / 20.3; 7B o 160 rows 16.5 / 15.6
+//   k in slices     13B o 160 rows 20.7 / 22.8; down 160 rows 45.3 / 47.7, 176 rows 51.1 / 48.2; 7B down 176 rows 34.1 / 32.9
+//   neither         7B q|k|v 160 rows 32.7 / 34.8, 192 rows 35.8 / 35.2, gate|up 176 rows 54.0 / 56.8, 192 rows 56.4 / 58.5,
+//                   208 rows 68.0 / 58.3, head 192 rows 78.5 / 85.6; 13B gate|up 192 rows 83.3 / 94.3; d 8192 139 / 157
+int sweep_rows(size_t w_per_cu, int units, int n_cu)
+{
+    if (w_per_cu < ((size_t)192 << 10)) return 144;
+    return units > 2 * n_cu && w_per_cu >= ((size_t)384 << 10) ? kSweepMaxRows : 160;
+}
+
 GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ksplit)
 {
     GemmPlan p{1, 2, 4, 1, 0, 0, 1, 0, -1, 4};
@@ -84,10 +97,11 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
     if (m_rows <= kSweepMaxRows) {
         const size_t w_per_cu = (size_t)N * (size_t)Kp * 2 / (size_t)n_cu;
         const size_t mt_rows = (size_t)(m_rows + 15) / 16;   // activation re-reads grow with the row strips: sweep earlier
-        if (mode == 2 || (mode == 0 && m_rows <= kSweepAutoRows && w_per_cu * mt_rows >= ((size_t)160 << 10))) {
+        const int nbw = sweep_nbw(epilogue, m_rows);
+        const int units = (N / 16 + nbw - 1) / nbw;
+        if (mode == 2 ||
+            (mode == 0 && m_rows <= sweep_rows(w_per_cu, units, n_cu) && w_per_cu * mt_rows >= ((size_t)160 << 10))) {
             if (epilogue == EPI_SWIGLU) max_ksplit = 1;   // fused epilogue: no k-slices
-            const int nbw = sweep_nbw(epilogue, m_rows);
-            const int units = (N / 16 + nbw - 1) / nbw;
             while (units * p.ksplit < 4 * n_cu && p.ksplit * 2 <= max_ksplit && p.ksplit < kSmallMaxKsplit &&
                    KB / (p.ksplit * 2) >= 16)
                 p.ksplit *= 2;

@@ -10,10 +10,7 @@ namespace ss {
 // EPI_RESIDUAL and EPI_QKV: block kernel without k-slices only; planned as EPI_PARTIAL.
 enum Epilogue { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_RESIDUAL = 2, EPI_QKV = 3 };
 
-constexpr int kSweepMaxRows = 256;   // 16 row strips: accumulators and the LDS chunk of the sweep kernel still fit
-// Rows up to which it is chosen: 9 row strips.  Per step of the sweep / block kernel, 7B, microseconds: 130 rows q|k|v
-// 28.5 / 30.6, gate|up 44.6 / 48.4, down 28.3 / 29.2, o 14.7 / 14.1; 163 rows 36.7 / 31.3, 58.9 / 51.3, 33.0 / 29.9, 16.6 / 14.5.
-constexpr int kSweepAutoRows = 144;
+constexpr int kSweepMaxRows = 192;   // 12 row strips: beyond, the sweep kernel is never the faster one (see sweep_rows)
 
 constexpr int kNarrowMaxRows = 96;   // most token-rows for which the 12-bit weights are read
 
@@ -36,7 +33,7 @@ struct GemmPlan {
     int tms;        // block kernel: row strips per wave, 8 with the largest tile, else 4
 };
 
-constexpr int kTiledTallFrom = 896;   // token-rows from which the block kernel may use its largest tile
+constexpr int kTiledTallFrom = 896;   // token-rows (in whole strips) from which the block kernel may use its largest tile
 
 // n_cu: compute units of the device (the sweep kernel runs one workgroup per unit).
 // max_ksplit: 1 when the consumer reads the output directly (logits).
@@ -49,6 +46,9 @@ int sweep_nbw(int epilogue, int m_rows);
 // [N, *] matrix and 1 <= m_rows <= n_max fits: an upper bound of ksplit * m_rows over that range.
 // sliced_only: count only plans with ksplit > 1 (a buffer that is used only then).
 size_t gemm_partial_rows_bound(int N, int n_max, bool sliced_only = false);
+
+// Rows up to which the sweep kernel is chosen for a matrix of w_per_cu weight bytes per compute unit and this many units.
+int sweep_rows(size_t w_per_cu, int units, int n_cu);
 
 // Testing aid: 0 = choose per shape (default), 1 = never use the sweep kernel, 2 = use it for every
 // projection of at most kSweepMaxRows rows.

@@ -63,3 +63,49 @@ def test_row_counts_of_one_strip_share_a_plan(tmp_path):
             });
         }
     """)
+
+
+def test_kernel_choice_follows_the_measurements(tmp_path):
+    """Sweep or block kernel at 145 to 256 rows, on 256 compute units, wherever one of them was measured 4 % faster or more."""
+    _run(tmp_path, r"""
+        struct Point { int N, Kp, epi, max_ksplit, rows; bool sweep; };
+        int main() {
+            const int P = ss::EPI_PARTIAL, S = ss::EPI_SWIGLU;
+            const Point points[] = {
+                // d 4096, ffn 11008: q|k|v, gate|up, head (us, sweep / block)
+                {12288, 4096, P, 8, 160, true},     // 32.7 / 34.8
+                {22016, 4096, S, 8, 160, true},     // 50.0 / 56.5
+                {22016, 4096, S, 8, 176, true},     // 54.0 / 56.8
+                {22016, 4096, S, 8, 208, false},    // 68.0 / 58.3
+                {32000, 4096, P, 1, 160, true},     // 66.3 / 81.5
+                {32000, 4096, P, 1, 192, true},     // 78.5 / 85.6
+                {32000, 4096, P, 1, 224, false},    // 98.7 / 83.4
+                {12288, 4096, P, 8, 224, false},    // 47.2 / 38.0
+                {4096, 4096, P, 8, 176, false},     // 17.2 / 15.7
+                // d 5120, ffn 13824
+                {15360, 5120, P, 8, 160, true},     // 46.6 / 52.7
+                {15360, 5120, P, 8, 176, true},     // 51.1 / 54.0
+                {5120, 5120, P, 8, 160, true},      // 20.7 / 22.8
+                {27648, 5120, S, 8, 192, true},     // 83.3 / 94.3
+                {5120, 13824, P, 8, 160, true},     // 45.3 / 47.7
+                {5120, 13824, P, 8, 176, false},    // 51.1 / 48.2
+                {15360, 5120, P, 8, 224, false},    // 61.2 / 54.9
+                // d 3072, ffn 8192
+                {9216, 3072, P, 8, 160, true},      // 22.8 / 24.5
+                {16384, 3072, S, 8, 160, true},     // 31.2 / 33.8
+                {9216, 3072, P, 8, 192, false},     // 26.8 / 25.0
+                // d 2048, ffn 5504; d 1024, ffn 2752; d 8192, ffn 16384
+                {11008, 2048, S, 8, 176, false},    // 23.4 / 20.1
+                {6144, 2048, P, 8, 176, false},     // 15.1 / 13.7
+                {5504, 1024, S, 8, 160, false},     // 13.1 / 11.3
+                {32768, 8192, S, 8, 192, true},     // 139 / 157
+            };
+            for (const Point& q : points) {
+                const ss::GemmPlan p = ss::gemm_plan(q.N, q.Kp, q.rows, q.epi, 256, q.max_ksplit);
+                if ((p.sweep_gn > 0) == q.sweep && (p.block >= 0) != q.sweep) continue;
+                std::printf("N %d Kp %d, %d rows: the other kernel is chosen\n", q.N, q.Kp, q.rows);
+                return 1;
+            }
+            return 0;
+        }
+    """)
