@@ -8,6 +8,7 @@
 
 namespace {
 thread_local char g_err[512] = "";
+thread_local size_t g_missing = 0;
 std::atomic<int> g_verbose{0};
 }
 
@@ -21,6 +22,10 @@ int fail(int code, const char* fmt, ...)
     va_end(ap);
     return code;
 }
+
+size_t missing_bytes() { return g_missing; }
+
+void set_missing_bytes(size_t bytes) { g_missing = bytes; }
 
 void clear_error() { g_err[0] = '\0'; }
 

@@ -15,6 +15,7 @@
 #include <deque>
 #include <mutex>
 #include <numeric>
+#include <string>
 #include <thread>
 #include <vector>
 
@@ -73,6 +74,15 @@ struct Layer {
     PackedMat wqkv, wo, wgu, wd;
 };
 
+// A failed device allocation of `want` bytes: records how many bytes were missing.
+int no_device_memory(size_t want, hipError_t e)
+{
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) free_b = 0;
+    ss::set_missing_bytes(want > free_b ? want - free_b : 0);
+    return ss::fail(ss::kNoDeviceMemory, "hipMalloc(%zu bytes): %s", want, hipGetErrorString(e));
+}
+
 // A grow-only device buffer.
 struct Buf {
     void* p = nullptr;
@@ -89,7 +99,7 @@ struct Buf {
         hipError_t e = hipMalloc(&p, want);
         if (e != hipSuccess) {
             p = nullptr;
-            return ss::fail(SS_ENOMEM, "hipMalloc(%zu bytes): %s", want, hipGetErrorString(e));
+            return no_device_memory(want, e);
         }
         bytes = want;
         if (zero) {
@@ -204,12 +214,7 @@ struct ss_weights {
     std::atomic<int> busy{0};
     void* scratch_ptr = nullptr;   // device address of this device's static scratch array
     int in_flight = SS_IN_FLIGHT_DEFAULT;       // micro-batches a group pass keeps in flight (1 to kLanes)
-    bool has_narrow() const
-    {
-        for (const Layer& L : layers)
-            if (L.wqkv.pn || L.wo.pn || L.wgu.pn || L.wd.pn) return true;
-        return lm_head.pn != nullptr;
-    }
+    size_t copy_bytes = 0;                      // device memory of the 12-bit weight copies; 0 = there are none
 };
 
 namespace {
@@ -228,7 +233,7 @@ int dev_alloc(ss_weights* w, void** out, size_t bytes, bool zero)
 {
     void* p = nullptr;
     hipError_t e = hipMalloc(&p, bytes);
-    if (e != hipSuccess) return ss::fail(SS_ENOMEM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
+    if (e != hipSuccess) return no_device_memory(bytes, e);
     w->allocs.push_back(p);
     if (zero) HIPCHK(hipMemset(p, 0, bytes));
     *out = p;
@@ -281,8 +286,12 @@ std::vector<PackedMat*> all_matrices(ss_weights* w)
     return m;
 }
 
+// Bytes of a matrix's 12-bit copy: one group of 4 k-blocks is 3 KiB.
+size_t narrow_groups(const PackedMat& m) { return m.Kp % 128 == 0 ? (size_t)(m.N / 16) * (m.Kp / 128) : 0; }
+
 void drop_narrow(ss_weights* w)
 {
+    w->copy_bytes = 0;
     for (PackedMat* m : all_matrices(w)) {
         if (m->pn) (void)hipFree(m->pn);
         m->pn = nullptr;
@@ -293,57 +302,76 @@ void drop_narrow(ss_weights* w)
 // once more.  Only when they take at most an eighth of the device memory that is free now, so that they do not stand in
 // the way of key/value caches (and a call that runs out of memory all the same drops them, see with_memory); a matrix
 // that has a value without a 12-bit form, or whose K is no multiple of a group, goes without.
-int make_narrow(ss_weights* w)
+// any_room: whatever they take of the free memory (they had it until now).
+int make_narrow(ss_weights* w, bool any_room = false)
 {
+    drop_narrow(w);
     const std::vector<PackedMat*> mats = all_matrices(w);
-    auto fits = [](const PackedMat* m) { return m->Kp % 128 == 0; };
-    auto groups = [](const PackedMat* m) { return (size_t)(m->N / 16) * (m->Kp / 128); };
     size_t need = 0, free_b = 0, total_b = 0;
-    for (const PackedMat* m : mats)
-        if (fits(m)) need += groups(m) * 3072;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need == 0 || need > free_b / 8) return SS_OK;
+    for (const PackedMat* m : mats) need += narrow_groups(*m) * 3072;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need == 0 || (!any_room && need > free_b / 8))
+        return SS_OK;
     struct Flags {
         Buf b;
         ~Flags() { b.release(); }
     } flags;
-    if (int rc = flags.b.ensure(mats.size() * 4, true)) return rc;
+    std::vector<int32_t> unfit(mats.size());
+    if (const int rc = flags.b.ensure(mats.size() * 4, true)) {
+        if (rc != ss::kNoDeviceMemory) return rc;
+        (void)hipGetLastError();   // no room: none of them
+        ss::clear_error();
+        return SS_OK;
+    }
     hipStream_t s = w->lane[0].stream;
     for (size_t i = 0; i < mats.size(); ++i) {
         PackedMat* m = mats[i];
-        if (!fits(m)) continue;
-        if (hipMalloc(&m->pn, groups(m) * 3072) != hipSuccess) {   // no room after all: none of them
+        if (narrow_groups(*m) == 0) continue;
+        if (hipMalloc(&m->pn, narrow_groups(*m) * 3072) != hipSuccess) {   // no room after all: none of them
             (void)hipGetLastError();
             m->pn = nullptr;
             HIPCHK(hipStreamSynchronize(s));
             drop_narrow(w);
             return SS_OK;
         }
-        ss::launch_narrow_weight(m->p, m->pn, groups(m), flags.b.as<int32_t>() + i, s);
+        ss::launch_narrow_weight(m->p, m->pn, narrow_groups(*m), flags.b.as<int32_t>() + i, s);
     }
-    std::vector<int32_t> unfit(mats.size());
     HIPCHK(hipStreamSynchronize(s));
     HIPCHK(hipMemcpy(unfit.data(), flags.b.p, mats.size() * 4, hipMemcpyDeviceToHost));
     for (size_t i = 0; i < mats.size(); ++i)
         if (unfit[i] && mats[i]->pn) {
             (void)hipFree(mats[i]->pn);
             mats[i]->pn = nullptr;
+        } else if (mats[i]->pn) {
+            w->copy_bytes += narrow_groups(*mats[i]) * 3072;
         }
     return SS_OK;
 }
 
-// Runs a call's body; if it runs out of device memory while the handle holds 12-bit weight copies, gives those back
-// and runs it once more (from the start: a body writes its outputs from scratch).  Nothing else is in flight on the
-// handle: the caller holds its busy flag, and a body's lanes have ended when it returns.
+// Runs a call's body; if a device allocation fails and the handle's 12-bit weight copies hold as much as was missing,
+// gives them back and runs it once more (from the start: a body writes its outputs from scratch).  If that was not enough
+// after all (the figure is that of one allocation), the workspace that grew goes and the copies are made again: a call that
+// fails slows no later one down.  Nothing else is in flight on the handle: the caller holds its busy flag, and a body's lanes have ended when it returns.
 template <class F>
 int with_memory(ss_weights* w, F body)
 {
-    int rc = ss::no_throw(body);
-    if (rc != SS_ENOMEM || !w->has_narrow()) return rc;
-    for (Lane& ln : w->lane) (void)hipStreamSynchronize(ln.stream);
-    drop_narrow(w);
-    (void)hipGetLastError();
-    ss::clear_error();
-    return ss::no_throw(body);
+    return ss::no_throw([&]() -> int {
+        int rc = ss::no_throw(body);
+        if (rc == ss::kNoDeviceMemory && w->copy_bytes > 0 && w->copy_bytes >= ss::missing_bytes()) {
+            for (Lane& ln : w->lane) (void)hipStreamSynchronize(ln.stream);
+            drop_narrow(w);
+            (void)hipGetLastError();
+            ss::clear_error();
+            rc = ss::no_throw(body);
+            if (rc == ss::kNoDeviceMemory) {
+                const std::string text = ss_last_error();
+                (void)hipGetLastError();
+                for (Lane& ln : w->lane) ln.ws.release();
+                if (make_narrow(w, true) != SS_OK) (void)hipGetLastError();
+                return ss::fail(SS_ENOMEM, "%s", text.c_str());
+            }
+        }
+        return rc == ss::kNoDeviceMemory ? SS_ENOMEM : rc;
+    });
 }
 
 int check_cfg(const ss_model_cfg* c)
@@ -879,7 +907,7 @@ extern "C" int ss_weights_create(const ss_model_cfg* cfg, const void* const* ten
     const int rc = ss::no_throw([&] { return weights_create_impl(w, tensors, src_dtype); });
     if (rc != SS_OK) {
         ss_weights_destroy(w);
-        return rc;
+        return rc == ss::kNoDeviceMemory ? SS_ENOMEM : rc;
     }
     *out = w;
     return SS_OK;
@@ -895,6 +923,16 @@ extern "C" int ss_set_option(ss_weights* w, int32_t option, int32_t value)
         if (value < 1 || value > kLanes) return ss::fail(SS_EINVAL, "SS_OPT_IN_FLIGHT takes 1 to %d", kLanes);
         w->in_flight = value;
         return SS_OK;
+    }
+    if (option == SS_OPT_WEIGHT_COPIES) {
+        if (value != 0 && value != 1) return ss::fail(SS_EINVAL, "SS_OPT_WEIGHT_COPIES takes 0 or 1");
+        return ss::no_throw([&]() -> int {
+            HIPCHK(hipSetDevice(w->device));
+            if (value == 1) return w->copy_bytes > 0 ? SS_OK : make_narrow(w);
+            for (Lane& ln : w->lane) (void)hipStreamSynchronize(ln.stream);
+            drop_narrow(w);
+            return SS_OK;
+        });
     }
     return ss::fail(SS_EINVAL, "unknown option %d", option);
 }
@@ -979,7 +1017,7 @@ extern "C" int ss_decode_microbatch_static(ss_weights* w, const int32_t* prompt_
     view.ws.arena = (char*)w->scratch_ptr;
     view.ws.arena_bytes = kStaticScratchBytes;
     view.in();
-    return ss::no_throw([&] {   // (no with_memory: this call frees no device memory)
+    return ss::no_throw([&] {   // (no with_memory: this call allocates and frees no device memory)
         return decode_microbatch_impl(w, ln, prompt_tokens, prompt_offsets, B, max_new, target_lens, nullptr, flags,
                                       out_tokens, out_lens, out_failed, stats, s);
     });
@@ -1304,6 +1342,7 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
         std::atomic<int> stop{0};
         std::mutex mu;                 // guards gs, failed, rc/err and the progress lines
         int rc = SS_OK;
+        size_t missing = 0;            // with rc == kNoDeviceMemory
         char err[512] = "";            // fixed storage: recording an error allocates nothing
     };
 
@@ -1317,6 +1356,7 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
             std::lock_guard<std::mutex> lock(ps.mu);
             if (ps.rc == SS_OK) {
                 ps.rc = rc;
+                ps.missing = ss::missing_bytes();
                 std::snprintf(ps.err, sizeof(ps.err), "%s", ss_last_error());
             }
             ps.stop.store(1);
@@ -1428,7 +1468,10 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
         }
         work_noexcept(ps, w->lane[0], s);
         for (int i = 0; i < n_others; ++i) others[i].join();
-        if (ps.rc != SS_OK) return ss::fail(ps.rc, "%s", ps.err);
+        if (ps.rc != SS_OK) {
+            ss::set_missing_bytes(ps.missing);
+            return ss::fail(ps.rc, "%s", ps.err);
+        }
         return SS_OK;
     };
 
@@ -1585,38 +1628,45 @@ extern "C" int ss_bench_decode_steps_in_flight(ss_weights* w, const int32_t* pro
     if (lanes < 1 || lanes > kLanes) return ss::fail(SS_EINVAL, "lanes outside [1, %d]", kLanes);
     BusyGuard guard(w);
     if (!guard.ok) return ss::fail(SS_ESTATE, "another call is in flight on this handle");
-    std::atomic<int> gate{0};
-    int rc[kLanes] = {};
-    char err[kLanes][256] = {};
-    auto run = [&](int l) {   // a lane's thread lets no exception out; its error text is copied for the caller
-        rc[l] = ss::no_throw([&] {
-            return bench_decode_step_lane(w, w->lane[l], w->lane[l].stream, prompt_tokens, B, ctx, iters,
-                                          ms_out + (size_t)l * iters, &gate, lanes);
-        });
-        if (rc[l]) std::snprintf(err[l], sizeof(err[l]), "%s", ss_last_error());
-    };
-    std::thread others[kLanes];   // fixed storage: only starting a thread can fail below
-    int n_others = 0;
-    auto join_all = [&] {
-        for (int i = 0; i < n_others; ++i) others[i].join();
-    };
-    for (int l = 1; l < lanes; ++l) {
-        try {
-            others[n_others] = std::thread(run, l);
-            ++n_others;
-        } catch (...) {
-            // the lanes already started (1 .. l-1) wait at the gate for `lanes` arrivals: stand in for the ones
-            // that will not come (l .. lanes-1, and lane 0, which this thread would have run)
-            gate.fetch_add(lanes - l + 1);
-            join_all();
-            return ss::fail(SS_ESTATE, "could not start host thread %d", l);
+    return with_memory(w, [&]() -> int {
+        std::atomic<int> gate{0};
+        int rc[kLanes] = {};
+        size_t missing[kLanes] = {};
+        char err[kLanes][256] = {};
+        auto run = [&](int l) {   // a lane's thread lets no exception out; its error text is copied for the caller
+            rc[l] = ss::no_throw([&] {
+                return bench_decode_step_lane(w, w->lane[l], w->lane[l].stream, prompt_tokens, B, ctx, iters,
+                                              ms_out + (size_t)l * iters, &gate, lanes);
+            });
+            missing[l] = ss::missing_bytes();
+            if (rc[l]) std::snprintf(err[l], sizeof(err[l]), "%s", ss_last_error());
+        };
+        std::thread others[kLanes];   // fixed storage: only starting a thread can fail below
+        int n_others = 0;
+        auto join_all = [&] {
+            for (int i = 0; i < n_others; ++i) others[i].join();
+        };
+        for (int l = 1; l < lanes; ++l) {
+            try {
+                others[n_others] = std::thread(run, l);
+                ++n_others;
+            } catch (...) {
+                // the lanes already started (1 .. l-1) wait at the gate for `lanes` arrivals: stand in for the ones
+                // that will not come (l .. lanes-1, and lane 0, which this thread would have run)
+                gate.fetch_add(lanes - l + 1);
+                join_all();
+                return ss::fail(SS_ESTATE, "could not start host thread %d", l);
+            }
         }
-    }
-    run(0);
-    join_all();
-    for (int l = 0; l < lanes; ++l)
-        if (rc[l]) return ss::fail(rc[l], "%s", err[l]);
-    return SS_OK;
+        run(0);
+        join_all();
+        for (int l = 0; l < lanes; ++l)
+            if (rc[l]) {
+                ss::set_missing_bytes(missing[l]);
+                return ss::fail(rc[l], "%s", err[l]);
+            }
+        return SS_OK;
+    });
 }
 
 namespace {

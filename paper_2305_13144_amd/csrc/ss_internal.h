@@ -16,6 +16,13 @@ int fail(int code, const char* fmt, ...) __attribute__((format(printf, 2, 3)));
 void clear_error();
 int verbose();   // ss_set_verbose level
 
+// What an impl function returns when a device allocation failed: SS_ENOMEM to the caller, unless the library holds device
+// memory that it can give back (with_memory in the engine).  Never leaves an entry point.
+constexpr int kNoDeviceMemory = -1000;
+// Bytes that the last failed device allocation of this thread was short of (a lane's thread hands its figure on).
+size_t missing_bytes();
+void set_missing_bytes(size_t bytes);
+
 // Runs the body of an entry point (a callable returning an SS_* code) so that no C++ exception crosses the C ABI:
 // a failed host allocation becomes SS_ENOMEM, anything else SS_ESTATE, each with a message.
 template <class Body>
