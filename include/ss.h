@@ -131,8 +131,9 @@ typedef struct ss_weights ss_weights; /* opaque; owns packed bf16 weights and a 
  * element).  Everything stored as half saturates at +-65504.  A matrix whose values are all below 0.25 in magnitude is
  * kept a second time in a 12-bit form of the same values, which small decode batches stream instead (three quarters of
  * the packed bytes once more, only while all such copies take at most an eighth of the free device memory; a call that
- * runs out of device memory, and is short of no more than they hold, gives them back and is run again without them:
- * see SS_OPT_WEIGHT_COPIES).  Source values must be finite: they are not checked.
+ * runs out of device memory, and is short of no more than the copies of this process's handles on its GPU hold, takes its
+ * handle's and, if need be, those of others, and is run again; so does ss_weights_create: see SS_OPT_WEIGHT_COPIES).
+ * Source values must be finite: they are not checked.
  * A row whose logits are all NaN or -inf yields token id 0, never an id outside the vocabulary.
  * Errors: SS_EINVAL (shape), SS_EDEVICE (no usable GPU / HIP error), SS_ENOMEM.
  */
@@ -154,9 +155,11 @@ void ss_weights_destroy(ss_weights* w);
  *   and key/value cache per lane in use, each as large as the largest micro-batch that lane has run.
  *   option SS_OPT_WEIGHT_COPIES, value = 0 or 1: the handle's 12-bit weight copies.  0 gives their memory back; 1 makes
  *   those that it has not got, under the rule above (at most an eighth of the device memory that is free now; otherwise
- *   none, and still SS_OK).  A new handle has them (1).  A call that needed their memory leaves the handle as 0 does, until
- *   1 is set again.  With or without them the weights are the same values; logits agree to the rounding differences
- *   between launch shapes, as the two forms share out a sum differently.
+ *   none, and still SS_OK).  A new handle has them (1).  A call that needed their memory, on this handle or on another of
+ *   the process (which waits for a call in flight on this one to end), leaves the handle as 0 does, until 1 is set again.
+ *   Other users of the GPU cannot take them: a program that needs that memory itself sets 0.  With or without them the
+ *   weights are the same values; logits agree to the rounding differences between launch shapes, as the two forms share
+ *   out a sum differently.
  * Errors: SS_EINVAL (NULL handle, unknown option, value out of range), SS_ESTATE (a call is in flight).
  */
 #define SS_OPT_IN_FLIGHT 2

@@ -214,7 +214,12 @@ struct ss_weights {
     std::atomic<int> busy{0};
     void* scratch_ptr = nullptr;   // device address of this device's static scratch array
     int in_flight = SS_IN_FLIGHT_DEFAULT;       // micro-batches a group pass keeps in flight (1 to kLanes)
-    size_t copy_bytes = 0;                      // device memory of the 12-bit weight copies; 0 = there are none
+    // The 12-bit weight copies are read and changed under copies_mu: a call holds it while its body runs, a call on another
+    // handle that is short of memory takes it to have them.
+    std::mutex copies_mu;
+    std::atomic<size_t> copy_bytes{0};          // device memory of the copies; 0 = there are none
+    const void* taken_by = nullptr;             // the call that took them and has not ended yet (under g_handles_mu)
+    ss_weights* next = nullptr;                 // the process's handles (under g_handles_mu)
 };
 
 namespace {
@@ -347,28 +352,85 @@ int make_narrow(ss_weights* w, bool any_room = false)
     return SS_OK;
 }
 
-// Runs a call's body; if a device allocation fails and the handle's 12-bit weight copies hold as much as was missing,
-// gives them back and runs it once more (from the start: a body writes its outputs from scratch).  If that was not enough
-// after all (the figure is that of one allocation), the workspace that grew goes and the copies are made again: a call that
-// fails slows no later one down.  Nothing else is in flight on the handle: the caller holds its busy flag, and a body's lanes have ended when it returns.
+// Every handle of the process, for the device memory that they can give back.  Lock order: g_handles_mu, then a handle's
+// copies_mu; a call lets go of its own copies_mu before it takes g_handles_mu, so waiting for another call to end ends.
+std::mutex g_handles_mu;
+ss_weights* g_handles = nullptr;
+
+// The copies of one handle go (its copies_mu is held, no call on it runs).
+size_t take_copies(ss_weights* h, const void* by)
+{
+    const size_t had = h->copy_bytes;
+    if (had == 0) return 0;
+    for (Lane& ln : h->lane) (void)hipStreamSynchronize(ln.stream);
+    drop_narrow(h);
+    h->taken_by = by;
+    return had;
+}
+
+// Device memory for a call (`by`) that is short of `missing` bytes on `device`: the copies of `own` (null: a handle that
+// is being created), then those of handles without a call in flight, then, as their calls end, those of the others.
+// Nothing is touched if all of them together hold less.
+bool take_memory(int device, ss_weights* own, const void* by, size_t missing)
+{
+    std::lock_guard<std::mutex> all(g_handles_mu);
+    size_t there = 0, got = 0;
+    for (ss_weights* h = g_handles; h; h = h->next)
+        if (h->device == device) there += h->copy_bytes;
+    if (there == 0 || there < missing) return false;
+    if (own) {
+        std::lock_guard<std::mutex> lock(own->copies_mu);
+        got += take_copies(own, by);
+    }
+    for (const bool wait : {false, true})
+        for (ss_weights* h = g_handles; h && got < missing; h = h->next) {
+            if (h == own || h->device != device || h->copy_bytes == 0) continue;
+            std::unique_lock<std::mutex> lock(h->copies_mu, std::defer_lock);
+            if (wait) lock.lock();
+            else if (!lock.try_lock()) continue;
+            got += take_copies(h, by);
+        }
+    (void)hipGetLastError();
+    return true;
+}
+
+// The call that took copies has ended: they stay gone if it needed them, and are made again if it failed all the same.
+void settle_memory(const void* by, bool give)
+{
+    std::lock_guard<std::mutex> all(g_handles_mu);
+    for (ss_weights* h = g_handles; h; h = h->next) {
+        if (h->taken_by != by) continue;
+        h->taken_by = nullptr;
+        if (!give) continue;
+        std::lock_guard<std::mutex> lock(h->copies_mu);
+        if (make_narrow(h, true) != SS_OK) (void)hipGetLastError();
+    }
+}
+
+// Runs a call's body; if a device allocation fails and the 12-bit weight copies of the process's handles hold as much as
+// was missing, takes them and runs it once more (from the start: a body writes its outputs from scratch).  If that was not
+// enough after all (the figure is that of one allocation), the workspace that grew goes and the copies are made again: a
+// call that fails slows no later one down.  Nothing else is in flight on the handle: the caller holds its busy flag, and a
+// body's lanes have ended when it returns.
 template <class F>
 int with_memory(ss_weights* w, F body)
 {
     return ss::no_throw([&]() -> int {
-        int rc = ss::no_throw(body);
-        if (rc == ss::kNoDeviceMemory && w->copy_bytes > 0 && w->copy_bytes >= ss::missing_bytes()) {
-            for (Lane& ln : w->lane) (void)hipStreamSynchronize(ln.stream);
-            drop_narrow(w);
-            (void)hipGetLastError();
+        auto locked = [&] {
+            std::lock_guard<std::mutex> lock(w->copies_mu);
+            return ss::no_throw(body);
+        };
+        int rc = locked();
+        if (rc == ss::kNoDeviceMemory && take_memory(w->device, w, w, ss::missing_bytes())) {
             ss::clear_error();
-            rc = ss::no_throw(body);
+            rc = locked();
+            const std::string text = ss_last_error();
             if (rc == ss::kNoDeviceMemory) {
-                const std::string text = ss_last_error();
                 (void)hipGetLastError();
                 for (Lane& ln : w->lane) ln.ws.release();
-                if (make_narrow(w, true) != SS_OK) (void)hipGetLastError();
-                return ss::fail(SS_ENOMEM, "%s", text.c_str());
             }
+            settle_memory(w, rc == ss::kNoDeviceMemory);
+            if (rc == ss::kNoDeviceMemory) return ss::fail(SS_ENOMEM, "%s", text.c_str());
         }
         return rc == ss::kNoDeviceMemory ? SS_ENOMEM : rc;
     });
@@ -901,16 +963,33 @@ extern "C" int ss_weights_create(const ss_model_cfg* cfg, const void* const* ten
     int ndev = 0;
     if (hipGetDeviceCount(&ndev) != hipSuccess || ndev < 1) return ss::fail(SS_EDEVICE, "no HIP device available");
 
-    ss_weights* w = new (std::nothrow) ss_weights();
-    if (!w) return ss::fail(SS_ENOMEM, "host allocation failed");
-    w->cfg = *cfg;
-    const int rc = ss::no_throw([&] { return weights_create_impl(w, tensors, src_dtype); });
-    if (rc != SS_OK) {
-        ss_weights_destroy(w);
-        return rc == ss::kNoDeviceMemory ? SS_ENOMEM : rc;
-    }
-    *out = w;
-    return SS_OK;
+    return ss::no_throw([&]() -> int {
+        ss_weights* w = nullptr;
+        auto create = [&]() -> int {
+            w = new (std::nothrow) ss_weights();
+            if (!w) return ss::fail(SS_ENOMEM, "host allocation failed");
+            w->cfg = *cfg;
+            const int rc = ss::no_throw([&] { return weights_create_impl(w, tensors, src_dtype); });
+            if (rc != SS_OK) ss_weights_destroy(w);
+            return rc;
+        };
+        int rc = create(), device = 0;
+        // the copies of other handles stand back for a new one
+        if (rc == ss::kNoDeviceMemory && hipGetDevice(&device) == hipSuccess &&
+            take_memory(device, nullptr, &rc, ss::missing_bytes())) {
+            ss::clear_error();
+            rc = create();
+            const std::string text = ss_last_error();
+            settle_memory(&rc, rc == ss::kNoDeviceMemory);
+            if (rc != SS_OK) return ss::fail(rc == ss::kNoDeviceMemory ? SS_ENOMEM : rc, "%s", text.c_str());
+        }
+        if (rc != SS_OK) return rc == ss::kNoDeviceMemory ? SS_ENOMEM : rc;
+        std::lock_guard<std::mutex> lock(g_handles_mu);
+        w->next = g_handles;
+        g_handles = w;
+        *out = w;
+        return SS_OK;
+    });
 }
 
 extern "C" int ss_set_option(ss_weights* w, int32_t option, int32_t value)
@@ -927,6 +1006,7 @@ extern "C" int ss_set_option(ss_weights* w, int32_t option, int32_t value)
     if (option == SS_OPT_WEIGHT_COPIES) {
         if (value != 0 && value != 1) return ss::fail(SS_EINVAL, "SS_OPT_WEIGHT_COPIES takes 0 or 1");
         return ss::no_throw([&]() -> int {
+            std::lock_guard<std::mutex> lock(w->copies_mu);
             HIPCHK(hipSetDevice(w->device));
             if (value == 1) return w->copy_bytes > 0 ? SS_OK : make_narrow(w);
             for (Lane& ln : w->lane) (void)hipStreamSynchronize(ln.stream);
@@ -945,6 +1025,14 @@ extern "C" void ss_set_gemm_mode(int32_t mode)
 extern "C" void ss_weights_destroy(ss_weights* w)
 {
     if (!w) return;
+    {
+        std::lock_guard<std::mutex> lock(g_handles_mu);
+        for (ss_weights** at = &g_handles; *at; at = &(*at)->next)
+            if (*at == w) {
+                *at = w->next;
+                break;
+            }
+    }
     (void)hipSetDevice(w->device);
     for (Lane& ln : w->lane) {
         if (ln.stream) (void)hipStreamSynchronize(ln.stream);
@@ -1018,6 +1106,7 @@ extern "C" int ss_decode_microbatch_static(ss_weights* w, const int32_t* prompt_
     view.ws.arena_bytes = kStaticScratchBytes;
     view.in();
     return ss::no_throw([&] {   // (no with_memory: this call allocates and frees no device memory)
+        std::lock_guard<std::mutex> lock(w->copies_mu);
         return decode_microbatch_impl(w, ln, prompt_tokens, prompt_offsets, B, max_new, target_lens, nullptr, flags,
                                       out_tokens, out_lens, out_failed, stats, s);
     });

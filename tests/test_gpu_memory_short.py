@@ -147,6 +147,76 @@ def child_lanes(c):
         c.budget(None)
 
 
+def child_other_handles(c):
+    """A new handle, and a call on another one, take the copies of the handles that are there."""
+    a = c.weights()
+    held = c.copies(a)
+    before = c.live()
+    b = c.weights()
+    whole = c.live() - before                    # a handle with copies
+    want = c.microbatch(b, 16, 40)
+    need = c.live() - before - whole             # what the call takes
+    b.close()
+    c.budget(whole - held // 2)                  # room for a handle without copies, not for the rule that grants them
+    b = c.weights()
+    assert c.copies(a) == held                   # there was room: nothing was taken
+    b.close()
+    c.budget(whole - held - held // 2)           # half of what the first one's copies hold is missing
+    b = c.weights()
+    assert c.given_back(a)
+    a.set_option(c.ss.SS_OPT_WEIGHT_COPIES, 1)
+    assert c.copies(a) == held
+    c.microbatch(a, 4, 5)
+    b.set_option(c.ss.SS_OPT_WEIGHT_COPIES, 0)
+    halves = c.microbatch(a, 4, 5)
+    c.budget(need - held // 2)
+    got = c.microbatch(b, 16, 40)                # b has none of its own
+    assert c.given_back(a)
+    a.set_option(c.ss.SS_OPT_WEIGHT_COPIES, 1)
+    assert (got == want).mean() > 0.9            # other rounding, the same model
+    assert c.np.array_equal(c.microbatch(a, 4, 5), halves)
+    # far too much for both: nobody loses anything
+    c.budget(MB)
+    c.out_of_memory(lambda: c.microbatch(b, 64, 1000))
+    assert c.copies(a) == held
+    b.close()
+    # a handle that cannot be had: the first one keeps its copies
+    c.budget(whole - 3 * held)
+    c.out_of_memory(c.weights)
+    assert c.copies(a) == held
+
+
+def child_a_busy_handle_gives_back_when_its_call_ends(c):
+    import threading
+    a, b = c.weights(), c.weights()
+    held = c.copies(a)
+    b.set_option(c.ss.SS_OPT_WEIGHT_COPIES, 0)
+    before = c.live()
+    want = c.microbatch(b, 16, 40)
+    need = c.live() - before
+    b.close()
+    b = c.weights()
+    b.set_option(c.ss.SS_OPT_WEIGHT_COPIES, 0)
+    toks, offs = c.request(8, 20, seed=5)
+    long_call = lambda: c.ss.ss_decode_microbatch(a, toks, offs, 400, c.np.full(8, 400, c.np.int32))["tokens"]
+    ref = long_call()
+    out, started = [], threading.Event()
+
+    def run():
+        started.set()
+        out.append(long_call())
+
+    c.budget(need - held // 2)
+    t = threading.Thread(target=run)
+    t.start()
+    started.wait()
+    got = c.microbatch(b, 16, 40)                # waits for the long call where that is still running
+    t.join()
+    assert c.given_back(a)
+    assert c.np.array_equal(got, want)
+    assert (out[0] == ref).mean() > 0.9 and out[0].shape == ref.shape
+
+
 # ------------------------------------------------------------------------------------------------ in pytest
 @pytest.fixture(scope="module")
 def shim(tmp_path_factory):
