@@ -543,7 +543,6 @@ GemmArgs gemm_args(const ss_weights* w, const PackedMat& W, const f16_t* X, floa
     GemmArgs g{};
     g.W = W.p; g.Wn = W.pn; g.X = X; g.out = out; g.out_packed = outp; g.N = W.N; g.Kp = W.Kp;
     g.narrow = W.pn ? p.narrow : 0;
-    g.group4 = p.narrow;
     g.m_rows = rows; g.m_stride = rows; g.kp_out = kp_out; g.ksplit = p.ksplit; g.nb = p.nb; g.kd = p.kd;
     g.block = p.block; g.sweep_p = p.sweep_p; g.sweep_gn = p.sweep_gn; g.sweep_kh = p.sweep_kh; g.zero_blk = w->zero_blk;
     return g;

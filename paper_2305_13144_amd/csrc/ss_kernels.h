@@ -58,7 +58,6 @@ struct GemmArgs {
     int block;           // >= 0: block kernel with this tile (gemm_plan)
     int sweep_p;         // > 0: sweep kernel with this many waves per workgroup (gemm_plan)
     int sweep_gn;        //      its workgroups per k-slice
-    int group4;          // sweep and skinny kernels: k-slices are whole groups of 4 k-blocks (gemm_plan: narrow)
     int narrow;          // sweep and skinny kernels: read Wn (the plan allows it and the matrix has one)
     int sweep_kh;        //      2: two waves per unit, each half of every chunk's k-blocks (gemm_plan)
     const f16_t* zero_blk;   // kZeroBlkBytes of zeros: read in place of weights beyond a range (sweep kernel)

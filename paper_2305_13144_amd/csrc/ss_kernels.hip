@@ -1677,12 +1677,12 @@ void launch_rmsnorm(const MbState& st, float* x, const float* part, int ksplit, 
                            part ? ksplit : 0, part_stride, w, eps, sel, h_packed, d, n_max);
 }
 
-// k-blocks per slice; whole groups of 4 wherever a matrix with 12-bit weights would be read in that form, so that a
-// matrix without them adds up in the same order.
+// k-blocks per slice; whole groups of 4 where the 12-bit weights are read.  (The halves keep the even shares, and one wave
+// per unit up to 96 rows, that suit them: the two forms add up the same products in different orders.)
 static inline int slice_kb(const GemmArgs& a)
 {
     const int kbs = (a.Kp / 32 + a.ksplit - 1) / a.ksplit;
-    return a.group4 ? (kbs + 3) & ~3 : kbs;
+    return a.narrow ? (kbs + 3) & ~3 : kbs;
 }
 
 template <int MT, int NB, int KD, int EPI, int WN = 0>

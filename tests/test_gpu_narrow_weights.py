@@ -7,6 +7,7 @@ of its column by far more than that."""
 import numpy as np
 import pytest
 
+from oracle.model_oracle import OracleModel
 from paper_2305_13144_amd import binding as ss
 from paper_2305_13144_amd import synth
 
@@ -48,3 +49,32 @@ def test_logits_are_the_same_with_and_without_the_12_bit_copy(mode, rows):
     assert (a != b).mean() < 1e-3
     assert np.abs(a - b).max() <= 2.0 ** -22 * np.abs(a).max()
     assert not np.array_equal(out[0][:, 1039], out[1][:, 1039])
+
+
+@pytest.mark.parametrize("rows", [1, 16, 17, 48, 96])
+@pytest.mark.parametrize("mode", [0, 1, 2, 6])           # as chosen; skinny; sweep, two waves per unit and one
+def test_sliced_projections_agree_with_and_without_the_copies(mode, rows):
+    """The same handle with its copies and without, where k is cut in slices and shared by waves that do not divide it
+    (22 and 86 groups of 4 k-blocks; the two forms add up in different orders), and against the oracle."""
+    shape = synth.ModelShape("sliced", 1, 2816, 22, 128, 11008, 272)
+    rng = np.random.default_rng(rows)
+    W = synth.make_weights(shape, seed=3, threads=8)
+    toks = rng.integers(0, shape.vocab, rows * 4).astype(np.int32)
+    offs = np.arange(rows + 1, dtype=np.int32) * 4
+    gw = ss.Weights(shape, W)
+    ss.ss_set_gemm_mode(mode)
+    try:
+        out = []
+        for copies in (1, 0):
+            gw.set_option(ss.SS_OPT_WEIGHT_COPIES, copies)
+            out.append(ss.ss_forward_logits(gw, toks, offs, np.full(rows, 1, np.int32)))   # a prompt forward, three steps
+    finally:
+        ss.ss_set_gemm_mode(0)
+        gw.close()
+    # fp32 sums in another order move a projection input to the neighbouring half now and then (2^-11 of an element)
+    assert np.abs(out[0] - out[1]).max() <= 1e-3 * np.abs(out[1]).max()
+    om = OracleModel(shape, W, "f32")
+    for i in sorted({0, rows // 2, rows - 1}):
+        ref = om.teacher_forced(toks[offs[i]:offs[i + 1]], first=0)
+        for o in out:
+            assert np.abs(o[4 * i:4 * i + 4] - ref).max() <= 2e-3 * np.abs(ref).max(), (mode, rows, i)
