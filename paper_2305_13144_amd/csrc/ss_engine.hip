@@ -327,10 +327,15 @@ int make_narrow(ss_weights* w, bool any_room = false)
         ss::clear_error();
         return SS_OK;
     }
+    // matrices with a value that has no 12-bit form are found first: nothing is allocated for them, not even for a while
     hipStream_t s = w->lane[0].stream;
+    for (size_t i = 0; i < mats.size(); ++i)
+        if (const size_t n = narrow_groups(*mats[i])) ss::launch_narrow_weight(mats[i]->p, nullptr, n, flags.b.as<int32_t>() + i, s);
+    HIPCHK(hipStreamSynchronize(s));
+    HIPCHK(hipMemcpy(unfit.data(), flags.b.p, mats.size() * 4, hipMemcpyDeviceToHost));
     for (size_t i = 0; i < mats.size(); ++i) {
         PackedMat* m = mats[i];
-        if (narrow_groups(*m) == 0) continue;
+        if (narrow_groups(*m) == 0 || unfit[i]) continue;
         if (hipMalloc(&m->pn, narrow_groups(*m) * 3072) != hipSuccess) {   // no room after all: none of them
             (void)hipGetLastError();
             m->pn = nullptr;
@@ -339,16 +344,9 @@ int make_narrow(ss_weights* w, bool any_room = false)
             return SS_OK;
         }
         ss::launch_narrow_weight(m->p, m->pn, narrow_groups(*m), flags.b.as<int32_t>() + i, s);
+        w->copy_bytes += narrow_groups(*m) * 3072;
     }
     HIPCHK(hipStreamSynchronize(s));
-    HIPCHK(hipMemcpy(unfit.data(), flags.b.p, mats.size() * 4, hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < mats.size(); ++i)
-        if (unfit[i] && mats[i]->pn) {
-            (void)hipFree(mats[i]->pn);
-            mats[i]->pn = nullptr;
-        } else if (mats[i]->pn) {
-            w->copy_bytes += narrow_groups(*mats[i]) * 3072;
-        }
     return SS_OK;
 }
 

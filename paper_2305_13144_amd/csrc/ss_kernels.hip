@@ -162,6 +162,7 @@ __global__ __launch_bounds__(256) void k_narrow_weight(const u32x4* __restrict__
             o[3 * q + 2] = f[2] | ((f[3] >> 9) & 0x00070007u) | ((f[3] << 2) & 0x40004000u);
         }
         if (bad) *unfit = 1;
+        if (!dst) continue;
 #pragma unroll
         for (int p = 0; p < 3; ++p)
             dst[(g * 3 + p) * 64 + lane] = (u32x4){o[4 * p], o[4 * p + 1], o[4 * p + 2], o[4 * p + 3]};
