@@ -208,7 +208,7 @@ struct ss_weights {
     bf16_t* final_norm = nullptr;
     PackedMat lm_head;
     float *rope_cos = nullptr, *rope_sin = nullptr;
-    f16_t* zero_blk = nullptr;    // 1 KiB of zeros (see GemmArgs::zero_blk)
+    f16_t* zero_blk = nullptr;    // kZeroBlkBytes of zeros (see GemmArgs::zero_blk)
     int n_cu = 256;               // compute units of the device
     Lane lane[kLanes];
     std::atomic<int> busy{0};
@@ -469,8 +469,8 @@ int ensure_workspace(const ss_weights* w, Lane& ln, int n_max, int B, int n_sel,
         {&ws.ao, nr * d * 2, true},
         {&ws.act, nr * ss::padded_k(F) * 2, true},
         {&ws.qrot, nr * d * 4, false},
-        {&ws.pqkv, ss::gemm_partial_rows_bound(3 * d, n_max) * 3 * d * 4, false},
-        {&ws.pd, ss::gemm_partial_rows_bound(d, n_max) * d * 4, false},
+        {&ws.pqkv, ss::gemm_partial_rows_bound(n_max) * 3 * d * 4, false},
+        {&ws.pd, ss::gemm_partial_rows_bound(n_max) * d * 4, false},
         {&ws.hsel, (size_t)ss::round_up(n_sel, 128) * d * 2, true},
         {&ws.logits, (size_t)ss::round_up(n_sel, 16) * V * 4, false},
         {&ws.kv, (size_t)c.n_layers * 2 * slots * d * 2, false},

@@ -766,7 +766,7 @@ __device__ __forceinline__ void wait_copies()
 // read.  12311 token-rows, 7B, per layer: the rotation launch (184 us) is gone, the norms take 108 us instead of 167, o
 // and down 716 instead of 680, q|k|v 1112 instead of 1097 (k_rope_append and the sums in the norm stay for sliced launches).
 template <int MS, int NS, int WM, int WN, int ST, int EPI>
-__global__ __launch_bounds__(64 * WM * WN, MS * NS / (WM * WN) > 32 ? 1 : 2) void k_gemm_block(GemmArgs a, QkvOut qo, int kb_per_slice,
+__global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_block(GemmArgs a, QkvOut qo, int kb_per_slice,
                                                                                   int n_ntiles, int n_mtiles)
 {
     constexpr int W = WM * WN;                 // waves

@@ -89,7 +89,7 @@ int sweep_rows(size_t w_per_cu, int units, int n_cu)
 
 GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ksplit)
 {
-    GemmPlan p{1, 2, 4, 1, 0, 0, 1, 0, -1, 4};
+    GemmPlan p{1, 2, 4, 0, 0, 1, 0, -1};
     // whole strips: a micro-batch keeps its launch shapes, and its rows their last bits, while it shrinks inside a strip
     m_rows = (m_rows + 15) / 16 * 16;
     const int KB = Kp / 32;
@@ -136,7 +136,7 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
         return p;
     }
     if (epilogue == EPI_SWIGLU) max_ksplit = 1;   // fused epilogue: no k-slices
-    const bool tall = m_rows >= kTiledTallFrom && g_tall_tiles.load(std::memory_order_relaxed);
+    const bool tall = m_rows >= kBlockTallFrom && g_tall_tiles.load(std::memory_order_relaxed);
     const int most = m_rows <= kBlockRows4 ? 4 : m_rows <= kBlockRows2 ? 2 : 1;
     double best = 0.0;
     for (int t = tall ? 0 : 1; t < kBlockTiles; ++t)
@@ -148,16 +148,15 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
                 p.ksplit = ks;
             }
         }
-    p.tms = p.block == 0 ? 8 : 4;
     return p;
 }
 
-size_t gemm_partial_rows_bound(int N, int n_max, bool sliced_only)
+size_t gemm_partial_rows_bound(int n_max)
 {
     // up to kSweepMaxRows rows: at most kSmallMaxKsplit slices; the block kernel: 4 up to kBlockRows4 rows, 2 up to
-    // kBlockRows2.  sliced_only: plans with slices exist only without the SwiGLU epilogue, whatever the rows.
+    // kBlockRows2
     const size_t n = (size_t)std::max(n_max, 1);
-    size_t need = sliced_only ? 1 : n;
+    size_t need = n;
     need = std::max(need, (size_t)kSmallMaxKsplit * std::min<size_t>(n, (size_t)kSweepMaxRows));
     need = std::max(need, (size_t)4 * std::min<size_t>(n, (size_t)kBlockRows4));
     need = std::max(need, (size_t)2 * std::min<size_t>(n, (size_t)kBlockRows2));

@@ -24,16 +24,15 @@ constexpr int kBlockTiles = 5;
 extern const BlockTile block_tiles[kBlockTiles];
 
 struct GemmPlan {
-    int ksplit, nb, kd, kp;   // kp: k-parts inside a workgroup (1: no kernel splits k there)
+    int ksplit, nb, kd;
     int sweep_p, sweep_gn;
     int sweep_kh;   // sweep kernel: waves per unit (1 or 2)
     int narrow;     // sweep and skinny kernels: > 0 if the 12-bit form of the weights is read where the matrix has one;
                     // sweep kernel: then this many waves per unit
     int block;      // block kernel: index into block_tiles; -1: one of the others
-    int tms;        // block kernel: row strips per wave, 8 with the largest tile, else 4
 };
 
-constexpr int kTiledTallFrom = 896;   // token-rows (in whole strips) from which the block kernel may use its largest tile
+constexpr int kBlockTallFrom = 896;   // token-rows (in whole strips) from which the block kernel may use its largest tile
 
 // n_cu: compute units of the device (the sweep kernel runs one workgroup per unit).
 // max_ksplit: 1 when the consumer reads the output directly (logits).
@@ -44,8 +43,7 @@ int sweep_nbw(int epilogue, int m_rows);
 
 // Rows a [ksplit][rows][N] partial-sum buffer must hold so that every plan gemm_plan can return for an
 // [N, *] matrix and 1 <= m_rows <= n_max fits: an upper bound of ksplit * m_rows over that range.
-// sliced_only: count only plans with ksplit > 1 (a buffer that is used only then).
-size_t gemm_partial_rows_bound(int N, int n_max, bool sliced_only = false);
+size_t gemm_partial_rows_bound(int n_max);
 
 // Rows up to which the sweep kernel is chosen for a matrix of w_per_cu weight bytes per compute unit and this many units.
 int sweep_rows(size_t w_per_cu, int units, int n_cu);

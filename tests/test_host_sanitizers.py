@@ -104,12 +104,12 @@ PLAN_DRIVER = textwrap.dedent(r"""
                 for (int d : dims)
                     for (int F : ffns) {
                         const int Fp = (F + 63) / 64 * 64;
-                        struct { int N, Kp, epi; bool sliced_only; } mats[] = {
-                            {3 * d, d, ss::EPI_PARTIAL, false}, {d, d, ss::EPI_PARTIAL, false},
-                            {2 * F, d, ss::EPI_SWIGLU, true}, {d, Fp, ss::EPI_PARTIAL, false}};
+                        struct { int N, Kp, epi; } mats[] = {
+                            {3 * d, d, ss::EPI_PARTIAL}, {d, d, ss::EPI_PARTIAL},
+                            {2 * F, d, ss::EPI_SWIGLU}, {d, Fp, ss::EPI_PARTIAL}};
                         for (auto& m : mats)
                             for (int n_max : row_grid) {
-                                const size_t cap = ss::gemm_partial_rows_bound(m.N, n_max, m.sliced_only);
+                                const size_t cap = ss::gemm_partial_rows_bound(n_max);
                                 for (int n : row_grid) {
                                     if (n > n_max) break;
                                     const ss::GemmPlan p = ss::gemm_plan(m.N, m.Kp, n, m.epi, cu);
@@ -117,6 +117,9 @@ PLAN_DRIVER = textwrap.dedent(r"""
                                     // what the launchers assume of a plan
                                     const int KB = m.Kp / 32;
                                     bool ok = KB / p.ksplit >= 1 && (p.ksplit & (p.ksplit - 1)) == 0;
+                                    ok = ok && (m.epi != ss::EPI_SWIGLU || p.ksplit == 1);   // no buffer for its sums
+                                    // 12-bit weights: whole groups of 4 k-blocks
+                                    ok = ok && (p.narrow == 0 || (m.Kp % 128 == 0 && n <= ss::kNarrowMaxRows && p.block < 0));
                                     if (p.sweep_gn > 0) {        // sweep kernel: at most 8 units per workgroup, 4 with 4 waves
                                         const int nbw = ss::sweep_nbw(m.epi, n);
                                         const int units = (m.N / 16 + nbw - 1) / nbw;
@@ -124,22 +127,21 @@ PLAN_DRIVER = textwrap.dedent(r"""
                                         ok = ok && n <= ss::kSweepMaxRows && per >= 1 && per <= 8;
                                         ok = ok && (p.sweep_p == 8 || (p.sweep_p == 4 && per <= 4));
                                         ok = ok && (p.sweep_kh == 1 || (p.sweep_kh == 2 && p.sweep_p == 4 && n > 96));
-                                        ok = ok && (m.epi != ss::EPI_SWIGLU || p.ksplit == 1);
+                                        ok = ok && (p.narrow <= 1 || (p.narrow == 2 && p.sweep_p == 4)) && p.block < 0;
                                     } else if (n <= 64) {        // skinny kernel
                                         ok = ok && (p.nb == 2 || p.nb == 4) && (p.kd == 2 || p.kd == 4);
-                                        ok = ok && (m.epi != ss::EPI_SWIGLU || p.ksplit == 1);
-                                    } else {                     // tiled kernel
-                                        ok = ok && (p.kp == 1 || (p.kp == 2 && p.ksplit == 1)) && (p.tms == 4 || p.tms == 8);
-                                        ok = ok && p.ksplit <= 4 && (p.tms == 4 || n >= ss::kTiledTallFrom);
-                                        ok = ok && ((mode & 8) == 0 || p.tms == 4);
+                                        ok = ok && (p.narrow == 0 || (n <= 16 && p.kd == 4 && KB >= 16)) && p.block < 0;
+                                    } else {                     // block kernel
+                                        ok = ok && p.block >= 0 && p.block < ss::kBlockTiles && p.ksplit <= 4;
+                                        ok = ok && (p.block > 0 || (n > ss::kBlockTallFrom - 16 && (mode & 8) == 0));
                                     }
                                     if (!ok) {
                                         std::printf("plan breaks a launcher's assumption: mode %d N %d Kp %d rows %d cu %d: "
-                                                    "ksplit %d nb %d kd %d kp %d sweep %d/%d/%d tms %d\n", mode, m.N, m.Kp, n,
-                                                    cu, p.ksplit, p.nb, p.kd, p.kp, p.sweep_p, p.sweep_gn, p.sweep_kh, p.tms);
+                                                    "ksplit %d nb %d kd %d sweep %d/%d/%d narrow %d block %d\n", mode, m.N, m.Kp, n,
+                                                    cu, p.ksplit, p.nb, p.kd, p.sweep_p, p.sweep_gn, p.sweep_kh, p.narrow, p.block);
                                         return 7;
                                     }
-                                    if (m.sliced_only && p.ksplit == 1) continue;
+                                    if (m.epi == ss::EPI_SWIGLU) continue;
                                     if ((size_t)p.ksplit * (size_t)n > cap) {
                                         std::printf("overflow: N %d Kp %d rows %d (n_max %d) ksplit %d > %zu rows\n", m.N,
                                                     m.Kp, n, n_max, p.ksplit, cap);
@@ -153,12 +155,11 @@ PLAN_DRIVER = textwrap.dedent(r"""
         // dense sweep of the row count on the shapes the advisor's replay found overflowing
         ss::set_gemm_mode(0);
         for (int n_max = 1; n_max <= 12000; n_max += 7) {
-            const size_t c1 = ss::gemm_partial_rows_bound(1024, n_max), c2 = ss::gemm_partial_rows_bound(2 * 512, n_max, true);
+            const size_t c1 = ss::gemm_partial_rows_bound(n_max);
             for (int n = 1; n <= n_max; n += 13) {
                 if ((size_t)ss::gemm_plan(1024, 4096, n, ss::EPI_PARTIAL, 256).ksplit * n > c1) return 4;
                 if ((size_t)ss::gemm_plan(1024, 1024, n, ss::EPI_PARTIAL, 256).ksplit * n > c1) return 5;
-                const ss::GemmPlan g = ss::gemm_plan(2 * 512, 4096, n, ss::EPI_SWIGLU, 256);
-                if (g.ksplit > 1 && (size_t)g.ksplit * n > c2) return 6;
+                if (ss::gemm_plan(2 * 512, 4096, n, ss::EPI_SWIGLU, 256).ksplit > 1) return 6;
             }
         }
         std::printf("ok %ld\n", checked);
