@@ -1016,7 +1016,7 @@ extern "C" int ss_set_option(ss_weights* w, int32_t option, int32_t value)
 
 extern "C" void ss_set_gemm_mode(int32_t mode)
 {
-    if (mode >= 0 && mode <= 14 && (mode & 3) != 3) ss::set_gemm_mode(mode);
+    if (mode >= 0 && mode < 16 * (ss::kBlockTiles + 1) && (mode & 3) != 3) ss::set_gemm_mode(mode);
 }
 
 extern "C" void ss_weights_destroy(ss_weights* w)

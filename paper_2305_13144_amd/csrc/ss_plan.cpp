@@ -10,6 +10,7 @@ namespace {
 std::atomic<int> g_gemm_mode{0};
 std::atomic<int> g_sweep_split{1};
 std::atomic<int> g_tall_tiles{1};
+std::atomic<int> g_block_tile{-1};
 constexpr int kSmallMaxKsplit = 8;   // sweep and skinny kernels: at most 8 k-slices
 // Block kernel: rows up to which k may be cut in 4 and in 2 (more rows fill the chip without, and the partial sums of
 // every slice are written and read again)
@@ -50,6 +51,8 @@ void set_gemm_mode(int mode)
     g_sweep_split.store((mode & 4) ? 0 : 1, std::memory_order_relaxed);
     // bit 3 (value 8): the block kernel never uses its largest tile (A/B measurements)
     g_tall_tiles.store((mode & 8) ? 0 : 1, std::memory_order_relaxed);
+    // bits 4 to 6: 1 + the only tile the block kernel uses
+    g_block_tile.store(((mode >> 4) & 7) - 1, std::memory_order_relaxed);
     g_gemm_mode.store(mode & 3, std::memory_order_relaxed);
 }
 int gemm_mode() { return g_gemm_mode.load(std::memory_order_relaxed); }
@@ -139,7 +142,8 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
     const bool tall = m_rows >= kBlockTallFrom && g_tall_tiles.load(std::memory_order_relaxed);
     const int most = m_rows <= kBlockRows4 ? 4 : m_rows <= kBlockRows2 ? 2 : 1;
     double best = 0.0;
-    for (int t = tall ? 0 : 1; t < kBlockTiles; ++t)
+    const int only = g_block_tile.load(std::memory_order_relaxed);
+    for (int t = only >= 0 ? only : tall ? 0 : 1; t < (only >= 0 ? only + 1 : kBlockTiles); ++t)
         for (int ks = 1; ks <= std::min(most, max_ksplit) && (ks == 1 || KB / ks >= 16); ks *= 2) {
             const double ns = block_ns(block_tiles[t], ks, N, Kp, m_rows, epilogue, n_cu);
             if (p.block < 0 || ns < best) {

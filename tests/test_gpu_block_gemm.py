@@ -1,6 +1,7 @@
 """The projections of prompt forwards at the edges of the block kernel's tiles, through whole forwards, against the
 oracle: row counts around 16, 64, 128 and 256, widths that are no multiple of a tile (gate|up of 344 strips, a head of 65),
-an odd number of k-blocks per slice, the largest tile (from 896 token-rows on) and the others forced in its place."""
+an odd number of k-blocks per slice.  Modes 0 and 1 take the tiles that the plan picks, the others force each of the five
+tiles on every projection: rotation and slots, residual sums, SwiGLU and plain sums, with k-slices (down) and without."""
 import numpy as np
 import pytest
 
@@ -24,7 +25,7 @@ def model(oracle_built):
     gw.close()
 
 
-@pytest.mark.parametrize("mode", [0, 1, 8])
+@pytest.mark.parametrize("mode", [0, 1] + [1 + 16 * (t + 1) for t in range(5)])
 @pytest.mark.parametrize("rows", [65, 127, 129, 145, 256, 257, 513, 895, 897, 1025])
 def test_prompt_logits_match_the_oracle(model, rows, mode):
     gw, om = model

@@ -97,7 +97,7 @@ PLAN_DRIVER = textwrap.dedent(r"""
                                 32704, 32705, 100000, 1048576};
         const int cus[] = {64, 256, 304};
         long checked = 0;
-        const int modes[] = {0, 1, 2, 4, 5, 6, 8, 9, 10, 12, 13, 14};   // every mode the library accepts
+        const int modes[] = {0, 1, 2, 4, 5, 6, 8, 9, 10, 12, 13, 14, 17, 33, 49, 65, 81};
         for (int mode : modes) {
             ss::set_gemm_mode(mode);
             for (int cu : cus)
@@ -133,7 +133,9 @@ PLAN_DRIVER = textwrap.dedent(r"""
                                         ok = ok && (p.narrow == 0 || (n <= 16 && p.kd == 4 && KB >= 16)) && p.block < 0;
                                     } else {                     // block kernel
                                         ok = ok && p.block >= 0 && p.block < ss::kBlockTiles && p.ksplit <= 4;
-                                        ok = ok && (p.block > 0 || (n > ss::kBlockTallFrom - 16 && (mode & 8) == 0));
+                                        const int forced = (mode >> 4) - 1;
+                                        ok = ok && (forced < 0 || p.block == forced);
+                                        ok = ok && (forced >= 0 || p.block > 0 || (n > ss::kBlockTallFrom - 16 && (mode & 8) == 0));
                                     }
                                     if (!ok) {
                                         std::printf("plan breaks a launcher's assumption: mode %d N %d Kp %d rows %d cu %d: "
