@@ -97,6 +97,31 @@ int main()
     for (int i = 0; i < B; ++i) np_[i] = offs[i + 1] - offs[i];
     std::vector<float> lg2((size_t)offs[B] * V);
     OK(ss_forward_logits(w, toks.data(), offs.data(), B, np_.data(), 1, lg2.data(), nullptr));
+    STEP("forward_logits, results that host threads copy");   // 160 rows of 17 and of 19 positions, 4 KiB each: beyond 8 MiB
+    {
+        const int R = 160, steps = 16;
+        std::vector<int32_t> t((size_t)R * (3 + steps)), o(R + 1), np3(R, 3);
+        for (auto& x : t) x = rnd() % V;
+        for (int i = 0; i <= R; ++i) o[i] = i * (3 + steps);
+        std::vector<float> a((size_t)R * (steps + 1) * V), b((size_t)R * (steps + 1) * V);
+        OK(ss_forward_logits(w, t.data(), o.data(), R, np3.data(), 0, a.data(), nullptr));
+        OK(ss_forward_logits(w, t.data(), o.data(), R, np3.data(), 0, b.data(), nullptr));
+        if (memcmp(a.data(), b.data(), a.size() * 4)) { std::printf("logits differ between two calls\n"); return 1; }
+        for (int i = 0; i < R; ++i) np3[i] = 3 + steps;
+        std::vector<float> c((size_t)R * (3 + steps) * V);
+        OK(ss_forward_logits(w, t.data(), o.data(), R, np3.data(), 1, c.data(), nullptr));
+    }
+    STEP("weight copies off and on, two handles");
+    {
+        OK(ss_set_option(w, SS_OPT_WEIGHT_COPIES, 0));
+        OK(ss_set_option(w, SS_OPT_WEIGHT_COPIES, 0));
+        ss_weights* w2 = nullptr;
+        OK(ss_weights_create(&cfg, ptrs.data(), 0, &w2));
+        OK(ss_run_group(w, toks.data(), offs.data(), n, target.data(), pred.data(), 8, &pol, out.data(), lens.data(), &gs, nullptr));
+        OK(ss_set_option(w, SS_OPT_WEIGHT_COPIES, 1));
+        ss_weights_destroy(w2);
+        BAD(ss_set_option(w, SS_OPT_WEIGHT_COPIES, 2), SS_EINVAL);
+    }
     STEP("measurement entry points");
     std::vector<int32_t> pt(16 * 20);
     for (auto& t : pt) t = rnd() % V;

@@ -32,3 +32,25 @@ def test_logits_arrive_whole_and_in_place(rows, lens, all_prompt):
         at += k
     assert at == len(out)
     gw.close()
+
+
+def test_steps_of_more_pieces_than_the_ring_holds():
+    """163 rows of 32000 logits are six pieces of 4 MiB per forward, the ring holds four: while a step's last pieces wait for
+    the copier, the next forward already fills the other buffer, and the one after waits for this one's to have left."""
+    shape = synth.ModelShape("ring", 1, 256, 4, 64, 256, 32000)
+    rng = np.random.default_rng(3)
+    gw = ss.Weights(shape, synth.make_weights(shape, seed=4, threads=8))
+    rows, steps = 163, 5
+    plens = rng.integers(1, 9, rows).astype(np.int32)
+    n = (plens + rng.integers(steps - 1, steps + 1, rows)).astype(np.int32)   # some rows leave one step early
+    offs = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    toks = rng.integers(0, shape.vocab, int(offs[-1])).astype(np.int32)
+    out = ss.ss_forward_logits(gw, toks, offs, plens)
+    at = np.concatenate([[0], np.cumsum(n - plens + 1)])
+    assert at[-1] == len(out)
+    for i in range(0, rows, 9):
+        one = ss.ss_forward_logits(gw, toks[offs[i]:offs[i + 1]], [0, int(n[i])], [int(plens[i])])
+        assert np.abs(out[at[i]:at[i + 1]] - one).max() <= TOL * np.abs(one).max(), i
+    for _ in range(3):
+        assert np.array_equal(ss.ss_forward_logits(gw, toks, offs, plens), out)
+    gw.close()
