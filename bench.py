@@ -33,20 +33,33 @@ def log(msg: str) -> None:
     print(f"[bench] {msg}", file=sys.stderr, flush=True)
 
 
-def decode_step_bytes(shape, B: int, ctx: int) -> int:
+def matrix_bytes(shape) -> int:
+    """Bytes of the projection matrices at 2 per weight."""
+    return shape.weight_bytes_per_step() - (2 * shape.n_layers + 1) * shape.d_model * 2
+
+
+def decode_step_bytes(shape, B: int, ctx: int, matrices: int = None) -> int:
     """Algorithmic HBM bytes of one decode forward: every weight once, each live row's key/value history
-    read once, one new key/value slot and one embedding row per live row."""
+    read once, one new key/value slot and one embedding row per live row.  matrices: bytes of the projection matrices
+    as they are streamed, default 2 per weight."""
     kv = shape.kv_bytes_per_token()
-    return shape.weight_bytes_per_step() + B * (ctx + 1) * kv + B * kv + B * shape.d_model * 2
+    weights = shape.weight_bytes_per_step() - matrix_bytes(shape) + (matrix_bytes(shape) if matrices is None else matrices)
+    return weights + B * (ctx + 1) * kv + B * kv + B * shape.d_model * 2
+
+
+def streamed_matrix_bytes(ss, gw, shape, rows: int) -> int:
+    """Bytes of the matrices as a decode step of so many rows streams them: up to 96 rows the 12-bit copies of those that
+    have one, which is what the read probe reads."""
+    return ss.ss_bench_read_stream(gw, 1)[1] if rows <= 96 else matrix_bytes(shape)
 
 
 TRAFFIC_PROFILE = os.path.join("profiles", "decode_step_7b_hbm_traffic.txt")
 
 
-def profile_traffic(shape_name: str, rows: int, ctx: int, gemm_mode: int):
+def profile_traffic(shape_name: str, rows: int, ctx: int, gemm_mode: int, copies: bool = True):
     """HBM bytes per decode step from the committed rocprofv3 counter summary (FETCH_SIZE + WRITE_SIZE runs of
     `bench.py --roofline-only`); a figure from that file, not a live one: (None, reason) when the file is absent
-    or was taken at another shape."""
+    or was taken at another shape.  copies: whether the step streams the 12-bit copies of the weights."""
     path = os.path.join(ROOT, TRAFFIC_PROFILE)
     if not os.path.exists(path):
         return None, f"{TRAFFIC_PROFILE} absent"
@@ -55,12 +68,10 @@ def profile_traffic(shape_name: str, rows: int, ctx: int, gemm_mode: int):
         if line.startswith("@") and "=" in line:
             k, v = line[1:].split("=", 1)
             kv[k.strip()] = v.strip()
-    want = dict(shape=shape_name, rows=str(rows), ctx=str(ctx), gemm_mode=str(gemm_mode))
+    want = dict(shape=shape_name, rows=str(rows), ctx=str(ctx), gemm_mode=str(gemm_mode), copies=str(int(copies)))
     if any(kv.get(k) != v for k, v in want.items()) or "decode_step_hbm_bytes" not in kv:
         return None, f"{TRAFFIC_PROFILE} was taken at another shape or launch configuration"
-    narrow = kv.get("decode_step_hbm_bytes_12bit")
-    note = f"; weights as halves, with the 12-bit copies in use {narrow} bytes" if narrow else ""
-    return float(kv["decode_step_hbm_bytes"]), f"{TRAFFIC_PROFILE} (rocprofv3 counters of an earlier run, not live{note})"
+    return float(kv["decode_step_hbm_bytes"]), f"{TRAFFIC_PROFILE} (rocprofv3 counters of an earlier run, not live)"
 
 
 def ablation(a, ss, gw, wl, shape) -> int:
@@ -130,7 +141,7 @@ def sweeps(a, ss, gw, wl, shape) -> int:
         for what, B, ctx in points:
             ptoks = rng.integers(0, shape.vocab, size=B * ctx).astype(np.int32)
             ms = ss.ss_bench_decode_step(gw, ptoks, B, ctx, 11)[3:]
-            nbytes = decode_step_bytes(shape, B, ctx)
+            nbytes = decode_step_bytes(shape, B, ctx, streamed_matrix_bytes(ss, gw, shape, B))
             row = dict(sweep="step", vary=what, rows=B, ctx=ctx, ms=float(ms.mean()), ms_min=float(ms.min()),
                        algorithmic_bytes=nbytes, achieved_GBs=nbytes / (ms.mean() * 1e-3) / 1e9,
                        frac_of_hbm_peak=nbytes / (ms.mean() * 1e-3) / 1e9 / HBM_PEAK_GBS,
@@ -276,7 +287,8 @@ def main() -> int:
         B0, ctx = a.step_rows, a.step_ctx
         ptoks = np.random.default_rng(7).integers(0, shape.vocab, size=B0 * ctx).astype(np.int32)
         ms_l = ss.ss_bench_decode_steps_in_flight(gw, ptoks, B0, ctx, a.step_iters + 6, a.in_flight)[:, 3:-3]
-        ach_l = a.in_flight * decode_step_bytes(shape, B0, ctx) / (ms_l.mean() * 1e-3) / 1e9
+        nbytes = decode_step_bytes(shape, B0, ctx, streamed_matrix_bytes(ss, gw, shape, B0))
+        ach_l = a.in_flight * nbytes / (ms_l.mean() * 1e-3) / 1e9
         log(f"{a.in_flight} decode steps in flight, B={B0} ctx={ctx}: {ms_l.mean():.3f} ms each -> {ach_l:.0f} GB/s = "
             f"{ach_l / HBM_PEAK_GBS:.3f} of peak for the bytes of all")
         print(json.dumps(dict(lanes=a.in_flight, rows=B0, ctx=ctx, iters_per_lane=int(ms_l.shape[1]), ms=float(ms_l.mean()),
@@ -459,15 +471,17 @@ def main() -> int:
     ms_w, launches = ss.ss_bench_weight_stream(gw, B0, a.step_iters + 3)
     log("weight stream iterations (ms): " + " ".join(f"{x:.2f}" for x in ms_w))
     ms_w = ms_w[3:]
-    wbytes = shape.weight_bytes_per_step() - (2 * shape.n_layers + 1) * shape.d_model * 2   # matrices only
-    ach_w = wbytes / (ms_w.mean() * 1e-3) / 1e9
-    # the ceiling for those launches: the same matrices read by a plain stream kernel, launch by launch
+    # the ceiling for those launches: the same matrices read by a plain stream kernel, launch by launch.  It reads what a
+    # small batch streams, the 12-bit copies where there are any, and so says how many bytes that is
     ms_r, rbytes = ss.ss_bench_read_stream(gw, a.step_iters + 3)
     ms_r = ms_r[3:]
+    wbytes = streamed_matrix_bytes(ss, gw, shape, B0)
+    copies = wbytes < 0.99 * matrix_bytes(shape)
+    ach_w = wbytes / (ms_w.mean() * 1e-3) / 1e9
     rng = np.random.default_rng(7)
     ptoks = rng.integers(0, shape.vocab, size=B0 * ctx).astype(np.int32)
     ms_s = ss.ss_bench_decode_step(gw, ptoks, B0, ctx, a.step_iters + 3)[3:]
-    sbytes = decode_step_bytes(shape, B0, ctx)
+    sbytes, sbytes2 = decode_step_bytes(shape, B0, ctx, wbytes), decode_step_bytes(shape, B0, ctx)
     ach = sbytes / (ms_s.mean() * 1e-3) / 1e9
     # several such steps at once, one per lane, as a group pass runs its micro-batches: each streams the whole model
     # (not under --roofline-only: the profiles taken from that command keep every kernel's launches undisturbed)
@@ -477,29 +491,33 @@ def main() -> int:
         for lanes in sorted({2, a.in_flight}):
             ms_l = ss.ss_bench_decode_steps_in_flight(gw, ptoks, B0, ctx, a.step_iters + 6, lanes)[:, 3:-3]
             ach_l = lanes * sbytes / (ms_l.mean() * 1e-3) / 1e9
-            per_lanes[lanes] = dict(ms=float(ms_l.mean()), achieved=ach_l, frac=ach_l / HBM_PEAK_GBS)
+            per_lanes[lanes] = dict(ms=float(ms_l.mean()), achieved=ach_l, frac=ach_l / HBM_PEAK_GBS,
+                                    frac_at_2_bytes_per_weight=ach_l / HBM_PEAK_GBS * sbytes2 / sbytes)
         two = dict(what=f"{a.in_flight} such steps running at the same time on {a.in_flight} streams (as many micro-batches of a "
                         "group pass): bytes of all / the time one of them takes then",
                    lanes=a.in_flight, unit="GB/s", **per_lanes[a.in_flight],
                    **({"with_two_lanes": per_lanes[2]} if a.in_flight != 2 else {}))
     step_launches = launches + 3 * shape.n_layers + 3     # + attention and two norms per layer, embedding, final norm, token choice
-    traffic, traffic_source = profile_traffic(shape.name, B0, ctx, a.gemm_mode)
+    traffic, traffic_source = profile_traffic(shape.name, B0, ctx, a.gemm_mode, copies)
     roofline = dict(bound="hbm",
                     kernel=f"one whole decode step of {B0} rows at context {ctx}: all {step_launches} launches (projections, "
                            f"decode attention, RMSNorm, embedding, token choice)",
                     achieved=ach, peak=HBM_PEAK_GBS, unit="GB/s", frac=ach / HBM_PEAK_GBS, traffic=traffic,
                     traffic_source=traffic_source, ms=float(ms_s.mean()), ms_min=float(ms_s.min()),
                     algorithmic_bytes=sbytes, launches_per_step=step_launches,
-                    bytes_note="algorithmic bytes count 2 per weight; the small-batch projections stream a 12-bit form of the same "
-                               "values, so the step moves about a fifth less than that",
+                    bytes_note=("weights at the 1.5 bytes of the 12-bit copies that the small-batch projections stream" if copies
+                                else "weights at 2 bytes"),
+                    at_2_bytes_per_weight=dict(bytes=sbytes2, achieved=sbytes2 / (ms_s.mean() * 1e-3) / 1e9,
+                                               frac=sbytes2 / (ms_s.mean() * 1e-3) / 1e9 / HBM_PEAK_GBS),
                     steps_in_flight=two,
                     projection_launches=dict(
-                        what="the projection kernels of that step alone (k_gemm_sweep + k_gemm_skinny), back to back; bytes at 2 per "
-                             "weight, of which the kernels read the 12-bit form of the same values (three quarters)",
+                        what="the projection kernels of that step alone (k_gemm_sweep + k_gemm_skinny), back to back; weights as "
+                             "streamed",
                         ms=float(ms_w.mean()), achieved=ach_w, unit="GB/s", frac=ach_w / HBM_PEAK_GBS, launches=launches,
                         avg_launch_us=ms_w.mean() * 1e3 / launches, bytes_per_launch=wbytes / launches),
                     plain_read_stream=dict(
-                        what="one plain non-temporal read kernel per weight matrix, same bytes and launch sizes, nothing computed",
+                        what="one plain non-temporal read kernel per weight matrix, the bytes that a small batch streams in the same "
+                             "launch sizes, nothing computed",
                         ms=float(ms_r.mean()), achieved=rbytes / (ms_r.mean() * 1e-3) / 1e9, unit="GB/s",
                         projections_over_stream=float(ms_r.mean() / ms_w.mean()) * wbytes / rbytes))
     extras["decode_step"] = dict(rows=B0, ctx=ctx, ms=float(ms_s.mean()), ms_min=float(ms_s.min()),

@@ -358,8 +358,9 @@ int ss_bench_decode_steps_in_flight(ss_weights* w, const int32_t* prompt_tokens,
  * Measurement entry point: the projection kernels of one decode step alone.  Launches, back to back on
  * one stream, exactly the matrix kernels a B-row decode forward launches (per layer q|k|v, o, gate|up
  * with the SwiGLU epilogue, down; then the LM head) with the same launch configuration, on whatever the
- * activation buffers currently hold, `iters` times.  Every weight byte of the model is streamed once per
- * iteration, so bytes/iteration = the model's weight bytes.  ms_out: host, double[iters], device time of
+ * activation buffers currently hold, `iters` times.  Every matrix is streamed once per iteration, in the form that
+ * B rows read: the 12-bit copies up to 96 rows where there are any (ss_bench_read_stream gives their bytes), else 2
+ * bytes per weight.  ms_out: host, double[iters], device time of
  * each iteration (HIP events).  launches_out: host, nullable, number of kernel launches per iteration.
  */
 int ss_bench_weight_stream(ss_weights* w, int32_t B, int32_t iters, double* ms_out, int32_t* launches_out,
@@ -368,7 +369,8 @@ int ss_bench_weight_stream(ss_weights* w, int32_t B, int32_t iters, double* ms_o
 /*
  * Measurement entry point: the ceiling ss_bench_weight_stream is compared with.  Launches, back to back on one
  * stream, one plain read kernel per weight matrix in the order a decode forward uses them (per layer q|k|v, o,
- * gate|up, down; then the LM head): the same bytes in the same launch sizes, nothing computed, `iters` times.
+ * gate|up, down; then the LM head): the bytes that a batch of at most 16 rows streams (a matrix's 12-bit copy, or the
+ * halves where it has none), in the same launch sizes, nothing computed, `iters` times.
  *   ms_out     host, double[iters], device time of each iteration (HIP events)
  *   bytes_out  host, nullable: bytes read per iteration (each matrix rounded down to whole 64 KiB chunks)
  */

@@ -1771,7 +1771,8 @@ int bench_weight_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32
         return gemm_args(w, W, X, out, outp, rows, kp_out, p);
     };
     f16_t *h = ws.h.as<f16_t>(), *ao = ws.ao.as<f16_t>(), *act = ws.act.as<f16_t>();
-    float *pqkv = ws.pqkv.as<float>(), *pd = ws.pd.as<float>();
+    float *pqkv = ws.pqkv.as<float>(), *pd = ws.pd.as<float>(), *x = ws.x.as<float>();
+    const bool whole_o = p_o.block >= 0 && p_o.ksplit == 1, whole_d = p_d.block >= 0 && p_d.ksplit == 1;   // as in forward()
     EventList evl;
     if (int rc = evl.create(iters + 1)) return rc;
     const std::vector<hipEvent_t>& ev = evl.e;
@@ -1782,9 +1783,9 @@ int bench_weight_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32
         for (int l = 0; l < c.n_layers; ++l) {
             const Layer& L = w->layers[l];
             ss::launch_gemm(mk(L.wqkv, h, pqkv, nullptr, n, 0, p_qkv), ss::EPI_PARTIAL, s);
-            ss::launch_gemm(mk(L.wo, ao, pd, nullptr, n, 0, p_o), ss::EPI_PARTIAL, s);
+            ss::launch_gemm(mk(L.wo, ao, whole_o ? x : pd, nullptr, n, 0, p_o), whole_o ? ss::EPI_RESIDUAL : ss::EPI_PARTIAL, s);
             ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
-            ss::launch_gemm(mk(L.wd, act, pd, nullptr, n, 0, p_d), ss::EPI_PARTIAL, s);
+            ss::launch_gemm(mk(L.wd, act, whole_d ? x : pd, nullptr, n, 0, p_d), whole_d ? ss::EPI_RESIDUAL : ss::EPI_PARTIAL, s);
             launches += 4;
         }
         ss::launch_gemm(mk(w->lm_head, ws.hsel.as<f16_t>(), ws.logits.as<float>(), nullptr, n, 0, p_lm),
@@ -1809,7 +1810,11 @@ int bench_read_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32_t
     HIPCHK(hipSetDevice(w->device));
     if (int rc = ln.ws.ints.ensure(64, false)) return rc;
     uint32_t* sink = ln.ws.ints.as<uint32_t>();
-    auto mat_bytes = [](const PackedMat& m) { return ((size_t)m.N * m.Kp * 2) & ~(size_t)0xffff; };
+    // what a small decode batch streams: the 12-bit copy where the matrix has one
+    auto mat_bytes = [](const PackedMat& m) {
+        return (m.pn ? narrow_groups(m) * 3072 : (size_t)m.N * m.Kp * 2) & ~(size_t)0xffff;
+    };
+    auto mat_data = [](const PackedMat& m) { return m.pn ? (const f16_t*)m.pn : m.p; };
     EventList evl;
     if (int rc = evl.create(iters + 1)) return rc;
     const std::vector<hipEvent_t>& ev = evl.e;
@@ -1819,10 +1824,10 @@ int bench_read_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32_t
         bytes = 0;
         for (const Layer& L : w->layers)
             for (const PackedMat* m : {&L.wqkv, &L.wo, &L.wgu, &L.wd}) {
-                ss::launch_read_stream(m->p, mat_bytes(*m), sink, s);
+                ss::launch_read_stream(mat_data(*m), mat_bytes(*m), sink, s);
                 bytes += mat_bytes(*m);
             }
-        ss::launch_read_stream(w->lm_head.p, mat_bytes(w->lm_head), sink, s);
+        ss::launch_read_stream(mat_data(w->lm_head), mat_bytes(w->lm_head), sink, s);
         bytes += mat_bytes(w->lm_head);
         HIPCHK(hipEventRecord(ev[it + 1], s));
     }

@@ -31,6 +31,10 @@ def test_decode_step_bytes_is_weights_plus_history_plus_new_slot_plus_embedding(
     assert b == 13_214_687_232 + 16 * 201 * 524_288 + 16 * 524_288 + 16 * 8_192 == 14_909_317_120
     # at the chip's 8 TB/s that is the 1.86 ms floor the 70 % target is quoted against
     assert abs(b / 8e12 * 1e3 - 1.864) < 1e-3
+    # with the matrices at 1.5 bytes per weight, as the small batches stream them
+    assert bench.matrix_bytes(synth.LLAMA7B) == 13_214_687_232 - 65 * 4096 * 2
+    assert b - bench.decode_step_bytes(synth.LLAMA7B, 16, 200, bench.matrix_bytes(synth.LLAMA7B) * 3 // 4) == \
+        bench.matrix_bytes(synth.LLAMA7B) // 4
     # one more live row costs its history, its new slot and its embedding row
     assert bench.decode_step_bytes(synth.LLAMA7B, 17, 200) - b == 201 * 524_288 + 524_288 + 8_192
 
@@ -50,8 +54,10 @@ def test_roofline_traffic_comes_from_the_committed_counter_summary_or_is_null():
     configuration it was taken at; for any other it is null with the reason, never a stale constant."""
     got, source = bench.profile_traffic("llama7b", 16, 200, 0)
     assert got is not None and source.startswith("profiles/decode_step_7b_hbm_traffic.txt")
-    alg = bench.decode_step_bytes(synth.LLAMA7B, 16, 200)
+    # the step streams the 12-bit copies: 1.5 bytes per weight
+    alg = bench.decode_step_bytes(synth.LLAMA7B, 16, 200, bench.matrix_bytes(synth.LLAMA7B) * 3 // 4)
     assert 1.0 <= got / alg < 1.10          # measured traffic: a few per cent above the algorithmic bytes, no re-reads
-    for other in (("llama13b", 16, 200, 0), ("llama7b", 32, 200, 0), ("llama7b", 16, 100, 0), ("llama7b", 16, 200, 2)):
+    for other in (("llama13b", 16, 200, 0), ("llama7b", 32, 200, 0), ("llama7b", 16, 100, 0), ("llama7b", 16, 200, 2),
+                  ("llama7b", 16, 200, 0, False)):
         got, why = bench.profile_traffic(*other)
         assert got is None and "another shape" in why

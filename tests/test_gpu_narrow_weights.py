@@ -78,3 +78,20 @@ def test_sliced_projections_agree_with_and_without_the_copies(mode, rows):
         ref = om.teacher_forced(toks[offs[i]:offs[i + 1]], first=0)
         for o in out:
             assert np.abs(o[4 * i:4 * i + 4] - ref).max() <= 2e-3 * np.abs(ref).max(), (mode, rows, i)
+
+
+def test_read_probe_reads_what_small_batches_stream():
+    """The probe that the projections are compared with: three quarters of the bytes where a matrix has its copy."""
+    shape = synth.ModelShape("probe", 1, 1024, 8, 128, 2048, 4096)      # every matrix whole 64 KiB chunks in both forms
+    W = synth.make_weights(shape, seed=3, threads=8)
+    halves = (4 * 1024 * 1024 + 3 * 1024 * 2048 + 4096 * 1024) * 2
+    W[-1][5, 5] = synth.f32_to_bf16_bits(np.array([0.5], np.float32))[0]   # the head has no copy
+    gw = ss.Weights(shape, W)
+    head = 4096 * 1024 * 2
+    assert ss.ss_bench_read_stream(gw, 2)[1] == (halves - head) * 3 // 4 + head
+    gw.set_option(ss.SS_OPT_WEIGHT_COPIES, 0)
+    assert ss.ss_bench_read_stream(gw, 2)[1] == halves
+    for rows in (16, 200):
+        ms, launches = ss.ss_bench_weight_stream(gw, rows, 2)
+        assert launches == 5 and (ms > 0).all()
+    gw.close()
