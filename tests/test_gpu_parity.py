@@ -140,7 +140,7 @@ def test_wide_prompt_logits_across_attention_tiles(wide2):
 @pytest.mark.parametrize("rows", [1, 5, 16, 23, 40, 64, 100])
 def test_tiny_decode_logits_teacher_forced(tiny, rows):
     """Prompt forward then decode steps on forced tokens; row counts cover 1..4 strips of the skinny
-    kernel, its ragged tails, and the tiled kernel (100 rows); rows drop out at different steps."""
+    kernel, its ragged tails, and the block kernel (100 rows); rows drop out at different steps."""
     W, om, gw = tiny
     rng = np.random.default_rng(100 + rows)
     w = synth.make_group(synth.TINY, rows, 777 + rows, ("uniform", 3, 40), ("uniform", 1, 8), None, 8, 0, ())
@@ -157,7 +157,7 @@ def test_tiny_decode_logits_teacher_forced(tiny, rows):
 @pytest.mark.parametrize("rows", [1, 16, 23, 40, 64, 70, 100, 128])
 def test_tiny_decode_logits_each_small_batch_projection_kernel(tiny, rows, mode):
     """Both kernels for small-batch projections, forced for every projection: the k-splitting one (mode 1; the
-    tiled kernel above 64 rows) and the one that stages activations once per workgroup (mode 2, up to 128
+    block kernel above 64 rows) and the one that stages activations once per workgroup (mode 2, up to 128
     rows), here with fewer strips than compute units, idle waves, 1-8 row strips with ragged tails and a k
     range (ffn 688 -> 22 k-blocks) that ends inside a chunk."""
     W, om, gw = tiny
@@ -216,7 +216,7 @@ def test_tiny_long_contexts_decode_logits(tiny):
 
 
 def test_tiny_large_batch_with_compaction_matches_oracle_rows(tiny):
-    """600 rows in one micro-batch (tiled kernels for the prompt and the first steps, then the small-batch
+    """600 rows in one micro-batch (block kernel for the prompt and the first steps, then the small-batch
     kernels as rows finish and compaction shrinks the batch): lengths exact, sampled rows re-derived by the oracle."""
     W, om, gw = tiny
     w = synth.make_group(synth.TINY, 600, 31337, ("uniform", 4, 24), ("uniform", 1, 12), None, 12, 0, ())
@@ -291,9 +291,9 @@ def test_wide_decode_logits_each_small_batch_projection_kernel(wide2, mode):
 
 @pytest.mark.parametrize("rows", [17, 33, 48, 49, 64, 100, 128, 129, 176, 200, 256])
 def test_wide_decode_logits_across_row_strips(wide2, rows):
-    """7B widths, 2-16 row strips, the kernel choice of the library itself (mode 0) and the same with the
-    two-waves-per-unit split of the sweep kernel switched off (mode 4; the split is used above 96 rows),
-    ragged last strips.  Three rows against the oracle in each mode; the two modes differ only in the order of fp32
+    """7B widths, 2-16 row strips (from 161 rows on some, from 193 all projections run in the block kernel), the kernel
+    choice of the library itself (mode 0) and the same with the two-waves-per-unit split of the sweep kernel switched off
+    (mode 4; the split is used above 96 rows, and with the 12-bit weights below), ragged last strips.  Three rows against the oracle in each mode; the two modes differ only in the order of fp32
     sums, which can move an activation by one unit of its half-precision rounding (2^-11) and a logit by that order."""
     shape, W, om, gw = wide2
     rng = np.random.default_rng(500 + rows)
@@ -317,7 +317,7 @@ def test_wide_decode_logits_across_row_strips(wide2, rows):
 
 
 def test_wide_prompt_forward_through_tiled_kernel(wide2):
-    """> 64 prompt token-rows at real widths: tiled MFMA kernel incl. its ragged row and column tails."""
+    """> 64 prompt token-rows at real widths: block kernel incl. its ragged row and column tails."""
     shape, W, om, gw = wide2
     w = synth.make_workload(2, n=4, shape=shape)
     _say(f"7B-width x2 layers prompt logits, {int(w.prompt_offsets[-1])} token-rows")
@@ -533,7 +533,7 @@ def test_an_error_in_one_microbatch_ends_the_group_call_cleanly(tiny):
 
 def test_runs_are_bit_repeatable(tiny, wide2):
     """Race canary: every reduction is ordered (no float atomics), so two runs of the same call must agree
-    bit for bit - logits and tokens, skinny and tiled kernels, padded and compacted."""
+    bit for bit - logits and tokens, skinny and block kernels, padded and compacted."""
     W, om, gw = tiny
     w = synth.make_group(synth.TINY, 90, 99, ("uniform", 4, 30), ("uniform", 1, 20), None, 20, 0, ())
     a = ss.ss_forward_logits(gw, w.prompt_tokens, w.prompt_offsets, w.prompt_lens)
