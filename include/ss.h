@@ -198,7 +198,8 @@ typedef struct {
  *                   with it the live batch shrinks.  Lengths and flags are identical either way; tokens
  *                   are too, except where a row's two largest logits lie within the rounding difference
  *                   between two launch shapes (about 1e-3 of the largest logit) once the live batch has
- *                   shrunk past a multiple of 16 rows.
+ *                   shrunk past a multiple of 16 rows (or, in models of more than 32 heads, to where rows
+ *                   times heads is 512 or less).
  *   out_tokens      host, int32[B*max_new] row-major; -1 after the emitted length
  *   out_lens        host, int32[B]   = min(target, max_new)
  *   out_failed      host, uint8[B]   = target > max_new  (an FCR failure: to be recomputed later)
@@ -308,8 +309,8 @@ typedef struct {
  * opts->eos_id, reaches its optional target length, or has emitted max_new tokens.  End detection, the
  * shrinking of the live batch and the sampling all run on the device; the host only polls a counter.
  * Given the same weights, prompts and draws the output of a row does not depend on flags, on sync_every or on
- * what the other rows hold; across batch compositions that change the launch shapes (the total prompt length,
- * the number of 16-row strips) logits agree to about 1e-3 of the largest, and a sampled token can differ where its
+ * what the other rows hold; across batch compositions that change the launch shapes (the total prompt length, the
+ * longest prompt, the number of 16-row strips; rows times heads past 192 or 512) logits agree to about 1e-3 of the largest, and a sampled token can differ where its
  * draw lies within that of an interval edge.
  *   out_lens    host, int32[B]: tokens emitted (the end-of-sequence token included)
  *   out_failed  host, uint8[B]: the row was still unfinished after max_new tokens (Sec. 4.1 failure)
