@@ -310,8 +310,8 @@ typedef struct {
  * shrinking of the live batch and the sampling all run on the device; the host only polls a counter.
  * Given the same weights, prompts and draws the output of a row does not depend on flags, on sync_every or on
  * what the other rows hold; across batch compositions that change the launch shapes (the total prompt length, the
- * longest prompt, the number of 16-row strips; rows times heads past 192 or 512) logits agree to about 1e-3 of the largest, and a sampled token can differ where its
- * draw lies within that of an interval edge.
+ * longest prompt, the number of 16-row strips; rows times heads past 192 or 512) logits agree to about 1e-3 of the
+ * largest, and a sampled token can differ where its draw lies within that of an interval edge.
  *   out_lens    host, int32[B]: tokens emitted (the end-of-sequence token included)
  *   out_failed  host, uint8[B]: the row was still unfinished after max_new tokens (Sec. 4.1 failure)
  * Other arguments, ownership and errors as ss_decode_microbatch; additionally SS_EINVAL for a NULL opts,

@@ -294,13 +294,17 @@ std::vector<PackedMat*> all_matrices(ss_weights* w)
 // Bytes of a matrix's 12-bit copy: one group of 4 k-blocks is 3 KiB.
 size_t narrow_groups(const PackedMat& m) { return m.Kp % 128 == 0 ? (size_t)(m.N / 16) * (m.Kp / 128) : 0; }
 
+// Allocates nothing: ss_weights_destroy, where no exception may come from, calls it.
 void drop_narrow(ss_weights* w)
 {
     w->copy_bytes = 0;
-    for (PackedMat* m : all_matrices(w)) {
-        if (m->pn) (void)hipFree(m->pn);
-        m->pn = nullptr;
-    }
+    auto drop = [](PackedMat& m) {
+        if (m.pn) (void)hipFree(m.pn);
+        m.pn = nullptr;
+    };
+    for (Layer& L : w->layers)
+        for (PackedMat* m : {&L.wqkv, &L.wo, &L.wgu, &L.wd}) drop(*m);
+    drop(w->lm_head);
 }
 
 // Adds the 12-bit copies that decode batches stream (see k_narrow_weight): three quarters of the packed weights' bytes
@@ -308,9 +312,8 @@ void drop_narrow(ss_weights* w)
 // the way of key/value caches (and a call that runs out of memory all the same drops them, see with_memory); a matrix
 // that has a value without a 12-bit form, or whose K is no multiple of a group, goes without.
 // any_room: whatever they take of the free memory (they had it until now).
-int make_narrow(ss_weights* w, bool any_room = false)
+int make_narrow_impl(ss_weights* w, bool any_room)
 {
-    drop_narrow(w);
     const std::vector<PackedMat*> mats = all_matrices(w);
     size_t need = 0, free_b = 0, total_b = 0;
     for (const PackedMat* m : mats) need += narrow_groups(*m) * 3072;
@@ -348,6 +351,14 @@ int make_narrow(ss_weights* w, bool any_room = false)
     }
     HIPCHK(hipStreamSynchronize(s));
     return SS_OK;
+}
+
+int make_narrow(ss_weights* w, bool any_room = false)
+{
+    drop_narrow(w);
+    const int rc = ss::no_throw([&] { return make_narrow_impl(w, any_room); });
+    if (rc != SS_OK) drop_narrow(w);   // none rather than some that may not be written
+    return rc;
 }
 
 // Every handle of the process, for the device memory that they can give back.  Lock order: g_handles_mu, then a handle's
