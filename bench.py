@@ -471,7 +471,7 @@ def main() -> int:
     ms_w, launches = ss.ss_bench_weight_stream(gw, B0, a.step_iters + 3)
     log("weight stream iterations (ms): " + " ".join(f"{x:.2f}" for x in ms_w))
     ms_w = ms_w[3:]
-    # the ceiling for those launches: the same matrices read by a plain stream kernel, launch by launch.  It reads what a
+    # what those launches are compared with: the same matrices read by a plain stream kernel, launch by launch.  It reads what a
     # small batch streams, the 12-bit copies where there are any, and so says how many bytes that is
     ms_r, rbytes = ss.ss_bench_read_stream(gw, a.step_iters + 3)
     ms_r = ms_r[3:]

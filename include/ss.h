@@ -368,7 +368,7 @@ int ss_bench_weight_stream(ss_weights* w, int32_t B, int32_t iters, double* ms_o
                            void* hip_stream);
 
 /*
- * Measurement entry point: the ceiling ss_bench_weight_stream is compared with.  Launches, back to back on one
+ * Measurement entry point: what ss_bench_weight_stream is compared with.  Launches, back to back on one
  * stream, one plain read kernel per weight matrix in the order a decode forward uses them (per layer q|k|v, o,
  * gate|up, down; then the LM head): the bytes that a batch of at most 16 rows streams (a matrix's 12-bit copy, or the
  * halves where it has none), in the same launch sizes, nothing computed, `iters` times.

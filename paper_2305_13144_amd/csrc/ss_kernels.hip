@@ -1605,8 +1605,8 @@ __global__ __launch_bounds__(1024) void k_step_update(MbState st, int compact, i
 
 // ------------------------------------------------------------------------------------------ read probe
 // Measurement aid: a plain read stream over a packed weight matrix, one wave per 64 KiB chunk, 8 non-temporal
-// 16-byte loads per lane in flight, nothing computed.  The rate it reaches at a projection's size is the
-// ceiling that the projection kernels are compared with.
+// 16-byte loads per lane in flight, nothing computed.  The rate it reaches at a projection's size is what the
+// projection kernels are compared with (no ceiling: small matrices make few such waves).
 __global__ __launch_bounds__(256) void k_read_stream(const u32x4* __restrict__ p, int n_chunks, uint32_t* __restrict__ sink)
 {
     const int lane = threadIdx.x & 63;
