@@ -747,17 +747,25 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
 // The copies are written in assembly because the compiler would wait for all of them before every LDS read: it counts
 // only its own loads, and the waits here are written out.  They name no output register; waits that the compiler adds
 // for loads of its own can only be too strict.
-__device__ __forceinline__ void lds_copy_1k(unsigned lds_addr, const void* base, unsigned lane_off)
+__device__ __forceinline__ void lds_copy_1k(unsigned slot, unsigned place, const void* base, unsigned lane_off)
 {
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds_addr), "v"(lane_off), "s"(base)
-                 : "memory");
+    asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" ::"s"(slot), "s"(place), "v"(lane_off), "s"(base)
+                 : "memory", "scc");
 }
 
+// At most N copies of this wave are still on their way, its LDS reads are done, and then so are every other wave's.  The
+// builtin tells the compiler that the operands read before are in their registers (after a wait in assembly it would wait
+// for each of them once more).
 template <int N>
-__device__ __forceinline__ void wait_copies()
+__device__ __forceinline__ void wait_copies_and_meet()
 {
     static_assert(N < 64, "the counter has 6 bits");
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));   // vmcnt(N) lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
 }
 
 //
@@ -799,64 +807,53 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_block(GemmArgs a, QkvO
         for (int m = 0; m < RM; ++m) acc[i][m] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
     // this wave copies blocks wave*CP .. +CP-1 of a stage: the first MS are activation strips, the others weight strips
+    constexpr unsigned STAGE = SB * 1024;   // bytes
     const char* src[CP];
+    unsigned place[CP];
+    const unsigned ring0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)&ring[0][0][0];
 #pragma unroll
     for (int c = 0; c < CP; ++c) {
         const int blk = min(wave * CP + c, SB - 1);
         const char* p = blk < MS ? (const char*)a.X + (size_t)min(mb0 + blk, MBT - 1) * KB * 1024
                                  : (const char*)a.W + (size_t)min(nb0 + blk - MS, NBT - 1) * KB * 1024;
         src[c] = p + (size_t)s0 * 1024;
+        place[c] = ring0 + (unsigned)(blk * 1024);
     }
-    const unsigned lane_off = lane * 16;
-    const unsigned ring0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)&ring[0][0][0];
-    auto request = [&](int trip, int slot) {   // k-blocks beyond the slice: the last one once more, never used
-        const size_t at = (size_t)min(trip, trips - 1) * 1024;
-#pragma unroll
-        for (int c = 0; c < CP; ++c) lds_copy_1k(ring0 + (unsigned)((slot * SB + min(wave * CP + c, SB - 1)) * 1024), src[c] + at, lane_off);
-    };
+    // a lane's offset into the k-block of this trip, inside any strip; k-blocks beyond the slice: the last one once more, never used
+    auto lane_off = [&](int trip) { return (unsigned)(min(trip, trips - 1) * 1024 + lane * 16); };
     u32x4 xf[2][RM], wf[2][RN];
-    auto read = [&](int slot, u32x4 (&xv)[RM], u32x4 (&wv)[RN]) {
-#pragma unroll
-        for (int i = 0; i < RN; ++i) wv[i] = ring[slot][MS + wn * RN + i][lane];
-#pragma unroll
-        for (int m = 0; m < RM; ++m) xv[m] = ring[slot][wm * RM + m][lane];
-    };
     if (trips > 0) {
 #pragma unroll
-        for (int q = 0; q < ST; ++q) request(q, q);
-        wait_copies<(ST - 1) * CP>();
-        __builtin_amdgcn_s_barrier();
-        read(0, xf[0], wf[0]);
-        int slot = 0;
+        for (int q = 0; q < ST; ++q)
+#pragma unroll
+            for (int c = 0; c < CP; ++c) lds_copy_1k(q * STAGE, place[c], src[c], lane_off(q));
+        wait_copies_and_meet<(ST - 1) * CP>();
+#pragma unroll
+        for (int i = 0; i < RN; ++i) wf[0][i] = ring[0][MS + wn * RN + i][lane];
+#pragma unroll
+        for (int m = 0; m < RM; ++m) xf[0][m] = ring[0][wm * RM + m][lane];
+        unsigned slot = 0;   // byte offset of this trip's stage
         auto trip = [&](int it, u32x4 (&xc)[RM], u32x4 (&wc)[RN], u32x4 (&xn)[RM], u32x4 (&wn_)[RN]) {
-            // the operands of this trip are in registers (the wait covers their LDS reads); the next stage has landed
-            wait_copies<(ST - 2) * CP>();
-            __builtin_amdgcn_s_barrier();
-            const size_t at = (size_t)min(it + ST, trips - 1) * 1024;
-            const int free_slot = slot;
-            slot = slot + 1 == ST ? 0 : slot + 1;
-            const u32x4* st = &ring[slot][0][0] + lane;
-            // CP parts: one copy, a share of the operand reads, a share of the products.  (All copies at once hold up
-            // every wave of the workgroup behind the address unit at the start of the trip.)
+            // the operands of this trip are in registers; the next stage has landed, and this one's place is free
+            wait_copies_and_meet<(ST - 2) * CP>();
+            const unsigned at = lane_off(it + ST), free_slot = __builtin_amdgcn_readfirstlane(slot);
+            slot = slot + STAGE == ST * STAGE ? 0u : slot + STAGE;
+            const u32x4* st = (const u32x4*)((const char*)&ring[0][0][0] + slot) + lane;
+            // In exactly this order: a product each with the reads of the next trip's operands until all are on their way
+            // (the last ones would hold up the wait above otherwise), the copies evenly among the products (all at once
+            // they hold up every wave of the workgroup behind the address unit).
+            constexpr int R = RM + RN, E = RM * RN;
+            static_assert(R <= E && CP <= E, "a product for each");
 #pragma unroll
-            for (int c = 0; c < CP; ++c) {
-                lds_copy_1k(ring0 + (unsigned)((free_slot * SB + min(wave * CP + c, SB - 1)) * 1024), src[c] + at, lane_off);
-                constexpr int R = RM + RN, E = RM * RN;
+            for (int e = 0; e < E; ++e) {
+                acc[e % RN][e / RN] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wc[e % RN]),
+                                                                             __builtin_bit_cast(f16x8, xc[e / RN]),
+                                                                             acc[e % RN][e / RN], 0, 0, 0);
+                if (e < RN) wn_[e < RN ? e : 0] = st[(MS + wn * RN + e) * 64];
+                else if (e < R) xn[e >= RN && e < R ? e - RN : 0] = st[(wm * RM + e - RN) * 64];
 #pragma unroll
-                for (int q = c * R / CP; q < (c + 1) * R / CP; ++q) {
-                    if (q < RN) wn_[q < RN ? q : 0] = st[(MS + wn * RN + q) * 64];
-                    else xn[q >= RN ? q - RN : 0] = st[(wm * RM + q - RN) * 64];
-                }
-#pragma unroll
-                for (int e = c * E / CP; e < (c + 1) * E / CP; ++e)
-                    acc[e % RN][e / RN] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, wc[e % RN]),
-                                                                                 __builtin_bit_cast(f16x8, xc[e / RN]),
-                                                                                 acc[e % RN][e / RN], 0, 0, 0);
-#pragma unroll
-                for (int q = 0; q < R / CP; ++q) {
-                    __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x008, E / R, 0);
-                }
+                for (int c = 0; c < CP; ++c)
+                    if (c * E / CP == e) lds_copy_1k(free_slot, place[c], src[c], at);
                 __builtin_amdgcn_sched_barrier(0);
             }
         };
@@ -866,7 +863,7 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_block(GemmArgs a, QkvO
             trip(it + 1, xf[1], wf[1], xf[0], wf[0]);
         }
         if (it < trips) trip(it, xf[0], wf[0], xf[1], wf[1]);
-        wait_copies<0>();   // nothing may still be on its way into LDS when the workgroup ends
+        wait_copies_and_meet<0>();   // nothing may still be on its way into LDS when the workgroup ends
     }
 
     const int col4 = (lane >> 4) * 4;
