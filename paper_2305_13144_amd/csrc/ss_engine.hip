@@ -575,6 +575,31 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
     float* pd = ws.pd.as<float>();
     const int Fp = ss::padded_k(F);
 
+    // small models: a row's whole step in one workgroup
+    if (decode && !d_sel && !d_nsel && n_sel == n && ss::row_step_plan(c.n_layers, d, F, V, n, ln.max_ctx, w->n_cu)) {
+        ss::RowStepArgs a{};
+        for (int l = 0; l < c.n_layers; ++l) {
+            const Layer& L = w->layers[l];
+            a.layer[l] = {L.wqkv.p, L.wo.p, L.wgu.p, L.wd.p, L.attn_norm, L.mlp_norm};
+        }
+        a.embed = w->embed;
+        a.final_norm = w->final_norm;
+        a.lm_head = w->lm_head.p;
+        a.kv = ws.kv.as<ss::kv_t>();
+        a.kv_layer_stride = ln.kv_layer_stride;
+        a.rope_cos = w->rope_cos;
+        a.rope_sin = w->rope_sin;
+        a.logits = ln.cur_logits ? ln.cur_logits : ws.logits.as<float>();
+        const bool sample = ln.cur_inv_temp > 0.f;
+        a.am = ln.cur_choose && !sample ? st.am : nullptr;
+        a.n_layers = c.n_layers; a.d = d; a.H = H; a.F = F; a.Fp = Fp; a.V = V;
+        a.eps = c.rms_eps;
+        ss::launch_row_step(st, a, hd, n, s);
+        if (ln.cur_choose && sample)
+            ss::launch_sample(a.logits, V, st.d_n, st, ln.cur_draws, ln.cur_ids, ln.cur_seed, ln.cur_inv_temp, n_sel, s);
+        return;
+    }
+
     const Plans pl = make_plans(w, n, n_sel);
     const ss::GemmPlan &p_qkv = pl.qkv, &p_o = pl.o, &p_gu = pl.gu, &p_d = pl.down, &p_lm = pl.lm;
     const int ks_qkv = p_qkv.ksplit, ks_o = p_o.ksplit, ks_d = p_d.ksplit;

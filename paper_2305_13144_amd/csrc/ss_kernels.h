@@ -97,6 +97,24 @@ void launch_attention_decode(const MbState& st, const float* qkv_part, int kspli
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
                              f16_t* out_packed, int d, int H, int hd, int n_max, int mb_rows, int max_ctx,
                              hipStream_t s);
+// A decode step of n_max rows (at most), one workgroup each, from the embedding to the logits of row j at logits + j * V and,
+// with am, their argmax (row_step_plan says when).
+struct RowStepArgs {
+    struct Layer {
+        const f16_t *wqkv, *wo, *wgu, *wd;
+        const bf16_t *attn_norm, *mlp_norm;
+    } layer[kRowMaxLayers];
+    const bf16_t *embed, *final_norm;
+    const f16_t* lm_head;
+    kv_t* kv;                 // layer l: keys at kv + 2 * l * kv_layer_stride, values kv_layer_stride behind
+    size_t kv_layer_stride;
+    const float *rope_cos, *rope_sin;
+    float* logits;
+    int32_t* am;
+    int n_layers, d, H, F, Fp, V;
+    float eps;
+};
+void launch_row_step(const MbState& st, const RowStepArgs& a, int hd, int n_max, hipStream_t s);
 void launch_argmax(const float* logits, int vocab, const int32_t* d_nsel, int32_t* am, int n_max, hipStream_t s);
 // Temperature sampling in place of the argmax: st.am[j] for the first *d_nsel selected rows.  The draw of slot j
 // (row r = st.live_row[j], token number t = *st.d_step) is draws[r * st.max_new + t], or with draws == nullptr

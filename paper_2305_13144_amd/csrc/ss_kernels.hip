@@ -85,6 +85,26 @@ __device__ __forceinline__ float wave_max(float v)
     return v;
 }
 
+// v of another lane of the same row of 16 lanes (a DPP control), at the cost of a register move.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v)
+{
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140, kDppRotate8 = 0x128;
+
+// Sum over a group of 8 or 16 neighbouring lanes, in each of them.
+template <int N>
+__device__ __forceinline__ float group_sum(float v)
+{
+    static_assert(N == 8 || N == 16, "half a row or a row");
+    v += dpp<kDppXor1>(v);
+    v += dpp<kDppXor2>(v);
+    v += dpp<kDppHalfMirror>(v);   // the lanes of four are alike by now
+    if (N == 16) v += dpp<kDppMirror>(v);
+    return v;
+}
+
 // ------------------------------------------------------------------------------------------ weight packing
 // src is row-major [n_src, k] (bf16 bits or fp32, rounded to bf16 first); source row r lands in packed row
 // (strip * blk_stride + blk_off) * 16 + r%16, where strip = r/16, or with head_strips > 0 (q, k, v) the place that
@@ -1400,6 +1420,317 @@ __global__ __launch_bounds__(64 * NW) void k_attention_decode(MbState st, const 
     attend<HD, NW>(qs, sc, red, oacc, kc + base, vc + base, pos + 1, out, j, h * HD, d);
 }
 
+// ------------------------------------------------------------------------------------------ a row's whole decode step
+// Small models (row_step_plan): a decode step of 7 launches per layer is nothing but launches there, 3.4 us each for a few
+// hundred kilobytes.  Here one workgroup takes one row through the whole step, embedding to logits and their argmax: rows
+// need nothing from each other, so nothing but its own barriers is waited for.
+// What bounds it: every workgroup reads all the weights, 64 bytes a clock from the L2 of its die (151 GB/s alone, 138 each
+// for 256 workgroups; a launch that does nothing else takes 26 us for 3.6 MB), and the barriers' latencies, some 15 us in two
+// layers.  So the loads go on over the barriers: there is one loop for all matrices, and the block that a wave has used
+// last is replaced by the first one it needs of the next matrix.  (A loop per matrix is 5000 instructions, spills, and waits
+// for everything at each end: 58 us.)  Tiny model, 16 rows, context 20: 63 us as 19 launches -> 48; 250 rows 103 -> 58.
+// A wave owns pairs of output strips (the two halves of a head's strip, gate and up; two sums under way at once); the
+// matrix instruction's activation operand is the row's vector for all of its 16 columns, so that every lane ends up with
+// valid sums.  Rounding as in the other kernels: residual stream, sums, rotation and softmax in fp32; projection inputs,
+// keys and values as halves, once each.
+constexpr int kRowThreads = 64 * kRowWaves;
+constexpr int kRowGroup = 8;   // k-blocks of both strips that a wave has in flight: 128 KiB for the workgroup
+
+// Waits for this wave's LDS traffic and meets the others; loads from global memory stay on their way.
+__device__ __forceinline__ void row_meet()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// A group of a pair's k-blocks: scalar base and offsets (as plain loads the compiler keeps an address per load and lane).
+// Past a strip's last k-block that one is read again and meets zeros; an odd last strip comes twice.
+struct RowGroup {
+    __amdgpu_buffer_rsrc_t rsrc;
+    int at[2], left;
+    __device__ __forceinline__ RowGroup(const f16_t* W, int KB, int strips, int pair, int g)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc((void*)W, (short)0, strips * KB * 1024, 0x00020000)),
+          at{(2 * pair * KB + g * kRowGroup) * 1024, (min(2 * pair + 1, strips - 1) * KB + g * kRowGroup) * 1024},
+          left(KB - g * kRowGroup)
+    {
+    }
+    __device__ __forceinline__ u32x4 load(int i, int q) const
+    {
+        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, (threadIdx.x & 63) * 16, at[i] + min(q, left - 1) * 1024, 0);
+    }
+};
+
+__device__ __forceinline__ float pick4(const f32x4& v, int i) { return i < 2 ? (i == 0 ? v[0] : v[1]) : (i == 2 ? v[2] : v[3]); }
+
+// hb <- the normalised residual row as halves; gain: this thread's norm weight (thread = column)
+__device__ __forceinline__ void row_norm(const float* x, f16_t* hb, int d, float eps, bf16_t gain, int lane)
+{
+    float ss = 0.f;
+    for (int c = lane; c < d; c += 64) ss += x[c] * x[c];   // every wave by itself: no barrier
+    ss = group_sum<16>(ss);
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    const float r = rsqrtf(ss / (float)d + eps);
+    if ((int)threadIdx.x < d) hb[threadIdx.x] = f2h(x[threadIdx.x] * r * bf2f(gain));
+}
+
+template <int HD>
+__global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArgs a)
+{
+    constexpr int HALF = HD / 2, PH = HD / 32;            // PH: pairs of strips per head
+    constexpr int LPK = HD / 8, KPW = 64 / LPK, AU = 4;   // lanes per key, keys per wave load, loads in flight
+    const int j = blockIdx.x;
+    const int count = *st.d_n;
+    const int row = st.tr_row[j], pos = st.tr_pos[j], tok = st.tr_tok[j];
+    if (j >= count) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int d = a.d, H = a.H, dp = row_padded(d), fp = row_padded(a.Fp);
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    float* x = (float*)lds;                 // [d] residual stream
+    float* q = x + d;                       // [d] rotated query
+    float* cs = q + d;                      // [HD] cosines, then sines of this position
+    float* part = cs + HD;                  // [kRowWaves][HD + 4] attention: sums, maximum and total of every wave
+    f16_t* hb = (f16_t*)(part + kRowWaves * (HD + 4));   // [dp] input of q|k|v, o, gate|up, head
+    f16_t* act = hb + dp;                   // [fp] input of down
+    f16_t* kn = act + fp;                   // [d], [d] this position's key and value
+    f16_t* vn = kn + d;
+
+    // Phase 4 * l + t: matrix t (q|k|v, o, gate|up, down) of layer l; the last one is the head.
+    const int phases = 4 * a.n_layers + 1;
+    auto weights = [&](int ph) {
+        const RowStepArgs::Layer& L = a.layer[ph >> 2];
+        const int t = ph & 3;
+        return ph == phases - 1 ? a.lm_head : t == 0 ? L.wqkv : t == 1 ? L.wo : t == 2 ? L.wgu : L.wd;
+    };
+    auto kblocks = [&](int ph) { return (ph & 3) == 3 ? a.Fp >> 5 : d >> 5; };
+    auto strips_of = [&](int ph) {
+        const int t = ph & 3;
+        return ph == phases - 1 ? a.V >> 4 : t == 0 ? 3 * d >> 4 : t == 2 ? a.F >> 3 : d >> 4;
+    };
+    u32x4 v[2][kRowGroup];
+    {
+        const RowGroup n(weights(0), kblocks(0), strips_of(0), min(wave, (strips_of(0) >> 1) - 1), 0);
+#pragma unroll
+        for (int z = 0; z < kRowGroup; ++z) {
+            v[0][z] = n.load(0, z);
+            v[1][z] = n.load(1, z);
+        }
+    }
+    bf16_t gain = tid < d ? a.layer[0].attn_norm[tid] : 0;
+    if (tid < d) x[tid] = bf2f(a.embed[(size_t)tok * d + tid]);
+    if (tid < HD) cs[tid] = tid < HALF ? a.rope_cos[(size_t)pos * HALF + tid] : a.rope_sin[(size_t)pos * HALF + tid - HALF];
+    for (int c = d + tid; c < dp; c += kRowThreads) hb[c] = 0;
+    for (int c = a.F + tid; c < fp; c += kRowThreads) act[c] = 0;
+    const int64_t so = st.row_so[row];
+    const int cap = st.row_cap[row];
+    const int sel = lane & 3, col = (lane >> 4) * 4 + sel;   // a strip's 16 columns: one each in the lanes below
+    const bool owner = (lane & 15) < 4;
+    // a head's earlier slots are shared out to P waves, and inside a wave to groups of LPK lanes
+    const int P = kRowWaves / H, h = min(wave / P, H - 1), p = wave % P, sub = lane % LPK, kin = lane / LPK;
+    uint4 kr[AU], vr[AU];
+    float best = -3.4e38f;   // the head's largest logit and its column
+    int bi = 0x7fffffff;
+    row_meet();
+
+    for (int ph = 0; ph < phases; ++ph) {
+        const int t = ph == phases - 1 ? 4 : ph & 3;
+        kv_t* const kc = a.kv + (size_t)(ph >> 2) * 2 * a.kv_layer_stride + so * d;
+        kv_t* const vc = kc + a.kv_layer_stride;
+        const kv_t *kb = kc + (size_t)h * cap * HD + sub * 8, *vb = vc + (size_t)h * cap * HD + sub * 8;
+        // the first slots of a layer are asked for before anything that they do not depend on
+        auto slot = [&](int c0, int u) { return c0 + u * P * KPW + kin; };
+        auto load_slots = [&](uint4 (&r)[AU], const kv_t* from, int c0) {
+#pragma unroll
+            for (int u = 0; u < AU; ++u) r[u] = *(const uint4*)(from + (size_t)min(slot(c0, u), pos - 1) * HD);
+        };
+        if (t == 0) {
+            load_slots(kr, kb, p * KPW);
+            load_slots(vr, vb, p * KPW);
+        }
+        if ((t & 1) == 0) {   // normalised input
+            row_norm(x, hb, d, a.eps, gain, lane);
+            if (tid < d && t < 4)
+                gain = (t == 0 ? a.layer[ph >> 2].mlp_norm : ph + 3 == phases ? a.final_norm : a.layer[(ph >> 2) + 1].attn_norm)[tid];
+            row_meet();
+        }
+        // This wave's pairs of the matrix times the vector at xb.  A block is replaced by its successor, the first ones of
+        // the next matrix at the end, as soon as it is used: one unbroken row of loads, every wait for the oldest only.
+        {
+            const int KB = kblocks(ph), strips = strips_of(ph), pairs = (strips + 1) >> 1, after = min(ph + 1, phases - 1);
+            const f16_t *W = weights(ph), *W2 = weights(after), *xb = t == 3 ? act : hb;
+            const int KB2 = kblocks(after), strips2 = strips_of(after), first2 = min(wave, ((strips2 + 1) >> 1) - 1);
+            f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+            int pair = wave, g = 0;
+            do {   // a wave without a pair holds the last one's first group, and drops it
+                f16x8 b[kRowGroup];
+#pragma unroll
+                for (int z = 0; z < kRowGroup; ++z)
+                    b[z] = *(const f16x8*)(xb + (g * kRowGroup + z) * 32 + (lane >> 4) * 8);
+                const int now = pair;
+                const bool whole = KB - g * kRowGroup <= kRowGroup;
+                pair += whole ? kRowWaves : 0;
+                g = whole ? 0 : g + 1;
+                const bool more = pair < pairs;
+                const RowGroup n(more ? W : W2, more ? KB : KB2, more ? strips : strips2, more ? pair : first2, g);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int z = 0; z < kRowGroup; ++z) {
+                    a0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, v[0][z]), b[z], a0, 0, 0, 0);
+                    a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, v[1][z]), b[z], a1, 0, 0, 0);
+                    v[0][z] = n.load(0, z);
+                    v[1][z] = n.load(1, z);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                if (!whole) continue;
+                float s0 = pick4(a0, sel), s1 = pick4(a1, sel);   // column `col` of either strip
+                a0 = a1 = (f32x4){0.f, 0.f, 0.f, 0.f};
+                if (now >= pairs) continue;
+                if (t == 4) {
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        const float z = i ? s1 : s0;
+                        const int c = now * 32 + i * 16 + col;
+                        if (c >= a.V) continue;   // an odd last strip
+                        if (owner) a.logits[(size_t)j * a.V + c] = z;
+                        if (z > best || (z == best && c < bi)) {   // lowest index on ties, as in k_argmax
+                            best = z;
+                            bi = c;
+                        }
+                    }
+                } else if (owner) {
+                    if (t == 2) {
+                        act[now * 16 + col] = f2h(silu_f(s0) * s1);
+                    } else if (t != 0) {
+                        x[now * 32 + col] += s0;
+                        x[now * 32 + 16 + col] += s1;
+                    } else {   // elements e and e + HD/2 of a head (see qkv_strip)
+                        const int which = now / (d >> 5), r = now - which * (d >> 5), e = r / PH * HD + r % PH * 16 + col;
+                        if (which < 2) {
+                            const float c = cs[e % HD], s = cs[HALF + e % HD], r0 = s0 * c - s1 * s, r1 = s0 * s + s1 * c;
+                            s0 = r0;
+                            s1 = r1;
+                        }
+                        if (which == 0) {
+                            q[e] = s0;
+                            q[e + HALF] = s1;
+                        } else {
+                            kv_t* n1 = (which == 1 ? kn : vn) + e;
+                            n1[0] = f2kv(s0);
+                            n1[HALF] = f2kv(s1);
+                        }
+                    }
+                }
+            } while (pair < pairs || g != 0);
+        }
+        row_meet();
+        if (t != 0) continue;
+        // Attention: every wave keeps a softmax of its own; the slots before this one come from the cache, this one from LDS.
+        if (tid < d) {
+            const size_t at = ((size_t)(tid / HD) * cap + pos) * HD + tid % HD;
+            kc[at] = kn[tid];
+            vc[at] = vn[tid];
+        }
+        if (wave < H * P) {
+            const float scale = rsqrtf((float)HD);
+            float qf[8], m = -3.0e38f, tot = 0.f, acc[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                qf[e] = q[h * HD + sub * 8 + e];
+                acc[e] = 0.f;
+            }
+            auto score = [&](const uint4& raw) {
+                const kv_t* k = (const kv_t*)&raw;
+                float s = 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) s += qf[e] * kv2f(k[e]);
+                return group_sum<LPK>(s) * scale;
+            };
+            auto add = [&](float w, const uint4& raw) {
+                const kv_t* u = (const kv_t*)&raw;
+                tot += w;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] += w * kv2f(u[e]);
+            };
+            auto largest = [](float z) {   // of the wave's groups
+                if (LPK == 8) z = fmaxf(z, dpp<kDppRotate8>(z));
+                z = fmaxf(z, __shfl_xor(z, 16, 64));
+                return fmaxf(z, __shfl_xor(z, 32, 64));
+            };
+            if (p == 0) {   // this slot: the same in every group, counted in the first
+                m = score(*(const uint4*)(kn + h * HD + sub * 8));
+                add(kin == 0 ? 1.f : 0.f, *(const uint4*)(vn + h * HD + sub * 8));
+            }
+            for (int c0 = p * KPW; c0 < pos; c0 += P * KPW * AU) {   // wave-uniform
+                const int c1 = c0 + P * KPW * AU;
+                float s[AU], top = m;
+#pragma unroll
+                for (int u = 0; u < AU; ++u) {
+                    s[u] = slot(c0, u) < pos ? score(kr[u]) : -3.0e38f;
+                    top = fmaxf(top, s[u]);
+                }
+                if (c1 < pos) load_slots(kr, kb, c1);
+                top = largest(top);
+                const float keep = __expf(m - top);
+                m = top;
+                tot *= keep;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] *= keep;
+#pragma unroll
+                for (int u = 0; u < AU; ++u) add(slot(c0, u) < pos ? __expf(s[u] - m) : 0.f, vr[u]);
+                if (c1 < pos) load_slots(vr, vb, c1);
+            }
+            auto over_groups = [](float z) {
+                if (LPK == 8) z += dpp<kDppRotate8>(z);
+                z += __shfl_xor(z, 16, 64);
+                return z + __shfl_xor(z, 32, 64);
+            };
+            tot = over_groups(tot);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[e] = over_groups(acc[e]);
+            float* w = part + wave * (HD + 4);
+            if (kin == 0) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) w[sub * 8 + e] = acc[e];
+                if (sub == 0) {
+                    w[HD] = m;
+                    w[HD + 1] = tot;
+                }
+            }
+        }
+        row_meet();
+        if (tid < d) {
+            const float* w = part + tid / HD * P * (HD + 4);
+            float m = -3.0e38f, tot = 0.f, sum = 0.f;
+            for (int z = 0; z < P; ++z) m = fmaxf(m, w[z * (HD + 4) + HD]);
+            for (int z = 0; z < P; ++z) {
+                const float f = __expf(w[z * (HD + 4) + HD] - m);
+                tot += f * w[z * (HD + 4) + HD + 1];
+                sum += f * w[z * (HD + 4) + tid % HD];
+            }
+            hb[tid] = f2h(sum / tot);
+        }
+        row_meet();
+    }
+    if (!a.am) return;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) {
+        const float ob = __shfl_xor(best, m, 64);
+        const int oi = __shfl_xor(bi, m, 64);
+        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
+    }
+    float* const sb = part;
+    int* const si = (int*)(part + kRowWaves);
+    if (lane == 0) { sb[wave] = best; si[wave] = bi; }
+    row_meet();
+    if (tid == 0) {
+        for (int w = 1; w < kRowWaves; ++w)
+            if (sb[w] > best || (sb[w] == best && si[w] < bi)) { best = sb[w]; bi = si[w]; }
+        a.am[j] = (unsigned)bi < (unsigned)a.V ? bi : 0;
+    }
+}
+
 // ------------------------------------------------------------------------------------------ argmax
 // Greedy choice per selected row: index of the largest logit, lowest index on exact ties.
 // 1024 threads per row, all of a thread's loads issued before the first compare.
@@ -1869,6 +2200,13 @@ void launch_attention_prompt(const MbState& st, const float* qrot, const kv_t* k
         else hipLaunchKernelGGL((k_attention_prompt<64, 1, 1>), SS_ATTN_ARGS);
     }
 #undef SS_ATTN_ARGS
+}
+
+void launch_row_step(const MbState& st, const RowStepArgs& a, int hd, int n_max, hipStream_t s)
+{
+    const size_t lds = row_step_lds_bytes(a.d, a.Fp, hd);
+    if (hd == 128) hipLaunchKernelGGL((k_row_step<128>), dim3(n_max), dim3(kRowThreads), lds, s, st, a);
+    else hipLaunchKernelGGL((k_row_step<64>), dim3(n_max), dim3(kRowThreads), lds, s, st, a);
 }
 
 void launch_argmax(const float* logits, int vocab, const int32_t* d_nsel, int32_t* am, int n_max, hipStream_t s)

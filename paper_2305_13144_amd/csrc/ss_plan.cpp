@@ -155,6 +155,25 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
     return p;
 }
 
+// A workgroup of k_row_step reads the whole model and its row's slots by itself: some 75 bytes per ns of weights over all its
+// phases, 61 of slots, where a launch of the other kernels costs 3.4 us.  So 340 KB of weights, or half as much of slots, for each
+// launch that it replaces.  Steps in microseconds, launches / this kernel: tiny (2 layers, 256 wide, 3.6 MB) 16 rows at context 20
+// 63.0 / 48.1, 200 68.4 / 59.7, 500 72.6 / 67.1, 1000 76.8 / 80.9, 250 rows 103 / 58; 2 layers 128 wide 61.5 / 35.9; 4 layers 256 wide
+// 117 / 95.  (1 layer 512 wide, 7.5 MB, is 44 in launches.)
+constexpr size_t kRowBytesPerLaunch = (size_t)340 << 10;
+
+bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, int n_cu)
+{
+    // the testing aids choose among the projection kernels: they get those
+    if (gemm_mode() != 0 || g_block_tile.load(std::memory_order_relaxed) >= 0 || !g_sweep_split.load(std::memory_order_relaxed) ||
+        !g_tall_tiles.load(std::memory_order_relaxed))
+        return false;
+    if (n_layers > kRowMaxLayers || d > kRowMaxModel || F > kRowMaxFfn) return false;
+    if ((n_rows + 15) / 16 * 16 > n_cu) return false;   // a unit each, by whole strips like the other plans
+    const size_t layer = ((size_t)4 * d * d + (size_t)3 * d * F) * 2 + 2 * (size_t)max_ctx * d * 4;
+    return n_layers * layer + (size_t)V * d * 2 <= (size_t)(7 * n_layers + 4) * kRowBytesPerLaunch;
+}
+
 size_t gemm_partial_rows_bound(int n_max)
 {
     // up to kSweepMaxRows rows: at most kSmallMaxKsplit slices; the block kernel: 4 up to kBlockRows4 rows, 2 up to

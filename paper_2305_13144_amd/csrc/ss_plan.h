@@ -48,6 +48,20 @@ size_t gemm_partial_rows_bound(int n_max);
 // Rows up to which the sweep kernel is chosen for a matrix of w_per_cu weight bytes per compute unit and this many units.
 int sweep_rows(size_t w_per_cu, int units, int n_cu);
 
+// Decode steps of small models: whether n_rows rows with contexts of at most max_ctx slots go through k_row_step, one
+// workgroup for a row's whole step, instead of 7 launches per layer.
+constexpr int kRowMaxLayers = 16;
+constexpr int kRowWaves = 8;
+constexpr int kRowMaxModel = 64 * kRowWaves;   // model width: a thread per element, and at least a wave per head
+constexpr int kRowMaxFfn = 8192;
+bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, int n_cu);
+constexpr int row_padded(int k) { return (k + 255) / 256 * 256; }   // whole groups of 8 k-blocks
+// Its LDS: residual row, query, rotation, attention sums of every wave, the two projection inputs, this position's key and value.
+constexpr size_t row_step_lds_bytes(int d, int Fp, int hd)
+{
+    return (size_t)(2 * d + hd + kRowWaves * (hd + 4)) * 4 + (size_t)(row_padded(d) + row_padded(Fp) + 2 * d) * 2;
+}
+
 // Testing aid: 0 = choose per shape (default), 1 = never use the sweep kernel, 2 = use it for every
 // projection of at most kSweepMaxRows rows.
 void set_gemm_mode(int mode);
