@@ -145,15 +145,18 @@ void ss_weights_destroy(ss_weights* w);
  * Per-handle options.
  *   option SS_OPT_IN_FLIGHT, value = 1 .. SS_IN_FLIGHT_MAX: how many micro-batches of a group pass (ss_run_group,
  *   ss_run_group_generate) are generated at the same time.  The micro-batches of a pass (Sec. 4.1) are independent
- *   of each other, and a decode step of a few rows leaves the memory system idle between its kernels; with more than
- *   one the call hands the pass's micro-batches, longest cap first, to that many host threads, each with a stream, a
- *   workspace and a key/value cache of its own, so that one micro-batch's kernels run in the others' gaps (measured
- *   at the 7B shape, 16-row steps: 51 % of the HBM peak with one in flight, 65 % with two, 69 % with four; on a whole
- *   group the third and fourth also shorten the tail at the end of a pass).  Every query's tokens
- *   are the same as with 1; only the order in which micro-batches finish changes.  The stream argument of the call
- *   is used for one of them; the others run on streams the handle owns.  The call returns when all are done.  Device
- *   time in the statistics is summed per micro-batch and so can exceed the wall time.  Device memory: one workspace
- *   and key/value cache per lane in use, each as large as the largest micro-batch that lane has run.
+ *   of each other, and a decode step of a few rows is the time of its weights.  With more than one, ss_run_group lets
+ *   micro-batches of at most 16 rows share their decode forwards, that many at a time and longest cap first: each has its
+ *   own prompt forward, cap and end, and the forwards in between hold the rows of all (models with 50 MB of weights a layer
+ *   and more: below, launches are what takes time, and streams hide them better; measured at the 7B shape, four
+ *   micro-batches of 16 rows: a forward of 64 rows takes 3.8 ms, four of 16 rows 11.5 one after another and 8.4 at the same
+ *   time).  Larger micro-batches, and all of ss_run_group_generate's, go to as many host threads, each with a stream, a
+ *   workspace and a key/value cache of its own, so that one micro-batch's kernels run in the others' gaps.
+ *   Every query's tokens are the same as with 1; only the order in which micro-batches finish changes.  The stream argument
+ *   of the call is used for one of them (or those that share); the others run on streams the handle owns.  The call returns
+ *   when all are done.  Device time in the statistics is summed per micro-batch, that of shared forwards counted once, and
+ *   can exceed the wall time.  Device memory: one workspace and key/value cache per lane in use, each as large as the
+ *   largest micro-batch, or micro-batches together, that lane has run.
  *   option SS_OPT_WEIGHT_COPIES, value = 0 or 1: the handle's 12-bit weight copies.  0 gives their memory back; 1 makes
  *   those that it has not got, under the rule above (at most an eighth of the device memory that is free now; otherwise
  *   none, and still SS_OK).  A new handle has them (1).  A call that needed their memory, on this handle or on another of

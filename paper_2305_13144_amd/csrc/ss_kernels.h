@@ -35,6 +35,7 @@ struct MbState {
     int32_t* row_plen;   // [B] prompt length
     int32_t* row_j0;     // [B] first token-row of the row in a prompt forward
     int32_t* row_limit;  // [B] min(target, cap): tokens the row emits; lowered by the device when the row emits its end id
+    const int32_t* row_stay;   // [B] or null: forwards that the row takes part in (micro-batches that share theirs)
     int64_t* row_so;     // [B] first key/value slot of the row's slab
     int32_t* row_cap;    // [B] slots in the row's slab (prompt + cap)
     int32_t* am;         // [n_sel_max] argmax of the selected rows' logits
@@ -91,12 +92,12 @@ void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, si
 // st.row_j0[i]; max_len = the longest row (sizes the grid).
 void launch_attention_prompt(const MbState& st, const float* qrot, const kv_t* kcache, const kv_t* vcache,
                              f16_t* out_packed, int d, int H, int hd, int B, int max_len, hipStream_t s);
-// n_max: rows of this launch; mb_rows, max_ctx: rows of the micro-batch, finished ones included, and an upper bound of its
+// n_max: rows of this launch; plan_rows, mb_rows, max_ctx: rows to choose its shape for (n_max, or those of one micro-batch of several), rows of the micro-batch, finished ones included, and an upper bound of its
 // contexts in this forward (they choose the launch shape).
 void launch_attention_decode(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
-                             f16_t* out_packed, int d, int H, int hd, int n_max, int mb_rows, int max_ctx,
-                             hipStream_t s);
+                             f16_t* out_packed, int d, int H, int hd, int n_max, int plan_rows, int mb_rows,
+                             int max_ctx, hipStream_t s);
 // A decode step of n_max rows (at most), one workgroup each, from the embedding to the logits of row j at logits + j * V and,
 // with am, their argmax (row_step_plan says when).
 struct RowStepArgs {

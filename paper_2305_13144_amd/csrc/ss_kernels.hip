@@ -1021,10 +1021,9 @@ __global__ __launch_bounds__(256) void k_rope_append(MbState st, const float* __
 // loads of a group that lie beyond the context are left out of both passes.  Per layer, 7B: 163 rows
 // 31.4 -> 27.1 us, 51 rows 15.7 -> 14.1, one row 8.1 -> 6.8 (contexts of 16 to 70).
 constexpr int kAttnUnroll = 8;
-constexpr int kAttnWideMaxGroups = 512;   // decode attention: (row, head) workgroups up to which 8 waves each are used
-constexpr int kAttnWidestMaxGroups = 192; //   ... and, of the whole micro-batch, 16 waves each, if some context is long enough
 
-template <int HD, int NW>
+// The slots are dealt to NW slices, one per wave, or NW / PW for each of PW waves: the sums are the same sums in the same order.
+template <int HD, int NW, int PW>
 __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __restrict__ sc, float* __restrict__ red,
                                        float (*__restrict__ oacc)[HD], const kv_t* __restrict__ kbase,
                                        const kv_t* __restrict__ vbase, int ctx, f16_t* __restrict__ out, int out_r,
@@ -1041,7 +1040,9 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     for (int e = 0; e < 8; ++e) q[e] = qs[sub * 8 + e];
 
     float mx = -3.0e38f;
-    for (int c0 = wave * KPW; c0 < ctx; c0 += NW * KPW * AU) {
+#pragma unroll
+    for (int v = wave; v < NW; v += PW)
+    for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
         uint4 raw[AU];
 #pragma unroll
         for (int u = 0; u < AU; ++u) {
@@ -1077,23 +1078,28 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     __syncthreads();
     mx = red[0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) mx = fmaxf(mx, red[w]);
-    float sum = 0.f;
-    for (int s = tid; s < ctx; s += 64 * NW) {
-        const float p = __expf(sc[s] - mx);
-        sc[s] = p;
-        sum += p;
+    for (int w = 1; w < PW; ++w) mx = fmaxf(mx, red[w]);
+#pragma unroll
+    for (int v = wave; v < NW; v += PW) {
+        float sum = 0.f;
+        for (int s = v * 64 + lane; s < ctx; s += 64 * NW) {
+            const float p = __expf(sc[s] - mx);
+            sc[s] = p;
+            sum += p;
+        }
+        sum = wave_sum(sum);
+        if (lane == 0) red[PW + v] = sum;
     }
-    sum = wave_sum(sum);
-    if (lane == 0) red[NW + wave] = sum;
     __syncthreads();
     float tot = 0.f;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) tot += red[NW + w];
+    for (int w = 0; w < NW; ++w) tot += red[PW + w];
     const float inv = 1.f / tot;
 
+#pragma unroll
+    for (int v = wave; v < NW; v += PW) {
     float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int c0 = wave * KPW; c0 < ctx; c0 += NW * KPW * AU) {
+    for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
         uint4 raw[AU];
 #pragma unroll
         for (int u = 0; u < AU; ++u) {
@@ -1119,7 +1125,8 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
         for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], m, 64);
     if (kin == 0)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) oacc[wave][sub * 8 + e] = o[e];
+        for (int e = 0; e < 8; ++e) oacc[v][sub * 8 + e] = o[e];
+    }
     __syncthreads();
     if (tid < HD / 4) {
         f16_t r[4];
@@ -1367,15 +1374,15 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
 // be resident with room to spare, 4 (128 slots) for larger batches, whose many workgroups already fill the chip, and 16
 // (512 slots) when the micro-batch has less than one workgroup per compute unit and a context exceeds 256 slots: what a
 // unit has in flight is then all that counts.
-template <int HD, int NW>
-__global__ __launch_bounds__(64 * NW) void k_attention_decode(MbState st, const float* __restrict__ part, int ksplit,
+template <int HD, int NW, int PW>
+__global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const float* __restrict__ part, int ksplit,
                                                           size_t part_stride, kv_t* __restrict__ kc,
                                                           kv_t* __restrict__ vc, const float* __restrict__ rcos,
                                                           const float* __restrict__ rsin, f16_t* __restrict__ out,
                                                           int d)
 {
     __shared__ float sc[kMaxPos];
-    __shared__ float red[2 * NW];
+    __shared__ float red[PW + NW];
     __shared__ float oacc[NW][HD];
     __shared__ float qs[HD];
     constexpr int HALF = HD / 2;
@@ -1417,7 +1424,7 @@ __global__ __launch_bounds__(64 * NW) void k_attention_decode(MbState st, const 
         }
     }
     __syncthreads();   // the new key/value slot and q are visible to the whole workgroup
-    attend<HD, NW>(qs, sc, red, oacc, kc + base, vc + base, pos + 1, out, j, h * HD, d);
+    attend<HD, NW, PW>(qs, sc, red, oacc, kc + base, vc + base, pos + 1, out, j, h * HD, d);
 }
 
 // ------------------------------------------------------------------------------------------ a row's whole decode step
@@ -1915,7 +1922,7 @@ __global__ __launch_bounds__(1024) void k_step_update(MbState st, int compact, i
             }
         }
         owes = s + 1 < lim;
-        keep = compact ? owes : 1;
+        keep = st.row_stay ? s + 1 < st.row_stay[row] : compact ? owes : 1;
     }
     const unsigned long long bal = __ballot(keep);
     const unsigned long long act = __ballot(owes);
@@ -2036,11 +2043,10 @@ static void launch_skinny_inst(const GemmArgs& a, hipStream_t s)
 template <int MT, int EPI>
 static void launch_skinny_mt(const GemmArgs& a, hipStream_t s)
 {
-    if constexpr (MT == 1)
-        if (a.narrow) {   // gemm_plan: one row strip, 4 k-blocks per load
-            if (a.nb == 2) return launch_skinny_inst<MT, 2, 4, EPI, 1>(a, s);
-            return launch_skinny_inst<MT, 4, 4, EPI, 1>(a, s);
-        }
+    if (a.narrow) {   // gemm_plan: for one row strip, 4 k-blocks per load; more strips are several such micro-batches
+        if (a.nb == 2) return launch_skinny_inst<MT, 2, 4, EPI, 1>(a, s);
+        return launch_skinny_inst<MT, 4, 4, EPI, 1>(a, s);
+    }
     if (a.nb == 2) {
         if (a.kd == 2) launch_skinny_inst<MT, 2, 2, EPI>(a, s);
         else launch_skinny_inst<MT, 2, 4, EPI>(a, s);
@@ -2150,35 +2156,38 @@ void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, si
                        vcache, rope_cos, rope_sin, d, H, hd);
 }
 
-template <int HD, int NW>
+template <int HD, int NW, int PW = NW>
 static void launch_attention_decode_inst(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                                          kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
                                          f16_t* out_packed, int d, int H, int n_max, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_attention_decode<HD, NW>), dim3(n_max, H), dim3(64 * NW), 0, s, st, qkv_part, ksplit, part_stride,
+    hipLaunchKernelGGL((k_attention_decode<HD, NW, PW>), dim3(n_max, H), dim3(64 * PW), 0, s, st, qkv_part, ksplit, part_stride,
                        kcache, vcache, rope_cos, rope_sin, out_packed, d);
 }
 
 void launch_attention_decode(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
-                             f16_t* out_packed, int d, int H, int hd, int n_max, int mb_rows, int max_ctx, hipStream_t s)
+                             f16_t* out_packed, int d, int H, int hd, int n_max, int plan_rows, int mb_rows, int max_ctx,
+                             hipStream_t s)
 {
     // measured at the 7B shape: 8 waves win at 16 rows (512 workgroups: 14.1 against 14.9 us per layer at context
     // 200), 4 waves win at 64 rows (2048 workgroups: 25.7 against 36.1 us at context 100)
-    const int groups = n_max * H;
     // 16 waves where 8 would need a second round trip (3 rows at context 2400: 47.5 -> 38 us); shorter contexts leave some
     // of them without a slot (tiny model, context 40: 6 us with 8 waves, 7.3 with 16).  Their sums add up in another order,
     // so the choice depends on the micro-batch and on how far it has come, not on how many of its rows are still alive: a
     // row's numbers are to be the same whether or when the others leave.
-    const bool wide = groups <= kAttnWideMaxGroups;
-    const bool widest = mb_rows * H <= kAttnWidestMaxGroups && max_ctx > 8 * kAttnUnroll * (512 / hd);
+    const bool wide = attention_wide(plan_rows, mb_rows, H);
+    const bool many = wide && n_max * H > kAttnWideMaxGroups;   // several micro-batches together: 8 slices, but 4 waves
+    const bool widest = attention_may_widen(mb_rows, H, max_ctx, hd);
 #define SS_ATTN_ARGS st, qkv_part, ksplit, part_stride, kcache, vcache, rope_cos, rope_sin, out_packed, d, H, n_max, s
     if (hd == 128) {
         if (widest) launch_attention_decode_inst<128, 16>(SS_ATTN_ARGS);
+        else if (many) launch_attention_decode_inst<128, 8, 4>(SS_ATTN_ARGS);
         else if (wide) launch_attention_decode_inst<128, 8>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<128, 4>(SS_ATTN_ARGS);
     } else {
         if (widest) launch_attention_decode_inst<64, 16>(SS_ATTN_ARGS);
+        else if (many) launch_attention_decode_inst<64, 8, 4>(SS_ATTN_ARGS);
         else if (wide) launch_attention_decode_inst<64, 8>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<64, 4>(SS_ATTN_ARGS);
     }

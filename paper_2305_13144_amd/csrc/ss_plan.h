@@ -62,6 +62,32 @@ constexpr size_t row_step_lds_bytes(int d, int Fp, int hd)
     return (size_t)(2 * d + hd + kRowWaves * (hd + 4)) * 4 + (size_t)(row_padded(d) + row_padded(Fp) + 2 * d) * 2;
 }
 
+// Decode attention: (row, head) pairs of a whole micro-batch up to which 16 waves each are used, once some context exceeds
+// what 8 have in flight.
+constexpr int kAttnWidestMaxGroups = 192;
+constexpr bool attention_may_widen(int mb_rows, int H, int max_ctx, int hd)
+{
+    return mb_rows * H <= kAttnWidestMaxGroups && max_ctx > 64 * (512 / hd);
+}
+
+// ... and 8 waves each (else 4), by whole strips of live rows, or the rows of a smaller micro-batch: a row's numbers are not to
+// depend on who else is still alive.
+constexpr int kAttnWideMaxGroups = 512;
+constexpr bool attention_wide(int n_rows, int mb_rows, int H)
+{
+    const int strips = (n_rows + 15) / 16 * 16;
+    return (mb_rows < strips ? mb_rows : strips) * H <= kAttnWideMaxGroups;
+}
+
+// Micro-batches of a group pass that share their decode forwards: rows of one (a strip: every plan of a strip holds for it
+// alone and for several together) and of all.
+constexpr int kSharedMbRows = 16, kSharedRows = 64;
+// Whether they do: where a launch is the time of its weights (7 MB and more each, 7 a layer).  Below that it is the time of
+// a launch, which several streams hide better.  Group passes, four micro-batches in flight on streams / sharing, ms: 4 layers
+// 512 wide 22.4 / 27.3, 12 layers 1024 wide (25 MB a layer) 74.5 / 85.4, 6 layers 2048 wide (101 MB) 63.6 / 61.8 and 31.7 / 26.3,
+// 4 layers 3072 wide 69.9 / 54.6, 4 layers of 7B 121 / 82 and 64 / 35.
+constexpr bool shared_forwards_pay(int d, int F) { return ((size_t)4 * d * d + (size_t)3 * d * F) * 2 >= (size_t)50 << 20; }
+
 // Testing aid: 0 = choose per shape (default), 1 = never use the sweep kernel, 2 = use it for every
 // projection of at most kSweepMaxRows rows.
 void set_gemm_mode(int mode);
