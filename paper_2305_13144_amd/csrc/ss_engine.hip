@@ -559,6 +559,32 @@ GemmArgs gemm_args(const ss_weights* w, const PackedMat& W, const f16_t* X, floa
     return g;
 }
 
+ss::RowStepArgs row_step_args(const ss_weights* w, const Lane& ln)
+{
+    const ss_model_cfg& c = w->cfg;
+    ss::RowStepArgs a{};
+    for (int l = 0; l < c.n_layers; ++l) {
+        const Layer& L = w->layers[l];
+        a.layer[l] = {L.wqkv.p, L.wo.p, L.wgu.p, L.wd.p, L.attn_norm, L.mlp_norm};
+    }
+    a.embed = w->embed;
+    a.final_norm = w->final_norm;
+    a.lm_head = w->lm_head.p;
+    a.kv = ln.ws.kv.as<ss::kv_t>();
+    a.kv_layer_stride = ln.kv_layer_stride;
+    a.rope_cos = w->rope_cos;
+    a.rope_sin = w->rope_sin;
+    a.logits = ln.cur_logits ? ln.cur_logits : ln.ws.logits.as<float>();
+    a.n_layers = c.n_layers;
+    a.d = c.d_model;
+    a.H = c.n_heads;
+    a.F = c.d_ffn;
+    a.Fp = ss::padded_k(c.d_ffn);
+    a.V = c.vocab;
+    a.eps = c.rms_eps;
+    return a;
+}
+
 // ---------------------------------------------------------------------------------------- one forward
 // Runs the decoder over the token-rows described by the device state (st.d_n of them, at most n of
 // them: n sizes the grids and picks the kernel variants).  Logits are produced for n_sel rows:
@@ -579,23 +605,9 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
 
     // small models: a row's whole step in one workgroup
     if (decode && !d_sel && !d_nsel && n_sel == n && ss::row_step_plan(c.n_layers, d, F, V, n, ln.max_ctx, w->n_cu)) {
-        ss::RowStepArgs a{};
-        for (int l = 0; l < c.n_layers; ++l) {
-            const Layer& L = w->layers[l];
-            a.layer[l] = {L.wqkv.p, L.wo.p, L.wgu.p, L.wd.p, L.attn_norm, L.mlp_norm};
-        }
-        a.embed = w->embed;
-        a.final_norm = w->final_norm;
-        a.lm_head = w->lm_head.p;
-        a.kv = ws.kv.as<ss::kv_t>();
-        a.kv_layer_stride = ln.kv_layer_stride;
-        a.rope_cos = w->rope_cos;
-        a.rope_sin = w->rope_sin;
-        a.logits = ln.cur_logits ? ln.cur_logits : ws.logits.as<float>();
         const bool sample = ln.cur_inv_temp > 0.f;
+        ss::RowStepArgs a = row_step_args(w, ln);
         a.am = ln.cur_choose && !sample ? st.am : nullptr;
-        a.n_layers = c.n_layers; a.d = d; a.H = H; a.F = F; a.Fp = Fp; a.V = V;
-        a.eps = c.rms_eps;
         ss::launch_row_step(st, a, hd, n, s);
         if (ln.cur_choose && sample)
             ss::launch_sample(a.logits, V, st.d_n, st, ln.cur_draws, ln.cur_ids, ln.cur_seed, ln.cur_inv_temp, n_sel, s);
@@ -836,15 +848,28 @@ int decode_microbatch_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_
     if (!gen) {
         std::vector<int32_t> sorted_limit(limit);
         std::sort(sorted_limit.begin(), sorted_limit.end());
+        // small models: all steps of a row in one launch where every one of them would go that way
+        const ss_model_cfg& c = w->cfg;
+        const int n_first = compact ? (int)(sorted_limit.end() - std::upper_bound(sorted_limit.begin(), sorted_limit.end(), 1)) : B;
+        const bool at_once = steps > 1 && ss::row_step_plan(c.n_layers, c.d_model, c.d_ffn, c.vocab, n_first,
+                                                            ln.prompt_max_len + steps - 1, w->n_cu);
+        if (at_once) {
+            ss::RowStepArgs a = row_step_args(w, ln);
+            a.am = st.am;
+            a.steps = steps - 1;
+            a.compact = compact;
+            ss::launch_row_step(st, a, c.head_dim, n_first, s);
+        }
         for (int g = 1; g < steps; ++g) {
             // rows alive for forward g: all of them, or with compaction those that owe more than g tokens
             int n_live = B;
             if (compact)
                 n_live = (int)(sorted_limit.end() - std::upper_bound(sorted_limit.begin(), sorted_limit.end(), g));
+            row_steps += n_live;
+            if (at_once) continue;
             ln.max_ctx = ln.prompt_max_len + g;
             forward(w, ln, n_live, n_live, nullptr, nullptr, true, s);
             ss::launch_step_update(st, compact, eos_id, s);
-            row_steps += n_live;
         }
         forwards = steps;
     } else {

@@ -98,8 +98,9 @@ void launch_attention_decode(const MbState& st, const float* qkv_part, int kspli
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
                              f16_t* out_packed, int d, int H, int hd, int n_max, int plan_rows, int mb_rows,
                              int max_ctx, hipStream_t s);
-// A decode step of n_max rows (at most), one workgroup each, from the embedding to the logits of row j at logits + j * V and,
-// with am, their argmax (row_step_plan says when).
+// Decode steps of n_max rows (at most), one workgroup each, from the embedding to the logits of row j at logits + j * V and,
+// with am, their argmax (row_step_plan says when).  steps > 0: greedy rows with known ends; each takes that many steps on its own
+// tokens, or with `compact` those that it owes, and writes them out itself (the tables of live rows stay as they are).
 struct RowStepArgs {
     struct Layer {
         const f16_t *wqkv, *wo, *wgu, *wd;
@@ -113,6 +114,7 @@ struct RowStepArgs {
     float* logits;
     int32_t* am;
     int n_layers, d, H, F, Fp, V;
+    int steps, compact;
     float eps;
 };
 void launch_row_step(const MbState& st, const RowStepArgs& a, int hd, int n_max, hipStream_t s);

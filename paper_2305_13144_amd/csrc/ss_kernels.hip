@@ -1490,7 +1490,8 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
     constexpr int LPK = HD / 8, KPW = 64 / LPK, AU = 4;   // lanes per key, keys per wave load, loads in flight
     const int j = blockIdx.x;
     const int count = *st.d_n;
-    const int row = st.tr_row[j], pos = st.tr_pos[j], tok = st.tr_tok[j];
+    const int row = st.tr_row[j], step0 = *st.d_step;
+    int pos = st.tr_pos[j], tok = st.tr_tok[j];
     if (j >= count) return;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int d = a.d, H = a.H, dp = row_padded(d), fp = row_padded(a.Fp);
@@ -1526,8 +1527,6 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
         }
     }
     bf16_t gain = tid < d ? a.layer[0].attn_norm[tid] : 0;
-    if (tid < d) x[tid] = bf2f(a.embed[(size_t)tok * d + tid]);
-    if (tid < HD) cs[tid] = tid < HALF ? a.rope_cos[(size_t)pos * HALF + tid] : a.rope_sin[(size_t)pos * HALF + tid - HALF];
     for (int c = d + tid; c < dp; c += kRowThreads) hb[c] = 0;
     for (int c = a.F + tid; c < fp; c += kRowThreads) act[c] = 0;
     const int64_t so = st.row_so[row];
@@ -1536,11 +1535,17 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
     const bool owner = (lane & 15) < 4;
     // a head's earlier slots are shared out to P waves, and inside a wave to groups of LPK lanes
     const int P = kRowWaves / H, h = min(wave / P, H - 1), p = wave % P, sub = lane % LPK, kin = lane / LPK;
+    const int limit = a.steps > 0 ? st.row_limit[row] : 0;
     uint4 kr[AU], vr[AU];
-    float best = -3.4e38f;   // the head's largest logit and its column
-    int bi = 0x7fffffff;
-    row_meet();
+    float best;   // the head's largest logit and its column
+    int bi;
 
+    for (int step = 0;; ++step) {
+    if (tid < d) x[tid] = bf2f(a.embed[(size_t)tok * d + tid]);
+    if (tid < HD) cs[tid] = tid < HALF ? a.rope_cos[(size_t)pos * HALF + tid] : a.rope_sin[(size_t)pos * HALF + tid - HALF];
+    best = -3.4e38f;
+    bi = 0x7fffffff;
+    row_meet();
     for (int ph = 0; ph < phases; ++ph) {
         const int t = ph == phases - 1 ? 4 : ph & 3;
         kv_t* const kc = a.kv + (size_t)(ph >> 2) * 2 * a.kv_layer_stride + so * d;
@@ -1558,14 +1563,15 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
         }
         if ((t & 1) == 0) {   // normalised input
             row_norm(x, hb, d, a.eps, gain, lane);
-            if (tid < d && t < 4)
-                gain = (t == 0 ? a.layer[ph >> 2].mlp_norm : ph + 3 == phases ? a.final_norm : a.layer[(ph >> 2) + 1].attn_norm)[tid];
+            if (tid < d)
+                gain = (t == 0 ? a.layer[ph >> 2].mlp_norm : t == 4 ? a.layer[0].attn_norm : ph + 3 == phases ? a.final_norm :
+                        a.layer[(ph >> 2) + 1].attn_norm)[tid];
             row_meet();
         }
         // This wave's pairs of the matrix times the vector at xb.  A block is replaced by its successor, the first ones of
         // the next matrix at the end, as soon as it is used: one unbroken row of loads, every wait for the oldest only.
         {
-            const int KB = kblocks(ph), strips = strips_of(ph), pairs = (strips + 1) >> 1, after = min(ph + 1, phases - 1);
+            const int KB = kblocks(ph), strips = strips_of(ph), pairs = (strips + 1) >> 1, after = ph + 1 < phases ? ph + 1 : 0;
             const f16_t *W = weights(ph), *W2 = weights(after), *xb = t == 3 ? act : hb;
             const int KB2 = kblocks(after), strips2 = strips_of(after), first2 = min(wave, ((strips2 + 1) >> 1) - 1);
             f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
@@ -1600,7 +1606,7 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
                         const float z = i ? s1 : s0;
                         const int c = now * 32 + i * 16 + col;
                         if (c >= a.V) continue;   // an odd last strip
-                        if (owner) a.logits[(size_t)j * a.V + c] = z;
+                        if (owner && a.steps <= 0) a.logits[(size_t)j * a.V + c] = z;
                         if (z > best || (z == best && c < bi)) {   // lowest index on ties, as in k_argmax
                             best = z;
                             bi = c;
@@ -1731,10 +1737,23 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
     int* const si = (int*)(part + kRowWaves);
     if (lane == 0) { sb[wave] = best; si[wave] = bi; }
     row_meet();
-    if (tid == 0) {
-        for (int w = 1; w < kRowWaves; ++w)
-            if (sb[w] > best || (sb[w] == best && si[w] < bi)) { best = sb[w]; bi = si[w]; }
-        a.am[j] = (unsigned)bi < (unsigned)a.V ? bi : 0;
+    best = sb[0];
+    bi = si[0];
+#pragma unroll
+    for (int w = 1; w < kRowWaves; ++w)
+        if (sb[w] > best || (sb[w] == best && si[w] < bi)) { best = sb[w]; bi = si[w]; }
+    tok = (unsigned)bi < (unsigned)a.V ? bi : 0;
+    if (a.steps <= 0) {
+        if (tid == 0) a.am[j] = tok;
+        return;
+    }
+    const int s = step0 + step;   // the number of this token
+    if (tid == 0 && s < limit) st.out_tok[(size_t)row * st.max_new + s] = tok;
+    if (step + 1 >= a.steps || (a.compact && s + 1 >= limit)) return;   // the same for the whole workgroup
+    ++pos;
+    // the key and value that this step stored are read by other waves in the next
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
+    row_meet();
     }
 }
 

@@ -58,13 +58,18 @@ def test_logits(model, rows, longest):
 
 @pytest.mark.parametrize("flags", [0, ss.SS_COMPACT])
 def test_tokens_are_the_argmax_of_the_logits(model, flags):
-    """Greedy tokens against the argmax of the logits of the same forwards (a row's numbers do not depend on the others)."""
+    """Greedy tokens (known ends: all steps of a row in one launch) against the argmax of the logits of the same forwards,
+    one launch each; a row's numbers do not depend on the others.  Slots written by one step are read by the next, across what
+    a wave has in flight."""
     shape, gw, _ = model
     rng = np.random.default_rng(7)
     plens = rng.integers(2, 30, 12)
-    targets = rng.integers(2, 9, 12).astype(np.int32)
+    plens[:2] = (100, 1)
+    targets = rng.integers(1, 40, 12).astype(np.int32)
     prompts = [rng.integers(0, shape.vocab, p).astype(np.int32) for p in plens]
-    r = ss.ss_decode_microbatch(gw, np.concatenate(prompts), _offs(plens), 9, targets, flags)
+    r = ss.ss_decode_microbatch(gw, np.concatenate(prompts), _offs(plens), 40, targets, flags)
+    assert np.array_equal(r["lens"], targets)
+    assert all((r["tokens"][i, t:] == -1).all() for i, t in enumerate(targets))
     seqs = [np.concatenate([p, r["tokens"][i, :targets[i] - 1]]) for i, p in enumerate(prompts)]
     lg = ss.ss_forward_logits(gw, np.concatenate(seqs), _offs([len(q) for q in seqs]), plens.astype(np.int32))
     at = 0
