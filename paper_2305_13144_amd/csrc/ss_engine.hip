@@ -643,7 +643,7 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
         }
         if (decode) {   // one token-row per row: rotation and append are fused into the attention kernel
             ss::launch_attention_decode(st, pqkv, ks_qkv, st_qkv, kc, vc, w->rope_cos, w->rope_sin, ao, d, H, hd, n,
-                                        plan_rows, ln.prompt_rows, ln.max_ctx, s);
+                                        plan_rows, ln.prompt_rows, ln.max_ctx, qrot, s);
         } else {
             if (!whole_qkv)
                 ss::launch_rope_append(st, pqkv, ks_qkv, st_qkv, qrot, kc, vc, w->rope_cos, w->rope_sin, d, H, hd, n, s);

@@ -1023,11 +1023,12 @@ __global__ __launch_bounds__(256) void k_rope_append(MbState st, const float* __
 constexpr int kAttnUnroll = 8;
 
 // The slots are dealt to NW slices, one per wave, or NW / PW for each of PW waves: the sums are the same sums in the same order.
-template <int HD, int NW, int PW>
+// SPLIT: the slots are a share of the row's; their sums, maximum and total go to `share` (see k_attention_join).
+template <int HD, int NW, int PW, bool SPLIT>
 __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __restrict__ sc, float* __restrict__ red,
                                        float (*__restrict__ oacc)[HD], const kv_t* __restrict__ kbase,
                                        const kv_t* __restrict__ vbase, int ctx, f16_t* __restrict__ out, int out_r,
-                                       int out_k0, int out_kp)
+                                       int out_k0, int out_kp, float* __restrict__ share)
 {
     constexpr int LPK = HD / 8;       // lanes per key
     constexpr int KPW = 64 / LPK;     // keys per wave load
@@ -1136,7 +1137,15 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
             float t = 0.f;
 #pragma unroll
             for (int w = 0; w < NW; ++w) t += oacc[w][c];
+            if (SPLIT) share[c] = t;
             r[e] = f2h(t * inv);
+        }
+        if (SPLIT) {
+            if (tid == 0) {
+                share[HD] = mx;
+                share[HD + 1] = tot;
+            }
+            return;
         }
         const size_t at = pk_index(out_r, out_k0 + tid * 4, out_kp);
         *(uint2*)(out + at) = *(const uint2*)r;
@@ -1374,12 +1383,14 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
 // be resident with room to spare, 4 (128 slots) for larger batches, whose many workgroups already fill the chip, and 16
 // (512 slots) when the micro-batch has less than one workgroup per compute unit and a context exceeds 256 slots: what a
 // unit has in flight is then all that counts.
-template <int HD, int NW, int PW>
+// SPLIT: the workgroups of a pair along z share out its slots (few pairs, long contexts: see attention_split); the one that holds
+// the new slot appends it.
+template <int HD, int NW, int PW, bool SPLIT>
 __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const float* __restrict__ part, int ksplit,
                                                           size_t part_stride, kv_t* __restrict__ kc,
                                                           kv_t* __restrict__ vc, const float* __restrict__ rcos,
                                                           const float* __restrict__ rsin, f16_t* __restrict__ out,
-                                                          int d)
+                                                          int d, float* __restrict__ shares)
 {
     __shared__ float sc[kMaxPos];
     __shared__ float red[PW + NW];
@@ -1394,7 +1405,19 @@ __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const 
     if (j >= count) return;
     const size_t base = (size_t)st.row_so[row] * d + (size_t)h * st.row_cap[row] * HD;
     const int which = threadIdx.x / HALF, e = threadIdx.x % HALF;   // 0 q, 1 k, 2 v
-    if (which < 3) {
+    int begin = 0, slots = pos + 1;
+    float* share = nullptr;
+    if (SPLIT) {
+        const int S = gridDim.z, per = ((pos + S) / S + 63) & ~63;
+        begin = blockIdx.z * per;
+        slots = min(pos + 1 - begin, per);
+        share = shares + (((size_t)j * gridDim.y + h) * S + blockIdx.z) * (HD + 2);
+        if (slots <= 0) {   // a shorter row than the micro-batch's longest
+            if (threadIdx.x < HD + 2) share[threadIdx.x] = threadIdx.x == HD ? -3.0e38f : 0.f;
+            return;
+        }
+    }
+    if (which < 3 && (!SPLIT || which == 0 || begin + slots == pos + 1)) {
         const float* p = part + (size_t)j * 3 * d + (size_t)which * d + h * HD + qkv_col(e);
         float pa[kNormMaxSplit], pb[kNormMaxSplit];   // every k-slice load issued before the first add
 #pragma unroll
@@ -1424,7 +1447,41 @@ __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const 
         }
     }
     __syncthreads();   // the new key/value slot and q are visible to the whole workgroup
-    attend<HD, NW, PW>(qs, sc, red, oacc, kc + base, vc + base, pos + 1, out, j, h * HD, d);
+    attend<HD, NW, PW, SPLIT>(qs, sc, red, oacc, kc + base + (size_t)begin * HD, vc + base + (size_t)begin * HD, slots, out, j, h * HD, d,
+                              share);
+}
+
+// The shares of a pair's slots put together: one wave per pair, two elements a lane (HD 64: half the lanes).
+template <int HD>
+__global__ __launch_bounds__(64) void k_attention_join(MbState st, const float* __restrict__ shares, int S, f16_t* __restrict__ out, int d)
+{
+    const int j = blockIdx.x, h = blockIdx.y, e = threadIdx.x * 2;
+    const int count = *st.d_n;
+    if (e >= HD) return;
+    const float* p = shares + ((size_t)j * gridDim.y + h) * S * (HD + 2);
+    float2 o[kAttnMaxSplit];
+    float m[kAttnMaxSplit], t[kAttnMaxSplit], top = -3.0e38f;
+#pragma unroll
+    for (int s = 0; s < kAttnMaxSplit; ++s) {   // all loads on their way together; beyond S the last one again, without weight
+        const float* q = p + (size_t)min(s, S - 1) * (HD + 2);
+        o[s] = *(const float2*)(q + e);
+        m[s] = q[HD];
+        t[s] = q[HD + 1];
+    }
+    if (j >= count) return;
+#pragma unroll
+    for (int s = 0; s < kAttnMaxSplit; ++s) top = fmaxf(top, m[s]);
+    float all = 0.f, o0 = 0.f, o1 = 0.f;
+#pragma unroll
+    for (int s = 0; s < kAttnMaxSplit; ++s) {
+        const float f = s < S ? __expf(m[s] - top) : 0.f;   // an empty share: its total and sums are 0
+        all += f * t[s];
+        o0 += f * o[s].x;
+        o1 += f * o[s].y;
+    }
+    const float inv = 1.f / all;
+    const f16_t r[2] = {f2h(o0 * inv), f2h(o1 * inv)};
+    *(uint32_t*)(out + pk_index(j, h * HD + e, d)) = *(const uint32_t*)r;
 }
 
 // ------------------------------------------------------------------------------------------ a row's whole decode step
@@ -2175,19 +2232,20 @@ void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, si
                        vcache, rope_cos, rope_sin, d, H, hd);
 }
 
-template <int HD, int NW, int PW = NW>
+template <int HD, int NW, int PW = NW, bool SPLIT = false>
 static void launch_attention_decode_inst(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                                          kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
-                                         f16_t* out_packed, int d, int H, int n_max, hipStream_t s)
+                                         f16_t* out_packed, int d, int H, int n_max, float* shares, int S, hipStream_t s)
 {
-    hipLaunchKernelGGL((k_attention_decode<HD, NW, PW>), dim3(n_max, H), dim3(64 * PW), 0, s, st, qkv_part, ksplit, part_stride,
-                       kcache, vcache, rope_cos, rope_sin, out_packed, d);
+    hipLaunchKernelGGL((k_attention_decode<HD, NW, PW, SPLIT>), dim3(n_max, H, S), dim3(64 * PW), 0, s, st, qkv_part, ksplit, part_stride,
+                       kcache, vcache, rope_cos, rope_sin, out_packed, d, shares);
+    if (SPLIT) hipLaunchKernelGGL((k_attention_join<HD>), dim3(n_max, H), dim3(64), 0, s, st, shares, S, out_packed, d);
 }
 
 void launch_attention_decode(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
                              f16_t* out_packed, int d, int H, int hd, int n_max, int plan_rows, int mb_rows, int max_ctx,
-                             hipStream_t s)
+                             float* scratch, hipStream_t s)
 {
     // measured at the 7B shape: 8 waves win at 16 rows (512 workgroups: 14.1 against 14.9 us per layer at context
     // 200), 4 waves win at 64 rows (2048 workgroups: 25.7 against 36.1 us at context 100)
@@ -2198,14 +2256,17 @@ void launch_attention_decode(const MbState& st, const float* qkv_part, int kspli
     const bool wide = attention_wide(plan_rows, mb_rows, H);
     const bool many = wide && n_max * H > kAttnWideMaxGroups;   // several micro-batches together: 8 slices, but 4 waves
     const bool widest = attention_may_widen(mb_rows, H, max_ctx, hd);
-#define SS_ATTN_ARGS st, qkv_part, ksplit, part_stride, kcache, vcache, rope_cos, rope_sin, out_packed, d, H, n_max, s
+    const int S = attention_split(mb_rows, H, max_ctx);
+#define SS_ATTN_ARGS st, qkv_part, ksplit, part_stride, kcache, vcache, rope_cos, rope_sin, out_packed, d, H, n_max, scratch, S, s
     if (hd == 128) {
-        if (widest) launch_attention_decode_inst<128, 16>(SS_ATTN_ARGS);
+        if (S > 1) launch_attention_decode_inst<128, 8, 8, true>(SS_ATTN_ARGS);
+        else if (widest) launch_attention_decode_inst<128, 16>(SS_ATTN_ARGS);
         else if (many) launch_attention_decode_inst<128, 8, 4>(SS_ATTN_ARGS);
         else if (wide) launch_attention_decode_inst<128, 8>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<128, 4>(SS_ATTN_ARGS);
     } else {
-        if (widest) launch_attention_decode_inst<64, 16>(SS_ATTN_ARGS);
+        if (S > 1) launch_attention_decode_inst<64, 8, 8, true>(SS_ATTN_ARGS);
+        else if (widest) launch_attention_decode_inst<64, 16>(SS_ATTN_ARGS);
         else if (many) launch_attention_decode_inst<64, 8, 4>(SS_ATTN_ARGS);
         else if (wide) launch_attention_decode_inst<64, 8>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<64, 4>(SS_ATTN_ARGS);

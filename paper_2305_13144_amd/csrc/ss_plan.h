@@ -70,6 +70,10 @@ constexpr bool attention_may_widen(int mb_rows, int H, int max_ctx, int hd)
     return mb_rows * H <= kAttnWidestMaxGroups && max_ctx > 64 * (512 / hd);
 }
 
+// Workgroups that share out the slots of one pair (1: no split), up to kAttnMaxSplit, at least kAttnSplitSlots slots each.
+constexpr int kAttnMaxSplit = 16, kAttnSplitSlots = 256, kAttnSplitFrom = 1024, kAttnSplitMaxGroups = 96;
+int attention_split(int mb_rows, int H, int max_ctx);
+
 // ... and 8 waves each (else 4), by whole strips of live rows, or the rows of a smaller micro-batch: a row's numbers are not to
 // depend on who else is still alive.
 constexpr int kAttnWideMaxGroups = 512;

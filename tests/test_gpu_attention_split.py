@@ -1,0 +1,57 @@
+"""Decode attention whose slots several workgroups share out (few pairs, long contexts): contexts around its beginning and around
+whole shares, short rows beside a long one (shares without a slot), both head sizes, against the oracle; and a row's numbers while
+the others leave."""
+import numpy as np
+import pytest
+
+from oracle.model_oracle import OracleModel
+from paper_2305_13144_amd import binding as ss
+from paper_2305_13144_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = {
+    "hd64": synth.ModelShape("split64", 1, 512, 8, 64, 256, 272),
+    "hd128": synth.ModelShape("split128", 1, 512, 4, 128, 256, 272),
+}
+TOL = 4e-3   # as for decode attention in general: one layer, 11-bit inputs, slots and scores with a spread of some units
+
+
+@pytest.fixture(scope="module", params=sorted(SHAPES))
+def model(request, oracle_built):
+    shape = SHAPES[request.param]
+    W = synth.make_weights(shape, seed=34, std=0.08, norm_jitter=0.1, threads=1)
+    gw = ss.Weights(shape, W)
+    ss.ss_set_gemm_mode(1)   # small models would go through k_row_step
+    yield shape, gw, OracleModel(shape, W, "f32")
+    ss.ss_set_gemm_mode(0)
+    gw.close()
+
+
+def _forced(gw, seqs, plens):
+    offs = np.concatenate([[0], np.cumsum([len(q) for q in seqs])]).astype(np.int32)
+    return ss.ss_forward_logits(gw, np.concatenate(seqs), offs, np.array(plens, np.int32))
+
+
+@pytest.mark.parametrize("plens", [[1022], [1087, 3], [1535, 64, 1, 700], [4000, 2, 255, 256, 257, 1025, 320, 63, 2049, 17, 1, 640]],
+                         ids=lambda v: "x".join(map(str, v)))
+def test_logits(model, plens):
+    shape, gw, om = model
+    rng = np.random.default_rng(sum(plens))
+    steps = 4
+    seqs = [rng.integers(0, shape.vocab, p + steps).astype(np.int32) for p in plens]
+    got = _forced(gw, seqs, plens)
+    for i in range(min(len(plens), 5)):
+        ref = om.teacher_forced(seqs[i], first=plens[i] - 1)
+        err = np.abs(got[i * (steps + 1):(i + 1) * (steps + 1)] - ref).max() / np.abs(ref).max()
+        assert err <= TOL, (plens, i, err)
+
+
+def test_rows_that_leave_do_not_change_the_others(model):
+    shape, gw, _ = model
+    rng = np.random.default_rng(3)
+    plens, steps = [1300, 40, 900, 1100], 6
+    seqs = [rng.integers(0, shape.vocab, p + steps).astype(np.int32) for p in plens]
+    whole = _forced(gw, seqs, plens)
+    cut = _forced(gw, [seqs[0]] + [q[:len(q) - 4] for q in seqs[1:]], plens)
+    assert np.array_equal(whole[:steps + 1], cut[:steps + 1])
