@@ -1042,7 +1042,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
 
     float mx = -3.0e38f;
 #pragma unroll
-    for (int v = wave; v < NW; v += PW)
+    for (int i = 0, v = wave; i < NW / PW; ++i, v += PW)
     for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
         uint4 raw[AU];
 #pragma unroll
@@ -1081,7 +1081,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
 #pragma unroll
     for (int w = 1; w < PW; ++w) mx = fmaxf(mx, red[w]);
 #pragma unroll
-    for (int v = wave; v < NW; v += PW) {
+    for (int i = 0, v = wave; i < NW / PW; ++i, v += PW) {
         float sum = 0.f;
         for (int s = v * 64 + lane; s < ctx; s += 64 * NW) {
             const float p = __expf(sc[s] - mx);
@@ -1098,7 +1098,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     const float inv = 1.f / tot;
 
 #pragma unroll
-    for (int v = wave; v < NW; v += PW) {
+    for (int i = 0, v = wave; i < NW / PW; ++i, v += PW) {
     float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
         uint4 raw[AU];
