@@ -483,7 +483,8 @@ def main() -> int:
     ms_s = ss.ss_bench_decode_step(gw, ptoks, B0, ctx, a.step_iters + 3)[3:]
     sbytes, sbytes2 = decode_step_bytes(shape, B0, ctx, wbytes), decode_step_bytes(shape, B0, ctx)
     ach = sbytes / (ms_s.mean() * 1e-3) / 1e9
-    # several such steps at once, one per lane, as a group pass runs its micro-batches: each streams the whole model
+    # several such steps at once, one per lane, as a group pass runs micro-batches that share no forwards (larger ones,
+    # smaller models, sampled passes): each streams the whole model
     # (not under --roofline-only: the profiles taken from that command keep every kernel's launches undisturbed)
     two = None
     if not a.roofline_only and a.in_flight > 1:
@@ -493,8 +494,8 @@ def main() -> int:
             ach_l = lanes * sbytes / (ms_l.mean() * 1e-3) / 1e9
             per_lanes[lanes] = dict(ms=float(ms_l.mean()), achieved=ach_l, frac=ach_l / HBM_PEAK_GBS,
                                     frac_at_2_bytes_per_weight=ach_l / HBM_PEAK_GBS * sbytes2 / sbytes)
-        two = dict(what=f"{a.in_flight} such steps running at the same time on {a.in_flight} streams (as many micro-batches of a "
-                        "group pass): bytes of all / the time one of them takes then",
+        two = dict(what=f"{a.in_flight} such steps running at the same time on {a.in_flight} streams (micro-batches "
+                        "of a group pass that share no forwards): bytes of all / the time one of them takes then",
                    lanes=a.in_flight, unit="GB/s", **per_lanes[a.in_flight],
                    **({"with_two_lanes": per_lanes[2]} if a.in_flight != 2 else {}))
     step_launches = launches + 3 * shape.n_layers + 3     # + attention and two norms per layer, embedding, final norm, token choice

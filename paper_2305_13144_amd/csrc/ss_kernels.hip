@@ -759,11 +759,13 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
 // requested ST - 1 trips before it is read.  One trip: wait until the next stage has landed, barrier, then, spread over
 // the matrix instructions of this trip, the copies of the stage ST ahead into the slot that the barrier has just freed
 // and the LDS reads of the next trip's operands.
-// What bounds it: with nothing to copy the same loop reaches 1.54 PFLOP/s on a full chip (the clock under matrix load),
-// with the copies 1.28; LDS reads and the order of the tiles change nothing any more.  Measured against the kernel it
-// replaced (weights straight from L2 to registers, 64 or 128 rows per tile), gate|up at the 7B width: 256 rows
-// 73.7 -> 56.3 us, 494 123 -> 81, 995 216 -> 166, 3146 544 -> 488, 12311 1989 -> 1743 (1.27 PFLOP/s); down 494 67 -> 49,
-// 995 98 -> 87, 4200 504 -> 351.
+// What bounds it: the power the chip may take.  On random data the matrix instructions alone run at 2.0 PFLOP/s (the clock
+// falls to 2.06 GHz), with the LDS reads beside them at 1.68, with the copies too at 1.33 to 1.38.  A trip (256 x 256 x 32)
+// takes 1131 clocks (1249 before the reads were given out between the products and the copies' addresses cut to one
+// addition), 1024 of them matrix work: with the order of the tiles, gate|up of 7B at 12311 rows takes 1603 us instead of 1743
+// (1.38 PFLOP/s).  Measured against the kernel it replaced (weights straight from L2 to registers, 64 or 128 rows per tile)
+// before that, gate|up: 256 rows 73.7 -> 56.3 us, 494 123 -> 81, 995 216 -> 166, 3146 544 -> 488, 12311 1989 -> 1743; down
+// 494 67 -> 49, 995 98 -> 87, 4200 504 -> 351.
 // The copies are written in assembly because the compiler would wait for all of them before every LDS read: it counts
 // only its own loads, and the waits here are written out.  They name no output register; waits that the compiler adds
 // for loads of its own can only be too strict.
@@ -1043,30 +1045,30 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     float mx = -3.0e38f;
 #pragma unroll
     for (int i = 0, v = wave; i < NW / PW; ++i, v += PW)
-    for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
-        uint4 raw[AU];
+        for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
+            uint4 raw[AU];
 #pragma unroll
-        for (int u = 0; u < AU; ++u) {
-            const int s = c0 + u * NW * KPW + kin;
-            raw[u] = s < ctx ? *(const uint4*)(kbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
-        }
+            for (int u = 0; u < AU; ++u) {
+                const int s = c0 + u * NW * KPW + kin;
+                raw[u] = s < ctx ? *(const uint4*)(kbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
+            }
 #pragma unroll
-        for (int u = 0; u < AU; ++u) {
-            if (c0 + u * NW * KPW >= ctx) break;   // wave-uniform: nothing of this load is inside the context
-            const int s = c0 + u * NW * KPW + kin;
-            const kv_t* kv = (const kv_t*)&raw[u];
-            float part = 0.f;
+            for (int u = 0; u < AU; ++u) {
+                if (c0 + u * NW * KPW >= ctx) break;   // wave-uniform: nothing of this load is inside the context
+                const int s = c0 + u * NW * KPW + kin;
+                const kv_t* kv = (const kv_t*)&raw[u];
+                float part = 0.f;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) part += q[e] * kv2f(kv[e]);
+                for (int e = 0; e < 8; ++e) part += q[e] * kv2f(kv[e]);
 #pragma unroll
-            for (int m = 1; m < LPK; m <<= 1) part += __shfl_xor(part, m, 64);
-            part *= scale;
-            if (s < ctx) {
-                if (sub == 0) sc[s] = part;
-                mx = fmaxf(mx, part);
+                for (int m = 1; m < LPK; m <<= 1) part += __shfl_xor(part, m, 64);
+                part *= scale;
+                if (s < ctx) {
+                    if (sub == 0) sc[s] = part;
+                    mx = fmaxf(mx, part);
+                }
             }
         }
-    }
     // the first chunk of V does not depend on the scores: get it moving before the reductions
     uint4 vraw[AU];
 #pragma unroll
@@ -1099,34 +1101,34 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
 
 #pragma unroll
     for (int i = 0, v = wave; i < NW / PW; ++i, v += PW) {
-    float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
-        uint4 raw[AU];
+        float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
+            uint4 raw[AU];
 #pragma unroll
-        for (int u = 0; u < AU; ++u) {
-            const int s = c0 + u * NW * KPW + kin;
-            if (c0 == wave * KPW)
-                raw[u] = vraw[u];
-            else
-                raw[u] = s < ctx ? *(const uint4*)(vbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
+            for (int u = 0; u < AU; ++u) {
+                const int s = c0 + u * NW * KPW + kin;
+                if (c0 == wave * KPW)
+                    raw[u] = vraw[u];
+                else
+                    raw[u] = s < ctx ? *(const uint4*)(vbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
+            }
+#pragma unroll
+            for (int u = 0; u < AU; ++u) {
+                if (c0 + u * NW * KPW >= ctx) break;
+                const int s = c0 + u * NW * KPW + kin;
+                const float p = s < ctx ? sc[s] : 0.f;
+                const kv_t* vv = (const kv_t*)&raw[u];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) o[e] += p * kv2f(vv[e]);
+            }
         }
 #pragma unroll
-        for (int u = 0; u < AU; ++u) {
-            if (c0 + u * NW * KPW >= ctx) break;
-            const int s = c0 + u * NW * KPW + kin;
-            const float p = s < ctx ? sc[s] : 0.f;
-            const kv_t* vv = (const kv_t*)&raw[u];
+        for (int m = LPK; m < 64; m <<= 1)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] += p * kv2f(vv[e]);
-        }
-    }
+            for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], m, 64);
+        if (kin == 0)
 #pragma unroll
-    for (int m = LPK; m < 64; m <<= 1)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) o[e] += __shfl_xor(o[e], m, 64);
-    if (kin == 0)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) oacc[v][sub * 8 + e] = o[e];
+            for (int e = 0; e < 8; ++e) oacc[v][sub * 8 + e] = o[e];
     }
     __syncthreads();
     if (tid < HD / 4) {
@@ -1493,6 +1495,8 @@ __global__ __launch_bounds__(64) void k_attention_join(MbState st, const float* 
 // layers.  So the loads go on over the barriers: there is one loop for all matrices, and the block that a wave has used
 // last is replaced by the first one it needs of the next matrix.  (A loop per matrix is 5000 instructions, spills, and waits
 // for everything at each end: 58 us.)  Tiny model, 16 rows, context 20: 63 us as 19 launches -> 48; 250 rows 103 -> 58.
+// With a.steps a launch takes its rows to their ends (their limits are known and nothing is compacted or polled): group of 16,
+// 47 forwards, 2.83 -> 2.50 ms, the weights' first blocks wait in registers when a step begins.
 // A wave owns pairs of output strips (the two halves of a head's strip, gate and up; two sums under way at once); the
 // matrix instruction's activation operand is the row's vector for all of its 16 columns, so that every lane ends up with
 // valid sums.  Rounding as in the other kernels: residual stream, sums, rotation and softmax in fp32; projection inputs,
@@ -1598,219 +1602,222 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
     int bi;
 
     for (int step = 0;; ++step) {
-    if (tid < d) x[tid] = bf2f(a.embed[(size_t)tok * d + tid]);
-    if (tid < HD) cs[tid] = tid < HALF ? a.rope_cos[(size_t)pos * HALF + tid] : a.rope_sin[(size_t)pos * HALF + tid - HALF];
-    best = -3.4e38f;
-    bi = 0x7fffffff;
-    row_meet();
-    for (int ph = 0; ph < phases; ++ph) {
-        const int t = ph == phases - 1 ? 4 : ph & 3;
-        kv_t* const kc = a.kv + (size_t)(ph >> 2) * 2 * a.kv_layer_stride + so * d;
-        kv_t* const vc = kc + a.kv_layer_stride;
-        const kv_t *kb = kc + (size_t)h * cap * HD + sub * 8, *vb = vc + (size_t)h * cap * HD + sub * 8;
-        // the first slots of a layer are asked for before anything that they do not depend on
-        auto slot = [&](int c0, int u) { return c0 + u * P * KPW + kin; };
-        auto load_slots = [&](uint4 (&r)[AU], const kv_t* from, int c0) {
+        if (tid < d) x[tid] = bf2f(a.embed[(size_t)tok * d + tid]);
+        if (tid < HD) cs[tid] = tid < HALF ? a.rope_cos[(size_t)pos * HALF + tid] : a.rope_sin[(size_t)pos * HALF + tid - HALF];
+        best = -3.4e38f;
+        bi = 0x7fffffff;
+        row_meet();
+        for (int ph = 0; ph < phases; ++ph) {
+            const int t = ph == phases - 1 ? 4 : ph & 3;
+            kv_t* const kc = a.kv + (size_t)(ph >> 2) * 2 * a.kv_layer_stride + so * d;
+            kv_t* const vc = kc + a.kv_layer_stride;
+            const kv_t *kb = kc + (size_t)h * cap * HD + sub * 8, *vb = vc + (size_t)h * cap * HD + sub * 8;
+            // the first slots of a layer are asked for before anything that they do not depend on
+            auto slot = [&](int c0, int u) { return c0 + u * P * KPW + kin; };
+            auto load_slots = [&](uint4 (&r)[AU], const kv_t* from, int c0) {
 #pragma unroll
-            for (int u = 0; u < AU; ++u) r[u] = *(const uint4*)(from + (size_t)min(slot(c0, u), pos - 1) * HD);
-        };
-        if (t == 0) {
-            load_slots(kr, kb, p * KPW);
-            load_slots(vr, vb, p * KPW);
-        }
-        if ((t & 1) == 0) {   // normalised input
-            row_norm(x, hb, d, a.eps, gain, lane);
-            if (tid < d)
-                gain = (t == 0 ? a.layer[ph >> 2].mlp_norm : t == 4 ? a.layer[0].attn_norm : ph + 3 == phases ? a.final_norm :
-                        a.layer[(ph >> 2) + 1].attn_norm)[tid];
+                for (int u = 0; u < AU; ++u) r[u] = *(const uint4*)(from + (size_t)min(slot(c0, u), pos - 1) * HD);
+            };
+            if (t == 0) {
+                load_slots(kr, kb, p * KPW);
+                load_slots(vr, vb, p * KPW);
+            }
+            if ((t & 1) == 0) {   // normalised input
+                row_norm(x, hb, d, a.eps, gain, lane);
+                if (tid < d)
+                    gain = (t == 0 ? a.layer[ph >> 2].mlp_norm : t == 4 ? a.layer[0].attn_norm :
+                            ph + 3 == phases ? a.final_norm :
+                            a.layer[(ph >> 2) + 1].attn_norm)[tid];
+                row_meet();
+            }
+            // This wave's pairs of the matrix times the vector at xb.  A block is replaced by its successor, the first ones of
+            // the next matrix at the end, as soon as it is used: one unbroken row of loads, every wait for the oldest only.
+            {
+                const int KB = kblocks(ph), strips = strips_of(ph), pairs = (strips + 1) >> 1;
+                const int after = ph + 1 < phases ? ph + 1 : 0;
+                const f16_t *W = weights(ph), *W2 = weights(after), *xb = t == 3 ? act : hb;
+                const int KB2 = kblocks(after), strips2 = strips_of(after), first2 = min(wave, ((strips2 + 1) >> 1) - 1);
+                f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
+                int pair = wave, g = 0;
+                do {   // a wave without a pair holds the last one's first group, and drops it
+                    f16x8 b[kRowGroup];
+#pragma unroll
+                    for (int z = 0; z < kRowGroup; ++z)
+                        b[z] = *(const f16x8*)(xb + (g * kRowGroup + z) * 32 + (lane >> 4) * 8);
+                    const int now = pair;
+                    const bool whole = KB - g * kRowGroup <= kRowGroup;
+                    pair += whole ? kRowWaves : 0;
+                    g = whole ? 0 : g + 1;
+                    const bool more = pair < pairs;
+                    const RowGroup n(more ? W : W2, more ? KB : KB2, more ? strips : strips2, more ? pair : first2, g);
+                    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                    for (int z = 0; z < kRowGroup; ++z) {
+                        a0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, v[0][z]), b[z], a0, 0, 0, 0);
+                        a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, v[1][z]), b[z], a1, 0, 0, 0);
+                        v[0][z] = n.load(0, z);
+                        v[1][z] = n.load(1, z);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    if (!whole) continue;
+                    float s0 = pick4(a0, sel), s1 = pick4(a1, sel);   // column `col` of either strip
+                    a0 = a1 = (f32x4){0.f, 0.f, 0.f, 0.f};
+                    if (now >= pairs) continue;
+                    if (t == 4) {
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            const float z = i ? s1 : s0;
+                            const int c = now * 32 + i * 16 + col;
+                            if (c >= a.V) continue;   // an odd last strip
+                            if (owner && a.steps <= 0) a.logits[(size_t)j * a.V + c] = z;
+                            if (z > best || (z == best && c < bi)) {   // lowest index on ties, as in k_argmax
+                                best = z;
+                                bi = c;
+                            }
+                        }
+                    } else if (owner) {
+                        if (t == 2) {
+                            act[now * 16 + col] = f2h(silu_f(s0) * s1);
+                        } else if (t != 0) {
+                            x[now * 32 + col] += s0;
+                            x[now * 32 + 16 + col] += s1;
+                        } else {   // elements e and e + HD/2 of a head (see qkv_strip)
+                            const int which = now / (d >> 5), r = now - which * (d >> 5), e = r / PH * HD + r % PH * 16 + col;
+                            if (which < 2) {
+                                const float c = cs[e % HD], s = cs[HALF + e % HD], r0 = s0 * c - s1 * s, r1 = s0 * s + s1 * c;
+                                s0 = r0;
+                                s1 = r1;
+                            }
+                            if (which == 0) {
+                                q[e] = s0;
+                                q[e + HALF] = s1;
+                            } else {
+                                kv_t* n1 = (which == 1 ? kn : vn) + e;
+                                n1[0] = f2kv(s0);
+                                n1[HALF] = f2kv(s1);
+                            }
+                        }
+                    }
+                } while (pair < pairs || g != 0);
+            }
+            row_meet();
+            if (t != 0) continue;
+            // Attention: every wave keeps a softmax of its own; the slots before this one come from the cache, this one
+            // from LDS.
+            if (tid < d) {
+                const size_t at = ((size_t)(tid / HD) * cap + pos) * HD + tid % HD;
+                kc[at] = kn[tid];
+                vc[at] = vn[tid];
+            }
+            if (wave < H * P) {
+                const float scale = rsqrtf((float)HD);
+                float qf[8], m = -3.0e38f, tot = 0.f, acc[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    qf[e] = q[h * HD + sub * 8 + e];
+                    acc[e] = 0.f;
+                }
+                auto score = [&](const uint4& raw) {
+                    const kv_t* k = (const kv_t*)&raw;
+                    float s = 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) s += qf[e] * kv2f(k[e]);
+                    return group_sum<LPK>(s) * scale;
+                };
+                auto add = [&](float w, const uint4& raw) {
+                    const kv_t* u = (const kv_t*)&raw;
+                    tot += w;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[e] += w * kv2f(u[e]);
+                };
+                auto largest = [](float z) {   // of the wave's groups
+                    if (LPK == 8) z = fmaxf(z, dpp<kDppRotate8>(z));
+                    z = fmaxf(z, __shfl_xor(z, 16, 64));
+                    return fmaxf(z, __shfl_xor(z, 32, 64));
+                };
+                if (p == 0) {   // this slot: the same in every group, counted in the first
+                    m = score(*(const uint4*)(kn + h * HD + sub * 8));
+                    add(kin == 0 ? 1.f : 0.f, *(const uint4*)(vn + h * HD + sub * 8));
+                }
+                for (int c0 = p * KPW; c0 < pos; c0 += P * KPW * AU) {   // wave-uniform
+                    const int c1 = c0 + P * KPW * AU;
+                    float s[AU], top = m;
+#pragma unroll
+                    for (int u = 0; u < AU; ++u) {
+                        s[u] = slot(c0, u) < pos ? score(kr[u]) : -3.0e38f;
+                        top = fmaxf(top, s[u]);
+                    }
+                    if (c1 < pos) load_slots(kr, kb, c1);
+                    top = largest(top);
+                    const float keep = __expf(m - top);
+                    m = top;
+                    tot *= keep;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[e] *= keep;
+#pragma unroll
+                    for (int u = 0; u < AU; ++u) add(slot(c0, u) < pos ? __expf(s[u] - m) : 0.f, vr[u]);
+                    if (c1 < pos) load_slots(vr, vb, c1);
+                }
+                auto over_groups = [](float z) {
+                    if (LPK == 8) z += dpp<kDppRotate8>(z);
+                    z += __shfl_xor(z, 16, 64);
+                    return z + __shfl_xor(z, 32, 64);
+                };
+                tot = over_groups(tot);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] = over_groups(acc[e]);
+                float* w = part + wave * (HD + 4);
+                if (kin == 0) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) w[sub * 8 + e] = acc[e];
+                    if (sub == 0) {
+                        w[HD] = m;
+                        w[HD + 1] = tot;
+                    }
+                }
+            }
+            row_meet();
+            if (tid < d) {
+                const float* w = part + tid / HD * P * (HD + 4);
+                float m = -3.0e38f, tot = 0.f, sum = 0.f;
+                for (int z = 0; z < P; ++z) m = fmaxf(m, w[z * (HD + 4) + HD]);
+                for (int z = 0; z < P; ++z) {
+                    const float f = __expf(w[z * (HD + 4) + HD] - m);
+                    tot += f * w[z * (HD + 4) + HD + 1];
+                    sum += f * w[z * (HD + 4) + tid % HD];
+                }
+                hb[tid] = f2h(sum / tot);
+            }
             row_meet();
         }
-        // This wave's pairs of the matrix times the vector at xb.  A block is replaced by its successor, the first ones of
-        // the next matrix at the end, as soon as it is used: one unbroken row of loads, every wait for the oldest only.
-        {
-            const int KB = kblocks(ph), strips = strips_of(ph), pairs = (strips + 1) >> 1, after = ph + 1 < phases ? ph + 1 : 0;
-            const f16_t *W = weights(ph), *W2 = weights(after), *xb = t == 3 ? act : hb;
-            const int KB2 = kblocks(after), strips2 = strips_of(after), first2 = min(wave, ((strips2 + 1) >> 1) - 1);
-            f32x4 a0 = {0.f, 0.f, 0.f, 0.f}, a1 = a0;
-            int pair = wave, g = 0;
-            do {   // a wave without a pair holds the last one's first group, and drops it
-                f16x8 b[kRowGroup];
+        if (!a.am) return;
 #pragma unroll
-                for (int z = 0; z < kRowGroup; ++z)
-                    b[z] = *(const f16x8*)(xb + (g * kRowGroup + z) * 32 + (lane >> 4) * 8);
-                const int now = pair;
-                const bool whole = KB - g * kRowGroup <= kRowGroup;
-                pair += whole ? kRowWaves : 0;
-                g = whole ? 0 : g + 1;
-                const bool more = pair < pairs;
-                const RowGroup n(more ? W : W2, more ? KB : KB2, more ? strips : strips2, more ? pair : first2, g);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int z = 0; z < kRowGroup; ++z) {
-                    a0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, v[0][z]), b[z], a0, 0, 0, 0);
-                    a1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, v[1][z]), b[z], a1, 0, 0, 0);
-                    v[0][z] = n.load(0, z);
-                    v[1][z] = n.load(1, z);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-                if (!whole) continue;
-                float s0 = pick4(a0, sel), s1 = pick4(a1, sel);   // column `col` of either strip
-                a0 = a1 = (f32x4){0.f, 0.f, 0.f, 0.f};
-                if (now >= pairs) continue;
-                if (t == 4) {
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const float z = i ? s1 : s0;
-                        const int c = now * 32 + i * 16 + col;
-                        if (c >= a.V) continue;   // an odd last strip
-                        if (owner && a.steps <= 0) a.logits[(size_t)j * a.V + c] = z;
-                        if (z > best || (z == best && c < bi)) {   // lowest index on ties, as in k_argmax
-                            best = z;
-                            bi = c;
-                        }
-                    }
-                } else if (owner) {
-                    if (t == 2) {
-                        act[now * 16 + col] = f2h(silu_f(s0) * s1);
-                    } else if (t != 0) {
-                        x[now * 32 + col] += s0;
-                        x[now * 32 + 16 + col] += s1;
-                    } else {   // elements e and e + HD/2 of a head (see qkv_strip)
-                        const int which = now / (d >> 5), r = now - which * (d >> 5), e = r / PH * HD + r % PH * 16 + col;
-                        if (which < 2) {
-                            const float c = cs[e % HD], s = cs[HALF + e % HD], r0 = s0 * c - s1 * s, r1 = s0 * s + s1 * c;
-                            s0 = r0;
-                            s1 = r1;
-                        }
-                        if (which == 0) {
-                            q[e] = s0;
-                            q[e + HALF] = s1;
-                        } else {
-                            kv_t* n1 = (which == 1 ? kn : vn) + e;
-                            n1[0] = f2kv(s0);
-                            n1[HALF] = f2kv(s1);
-                        }
-                    }
-                }
-            } while (pair < pairs || g != 0);
+        for (int m = 32; m >= 1; m >>= 1) {
+            const float ob = __shfl_xor(best, m, 64);
+            const int oi = __shfl_xor(bi, m, 64);
+            if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
         }
+        float* const sb = part;
+        int* const si = (int*)(part + kRowWaves);
+        if (lane == 0) { sb[wave] = best; si[wave] = bi; }
         row_meet();
-        if (t != 0) continue;
-        // Attention: every wave keeps a softmax of its own; the slots before this one come from the cache, this one from LDS.
-        if (tid < d) {
-            const size_t at = ((size_t)(tid / HD) * cap + pos) * HD + tid % HD;
-            kc[at] = kn[tid];
-            vc[at] = vn[tid];
+        best = sb[0];
+        bi = si[0];
+#pragma unroll
+        for (int w = 1; w < kRowWaves; ++w)
+            if (sb[w] > best || (sb[w] == best && si[w] < bi)) { best = sb[w]; bi = si[w]; }
+        tok = (unsigned)bi < (unsigned)a.V ? bi : 0;
+        if (a.steps <= 0) {
+            if (tid == 0) a.am[j] = tok;
+            return;
         }
-        if (wave < H * P) {
-            const float scale = rsqrtf((float)HD);
-            float qf[8], m = -3.0e38f, tot = 0.f, acc[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                qf[e] = q[h * HD + sub * 8 + e];
-                acc[e] = 0.f;
-            }
-            auto score = [&](const uint4& raw) {
-                const kv_t* k = (const kv_t*)&raw;
-                float s = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) s += qf[e] * kv2f(k[e]);
-                return group_sum<LPK>(s) * scale;
-            };
-            auto add = [&](float w, const uint4& raw) {
-                const kv_t* u = (const kv_t*)&raw;
-                tot += w;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[e] += w * kv2f(u[e]);
-            };
-            auto largest = [](float z) {   // of the wave's groups
-                if (LPK == 8) z = fmaxf(z, dpp<kDppRotate8>(z));
-                z = fmaxf(z, __shfl_xor(z, 16, 64));
-                return fmaxf(z, __shfl_xor(z, 32, 64));
-            };
-            if (p == 0) {   // this slot: the same in every group, counted in the first
-                m = score(*(const uint4*)(kn + h * HD + sub * 8));
-                add(kin == 0 ? 1.f : 0.f, *(const uint4*)(vn + h * HD + sub * 8));
-            }
-            for (int c0 = p * KPW; c0 < pos; c0 += P * KPW * AU) {   // wave-uniform
-                const int c1 = c0 + P * KPW * AU;
-                float s[AU], top = m;
-#pragma unroll
-                for (int u = 0; u < AU; ++u) {
-                    s[u] = slot(c0, u) < pos ? score(kr[u]) : -3.0e38f;
-                    top = fmaxf(top, s[u]);
-                }
-                if (c1 < pos) load_slots(kr, kb, c1);
-                top = largest(top);
-                const float keep = __expf(m - top);
-                m = top;
-                tot *= keep;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[e] *= keep;
-#pragma unroll
-                for (int u = 0; u < AU; ++u) add(slot(c0, u) < pos ? __expf(s[u] - m) : 0.f, vr[u]);
-                if (c1 < pos) load_slots(vr, vb, c1);
-            }
-            auto over_groups = [](float z) {
-                if (LPK == 8) z += dpp<kDppRotate8>(z);
-                z += __shfl_xor(z, 16, 64);
-                return z + __shfl_xor(z, 32, 64);
-            };
-            tot = over_groups(tot);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) acc[e] = over_groups(acc[e]);
-            float* w = part + wave * (HD + 4);
-            if (kin == 0) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) w[sub * 8 + e] = acc[e];
-                if (sub == 0) {
-                    w[HD] = m;
-                    w[HD + 1] = tot;
-                }
-            }
-        }
+        const int s = step0 + step;   // the number of this token
+        if (tid == 0 && s < limit) st.out_tok[(size_t)row * st.max_new + s] = tok;
+        if (step + 1 >= a.steps || (a.compact && s + 1 >= limit)) return;   // the same for the whole workgroup
+        ++pos;
+        // the key and value that this step stored are read by other waves in the next
+        __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
         row_meet();
-        if (tid < d) {
-            const float* w = part + tid / HD * P * (HD + 4);
-            float m = -3.0e38f, tot = 0.f, sum = 0.f;
-            for (int z = 0; z < P; ++z) m = fmaxf(m, w[z * (HD + 4) + HD]);
-            for (int z = 0; z < P; ++z) {
-                const float f = __expf(w[z * (HD + 4) + HD] - m);
-                tot += f * w[z * (HD + 4) + HD + 1];
-                sum += f * w[z * (HD + 4) + tid % HD];
-            }
-            hb[tid] = f2h(sum / tot);
-        }
-        row_meet();
-    }
-    if (!a.am) return;
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) {
-        const float ob = __shfl_xor(best, m, 64);
-        const int oi = __shfl_xor(bi, m, 64);
-        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-    }
-    float* const sb = part;
-    int* const si = (int*)(part + kRowWaves);
-    if (lane == 0) { sb[wave] = best; si[wave] = bi; }
-    row_meet();
-    best = sb[0];
-    bi = si[0];
-#pragma unroll
-    for (int w = 1; w < kRowWaves; ++w)
-        if (sb[w] > best || (sb[w] == best && si[w] < bi)) { best = sb[w]; bi = si[w]; }
-    tok = (unsigned)bi < (unsigned)a.V ? bi : 0;
-    if (a.steps <= 0) {
-        if (tid == 0) a.am[j] = tok;
-        return;
-    }
-    const int s = step0 + step;   // the number of this token
-    if (tid == 0 && s < limit) st.out_tok[(size_t)row * st.max_new + s] = tok;
-    if (step + 1 >= a.steps || (a.compact && s + 1 >= limit)) return;   // the same for the whole workgroup
-    ++pos;
-    // the key and value that this step stored are read by other waves in the next
-    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0) lgkmcnt(0)
-    row_meet();
     }
 }
 
