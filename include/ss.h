@@ -350,8 +350,8 @@ int ss_bench_decode_step(ss_weights* w, const int32_t* prompt_tokens, int32_t B,
 
 /*
  * Measurement entry point: ss_bench_decode_step on `lanes` lanes at once (1 .. SS_IN_FLIGHT_MAX), as a group pass
- * with SS_OPT_IN_FLIGHT = lanes runs that many micro-batches that share no forwards: each of `lanes` host threads prefills its own B rows of
- * ctx tokens on its own stream, all wait for each other, then each times `iters` decode forwards.
+ * with SS_OPT_IN_FLIGHT = lanes runs that many micro-batches that share no forwards: each of `lanes` host threads
+ * prefills its own B rows of ctx tokens on its own stream, all wait for each other, then each times `iters` decode forwards.
  *   ms_out  host, double[lanes*iters]: lane 0's forwards, then lane 1's, ... (device time of each, HIP events on
  *           that lane's stream).  Every lane streams the whole model once per forward.
  */

@@ -935,10 +935,11 @@ int decode_microbatch_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_
 
 // Several micro-batches of a group pass with known lengths, generated together: every prompt forward is the micro-batch's
 // own, the decode forwards are shared.  A decode step of a few rows is the time of its weights, so a forward for the rows of
-// four micro-batches of 16 costs half of what four forwards do, also of four that run at the same time (7B, context 200:
-// 64 rows 3.8 ms a step, four steps of 16 rows 11.5 one after another and 8.4 on four streams; a pass of four micro-batches of 16
-// rows, 40 tokens, 527 -> 200 ms against one at a time).  A row's numbers do not depend on what else is in its forward: the launches are planned as for one of the micro-batches
-// alone (one strip of rows), which the kernels do for up to four strips with the same sums in the same order.
+// four micro-batches of 16 costs half of what four forwards do, also of four that run at the same time (7B, context 200: 64
+// rows 3.8 ms a step, four steps of 16 rows 11.5 one after another and 8.4 on four streams; a pass of four micro-batches of
+// 16 rows, 40 tokens, 527 -> 200 ms against one at a time).  A row's numbers do not depend on what else is in its forward:
+// the launches are planned as for one of the micro-batches alone (one strip of rows), which the kernels do for up to four
+// strips with the same sums in the same order.
 struct SharedMb {
     int row0, rows, cap, steps;   // rows of the joint batch; forwards, counting the prompt's
     ss_stats stats;
@@ -1788,8 +1789,9 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
                 const int64_t cb = (int64_t)pl->mb_cap[b] * (64 + pl->mb_offsets[b + 1] - pl->mb_offsets[b]);
                 return ca > cb;
             });
-        // Micro-batches of one strip share their decode forwards where that pays, as many as may be in flight (not those whose few rows get
-        // 16 attention waves each at long contexts: their plan is not that of a strip; nor rows that the host has to watch).
+        // Micro-batches of one strip share their decode forwards where that pays, as many as may be in flight (not those
+        // whose few rows get 16 attention waves each at long contexts: their plan is not that of a strip; nor rows that the
+        // host has to watch).
         auto can_share = [&](int k) {
             const int b0 = pl->mb_offsets[k], rows = pl->mb_offsets[k + 1] - b0;
             int ctx = 0;

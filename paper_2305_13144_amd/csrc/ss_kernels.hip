@@ -80,9 +80,9 @@ __device__ __forceinline__ float dpp(float v)
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
 constexpr int kDppRotate4 = 0x124, kDppRotate8 = 0x128;
 
-// op(v, v of the lane M = 16 or 32 away), M being a bit of the lane's number: two rows or halves of the wave change places, which
-// takes no trip through LDS as a general shuffle does (the norms and the decode attention are chains of such latencies: with general
-// shuffles, decode of 7B, one row, 24 steps 64.3 ms instead of 63.5, 16 rows 79.6 / 78.9, 51 rows 58.4 / 57.8).
+// op(v, v of the lane M = 16 or 32 away), M being a bit of the lane's number: two rows or halves of the wave change places,
+// which takes no trip through LDS as a general shuffle does (the norms and the decode attention are chains of such latencies:
+// with general shuffles, decode of 7B, one row, 24 steps 64.3 ms instead of 63.5, 16 rows 79.6 / 78.9, 51 rows 58.4 / 57.8).
 template <int M, typename Op>
 __device__ __forceinline__ float across(float v, Op op)
 {
@@ -776,10 +776,10 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
 // What bounds it: the power the chip may take.  On random data the matrix instructions alone run at 2.0 PFLOP/s (the clock
 // falls to 2.06 GHz), with the LDS reads beside them at 1.68, with the copies too at 1.33 to 1.38.  A trip (256 x 256 x 32)
 // takes 1131 clocks (1249 before the reads were given out between the products and the copies' addresses cut to one
-// addition), 1024 of them matrix work: with the order of the tiles, gate|up of 7B in a prompt forward of 12311 rows takes 1692 us
-// instead of 1748 (1.31 PFLOP/s; launched alone, 1603).  Measured against the kernel it replaced (weights straight from L2 to registers, 64 or 128 rows per tile)
-// before that, gate|up: 256 rows 73.7 -> 56.3 us, 494 123 -> 81, 995 216 -> 166, 3146 544 -> 488, 12311 1989 -> 1743; down
-// 494 67 -> 49, 995 98 -> 87, 4200 504 -> 351.
+// addition), 1024 of them matrix work: with the order of the tiles, gate|up of 7B in a prompt forward of 12311 rows takes
+// 1692 us instead of 1748 (1.31 PFLOP/s; launched alone, 1603).  Measured against the kernel it replaced (weights straight
+// from L2 to registers, 64 or 128 rows per tile) before that, gate|up: 256 rows 73.7 -> 56.3 us, 494 123 -> 81, 995 216 ->
+// 166, 3146 544 -> 488, 12311 1989 -> 1743; down 494 67 -> 49, 995 98 -> 87, 4200 504 -> 351.
 // The copies are written in assembly because the compiler would wait for all of them before every LDS read: it counts
 // only its own loads, and the waits here are written out.  They name no output register; waits that the compiler adds
 // for loads of its own can only be too strict.
