@@ -468,7 +468,7 @@ int ensure_workspace(const ss_weights* w, Lane& ln, int n_max, int B, int n_sel,
     const ss_model_cfg& c = w->cfg;
     const int d = c.d_model, F = c.d_ffn, V = c.vocab;
     Workspace& ws = ln.ws;
-    const size_t nr = (size_t)ss::round_up(n_max, 128);
+    const size_t nr = (size_t)ss::round_up(n_max, ss::kWorkspaceRows);
     const size_t Bp = ss::round_up(B, 4), np = ss::round_up(n_max, 4), sp = ss::round_up(n_sel, 4);
     const size_t n_i32 = 4 + 3 * np + 5 * Bp + 2 * sp + (size_t)B * max_new;
     ln.kv_layer_stride = slots * d;

@@ -94,7 +94,7 @@ void launch_attention_prompt(const MbState& st, const float* qrot, const kv_t* k
                              f16_t* out_packed, int d, int H, int hd, int B, int max_len, hipStream_t s);
 // n_max: rows of this launch; plan_rows, mb_rows, max_ctx: rows to choose its shape for (n_max, or those of one micro-batch
 // of several), rows of the micro-batch, finished ones included, and an upper bound of its contexts in this forward (they
-// choose the launch shape).  scratch: 128 rows of d floats.
+// choose the launch shape).  scratch: kWorkspaceRows rows of d floats (attention_split keeps to them).
 void launch_attention_decode(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride,
                              kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin,
                              f16_t* out_packed, int d, int H, int hd, int n_max, int plan_rows, int mb_rows,

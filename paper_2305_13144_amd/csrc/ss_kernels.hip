@@ -2270,7 +2270,7 @@ void launch_attention_decode(const MbState& st, const float* qkv_part, int kspli
     const bool wide = attention_wide(plan_rows, mb_rows, H);
     const bool many = wide && n_max * H > kAttnWideMaxGroups;   // several micro-batches together: 8 slices, but 4 waves
     const bool widest = attention_may_widen(mb_rows, H, max_ctx, hd);
-    const int S = attention_split(mb_rows, H, max_ctx);
+    const int S = attention_split(std::max(mb_rows, n_max), H, hd, max_ctx);
 #define SS_ATTN_ARGS st, qkv_part, ksplit, part_stride, kcache, vcache, rope_cos, rope_sin, out_packed, d, H, n_max, scratch, S, s
     if (hd == 128) {
         if (S > 1) launch_attention_decode_inst<128, 8, 8, true>(SS_ATTN_ARGS);

@@ -178,12 +178,13 @@ bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, i
 // micro-batch and its progress, like the waves.  Decode step of 7B per layer, us, 16 waves a pair / split: one row at context 1000
 // 90.4 / 89.2, 1400 94.7 / 88.7, 2000 99.8 / 89.5, 3900 118 / 94; two rows 1000 90.9 / 90.4, 2000 101 / 94, 3900 121 / 105; three 1000
 // 92.0 / 92.3, 2000 103 / 100, 3900 124 / 117; four 1000 92.3 / 93.4, 2000 104 / 106; six 2000 113 / 122 (what a unit of 16 waves
-// keeps in flight is enough there).
-int attention_split(int mb_rows, int H, int max_ctx)
+// keeps in flight is enough there).  With fewer than 5 heads the shares of many rows would not fit the buffer: fewer then.
+int attention_split(int mb_rows, int H, int hd, int max_ctx)
 {
     const int pairs = mb_rows * H;
     if (pairs > kAttnSplitMaxGroups || max_ctx < kAttnSplitFrom) return 1;
-    return std::min({kAttnMaxSplit, (512 + pairs - 1) / pairs, max_ctx / kAttnSplitSlots});
+    const int fit = (int)((size_t)kWorkspaceRows * H * hd / attention_share_floats(mb_rows, H, hd, 1));
+    return std::max(1, std::min({kAttnMaxSplit, (512 + pairs - 1) / pairs, max_ctx / kAttnSplitSlots, fit}));
 }
 
 size_t gemm_partial_rows_bound(int n_max)

@@ -1,6 +1,6 @@
 """Decode attention whose slots several workgroups share out (few pairs, long contexts): contexts around its beginning and around
-whole shares, short rows beside a long one (shares without a slot), both head sizes, against the oracle; and a row's numbers while
-the others leave."""
+whole shares, short rows beside a long one (shares without a slot), both head sizes, against the oracle; few heads and short
+prompts, where the buffer of the shares is smallest; and a row's numbers while the others leave."""
 import numpy as np
 import pytest
 
@@ -55,3 +55,43 @@ def test_rows_that_leave_do_not_change_the_others(model):
     whole = _forced(gw, seqs, plens)
     cut = _forced(gw, [seqs[0]] + [q[:len(q) - 4] for q in seqs[1:]], plens)
     assert np.array_equal(whole[:steps + 1], cut[:steps + 1])
+
+
+# Prompts of 5 tokens: activation buffers of 128 rows, the smallest there are.  4 heads of 64 and 24 rows, 2 of 128 and 42 rows
+# fill the buffer with shares; 1 head of 64 and 90 rows has no room for a second one.
+# (In mode 0 the first model's steps leave k_row_step by themselves at about 1350 slots.)
+FEW = [(4, 64, 24, 1660, 0), (2, 128, 42, 1300, 1), (1, 64, 90, 1100, 1)]
+
+
+@pytest.mark.parametrize("heads,hd,rows,steps,mode", FEW, ids=lambda v: str(v))
+def test_few_heads_and_short_prompts(oracle_built, heads, hd, rows, steps, mode):
+    """Both entry points give the same tokens, the oracle's wherever its two largest logits are apart; the same tokens given as
+    inputs have its logits."""
+    shape = synth.ModelShape("few", 1, heads * hd, heads, hd, 256, 272)
+    W = synth.make_weights(shape, seed=35, std=0.08, norm_jitter=0.1, threads=1)
+    om = OracleModel(shape, W, "f32")
+    gw = ss.Weights(shape, W)
+    rng = np.random.default_rng(heads)
+    plen = 5
+    toks = rng.integers(0, shape.vocab, rows * plen).astype(np.int32)
+    offs = (np.arange(rows + 1) * plen).astype(np.int32)
+    limits = np.full(rows, steps, np.int32)
+    ss.ss_set_gemm_mode(mode)
+    try:
+        got = ss.ss_decode_microbatch(gw, toks, offs, steps, limits)["tokens"]
+        static = ss.ss_decode_microbatch_static(gw, toks, offs, steps, limits)["tokens"]
+        assert np.array_equal(got, static)
+        seqs = [np.concatenate([toks[i * plen:(i + 1) * plen], got[i, :-1]]) for i in range(rows)]
+        forced = _forced(gw, seqs, [plen] * rows).reshape(rows, steps, shape.vocab)
+        decided = 0
+        for i in (0, rows // 2, rows - 1):
+            ref = om.teacher_forced(seqs[i], first=plen - 1)
+            assert np.abs(forced[i] - ref).max() <= TOL * np.abs(ref).max(), i
+            top = np.partition(ref, -2, axis=-1)
+            clear = top[:, -1] - top[:, -2] > 2 * TOL * np.abs(ref).max()
+            assert np.array_equal(got[i][clear], ref.argmax(-1)[clear]), i
+            decided += clear.sum()
+        assert decided > steps
+    finally:
+        ss.ss_set_gemm_mode(0)
+        gw.close()
