@@ -941,7 +941,8 @@ int decode_microbatch_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_
 // the launches are planned as for one of the micro-batches alone (one strip of rows), which the kernels do for up to four
 // strips with the same sums in the same order.
 struct SharedMb {
-    int row0, rows, cap, steps;   // rows of the joint batch; forwards, counting the prompt's
+    int row0, rows, cap;   // rows of the joint batch
+    ss::SharedShape shape;
     ss_stats stats;
 };
 
@@ -955,7 +956,7 @@ int decode_shared_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_toke
     size_t slots = 0;
     int n_max = B, steps = 0;
     for (SharedMb& mb : mbs) {
-        mb.steps = 0;
+        mb.shape = {};
         mb.stats = ss_stats{};
         for (int i = mb.row0; i < mb.row0 + mb.rows; ++i) {
             if (target_lens[i] < 1) return ss::fail(SS_EINVAL, "target_lens[%d] < 1", i - mb.row0);
@@ -965,14 +966,15 @@ int decode_shared_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_toke
             slab[i] = len + mb.cap;
             slots += (size_t)slab[i];
             limit[i] = std::min(target_lens[i], mb.cap);
-            mb.steps = std::max(mb.steps, limit[i]);
+            mb.shape.prompt = std::max(mb.shape.prompt, len);
+            mb.shape.steps = std::max(mb.shape.steps, limit[i]);
         }
         for (int i = mb.row0; i < mb.row0 + mb.rows; ++i) {
-            stay[i] = compact ? limit[i] : mb.steps;
+            stay[i] = compact ? limit[i] : mb.shape.steps;
             mb.stats.row_steps += stay[i];
         }
-        steps = std::max(steps, mb.steps);
-        mb.stats.steps = mb.steps;
+        steps = std::max(steps, mb.shape.steps);
+        mb.stats.steps = mb.shape.steps;
         mb.stats.rows = mb.rows;
         mb.stats.prompt_tokens = prompt_offsets[mb.row0 + mb.rows] - prompt_offsets[mb.row0];
         n_max = std::max(n_max, (int)mb.stats.prompt_tokens);
@@ -1037,7 +1039,6 @@ int decode_shared_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_toke
     const hipEvent_t e0 = ln.ev[0], e1 = ln.ev[1], e2 = ln.ev[2];
     HIPCHK(hipEventRecord(e0, s));
     const MbState& joint = restore.st;
-    int longest_prompt = 0;
     for (int k = 0; k < n_mb; ++k) {
         const SharedMb& mb = mbs[k];
         const int n = (int)mb.stats.prompt_tokens;
@@ -1053,10 +1054,7 @@ int decode_shared_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_toke
         ln.st.row_cap += mb.row0;
         ln.st.am += mb.row0;
         ln.prompt_rows = mb.rows;
-        ln.prompt_max_len = 0;
-        for (int i = mb.row0; i < mb.row0 + mb.rows; ++i)
-            ln.prompt_max_len = std::max(ln.prompt_max_len, prompt_offsets[i + 1] - prompt_offsets[i]);
-        longest_prompt = std::max(longest_prompt, ln.prompt_max_len);
+        ln.prompt_max_len = mb.shape.prompt;
         forward(w, ln, n, mb.rows, t + 4 + 3 * n, t + 1, false, s);
     }
     ln.st = joint;
@@ -1065,13 +1063,16 @@ int decode_shared_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_toke
     HIPCHK(hipEventRecord(e1, s));
     ln.plan_rows = ss::kSharedMbRows;
     ln.prompt_rows = 0;   // what the attention's plan calls the rows of a micro-batch
-    for (const SharedMb& mb : mbs) ln.prompt_rows = std::max(ln.prompt_rows, mb.rows);
-    ln.prompt_max_len = longest_prompt;
+    std::vector<ss::SharedShape> shapes;
+    for (const SharedMb& mb : mbs) {
+        ln.prompt_rows = std::max(ln.prompt_rows, mb.rows);
+        shapes.push_back(mb.shape);
+    }
     std::vector<int32_t> sorted_stay(stay);
     std::sort(sorted_stay.begin(), sorted_stay.end());
     for (int g = 1; g < steps; ++g) {
         const int n_live = (int)(sorted_stay.end() - std::upper_bound(sorted_stay.begin(), sorted_stay.end(), g));
-        ln.max_ctx = longest_prompt + g;
+        ln.max_ctx = ss::shared_context(shapes.data(), n_mb, g);
         forward(w, ln, n_live, n_live, nullptr, nullptr, true, s);
         ss::launch_step_update(ln.st, 0, -1, s);
     }
@@ -1692,7 +1693,7 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
             for (int k : unit) cap = std::max(cap, pl->mb_cap[k]);
             for (int k : unit) {
                 const int b0 = pl->mb_offsets[k], rows = pl->mb_offsets[k + 1] - b0;
-                mbs.push_back({(int)mb_ids.size(), rows, pl->mb_cap[k], 0, {}});
+                mbs.push_back({(int)mb_ids.size(), rows, pl->mb_cap[k], {}, {}});
                 for (int r = 0; r < rows; ++r) {
                     const int qi = pl->query_idx[b0 + r];
                     mb_toks.insert(mb_toks.end(), prompt_tokens + prompt_offsets[qi], prompt_tokens + prompt_offsets[qi + 1]);

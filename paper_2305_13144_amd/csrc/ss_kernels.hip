@@ -2261,28 +2261,19 @@ void launch_attention_decode(const MbState& st, const float* qkv_part, int kspli
                              f16_t* out_packed, int d, int H, int hd, int n_max, int plan_rows, int mb_rows, int max_ctx,
                              float* scratch, hipStream_t s)
 {
-    // measured at the 7B shape: 8 waves win at 16 rows (512 workgroups: 14.1 against 14.9 us per layer at context
-    // 200), 4 waves win at 64 rows (2048 workgroups: 25.7 against 36.1 us at context 100)
-    // 16 waves where 8 would need a second round trip (3 rows at context 2400: 47.5 -> 38 us); shorter contexts leave some
-    // of them without a slot (tiny model, context 40: 6 us with 8 waves, 7.3 with 16).  Their sums add up in another order,
-    // so the choice depends on the micro-batch and on how far it has come, not on how many of its rows are still alive: a
-    // row's numbers are to be the same whether or when the others leave.
-    const bool wide = attention_wide(plan_rows, mb_rows, H);
-    const bool many = wide && n_max * H > kAttnWideMaxGroups;   // several micro-batches together: 8 slices, but 4 waves
-    const bool widest = attention_may_widen(mb_rows, H, max_ctx, hd);
-    const int S = attention_split(std::max(mb_rows, n_max), H, hd, max_ctx);
-#define SS_ATTN_ARGS st, qkv_part, ksplit, part_stride, kcache, vcache, rope_cos, rope_sin, out_packed, d, H, n_max, scratch, S, s
+    const AttentionPlan p = attention_plan(n_max, plan_rows, mb_rows, H, hd, max_ctx);
+#define SS_ATTN_ARGS st, qkv_part, ksplit, part_stride, kcache, vcache, rope_cos, rope_sin, out_packed, d, H, n_max, scratch, p.split, s
     if (hd == 128) {
-        if (S > 1) launch_attention_decode_inst<128, 8, 8, true>(SS_ATTN_ARGS);
-        else if (widest) launch_attention_decode_inst<128, 16>(SS_ATTN_ARGS);
-        else if (many) launch_attention_decode_inst<128, 8, 4>(SS_ATTN_ARGS);
-        else if (wide) launch_attention_decode_inst<128, 8>(SS_ATTN_ARGS);
+        if (p.split > 1) launch_attention_decode_inst<128, 8, 8, true>(SS_ATTN_ARGS);
+        else if (p.slices == 16) launch_attention_decode_inst<128, 16>(SS_ATTN_ARGS);
+        else if (p.slices == 8 && p.waves == 4) launch_attention_decode_inst<128, 8, 4>(SS_ATTN_ARGS);
+        else if (p.slices == 8) launch_attention_decode_inst<128, 8>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<128, 4>(SS_ATTN_ARGS);
     } else {
-        if (S > 1) launch_attention_decode_inst<64, 8, 8, true>(SS_ATTN_ARGS);
-        else if (widest) launch_attention_decode_inst<64, 16>(SS_ATTN_ARGS);
-        else if (many) launch_attention_decode_inst<64, 8, 4>(SS_ATTN_ARGS);
-        else if (wide) launch_attention_decode_inst<64, 8>(SS_ATTN_ARGS);
+        if (p.split > 1) launch_attention_decode_inst<64, 8, 8, true>(SS_ATTN_ARGS);
+        else if (p.slices == 16) launch_attention_decode_inst<64, 16>(SS_ATTN_ARGS);
+        else if (p.slices == 8 && p.waves == 4) launch_attention_decode_inst<64, 8, 4>(SS_ATTN_ARGS);
+        else if (p.slices == 8) launch_attention_decode_inst<64, 8>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<64, 4>(SS_ATTN_ARGS);
     }
 #undef SS_ATTN_ARGS

@@ -187,6 +187,29 @@ int attention_split(int mb_rows, int H, int hd, int max_ctx)
     return std::max(1, std::min({kAttnMaxSplit, (512 + pairs - 1) / pairs, max_ctx / kAttnSplitSlots, fit}));
 }
 
+AttentionPlan attention_plan(int n_rows, int plan_rows, int mb_rows, int H, int hd, int max_ctx)
+{
+    // measured at the 7B shape: 8 waves win at 16 rows (512 workgroups: 14.1 against 14.9 us per layer at context
+    // 200), 4 waves win at 64 rows (2048 workgroups: 25.7 against 36.1 us at context 100)
+    // 16 waves where 8 would need a second round trip (3 rows at context 2400: 47.5 -> 38 us); shorter contexts leave some
+    // of them without a slot (tiny model, context 40: 6 us with 8 waves, 7.3 with 16).  Their sums add up in another order,
+    // so the choice depends on the micro-batch and on how far it has come, not on how many of its rows are still alive: a
+    // row's numbers are to be the same whether or when the others leave.
+    const int split = attention_split(std::max(mb_rows, n_rows), H, hd, max_ctx);
+    if (split > 1) return {8, 8, split};
+    if (attention_may_widen(mb_rows, H, max_ctx, hd)) return {16, 16, 1};
+    if (!attention_wide(plan_rows, mb_rows, H)) return {4, 4, 1};
+    return {8, n_rows * H > kAttnWideMaxGroups ? 4 : 8, 1};   // several micro-batches together: 8 slices, but 4 waves
+}
+
+int shared_context(const SharedShape* mb, int n_mb, int g)
+{
+    int ctx = 0;
+    for (int k = 0; k < n_mb; ++k)
+        if (mb[k].steps > g) ctx = std::max(ctx, mb[k].prompt + g);
+    return ctx;
+}
+
 size_t gemm_partial_rows_bound(int n_max)
 {
     // up to kSweepMaxRows rows: at most kSmallMaxKsplit slices; the block kernel: 4 up to kBlockRows4 rows, 2 up to

@@ -88,9 +88,24 @@ constexpr bool attention_wide(int n_rows, int mb_rows, int H)
     return (mb_rows < strips ? mb_rows : strips) * H <= kAttnWideMaxGroups;
 }
 
+// Launch shape of the decode attention: slices that a pair's slots are dealt to (their number is the order of the sums), waves
+// that take them, workgroups that share out the slots.  n_rows: rows of the launch; plan_rows: rows that its sums are planned for
+// (n_rows, or those of one micro-batch of several); mb_rows: rows of the micro-batch, finished ones included; max_ctx: longest
+// context in this forward, were all alive.
+struct AttentionPlan {
+    int slices, waves, split;
+};
+AttentionPlan attention_plan(int n_rows, int plan_rows, int mb_rows, int H, int hd, int max_ctx);
+
 // Micro-batches of a group pass that share their decode forwards: rows of one (a strip: every plan of a strip holds for it
 // alone and for several together) and of all.
 constexpr int kSharedMbRows = 16, kSharedRows = 64;
+// One of them: its longest prompt, and forwards, counting the prompt's.  The longest context of forward g is that of the
+// micro-batches that still take part: each stays below where its attention would widen, and so do those that are there.
+struct SharedShape {
+    int prompt, steps;
+};
+int shared_context(const SharedShape* mb, int n_mb, int g);
 // Whether they do: where a launch is the time of its weights (7 MB and more each, 7 a layer).  Below that it is the time of
 // a launch, which several streams hide better.  Group passes, four micro-batches in flight on streams / sharing, ms: 4 layers
 // 512 wide 22.4 / 27.3, 12 layers 1024 wide (25 MB a layer) 74.5 / 85.4, 6 layers 2048 wide (101 MB) 63.6 / 61.8 and 31.7 / 26.3,

@@ -50,3 +50,27 @@ def test_tokens_and_counters_are_those_of_one_at_a_time(model, flags, batch, ple
     finally:
         gw.set_option(ss.SS_OPT_IN_FLIGHT, ss.SS_IN_FLIGHT_DEFAULT)
         gw.set_option(ss.SS_OPT_WEIGHT_COPIES, 1)
+
+
+@pytest.mark.parametrize("seed", [2, 3])
+def test_a_member_that_ends_early_leaves_the_others_their_sums(model, seed):
+    """Two micro-batches of 4 rows, few enough for 16 attention waves where a context is long enough, which neither's is: a long
+    prompt that ends early and a short one that runs on.  The first one's prompt does not count once it has ended."""
+    shape, gw = model
+    limit = 64 * 512 // shape.head_dim   # the longest context of 8 waves
+    rng = np.random.default_rng(seed)
+    plens = [limit - 56] * 4 + [16] * 4
+    targets = np.array([48] * 4 + [limit - 24] * 4, np.int32)
+    toks = rng.integers(0, shape.vocab, sum(plens)).astype(np.int32)
+    offs = np.concatenate([[0], np.cumsum(plens)]).astype(np.int32)
+    pol = ss.make_policy(("SORT", "BIN", "FCR"), 4, limit - 24, 16)
+    try:
+        got = []
+        for lanes in (1, 4):
+            gw.set_option(ss.SS_OPT_IN_FLIGHT, lanes)
+            r = ss.ss_run_group(gw, toks, offs, targets, targets, 8, pol)
+            assert r["stats"]["n_mb_first"] == 2 and r["stats"]["n_failed"] == 0
+            got.append(r["tokens"])
+        assert np.array_equal(got[0], got[1])
+    finally:
+        gw.set_option(ss.SS_OPT_IN_FLIGHT, ss.SS_IN_FLIGHT_DEFAULT)
