@@ -178,11 +178,18 @@ bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, i
 // micro-batch and its progress, like the waves.  Decode step of 7B per layer, us, 16 waves a pair / split: one row at context 1000
 // 90.4 / 89.2, 1400 94.7 / 88.7, 2000 99.8 / 89.5, 3900 118 / 94; two rows 1000 90.9 / 90.4, 2000 101 / 94, 3900 121 / 105; three 1000
 // 92.0 / 92.3, 2000 103 / 100, 3900 124 / 117; four 1000 92.3 / 93.4, 2000 104 / 106; six 2000 113 / 122 (what a unit of 16 waves
-// keeps in flight is enough there).  With fewer than 5 heads the shares of many rows would not fit the buffer: fewer then.
+// keeps in flight is enough there).  Other heads (8 layers, or 17 of up to 512 wide, whole step per layer):
+//   heads of 128   8 x 1 row 1030 35.9 / 35.4, 2100 42.5 / 35.0; 8 x 12 1030 43.7 / 43.8, 2100 56.3 / 51.0; 4 x 24 1030 43.4 / 43.5, 1300
+//                  46.7 / 44.4; 16 x 6 1030 48.7 / 48.7: as with 32 heads, from 1024 slots
+//   heads of 64    (half the bytes a slot) 32 x 1 1030 38.1 / 38.8, 1300 39.3 / 38.9; 32 x 3 1030 39.5 / 41.4, 1300 43.0 / 43.5, 2100 49.4 / 47.2;
+//                  16 x 4 1600 35.9 / 36.3, 2100 42.1 / 39.1; 8 x 6 1030 31.5 / 32.1, 1300 35.3 / 34.3; 4 x 12 1300 33.2 / 32.1: from 1280, and
+//                  from 1792 where there are more than 48 pairs
+// With fewer than 5 heads the shares of many rows would not fit the buffer: fewer then.
 int attention_split(int mb_rows, int H, int hd, int max_ctx)
 {
     const int pairs = mb_rows * H;
-    if (pairs > kAttnSplitMaxGroups || max_ctx < kAttnSplitFrom) return 1;
+    const int from = hd >= 128 ? 1024 : pairs <= kAttnSplitMaxGroups / 2 ? 1280 : 1792;
+    if (pairs > kAttnSplitMaxGroups || max_ctx < from) return 1;
     const int fit = (int)((size_t)kWorkspaceRows * H * hd / attention_share_floats(mb_rows, H, hd, 1));
     return std::max(1, std::min({kAttnMaxSplit, (512 + pairs - 1) / pairs, max_ctx / kAttnSplitSlots, fit}));
 }

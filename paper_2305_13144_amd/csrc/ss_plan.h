@@ -74,7 +74,7 @@ constexpr int kWorkspaceRows = 128;   // activation buffers hold whole multiples
 
 // Workgroups that share out the slots of one pair (1: no split), up to kAttnMaxSplit, at least kAttnSplitSlots slots each, and so
 // few that their sums fit a buffer of kWorkspaceRows rows.
-constexpr int kAttnMaxSplit = 16, kAttnSplitSlots = 256, kAttnSplitFrom = 1024, kAttnSplitMaxGroups = 96;
+constexpr int kAttnMaxSplit = 16, kAttnSplitSlots = 256, kAttnSplitMaxGroups = 96;
 int attention_split(int mb_rows, int H, int hd, int max_ctx);
 // Floats that the shares of n_rows rows take: the sums of a head, their maximum and their total each.
 constexpr size_t attention_share_floats(int n_rows, int H, int hd, int split) { return (size_t)n_rows * H * split * (hd + 2); }

@@ -28,6 +28,44 @@ def test_shares_fit_the_smallest_workspace(tmp_path):
     """)
 
 
+def test_slots_are_shared_out_where_that_was_measured_faster(tmp_path):
+    """Split or 16 waves a pair, wherever one of them was measured 1.5 % faster or more (a decode step's time per layer)."""
+    _run(tmp_path, r"""
+        struct Point { int rows, H, hd, ctx; bool split; };
+        int main() {
+            const Point points[] = {
+                // us, 16 waves / split
+                {1, 32, 128, 1030, true},    // 57.0 / 56.2
+                {3, 32, 128, 1300, true},    // 68.1 / 66.0
+                {4, 32, 128, 2000, false},   // 104 / 106
+                {6, 16, 128, 1300, true},    // 51.9 / 49.7
+                {12, 8, 128, 1300, true},    // 46.9 / 44.8
+                {16, 4, 128, 1030, true},    // 39.7 / 38.0
+                {24, 4, 128, 1300, true},    // 46.7 / 44.4
+                {1, 32, 64, 1030, false},    // 38.1 / 38.8
+                {3, 32, 64, 1030, false},    // 39.5 / 41.4
+                {6, 16, 64, 1030, false},    // 34.7 / 36.7
+                {12, 8, 64, 1030, false},    // 35.0 / 36.0
+                {12, 4, 64, 1030, false},    // 29.3 / 29.9
+                {24, 4, 64, 1030, false},    // 34.7 / 35.3
+                {2, 16, 64, 1300, true},     // 35.4 / 34.5
+                {6, 8, 64, 1300, true},      // 35.3 / 34.3
+                {12, 4, 64, 1300, true},     // 33.2 / 32.1
+                {1, 32, 64, 1600, true},     // 39.7 / 39.0
+                {3, 32, 64, 2100, true},     // 49.4 / 47.2
+                {4, 16, 64, 2100, true},     // 42.1 / 39.1
+                {12, 8, 64, 2100, true},     // 41.8 / 39.8
+            };
+            for (const Point& q : points) {
+                if ((ss::attention_plan(q.rows, q.rows, q.rows, q.H, q.hd, q.ctx).split > 1) == q.split) continue;
+                std::printf("%d rows, %d heads of %d, context %d\n", q.rows, q.H, q.hd, q.ctx);
+                return 1;
+            }
+            return 0;
+        }
+    """)
+
+
 def test_shared_forwards_keep_every_member_s_sums(tmp_path):
     """In every forward of micro-batches that share theirs, the attention's slices and shares are those that each of them gets alone:
     also when the one with the longest prompt has ended and those that remain run on."""

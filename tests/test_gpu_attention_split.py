@@ -33,7 +33,7 @@ def _forced(gw, seqs, plens):
     return ss.ss_forward_logits(gw, np.concatenate(seqs), offs, np.array(plens, np.int32))
 
 
-@pytest.mark.parametrize("plens", [[1022], [1087, 3], [1535, 64, 1, 700], [4000, 2, 255, 256, 257, 1025, 320, 63, 2049, 17, 1, 640]],
+@pytest.mark.parametrize("plens", [[1022], [1087, 3], [1278], [1790, 5, 64, 1000, 1791, 300, 2], [1535, 64, 1, 700], [4000, 2, 255, 256, 257, 1025, 320, 63, 2049, 17, 1, 640]],
                          ids=lambda v: "x".join(map(str, v)))
 def test_logits(model, plens):
     shape, gw, om = model
@@ -60,7 +60,7 @@ def test_rows_that_leave_do_not_change_the_others(model):
 # Prompts of 5 tokens: activation buffers of 128 rows, the smallest there are.  4 heads of 64 and 24 rows, 2 of 128 and 42 rows
 # fill the buffer with shares; 1 head of 64 and 90 rows has no room for a second one.
 # (In mode 0 the first model's steps leave k_row_step by themselves at about 1350 slots.)
-FEW = [(4, 64, 24, 1660, 0), (2, 128, 42, 1300, 1), (1, 64, 90, 1100, 1)]
+FEW = [(4, 64, 24, 1900, 0), (2, 128, 42, 1300, 1), (1, 64, 90, 1100, 1)]
 
 
 @pytest.mark.parametrize("heads,hd,rows,steps,mode", FEW, ids=lambda v: str(v))
