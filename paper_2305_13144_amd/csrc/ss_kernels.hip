@@ -1039,6 +1039,8 @@ __global__ __launch_bounds__(256) void k_rope_append(MbState st, const float* __
 constexpr int kAttnUnroll = 8;
 
 // The slots are dealt to NW slices, one per wave, or NW / PW for each of PW waves: the sums are the same sums in the same order.
+// A wave's loads then go to its slices in turn, so that the workgroup walks over the slots as with NW = PW (one slice after the
+// other it asks for every second 4 KB at a time: 16 rows of 40 heads, context 1500, 174 us a layer instead of 165).
 // SPLIT: the slots are a share of the row's; their sums, maximum and total go to `share` (see k_attention_join).
 template <int HD, int NW, int PW, bool SPLIT>
 __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __restrict__ sc, float* __restrict__ red,
@@ -1051,41 +1053,41 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     constexpr int AU = kAttnUnroll;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = lane % LPK, kin = lane / LPK;
+    constexpr int R = NW / PW;        // slices per wave
+    static_assert(NW % PW == 0 && AU % R == 0, "every load of a trip belongs to one slice");
     const float scale = rsqrtf((float)HD);
     float q[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) q[e] = qs[sub * 8 + e];
 
     float mx = -3.0e38f;
+    for (int c0 = wave * KPW; c0 < ctx; c0 += PW * KPW * AU) {
+        uint4 raw[AU];
 #pragma unroll
-    for (int i = 0, v = wave; i < NW / PW; ++i, v += PW)
-        for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
-            uint4 raw[AU];
+        for (int u = 0; u < AU; ++u) {
+            const int s = c0 + u * PW * KPW + kin;
+            raw[u] = s < ctx ? *(const uint4*)(kbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
+        }
 #pragma unroll
-            for (int u = 0; u < AU; ++u) {
-                const int s = c0 + u * NW * KPW + kin;
-                raw[u] = s < ctx ? *(const uint4*)(kbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
-            }
+        for (int u = 0; u < AU; ++u) {
+            if (c0 + u * PW * KPW >= ctx) break;   // wave-uniform: nothing of this load is inside the context
+            const int s = c0 + u * PW * KPW + kin;
+            const kv_t* kv = (const kv_t*)&raw[u];
+            float part = 0.f;
 #pragma unroll
-            for (int u = 0; u < AU; ++u) {
-                if (c0 + u * NW * KPW >= ctx) break;   // wave-uniform: nothing of this load is inside the context
-                const int s = c0 + u * NW * KPW + kin;
-                const kv_t* kv = (const kv_t*)&raw[u];
-                float part = 0.f;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) part += q[e] * kv2f(kv[e]);
-                part = group_sum<LPK>(part) * scale;
-                if (s < ctx) {
-                    if (sub == 0) sc[s] = part;
-                    mx = fmaxf(mx, part);
-                }
+            for (int e = 0; e < 8; ++e) part += q[e] * kv2f(kv[e]);
+            part = group_sum<LPK>(part) * scale;
+            if (s < ctx) {
+                if (sub == 0) sc[s] = part;
+                mx = fmaxf(mx, part);
             }
         }
+    }
     // the first chunk of V does not depend on the scores: get it moving before the reductions
     uint4 vraw[AU];
 #pragma unroll
     for (int u = 0; u < AU; ++u) {
-        const int s = wave * KPW + u * NW * KPW + kin;
+        const int s = wave * KPW + u * PW * KPW + kin;
         vraw[u] = s < ctx ? *(const uint4*)(vbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
     }
     mx = wave_max(mx);
@@ -1094,16 +1096,20 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     mx = red[0];
 #pragma unroll
     for (int w = 1; w < PW; ++w) mx = fmaxf(mx, red[w]);
+    float sum[R] = {};
+    for (int s0 = wave * 64 + lane; s0 < ctx; s0 += 64 * NW)
 #pragma unroll
-    for (int i = 0, v = wave; i < NW / PW; ++i, v += PW) {
-        float sum = 0.f;
-        for (int s = v * 64 + lane; s < ctx; s += 64 * NW) {
+        for (int i = 0; i < R; ++i) {
+            const int s = s0 + i * 64 * PW;
+            if (i > 0 && s >= ctx) break;
             const float p = __expf(sc[s] - mx);
             sc[s] = p;
-            sum += p;
+            sum[i] += p;
         }
-        sum = wave_sum(sum);
-        if (lane == 0) red[PW + v] = sum;
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+        sum[i] = wave_sum(sum[i]);
+        if (lane == 0) red[PW + wave + i * PW] = sum[i];
     }
     __syncthreads();
     float tot = 0.f;
@@ -1111,37 +1117,37 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     for (int w = 0; w < NW; ++w) tot += red[PW + w];
     const float inv = 1.f / tot;
 
+    float o[R][8] = {};
+    for (int c0 = wave * KPW; c0 < ctx; c0 += PW * KPW * AU) {
+        uint4 raw[AU];
 #pragma unroll
-    for (int i = 0, v = wave; i < NW / PW; ++i, v += PW) {
-        float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        for (int c0 = v * KPW; c0 < ctx; c0 += NW * KPW * AU) {
-            uint4 raw[AU];
-#pragma unroll
-            for (int u = 0; u < AU; ++u) {
-                const int s = c0 + u * NW * KPW + kin;
-                if (c0 == wave * KPW)
-                    raw[u] = vraw[u];
-                else
-                    raw[u] = s < ctx ? *(const uint4*)(vbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
-            }
-#pragma unroll
-            for (int u = 0; u < AU; ++u) {
-                if (c0 + u * NW * KPW >= ctx) break;
-                const int s = c0 + u * NW * KPW + kin;
-                const float p = s < ctx ? sc[s] : 0.f;
-                const kv_t* vv = (const kv_t*)&raw[u];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) o[e] += p * kv2f(vv[e]);
-            }
+        for (int u = 0; u < AU; ++u) {
+            const int s = c0 + u * PW * KPW + kin;
+            if (c0 == wave * KPW)
+                raw[u] = vraw[u];
+            else
+                raw[u] = s < ctx ? *(const uint4*)(vbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
+        for (int u = 0; u < AU; ++u) {
+            if (c0 + u * PW * KPW >= ctx) break;
+            const int s = c0 + u * PW * KPW + kin;
+            const float p = s < ctx ? sc[s] : 0.f;
+            const kv_t* vv = (const kv_t*)&raw[u];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[u % R][e] += p * kv2f(vv[e]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+#pragma unroll
         for (int e = 0; e < 8; ++e) {
-            if (LPK == 8) o[e] += dpp<kDppRotate8>(o[e]);
-            o[e] = across<32>(across<16>(o[e], Add()), Add());
+            if (LPK == 8) o[i][e] += dpp<kDppRotate8>(o[i][e]);
+            o[i][e] = across<32>(across<16>(o[i][e], Add()), Add());
         }
         if (kin == 0)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) oacc[v][sub * 8 + e] = o[e];
+            for (int e = 0; e < 8; ++e) oacc[wave + i * PW][sub * 8 + e] = o[i][e];
     }
     __syncthreads();
     if (tid < HD / 4) {

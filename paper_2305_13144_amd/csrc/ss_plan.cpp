@@ -194,6 +194,20 @@ int attention_split(int mb_rows, int H, int hd, int max_ctx)
     return std::max(1, std::min({kAttnMaxSplit, (512 + pairs - 1) / pairs, max_ctx / kAttnSplitSlots, fit}));
 }
 
+namespace {
+// Waves that take the 8 slices of a pair; any number gives the same sums.  8 while all pairs are resident with room to spare, 4
+// beyond.  With somewhat more pairs than the chip's 256 units and long contexts, the units that have two pairs decide, and a
+// unit's lone pair is not to take the memory's time from them: 4 waves as well, from 650 slots of 128 elements or 1300 of 64.
+// Decode step per layer, us, 8 waves / 4: 32 heads of 128, 9 rows, context 500 71.6 / 71.4, 900 82.8 / 82.3, 1500 108.8 / 104.3, 3000 155.3 /
+// 143.0; 12 rows 300 66.8 / 67.3, 900 92.3 / 89.9, 1500 112.8 / 110.3; 14 rows 1500 117.9 / 118.2, 3000 179.6 / 180.9; 8 rows 900 76.2 /
+// 79.5, 1500 94.8 / 100.1; heads of 64, 32 x 11 900 54.3 / 54.5, 1500 65.0 / 63.5; 16 x 18 900 45.4 / 47.7, 1500 59.5 / 59.2, 3000 82.4 / 79.8.
+int attention_waves(int pairs, int hd, int max_ctx)
+{
+    if (pairs > kAttnWideMaxGroups) return 4;
+    return pairs > 256 && pairs <= 416 && max_ctx * hd > 650 * 128 ? 4 : 8;
+}
+}
+
 AttentionPlan attention_plan(int n_rows, int plan_rows, int mb_rows, int H, int hd, int max_ctx)
 {
     // measured at the 7B shape: 8 waves win at 16 rows (512 workgroups: 14.1 against 14.9 us per layer at context
@@ -206,7 +220,7 @@ AttentionPlan attention_plan(int n_rows, int plan_rows, int mb_rows, int H, int 
     if (split > 1) return {8, 8, split};
     if (attention_may_widen(mb_rows, H, max_ctx, hd)) return {16, 16, 1};
     if (!attention_wide(plan_rows, mb_rows, H)) return {4, 4, 1};
-    return {8, n_rows * H > kAttnWideMaxGroups ? 4 : 8, 1};   // several micro-batches together: 8 slices, but 4 waves
+    return {8, attention_waves(n_rows * H, hd, max_ctx), 1};
 }
 
 int shared_context(const SharedShape* mb, int n_mb, int g)

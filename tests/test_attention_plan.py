@@ -66,6 +66,44 @@ def test_slots_are_shared_out_where_that_was_measured_faster(tmp_path):
     """)
 
 
+def test_waves_follow_the_measurements(tmp_path):
+    """4 or 8 waves for the 8 slices of a pair, wherever one of them was measured 1.5 % faster or more (a decode step's time per
+    layer)."""
+    _run(tmp_path, r"""
+        struct Point { int rows, H, hd, ctx, waves; };
+        int main() {
+            const Point points[] = {
+                // us, 8 waves / 4
+                {8, 32, 128, 900, 8},     // 76.2 / 79.5
+                {8, 32, 128, 3000, 8},    // 128.8 / 137.3
+                {9, 32, 128, 1200, 4},    // 99.4 / 96.5
+                {9, 32, 128, 3000, 4},    // 155.3 / 143.0
+                {11, 32, 128, 700, 4},    // 80.6 / 79.2
+                {12, 32, 128, 900, 4},    // 92.3 / 89.9
+                {12, 32, 128, 1500, 4},   // 112.8 / 110.3
+                {16, 16, 128, 1500, 8},   // 72.0 / 77.9
+                {20, 16, 128, 1500, 4},   // 92.0 / 87.5
+                {24, 16, 128, 900, 4},    // 75.8 / 73.8
+                {8, 32, 64, 1500, 8},     // 55.1 / 60.1
+                {10, 32, 64, 900, 8},     // 52.6 / 54.3
+                {11, 32, 64, 300, 8},     // 41.8 / 42.8
+                {12, 32, 64, 1500, 4},    // 65.0 / 63.4
+                {11, 32, 64, 3000, 4},    // 89.4 / 85.0
+                {18, 16, 64, 900, 8},     // 45.4 / 47.7
+                {20, 16, 64, 1500, 4},    // 60.5 / 58.7
+                {16, 32, 64, 500, 8},     // 46.8 / 48.0
+            };
+            for (const Point& q : points) {
+                const ss::AttentionPlan p = ss::attention_plan(q.rows, q.rows, q.rows, q.H, q.hd, q.ctx);
+                if (p.slices == 8 && p.waves == q.waves) continue;
+                std::printf("%d rows, %d heads of %d, context %d: %d waves\n", q.rows, q.H, q.hd, q.ctx, p.waves);
+                return 1;
+            }
+            return 0;
+        }
+    """)
+
+
 def test_shared_forwards_keep_every_member_s_sums(tmp_path):
     """In every forward of micro-batches that share theirs, the attention's slices and shares are those that each of them gets alone:
     also when the one with the longest prompt has ended and those that remain run on."""
