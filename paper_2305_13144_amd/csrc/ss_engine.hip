@@ -1801,7 +1801,6 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
             return !gen && lanes > 1 && rows <= ss::kSharedMbRows && ss::shared_forwards_pay(w->cfg.d_model, w->cfg.d_ffn) &&
                    !ss::attention_may_widen(rows, w->cfg.n_heads, ctx + pl->mb_cap[k], w->cfg.head_dim);
         };
-        auto wide = [&](int k) { return ss::attention_wide(ss::kSharedMbRows, pl->mb_offsets[k + 1] - pl->mb_offsets[k], w->cfg.n_heads); };
         // While some share, those that cannot run beside them, one at a time: together no more than may be in flight.
         int n_share = 0;
         for (int k : order) n_share += can_share(k);
@@ -1812,8 +1811,7 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
             const int rows = pl->mb_offsets[k + 1] - pl->mb_offsets[k];
             if (!can_share(k)) {
                 ps.alone.list.push_back({k});
-            } else if (!sh.empty() && (int)sh.back().size() < together && rows_open + rows <= ss::kSharedRows &&
-                       wide(k) == wide(sh.back()[0])) {
+            } else if (!sh.empty() && (int)sh.back().size() < together && rows_open + rows <= ss::kSharedRows) {
                 sh.back().push_back(k);
                 rows_open += rows;
             } else {

@@ -219,7 +219,7 @@ AttentionPlan attention_plan(int n_rows, int plan_rows, int mb_rows, int H, int 
     const int split = attention_split(std::max(mb_rows, n_rows), H, hd, max_ctx);
     if (split > 1) return {8, 8, split};
     if (attention_may_widen(mb_rows, H, max_ctx, hd)) return {16, 16, 1};
-    if (!attention_wide(plan_rows, mb_rows, H)) return {4, 4, 1};
+    if (!attention_wide(attention_fewest_rows(plan_rows), H)) return {4, 4, 1};
     return {8, attention_waves(n_rows * H, hd, max_ctx), 1};
 }
 

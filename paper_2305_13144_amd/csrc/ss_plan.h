@@ -79,14 +79,13 @@ int attention_split(int mb_rows, int H, int hd, int max_ctx);
 // Floats that the shares of n_rows rows take: the sums of a head, their maximum and their total each.
 constexpr size_t attention_share_floats(int n_rows, int H, int hd, int split) { return (size_t)n_rows * H * split * (hd + 2); }
 
-// ... and 8 waves each (else 4), by whole strips of live rows, or the rows of a smaller micro-batch: a row's numbers are not to
-// depend on who else is still alive.
+// ... and 8 waves each (else 4).  The slots are dealt to 8 slices, whatever the waves, for every row count of a strip that holds
+// one so small: a row's numbers are not to depend on who else is still alive, its time may.  (40 heads, 16 rows that become
+// fewer; 4 slices for the whole strip / 8, decode step of 13B per layer, us: 16 rows at context 50 110.6 / 111.0, 3 rows at 300 113.4 / 111.4,
+// one row at 600 117.5 / 113.7; without the MLP 4 rows at 3000 141.6 / 118.6.)
 constexpr int kAttnWideMaxGroups = 512;
-constexpr bool attention_wide(int n_rows, int mb_rows, int H)
-{
-    const int strips = (n_rows + 15) / 16 * 16;
-    return (mb_rows < strips ? mb_rows : strips) * H <= kAttnWideMaxGroups;
-}
+constexpr bool attention_wide(int n_rows, int H) { return n_rows * H <= kAttnWideMaxGroups; }
+constexpr int attention_fewest_rows(int n_rows) { return (n_rows + 15) / 16 * 16 - 15; }   // of n_rows' strip
 
 // Launch shape of the decode attention: slices that a pair's slots are dealt to (their number is the order of the sums), waves
 // that take them, workgroups that share out the slots.  n_rows: rows of the launch; plan_rows: rows that its sums are planned for

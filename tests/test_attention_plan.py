@@ -122,8 +122,7 @@ def test_shared_forwards_keep_every_member_s_sums(tmp_path):
                     mb[k] = {1 + std::rand() % (std::rand() % 2 ? 60 : 1200), 0};
                     const int cap = 1 + std::rand() % (std::rand() % 2 ? 60 : 700);
                     mb[k].steps = 1 + std::rand() % cap;
-                    shares = shares && !ss::attention_may_widen(rows[k], H, mb[k].prompt + cap, hd) &&
-                             ss::attention_wide(ss::kSharedMbRows, rows[k], H) == ss::attention_wide(ss::kSharedMbRows, rows[0], H);
+                    shares = shares && !ss::attention_may_widen(rows[k], H, mb[k].prompt + cap, hd);
                     all += rows[k];
                     most = rows[k] > most ? rows[k] : most;
                     last = mb[k].steps > last ? mb[k].steps : last;
@@ -143,5 +142,35 @@ def test_shared_forwards_keep_every_member_s_sums(tmp_path):
                         }
             }
             return checked > 100000 ? 0 : 2;
+        }
+    """)
+
+
+def test_a_shrinking_micro_batch_keeps_its_slices_and_gains_waves(tmp_path):
+    """Inside a strip the slices (the order of the sums) stay the same for every count of live rows; 8 waves take a pair's slots
+    as soon as at most 256 pairs are alive, or 512 in short contexts."""
+    _run(tmp_path, r"""
+        int main() {
+            int fewer = 0;
+            for (int hd : {64, 128})
+                for (int H = 1; H * hd <= 8192; ++H)
+                    for (int mb = 1; mb <= 300; ++mb)
+                        for (int ctx : {40, 300, 700, 2000}) {
+                            ss::AttentionPlan strip{};
+                            for (int n = mb; n >= 1; --n) {
+                                const ss::AttentionPlan p = ss::attention_plan(n, n, mb, H, hd, ctx);
+                                if (n < mb && n % 16 && (p.slices != strip.slices || p.split != strip.split)) {
+                                    std::printf("%d heads of %d, %d of %d rows, context %d: %d slices, %d\n", H, hd, n, mb, ctx, p.slices, strip.slices);
+                                    return 1;
+                                }
+                                strip = p;
+                                if (p.waves < (n * H <= (ctx < 600 ? 512 : 256) ? 8 : 4) || p.slices < p.waves || p.slices % p.waves) {
+                                    std::printf("%d heads of %d, %d of %d rows, context %d: %d waves, %d slices\n", H, hd, n, mb, ctx, p.waves, p.slices);
+                                    return 2;
+                                }
+                                fewer += p.waves < p.slices;
+                            }
+                        }
+            return fewer ? 0 : 3;
         }
     """)
