@@ -1621,7 +1621,7 @@ namespace {
 // A pass over a plan hands its micro-batches out longest cap first: those of one strip of rows several at a time to the
 // calling thread on lane 0, where they share their decode forwards (decode_shared_impl), the others one at a time to the lanes
 // that are left, host threads with a stream and a workspace of their own each, so that one micro-batch's kernels fill the
-// gaps between the others'; and to all lanes once nothing shares any more.  What a query receives does not depend on the
+// gaps between the others'; and to all lanes once nothing shares any more (pass_units).  What a query receives does not depend on the
 // lane, the company or the order: micro-batches are independent, failures are sorted before they are rescheduled.
 int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* prompt_offsets, int32_t n,
                    const int32_t* target_lens, const int32_t* pred_lens, int32_t bin, const ss_policy* policy,
@@ -1660,8 +1660,9 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
         char err[512] = "";            // fixed storage: recording an error allocates nothing
     };
 
-    // One lane's share of a pass.  Runs on the calling thread (lane 0) or on a thread of its own (the other lanes).
-    auto work = [&](Pass& ps, Pass::Units& units, Lane& ln, hipStream_t ls) {
+    // One lane's share of a pass, at most so many units.  Runs on the calling thread (lane 0) or on a thread of its own (the other
+    // lanes).
+    auto work = [&](Pass& ps, Pass::Units& units, int most, Lane& ln, hipStream_t ls) {
         std::vector<int32_t> mb_toks, mb_offs, mb_tl, mb_out, mb_lens, mb_ids;
         std::vector<float> mb_draws;
         std::vector<uint8_t> mb_failed;
@@ -1677,7 +1678,7 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
             ps.stop.store(1);
         };
         if (hipSetDevice(w->device) != hipSuccess) return give_up(ss::fail(SS_EDEVICE, "hipSetDevice failed"));
-        while (!ps.stop.load()) {
+        for (; most > 0 && !ps.stop.load(); --most) {
             const int at = units.next.fetch_add(1);
             if (at >= (int)units.list.size()) break;
             const std::vector<int>& unit = units.list[at];
@@ -1764,9 +1765,9 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
         }
     };
     // A lane's share with nothing escaping the thread it runs on.
-    auto work_noexcept = [&](Pass& ps, Pass::Units& units, Lane& ln, hipStream_t ls) {
+    auto work_noexcept = [&](Pass& ps, Pass::Units& units, int most, Lane& ln, hipStream_t ls) {
         try {
-            work(ps, units, ln, ls);
+            work(ps, units, most, ln, ls);
         } catch (...) {
             std::lock_guard<std::mutex> lock(ps.mu);
             if (ps.rc == SS_OK) {
@@ -1801,44 +1802,35 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
             return !gen && lanes > 1 && rows <= ss::kSharedMbRows && ss::shared_forwards_pay(w->cfg.d_model, w->cfg.d_ffn) &&
                    !ss::attention_may_widen(rows, w->cfg.n_heads, ctx + pl->mb_cap[k], w->cfg.head_dim);
         };
-        // While some share, those that cannot run beside them, one at a time: together no more than may be in flight.
-        int n_share = 0;
-        for (int k : order) n_share += can_share(k);
-        const int together = n_share == pl->n_mb ? lanes : std::max(2, lanes - 1);
-        int rows_open = 0;
-        for (int k : order) {
-            auto& sh = ps.shared.list;
-            const int rows = pl->mb_offsets[k + 1] - pl->mb_offsets[k];
-            if (!can_share(k)) {
-                ps.alone.list.push_back({k});
-            } else if (!sh.empty() && (int)sh.back().size() < together && rows_open + rows <= ss::kSharedRows) {
-                sh.back().push_back(k);
-                rows_open += rows;
-            } else {
-                sh.push_back({k});
-                rows_open = rows;
-            }
+        std::vector<int> rows((size_t)pl->n_mb);
+        std::vector<char> share((size_t)pl->n_mb);
+        for (int k = 0; k < pl->n_mb; ++k) {
+            rows[k] = pl->mb_offsets[k + 1] - pl->mb_offsets[k];
+            share[k] = can_share(k);
         }
-        const int beside = ps.shared.list.empty() ? lanes - 1 : std::min(lanes - together, (int)ps.alone.list.size());
+        ss::PassUnits units = ss::pass_units(order, rows, share, lanes);
+        ps.alone.list = std::move(units.alone);
+        ps.shared.list = std::move(units.shared);
         std::thread others[kLanes];   // fixed storage: from here on nothing can throw past the joins
         int n_others = 0;
+        auto left = [&] { return std::max(0, (int)ps.alone.list.size() - ps.alone.next.load()); };
         auto start = [&](int up_to) {   // lanes 1 .. up_to
             while (n_others < up_to) {
                 const int l = n_others + 1;
                 try {
-                    others[n_others] = std::thread([&, l] { work_noexcept(ps, ps.alone, w->lane[l], w->lane[l].stream); });
+                    others[n_others] = std::thread([&, l] { work_noexcept(ps, ps.alone, pl->n_mb, w->lane[l], w->lane[l].stream); });
                     ++n_others;
                 } catch (...) {   // no further thread to be had: the pass runs on those it has
                     break;
                 }
             }
         };
-        start(beside);
-        if (!ps.shared.list.empty()) {
-            work_noexcept(ps, ps.shared, w->lane[0], s);
-            start(std::min(lanes - 1, beside + std::max(0, (int)ps.alone.list.size() - ps.alone.next.load())));
+        for (int beside : units.beside) {
+            start(std::min(beside, n_others + left()));
+            work_noexcept(ps, ps.shared, 1, w->lane[0], s);
         }
-        work_noexcept(ps, ps.alone, w->lane[0], s);
+        start(std::min(lanes, n_others + left()) - 1);
+        work_noexcept(ps, ps.alone, pl->n_mb, w->lane[0], s);
         for (int i = 0; i < n_others; ++i) others[i].join();
         if (ps.rc != SS_OK) {
             ss::set_missing_bytes(ps.missing);

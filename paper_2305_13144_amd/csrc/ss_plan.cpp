@@ -231,6 +231,38 @@ int shared_context(const SharedShape* mb, int n_mb, int g)
     return ctx;
 }
 
+PassUnits pass_units(const std::vector<int>& order, const std::vector<int>& rows, const std::vector<char>& can_share, int lanes)
+{
+    int n_share = 0;
+    for (int k : order) n_share += can_share[k];
+    const int together = n_share == (int)order.size() ? lanes : std::max(2, lanes - 1);
+    std::vector<std::vector<int>> units;
+    std::vector<int> unit_of(rows.size(), -1);
+    int rows_open = 0;
+    for (int k : order) {
+        if (!can_share[k]) continue;
+        if (units.empty() || (int)units.back().size() >= together || rows_open + rows[k] > kSharedRows) {
+            units.emplace_back();
+            rows_open = 0;
+        }
+        unit_of[k] = (int)units.size() - 1;
+        units.back().push_back(k);
+        rows_open += rows[k];
+    }
+    PassUnits p;
+    for (int k : order)
+        if (unit_of[k] < 0 || units[unit_of[k]].size() < 2) p.alone.push_back({k});
+    for (auto& u : units)
+        if (u.size() > 1) p.shared.push_back(std::move(u));
+    p.beside.resize(p.shared.size());
+    int most = 0;
+    for (size_t u = p.shared.size(); u-- > 0;) {
+        most = std::max(most, (int)p.shared[u].size());
+        p.beside[u] = lanes - most;
+    }
+    return p;
+}
+
 size_t gemm_partial_rows_bound(int n_max)
 {
     // up to kSweepMaxRows rows: at most kSmallMaxKsplit slices; the block kernel: 4 up to kBlockRows4 rows, 2 up to

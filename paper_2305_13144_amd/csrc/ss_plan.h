@@ -4,6 +4,7 @@
 #define SS_PLAN_H
 
 #include <cstddef>
+#include <vector>
 
 namespace ss {
 
@@ -110,6 +111,15 @@ int shared_context(const SharedShape* mb, int n_mb, int g);
 // 512 wide 22.4 / 27.3, 12 layers 1024 wide (25 MB a layer) 74.5 / 85.4, 6 layers 2048 wide (101 MB) 63.6 / 61.8 and 31.7 / 26.3,
 // 4 layers 3072 wide 69.9 / 54.6, 4 layers of 7B 121 / 82 and 64 / 35.
 constexpr bool shared_forwards_pay(int d, int F) { return ((size_t)4 * d * d + (size_t)3 * d * F) * 2 >= (size_t)50 << 20; }
+
+// How a group pass hands out its micro-batches, given in the order of their length: those that share their decode forwards, as many
+// as may be in flight, or one fewer if others are there to run beside them; and those that run one at a time, the left-over that
+// found no company among them.  beside[u]: lanes that may run while shared unit u and those after it do.
+struct PassUnits {
+    std::vector<std::vector<int>> shared, alone;
+    std::vector<int> beside;
+};
+PassUnits pass_units(const std::vector<int>& order, const std::vector<int>& rows, const std::vector<char>& can_share, int lanes);
 
 // Testing aid: 0 = choose per shape (default), 1 = never use the sweep kernel, 2 = use it for every
 // projection of at most kSweepMaxRows rows.
