@@ -156,7 +156,8 @@ void ss_weights_destroy(ss_weights* w);
  *   of the call is used for one of them (or those that share); the others run on streams the handle owns.  The call returns
  *   when all are done.  Device time in the statistics is summed per micro-batch, that of shared forwards counted once, and
  *   can exceed the wall time.  Device memory: one workspace and key/value cache per lane in use, each as large as the
- *   largest micro-batch, or micro-batches together, that lane has run.
+ *   largest micro-batch, or micro-batches together, that lane has run; a group that cannot have that much runs again without
+ *   sharing, which takes one micro-batch's a lane.
  *   option SS_OPT_WEIGHT_COPIES, value = 0 or 1: the handle's 12-bit weight copies.  0 gives their memory back; 1 makes
  *   those that it has not got, under the rule above (at most an eighth of the device memory that is free now; otherwise
  *   none, and still SS_OK).  A new handle has them (1).  A call that needed their memory, on this handle or on another of

@@ -1623,9 +1623,11 @@ namespace {
 // that are left, host threads with a stream and a workspace of their own each, so that one micro-batch's kernels fill the
 // gaps between the others'; and to all lanes once nothing shares any more (pass_units).  What a query receives does not depend on the
 // lane, the company or the order: micro-batches are independent, failures are sorted before they are rescheduled.
+//   may_share, *shared   whether micro-batches may share their forwards, and whether any were to
 int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* prompt_offsets, int32_t n,
                    const int32_t* target_lens, const int32_t* pred_lens, int32_t bin, const ss_policy* policy,
-                   const ss_gen_opts* gen, int32_t* out_tokens, int32_t* out_lens, ss_group_stats* stats, hipStream_t s)
+                   const ss_gen_opts* gen, int32_t* out_tokens, int32_t* out_lens, ss_group_stats* stats, hipStream_t s,
+                   bool may_share, bool* shared)
 {
     using clk = std::chrono::steady_clock;
     const auto t_plan0 = clk::now();
@@ -1799,7 +1801,7 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
             int ctx = 0;
             for (int r = 0; r < rows; ++r)
                 ctx = std::max(ctx, prompt_offsets[pl->query_idx[b0 + r] + 1] - prompt_offsets[pl->query_idx[b0 + r]]);
-            return !gen && lanes > 1 && rows <= ss::kSharedMbRows && ss::shared_forwards_pay(w->cfg.d_model, w->cfg.d_ffn) &&
+            return may_share && lanes > 1 && rows <= ss::kSharedMbRows && ss::shared_forwards_pay(w->cfg.d_model, w->cfg.d_ffn) &&
                    !ss::attention_may_widen(rows, w->cfg.n_heads, ctx + pl->mb_cap[k], w->cfg.head_dim);
         };
         std::vector<int> rows((size_t)pl->n_mb);
@@ -1811,6 +1813,7 @@ int run_group_impl(ss_weights* w, const int32_t* prompt_tokens, const int32_t* p
         ss::PassUnits units = ss::pass_units(order, rows, share, lanes);
         ps.alone.list = std::move(units.alone);
         ps.shared.list = std::move(units.shared);
+        *shared = *shared || !ps.shared.list.empty();
         std::thread others[kLanes];   // fixed storage: from here on nothing can throw past the joins
         int n_others = 0;
         auto left = [&] { return std::max(0, (int)ps.alone.list.size() - ps.alone.next.load()); };
@@ -1880,8 +1883,19 @@ extern "C" int ss_run_group(ss_weights* w, const int32_t* prompt_tokens, const i
         if (target_lens[i] < 1 || target_lens[i] > policy->base_len)
             return ss::fail(SS_EINVAL, "target_lens[%d] outside [1, base_len]", i);
     return with_memory(w, [&] {
-        return run_group_impl(w, prompt_tokens, prompt_offsets, n, target_lens, pred_lens, bin, policy, nullptr,
-                              out_tokens, out_lens, stats, s);
+        // Micro-batches that share hold their keys and values on one lane together, and the other lanes hold theirs: more than
+        // one each.  Where that is not to be had the group runs again with one each.
+        bool shared = false;
+        auto run = [&](bool may_share) {
+            return run_group_impl(w, prompt_tokens, prompt_offsets, n, target_lens, pred_lens, bin, policy, nullptr,
+                                  out_tokens, out_lens, stats, s, may_share, &shared);
+        };
+        const int rc = run(true);
+        if (rc != ss::kNoDeviceMemory || !shared) return rc;
+        (void)hipGetLastError();
+        for (Lane& l : w->lane) l.ws.release();
+        ss::clear_error();
+        return run(false);
     });
 }
 
@@ -1901,8 +1915,9 @@ extern "C" int ss_run_group_generate(ss_weights* w, const int32_t* prompt_tokens
     Lane& ln = w->lane[0];
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : ln.stream;
     return with_memory(w, [&] {
+        bool shared = false;
         return run_group_impl(w, prompt_tokens, prompt_offsets, n, nullptr, pred_lens, bin, policy, opts, out_tokens,
-                              out_lens, stats, s);
+                              out_lens, stats, s, false, &shared);
     });
 }
 

@@ -147,6 +147,49 @@ def child_lanes(c):
         c.budget(None)
 
 
+def child_shared_forwards(c):
+    """A group whose micro-batches share their decode forwards, with memory for one micro-batch a lane but not for the joint ones
+    beside others: it runs without sharing, and gives the same tokens."""
+    shape = c.synth.ModelShape("share", 2, 2048, 32, 64, 5504, 8000)
+    tensors = c.synth.make_weights(shape, seed=7, threads=8)
+    rng = c.np.random.default_rng(4)
+    plen, small, large = 10, 256, 128
+    targets = c.np.repeat([small, large], [4 * 16, 12 * 32]).astype(c.np.int32)   # four micro-batches of 16, twelve of 32
+    toks = rng.integers(0, shape.vocab, len(targets) * plen).astype(c.np.int32)
+    offs = (c.np.arange(len(targets) + 1) * plen).astype(c.np.int32)
+    pol = c.ss.make_policy(("SORT", "BIN", "FCR", "VBS"), 16, small, 32)
+
+    def handle():
+        w = c.ss.Weights(shape, tensors)
+        w.set_option(c.ss.SS_OPT_WEIGHT_COPIES, 0)
+        return w
+
+    run = lambda w: c.ss.ss_run_group(w, toks, offs, targets, targets, 8, pol)
+    w = handle()
+    before = c.live()
+    r = run(w)
+    together, want = c.live() - before, r["tokens"]
+    assert r["stats"]["n_mb_first"] == 16
+    w.close()
+    w = handle()
+    before = c.live()
+    for rows, new in ((16, small), (32, large)):
+        c.ss.ss_decode_microbatch(w, toks[:rows * plen], offs[:rows + 1], new, c.np.full(rows, 2, c.np.int32))
+    lane = c.live() - before                     # what one lane takes
+    w.close()
+    assert 4 * lane + 8 * MB < together, (lane, together)
+    w = handle()
+    c.budget(4 * lane + 8 * MB)
+    assert c.np.array_equal(run(w)["tokens"], want)
+    w.close()
+    w = handle()
+    c.budget(2 * lane)
+    c.out_of_memory(lambda: run(w))
+    c.budget(None)
+    assert c.np.array_equal(run(w)["tokens"], want)
+    w.close()
+
+
 def child_other_handles(c):
     """A new handle, and a call on another one, take the copies of the handles that are there."""
     a = c.weights()
