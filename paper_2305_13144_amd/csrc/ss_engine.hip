@@ -604,7 +604,7 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
     const int Fp = ss::padded_k(F);
 
     // small models: a row's whole step in one workgroup
-    if (decode && !d_sel && !d_nsel && n_sel == n && ss::row_step_plan(c.n_layers, d, F, V, n, ln.max_ctx, w->n_cu)) {
+    if (decode && !d_sel && !d_nsel && n_sel == n && ss::row_step_plan(c.n_layers, d, F, V, n, ln.max_ctx, w->n_cu, hd)) {
         const bool sample = ln.cur_inv_temp > 0.f;
         ss::RowStepArgs a = row_step_args(w, ln);
         a.am = ln.cur_choose && !sample ? st.am : nullptr;
@@ -850,9 +850,14 @@ int decode_microbatch_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_
         std::sort(sorted_limit.begin(), sorted_limit.end());
         // small models: all steps of a row in one launch where every one of them would go that way
         const ss_model_cfg& c = w->cfg;
-        const int n_first = compact ? (int)(sorted_limit.end() - std::upper_bound(sorted_limit.begin(), sorted_limit.end(), 1)) : B;
-        const bool at_once = steps > 1 && ss::row_step_plan(c.n_layers, c.d_model, c.d_ffn, c.vocab, n_first,
-                                                            ln.prompt_max_len + steps - 1, w->n_cu);
+        auto live = [&](int g) {   // rows alive for forward g: all of them, or with compaction those that owe more than g tokens
+            return compact ? (int)(sorted_limit.end() - std::upper_bound(sorted_limit.begin(), sorted_limit.end(), g)) : B;
+        };
+        const int n_first = live(1);
+        auto in_rows = [&](int n) {   // at the longest context; shorter ones, and counts of rows in between, then go that way too
+            return ss::row_step_plan(c.n_layers, c.d_model, c.d_ffn, c.vocab, n, ln.prompt_max_len + steps - 1, w->n_cu, c.head_dim);
+        };
+        const bool at_once = steps > 1 && in_rows(n_first) && in_rows(live(steps - 1));
         if (at_once) {
             ss::RowStepArgs a = row_step_args(w, ln);
             a.am = st.am;
@@ -861,10 +866,7 @@ int decode_microbatch_impl(const ss_weights* w, Lane& ln, const int32_t* prompt_
             ss::launch_row_step(st, a, c.head_dim, n_first, s);
         }
         for (int g = 1; g < steps; ++g) {
-            // rows alive for forward g: all of them, or with compaction those that owe more than g tokens
-            int n_live = B;
-            if (compact)
-                n_live = (int)(sorted_limit.end() - std::upper_bound(sorted_limit.begin(), sorted_limit.end(), g));
+            const int n_live = live(g);
             row_steps += n_live;
             if (at_once) continue;
             ln.max_ctx = ln.prompt_max_len + g;

@@ -155,14 +155,37 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
     return p;
 }
 
-// A workgroup of k_row_step reads the whole model and its row's slots by itself: some 75 bytes per ns of weights over all its
-// phases, 61 of slots, where a launch of the other kernels costs 3.4 us.  So 340 KB of weights, or half as much of slots, for each
-// launch that it replaces.  Steps in microseconds, launches / this kernel: tiny (2 layers, 256 wide, 3.6 MB) 16 rows at context 20
-// 63.0 / 48.1, 200 68.4 / 59.7, 500 72.6 / 67.1, 1000 76.8 / 80.9, 250 rows 103 / 58; 2 layers 128 wide 61.5 / 35.9; 4 layers 256 wide
-// 117 / 95.  (1 layer 512 wide, 7.5 MB, is 44 in launches.)
-constexpr size_t kRowBytesPerLaunch = (size_t)340 << 10;
+// Both ways to take a decode step of a small model, in microseconds, fitted to 1510 timings of either on 160 models of 1 to 16
+// layers, 64 to 512 wide, 1 to 250 rows, contexts of 8 to 1500 (row step 5 % off in the root mean square, launches 5 %).  The row
+// step is taken where it comes out 5 % ahead: one of those points is then more than 2 % slower than the other way (4.5 %), the
+// mean over all is 0.23 % above that of the better way.  Microseconds, launches / row step: tiny (2 layers, 256 wide, 3.6 MB) 16 rows at context 8
+// 65.0 / 47.8, 200 68.4 / 59.4, 600 72.7 / 70.4, one row 61.0 / 46.8, 600 65.5 / 68.0, 100 rows 8 99 / 50; 1 layer 64 wide, 6000 ids 35.0 /
+// 40.5, 2000 ids 34.2 / 25.7; 4 layers 64 wide, ffn 2048 103 / 128.
 
-bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, int n_cu)
+// A workgroup of k_row_step reads the whole model and its row's slots by itself: every pair of strips in whole groups of 8
+// k-blocks (past the end the last block again), 16 KB each at 120 GB/s; its phases wait for each other.  A head's slots go to
+// kRowWaves / heads waves, so some of them may be without.
+static double row_step_us(int n_layers, int d, int F, int V, int max_ctx, int hd)
+{
+    const double groups = row_padded(d) / 256;
+    const auto pairs = [](int strips) { return (double)((strips + 1) / 2); };
+    const double layer = (pairs(3 * d / 16) + pairs(d / 16) + pairs(F / 8)) * groups + pairs(d / 16) * (row_padded(F) / 256);
+    const double heads = d / hd, busy = heads * (int)(kRowWaves / heads) / kRowWaves;
+    return 8.0 + n_layers * (6.2 + 0.135 * layer + 0.0139 * max_ctx * d / 256 / busy) + 0.135 * pairs(V / 16) * groups;
+}
+
+// The launches of the other kernels: each the time of a launch with so many strips of rows, the weights, and what the slots add
+// (never more than in the row step: a context that grows does not turn a micro-batch back to it).
+static double step_launches_us(int n_layers, int d, int F, int V, int n_rows, int max_ctx)
+{
+    const int strips = (n_rows + 15) / 16;
+    const double launch = strips > 4 ? 4.4 + 0.5 * d / 256 : 3.0 + 0.24 * strips;
+    const double mb = (n_layers * (4.0 * d * d + 3.0 * d * F) + (double)V * d) * 2e-6;
+    return (7 * n_layers + 4) * launch + 0.6 * mb +
+           std::min(0.005 + 0.003 * (strips - 1), 0.0139) * n_layers * max_ctx * d / 256;
+}
+
+bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, int n_cu, int hd)
 {
     // the testing aids choose among the projection kernels: they get those
     if (gemm_mode() != 0 || g_block_tile.load(std::memory_order_relaxed) >= 0 || !g_sweep_split.load(std::memory_order_relaxed) ||
@@ -170,8 +193,7 @@ bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, i
         return false;
     if (n_layers > kRowMaxLayers || d > kRowMaxModel || F > kRowMaxFfn) return false;
     if ((n_rows + 15) / 16 * 16 > n_cu) return false;   // a unit each, by whole strips like the other plans
-    const size_t layer = ((size_t)4 * d * d + (size_t)3 * d * F) * 2 + 2 * (size_t)max_ctx * d * 4;
-    return n_layers * layer + (size_t)V * d * 2 <= (size_t)(7 * n_layers + 4) * kRowBytesPerLaunch;
+    return 1.05 * row_step_us(n_layers, d, F, V, max_ctx, hd) <= step_launches_us(n_layers, d, F, V, n_rows, max_ctx);
 }
 
 // Few pairs leave most of the chip idle over a long context; more workgroups each, and a launch that joins them.  By the

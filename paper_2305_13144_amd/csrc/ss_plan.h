@@ -55,7 +55,7 @@ constexpr int kRowMaxLayers = 16;
 constexpr int kRowWaves = 8;
 constexpr int kRowMaxModel = 64 * kRowWaves;   // model width: a thread per element, and at least a wave per head
 constexpr int kRowMaxFfn = 8192;
-bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, int n_cu);
+bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, int n_cu, int hd = 64);
 constexpr int row_padded(int k) { return (k + 255) / 256 * 256; }   // whole groups of 8 k-blocks
 // Its LDS: residual row, query, rotation, attention sums of every wave, the two projection inputs, this position's key and value.
 constexpr size_t row_step_lds_bytes(int d, int Fp, int hd)
