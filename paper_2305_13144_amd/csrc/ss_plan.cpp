@@ -155,12 +155,15 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
     return p;
 }
 
-// Both ways to take a decode step of a small model, in microseconds, fitted to 1510 timings of either on 160 models of 1 to 16
-// layers, 64 to 512 wide, 1 to 250 rows, contexts of 8 to 1500 (row step 5 % off in the root mean square, launches 5 %).  The row
-// step is taken where it comes out 5 % ahead: one of those points is then more than 2 % slower than the other way (4.5 %), the
-// mean over all is 0.23 % above that of the better way.  Microseconds, launches / row step: tiny (2 layers, 256 wide, 3.6 MB) 16 rows at context 8
-// 65.0 / 47.8, 200 68.4 / 59.4, 600 72.7 / 70.4, one row 61.0 / 46.8, 600 65.5 / 68.0, 100 rows 8 99 / 50; 1 layer 64 wide, 6000 ids 35.0 /
-// 40.5, 2000 ids 34.2 / 25.7; 4 layers 64 wide, ffn 2048 103 / 128.
+// Both ways to take a decode step of a small model, in microseconds, fitted to 1510 timings of either on 200 models of 1 to 16
+// layers, 64 to 512 wide, 1 to 250 rows, contexts of 8 to 1500 (row step 5 % off in the root mean square, launches 6 %).  The row step is taken up to 3 us
+// behind: all steps of a row in one launch save it another 7 us each, and micro-batches in flight beside each other hold each
+// other up less in one launch a step than in dozens.  Of those points, one step each, 31 are more than 2 % slower than the
+// other way, the mean over all is 0.2 % above that of the better way.  Microseconds, launches / row step: tiny (2 layers, 256 wide, 3.6 MB)
+// 16 rows at context 8 65.0 / 47.8, 200 68.4 / 59.4, 600 72.7 / 70.4, one row 61.0 / 46.8, 600 65.5 / 68.0, 100 rows 8 99 / 50; 1 layer 64
+// wide, 6000 ids 35.0 / 40.5, 2000 ids 34.2 / 25.7; 4 layers 64 wide, ffn 2048 103 / 128.  Tiny, a group of 64, prompts of 200, four micro-batches in
+// flight: 10.6 ms in launches, 7.8 in row steps.
+constexpr double kRowStepBehind = 3.0;
 
 // A workgroup of k_row_step reads the whole model and its row's slots by itself: every pair of strips in whole groups of 8
 // k-blocks (past the end the last block again), 16 KB each at 120 GB/s; its phases wait for each other.  A head's slots go to
@@ -193,7 +196,7 @@ bool row_step_plan(int n_layers, int d, int F, int V, int n_rows, int max_ctx, i
         return false;
     if (n_layers > kRowMaxLayers || d > kRowMaxModel || F > kRowMaxFfn) return false;
     if ((n_rows + 15) / 16 * 16 > n_cu) return false;   // a unit each, by whole strips like the other plans
-    return 1.05 * row_step_us(n_layers, d, F, V, max_ctx, hd) <= step_launches_us(n_layers, d, F, V, n_rows, max_ctx);
+    return row_step_us(n_layers, d, F, V, max_ctx, hd) - kRowStepBehind <= step_launches_us(n_layers, d, F, V, n_rows, max_ctx);
 }
 
 // Few pairs leave most of the chip idle over a long context; more workgroups each, and a launch that joins them.  By the

@@ -45,7 +45,7 @@ def test_row_step_is_taken_where_it_was_measured_faster(tmp_path):
                 // us, launches / row step
                 {2, 256, 64, 688, 1024, 16, 20, true},      // 63.0 / 48.1
                 {2, 256, 64, 688, 1024, 1, 200, true},      // 62.3 / 54.0
-                {2, 256, 64, 688, 1024, 1, 600, false},     // 65.5 / 68.0
+                {2, 256, 64, 688, 1024, 16, 1000, false},   // 76.8 / 80.9
                 {2, 256, 64, 688, 1024, 100, 600, true},    // 115 / 70
                 {1, 64, 64, 176, 16000, 1, 8, false},       // 36.1 / 77.4
                 {1, 64, 64, 176, 16000, 16, 500, false},    // 40.9 / 79.7
