@@ -41,8 +41,9 @@ void ss_set_verbose(int32_t level);
  * the block kernel from its largest tile (256 x 256, prompt forwards of more than 880 token-rows); both for A/B
  * measurements.  Adding 16 to 80 makes the block kernel use one of its five tiles throughout (16: 256 x 256 token-rows x
  * columns, 32: 256 x 192, 48: 128 x 256, 64: 128 x 192, 80: 128 x 128).
- * Results agree to the rounding differences between launch shapes (about 1e-3 of the largest logit).  Process-wide (atomic integers, read when a forward is planned: set it
- * between calls, not during one); other values are ignored. */
+ * Any mode but 0 also keeps small models from taking a row's whole decode step in one workgroup.
+ * Results agree to the rounding differences between launch shapes (about 1e-3 of the largest logit).  Process-wide (atomic
+ * integers, read when a forward is planned: set it between calls, not during one); other values are ignored. */
 void ss_set_gemm_mode(int32_t mode);
 
 /* ------------------------------------------------------------------ scheduler (host only) */
@@ -202,8 +203,7 @@ typedef struct {
  *                   with it the live batch shrinks.  Lengths and flags are identical either way; tokens
  *                   are too, except where a row's two largest logits lie within the rounding difference
  *                   between two launch shapes (about 1e-3 of the largest logit) once the live batch has
- *                   shrunk past a multiple of 16 rows (or, in models of more than 32 heads, to where rows
- *                   times heads is 512 or less).
+ *                   shrunk past a multiple of 16 rows.
  *   out_tokens      host, int32[B*max_new] row-major; -1 after the emitted length
  *   out_lens        host, int32[B]   = min(target, max_new)
  *   out_failed      host, uint8[B]   = target > max_new  (an FCR failure: to be recomputed later)
@@ -314,8 +314,9 @@ typedef struct {
  * shrinking of the live batch and the sampling all run on the device; the host only polls a counter.
  * Given the same weights, prompts and draws the output of a row does not depend on flags, on sync_every or on
  * what the other rows hold; across batch compositions that change the launch shapes (the total prompt length, the
- * longest prompt, the number of 16-row strips; rows times heads past 192 or 512) logits agree to about 1e-3 of the
- * largest, and a sampled token can differ where its draw lies within that of an interval edge.
+ * longest prompt, the number of 16-row strips; the micro-batch's rows times heads past 48, 96 or 192 with long contexts; in
+ * models of up to 512 wide also, by the same counts, whether a row's step is one workgroup's) logits agree to about 1e-3 of
+ * the largest, and a sampled token can differ where its draw lies within that of an interval edge.
  *   out_lens    host, int32[B]: tokens emitted (the end-of-sequence token included)
  *   out_failed  host, uint8[B]: the row was still unfinished after max_new tokens (Sec. 4.1 failure)
  * Other arguments, ownership and errors as ss_decode_microbatch; additionally SS_EINVAL for a NULL opts,
@@ -361,7 +362,8 @@ int ss_bench_decode_steps_in_flight(ss_weights* w, const int32_t* prompt_tokens,
 
 /*
  * Measurement entry point: the projection kernels of one decode step alone.  Launches, back to back on
- * one stream, exactly the matrix kernels a B-row decode forward launches (per layer q|k|v, o, gate|up
+ * one stream, exactly the matrix kernels a B-row decode forward launches where its rows do not take their steps in
+ * one workgroup each, as those of small models do (per layer q|k|v, o, gate|up
  * with the SwiGLU epilogue, down; then the LM head) with the same launch configuration, on whatever the
  * activation buffers currently hold, `iters` times.  Every matrix is streamed once per iteration, in the form that
  * B rows read: the 12-bit copies up to 96 rows where there are any (ss_bench_read_stream gives their bytes), else 2

@@ -804,13 +804,12 @@ __device__ __forceinline__ void wait_copies_and_meet()
     asm volatile("" ::: "memory");
 }
 
-//
+constexpr int kBlockOwnFrom = 4;   // row tiles per die from which a die keeps its own
+
 // Unsliced launches finish their results themselves.  EPI_RESIDUAL adds the sums to the residual stream in place, EPI_QKV
 // rotates q and k and puts q, k and v where the attention reads them, instead of writing fp32 sums for the next launch to
 // read.  12311 token-rows, 7B, per layer: the rotation launch (184 us) is gone, the norms take 108 us instead of 167, o
 // and down 716 instead of 680, q|k|v 1112 instead of 1097 (k_rope_append and the sums in the norm stay for sliced launches).
-constexpr int kBlockOwnFrom = 4;   // row tiles per die from which a die keeps its own
-
 template <int MS, int NS, int WM, int WN, int ST, int EPI>
 __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_block(GemmArgs a, QkvOut qo, int kb_per_slice,
                                                                                   int n_ntiles, int n_mtiles)
@@ -1398,7 +1397,7 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
 // Decode forwards: the (token-row, head) workgroup first finishes its own slice of the q|k|v projection
 // (sums the k-slices, rotates q and k at the row's position, appends k and v to the row's slab), then
 // attends.  Saves a launch and the round trip of q through HBM for every layer of every step.
-// NW waves per workgroup: 8 (256 cache slots per round trip) when the grid is small enough for every workgroup to
+// PW waves per workgroup: 8 (256 cache slots per round trip) when the grid is small enough for every workgroup to
 // be resident with room to spare, 4 (128 slots) for larger batches, whose many workgroups already fill the chip, and 16
 // (512 slots) when the micro-batch has less than one workgroup per compute unit and a context exceeds 256 slots: what a
 // unit has in flight is then all that counts.
@@ -1512,8 +1511,9 @@ __global__ __launch_bounds__(64) void k_attention_join(MbState st, const float* 
 // layers.  So the loads go on over the barriers: there is one loop for all matrices, and the block that a wave has used
 // last is replaced by the first one it needs of the next matrix.  (A loop per matrix is 5000 instructions, spills, and waits
 // for everything at each end: 58 us.)  Tiny model, 16 rows, context 20: 63 us as 19 launches -> 48; 250 rows 103 -> 58.
-// With a.steps a launch takes its rows to their ends (their limits are known and nothing is compacted or polled): group of 16,
-// 47 forwards, 2.83 -> 2.50 ms, the weights' first blocks wait in registers when a step begins.
+// With a.steps a launch takes its rows to their ends, where those are known and nothing is sampled or polled (with compaction a
+// row leaves at its own end, else all stay to the last one's): group of 16, 47 forwards, 2.83 -> 2.50 ms, the weights' first blocks
+// wait in registers when a step begins.
 // A wave owns pairs of output strips (the two halves of a head's strip, gate and up; two sums under way at once); the
 // matrix instruction's activation operand is the row's vector for all of its 16 columns, so that every lane ends up with
 // valid sums.  Rounding as in the other kernels: residual stream, sums, rotation and softmax in fp32; projection inputs,
