@@ -1398,7 +1398,7 @@ __global__ __launch_bounds__(256, QT == 2 ? 2 : 3) void k_attention_prompt(MbSta
 // (sums the k-slices, rotates q and k at the row's position, appends k and v to the row's slab), then
 // attends.  Saves a launch and the round trip of q through HBM for every layer of every step.
 // PW waves per workgroup: 8 (256 cache slots per round trip) when the grid is small enough for every workgroup to
-// be resident with room to spare, 4 (128 slots) for larger batches, whose many workgroups already fill the chip, and 16
+// be resident with room to spare, 4 (128 slots) for larger batches, whose many workgroups already fill the chip, or 2, and 16
 // (512 slots) when the micro-batch has less than one workgroup per compute unit and a context exceeds 256 slots: what a
 // unit has in flight is then all that counts.
 // SPLIT: the workgroups of a pair along z share out its slots (few pairs, long contexts: see attention_split); the one that holds
@@ -1422,7 +1422,6 @@ __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const 
     const int row = st.tr_row[j], pos = st.tr_pos[j];
     if (j >= count) return;
     const size_t base = (size_t)st.row_so[row] * d + (size_t)h * st.row_cap[row] * HD;
-    const int which = threadIdx.x / HALF, e = threadIdx.x % HALF;   // 0 q, 1 k, 2 v
     int begin = 0, slots = pos + 1;
     float* share = nullptr;
     if (SPLIT) {
@@ -1435,7 +1434,9 @@ __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const 
             return;
         }
     }
-    if (which < 3 && (!SPLIT || which == 0 || begin + slots == pos + 1)) {
+    auto finish = [&](int t) {
+        const int which = t / HALF, e = t % HALF;   // 0 q, 1 k, 2 v
+        if (which >= 3 || (SPLIT && which != 0 && begin + slots != pos + 1)) return;
         const float* p = part + (size_t)j * 3 * d + (size_t)which * d + h * HD + qkv_col(e);
         float pa[kNormMaxSplit], pb[kNormMaxSplit];   // every k-slice load issued before the first add
 #pragma unroll
@@ -1463,7 +1464,9 @@ __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const 
             dst[0] = f2kv(a);
             dst[HALF] = f2kv(b);
         }
-    }
+    };
+    finish(threadIdx.x);
+    if (64 * PW < 3 * HALF) finish(threadIdx.x + 64 * PW);
     __syncthreads();   // the new key/value slot and q are visible to the whole workgroup
     attend<HD, NW, PW, SPLIT>(qs, sc, red, oacc, kc + base + (size_t)begin * HD, vc + base + (size_t)begin * HD, slots, out, j, h * HD, d,
                               share);
@@ -2272,14 +2275,18 @@ void launch_attention_decode(const MbState& st, const float* qkv_part, int kspli
     if (hd == 128) {
         if (p.split > 1) launch_attention_decode_inst<128, 8, 8, true>(SS_ATTN_ARGS);
         else if (p.slices == 16) launch_attention_decode_inst<128, 16>(SS_ATTN_ARGS);
+        else if (p.slices == 8 && p.waves == 2) launch_attention_decode_inst<128, 8, 2>(SS_ATTN_ARGS);
         else if (p.slices == 8 && p.waves == 4) launch_attention_decode_inst<128, 8, 4>(SS_ATTN_ARGS);
         else if (p.slices == 8) launch_attention_decode_inst<128, 8>(SS_ATTN_ARGS);
+        else if (p.waves == 2) launch_attention_decode_inst<128, 4, 2>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<128, 4>(SS_ATTN_ARGS);
     } else {
         if (p.split > 1) launch_attention_decode_inst<64, 8, 8, true>(SS_ATTN_ARGS);
         else if (p.slices == 16) launch_attention_decode_inst<64, 16>(SS_ATTN_ARGS);
+        else if (p.slices == 8 && p.waves == 2) launch_attention_decode_inst<64, 8, 2>(SS_ATTN_ARGS);
         else if (p.slices == 8 && p.waves == 4) launch_attention_decode_inst<64, 8, 4>(SS_ATTN_ARGS);
         else if (p.slices == 8) launch_attention_decode_inst<64, 8>(SS_ATTN_ARGS);
+        else if (p.waves == 2) launch_attention_decode_inst<64, 4, 2>(SS_ATTN_ARGS);
         else launch_attention_decode_inst<64, 4>(SS_ATTN_ARGS);
     }
 #undef SS_ATTN_ARGS

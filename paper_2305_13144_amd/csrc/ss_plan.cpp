@@ -220,15 +220,18 @@ int attention_split(int mb_rows, int H, int hd, int max_ctx)
 }
 
 namespace {
-// Waves that take the 8 slices of a pair; any number gives the same sums.  8 while all pairs are resident with room to spare, 4
-// beyond.  With somewhat more pairs than the chip's 256 units and long contexts, the units that have two pairs decide, and a
-// unit's lone pair is not to take the memory's time from them: 4 waves as well, from 650 slots of 128 elements or 1300 of 64.
-// Decode step per layer, us, 8 waves / 4: 32 heads of 128, 9 rows, context 500 71.6 / 71.4, 900 82.8 / 82.3, 1500 108.8 / 104.3, 3000 155.3 /
-// 143.0; 12 rows 300 66.8 / 67.3, 900 92.3 / 89.9, 1500 112.8 / 110.3; 14 rows 1500 117.9 / 118.2, 3000 179.6 / 180.9; 8 rows 900 76.2 /
-// 79.5, 1500 94.8 / 100.1; heads of 64, 32 x 11 900 54.3 / 54.5, 1500 65.0 / 63.5; 16 x 18 900 45.4 / 47.7, 1500 59.5 / 59.2, 3000 82.4 / 79.8.
+// Waves that take the slices of a pair; any number gives the same sums.  8 while all pairs are resident with room to spare, 4
+// beyond.  With somewhat more pairs than the chip's 256 units, or than two for each, and long contexts, the units that have a pair
+// more decide, and those that have not are not to take the memory's time from them: half as many waves, from 650 slots of 128
+// elements or 1300 of 64 (two for each: 1000 and 2000).  Decode step per layer, us, 32 heads of 128 unless it says otherwise:
+//   8 waves / 4   9 rows, context 500 71.6 / 71.4, 900 82.8 / 82.3, 1500 108.8 / 104.3, 3000 155.3 / 143.0; 12 rows 300 66.8 / 67.3, 900 92.3 /
+//                 89.9, 1500 112.8 / 110.3; 14 rows 1500 117.9 / 118.2, 3000 179.6 / 180.9; 8 rows 900 76.2 / 79.5, 1500 94.8 / 100.1; heads of 64,
+//                 32 x 11 900 54.3 / 54.5, 1500 65.0 / 63.5; 16 x 18 900 45.4 / 47.7, 1500 59.5 / 59.2, 3000 82.4 / 79.8
+//   4 waves / 2   17 rows 400 83.6 / 85.6, 1000 122.5 / 122.0, 1500 149.8 / 147.7, 3000 232.3 / 222.3; 20 rows 1500 158.1 / 156.3; 40 x 13 1500
+//                 155.3 / 152.3, 3000 234.0 / 224.4; heads of 64, 32 x 17 700 60.2 / 63.5, 1500 81.9 / 83.4, 2200 100.7 / 101.0, 3000 123.8 / 122.0
 int attention_waves(int pairs, int hd, int max_ctx)
 {
-    if (pairs > kAttnWideMaxGroups) return 4;
+    if (pairs > kAttnWideMaxGroups) return pairs <= 640 && max_ctx * hd > 1000 * 128 ? 2 : 4;
     return pairs > 256 && pairs <= 416 && max_ctx * hd > 650 * 128 ? 4 : 8;
 }
 }
@@ -244,8 +247,8 @@ AttentionPlan attention_plan(int n_rows, int plan_rows, int mb_rows, int H, int 
     const int split = attention_split(std::max(mb_rows, n_rows), H, hd, max_ctx);
     if (split > 1) return {8, 8, split};
     if (attention_may_widen(mb_rows, H, max_ctx, hd)) return {16, 16, 1};
-    if (!attention_wide(attention_fewest_rows(plan_rows), H)) return {4, 4, 1};
-    return {8, attention_waves(n_rows * H, hd, max_ctx), 1};
+    const int slices = attention_wide(attention_fewest_rows(plan_rows), H) ? 8 : 4;
+    return {slices, std::min(slices, attention_waves(n_rows * H, hd, max_ctx)), 1};
 }
 
 int shared_context(const SharedShape* mb, int n_mb, int g)

@@ -10,10 +10,10 @@ pytestmark = pytest.mark.gpu
 
 
 # 16 heads: 16 rows are 256 (row, head) pairs, 3 rows 48; 32 heads: 512 and 96.  40 and 48 heads: 640 and
-# 768, so 4 waves take 8 slices, and 8 waves as soon as 512 are left.  Contexts on both sides of what 8 waves have
+# 768, so 4 waves take 8 slices (2 up to 640 pairs at long contexts), and 8 waves as soon as 512 are left.  Contexts on both sides of what 8 waves have
 # in flight (256 slots of 128 elements, 512 of 64).
 @pytest.mark.parametrize("heads,head_dim,longest", [(16, 64, 600), (16, 64, 505), (32, 128, 300), (32, 128, 250),
-                                                    (40, 128, 300), (48, 64, 700)])
+                                                    (40, 128, 300), (48, 64, 700), (40, 128, 1100), (36, 64, 2100)])
 def test_rows_that_leave_do_not_change_the_others(heads, head_dim, longest):
     shape = synth.ModelShape("leave", 1, heads * head_dim, heads, head_dim, 256, 272)
     gw = ss.Weights(shape, synth.make_weights(shape, seed=8, std=0.04, threads=4))

@@ -1,6 +1,7 @@
 """Decode attention whose slots several workgroups share out (few pairs, long contexts): contexts around its beginning and around
 whole shares, short rows beside a long one (shares without a slot), both head sizes, against the oracle; few heads and short
-prompts, where the buffer of the shares is smallest; and a row's numbers while the others leave."""
+prompts, where the buffer of the shares is smallest; a row's numbers while the others leave; and the other way round, slightly more than two
+pairs for each unit, whose slots go to two waves."""
 import numpy as np
 import pytest
 
@@ -55,6 +56,23 @@ def test_rows_that_leave_do_not_change_the_others(model):
     whole = _forced(gw, seqs, plens)
     cut = _forced(gw, [seqs[0]] + [q[:len(q) - 4] for q in seqs[1:]], plens)
     assert np.array_equal(whole[:steps + 1], cut[:steps + 1])
+
+
+@pytest.mark.parametrize("pairs", [520, 640])
+@pytest.mark.parametrize("longest", [1001, 2003])   # 1000 slots of 128 elements and 2000 of 64 are the lines
+def test_two_waves_a_pair(model, pairs, longest):
+    shape, gw, om = model
+    rows = pairs // shape.n_heads
+    rng = np.random.default_rng(rows)
+    plens = rng.integers(1, 30, rows)
+    plens[[0, rows // 2]] = longest - 2, 700
+    steps = 3
+    seqs = [rng.integers(0, shape.vocab, p + steps).astype(np.int32) for p in plens]
+    got = _forced(gw, seqs, plens)
+    for i in (0, 1, rows // 2, rows - 1):
+        ref = om.teacher_forced(seqs[i], first=plens[i] - 1)
+        err = np.abs(got[i * (steps + 1):(i + 1) * (steps + 1)] - ref).max() / np.abs(ref).max()
+        assert err <= TOL, (rows, i, err)
 
 
 # Prompts of 5 tokens: activation buffers of 128 rows, the smallest there are.  4 heads of 64 and 24 rows, 2 of 128 and 42 rows
