@@ -292,8 +292,8 @@ std::vector<PackedMat*> all_matrices(ss_weights* w)
     return m;
 }
 
-// Bytes of a matrix's 12-bit copy: one group of 4 k-blocks is 3 KiB.
-size_t narrow_groups(const PackedMat& m) { return m.Kp % 128 == 0 ? (size_t)(m.N / 16) * (m.Kp / 128) : 0; }
+// Bytes of a matrix's 12-bit copy, 0 if it cannot have one.
+size_t narrow_bytes(const PackedMat& m) { return m.Kp % 128 == 0 ? (size_t)(m.N / 16) * ss::narrow_strip(m.Kp / 32) * 16 : 0; }
 
 // Allocates nothing: ss_weights_destroy, where no exception may come from, calls it.
 void drop_narrow(ss_weights* w)
@@ -317,7 +317,7 @@ int make_narrow_impl(ss_weights* w, bool any_room)
 {
     const std::vector<PackedMat*> mats = all_matrices(w);
     size_t need = 0, free_b = 0, total_b = 0;
-    for (const PackedMat* m : mats) need += narrow_groups(*m) * 3072;
+    for (const PackedMat* m : mats) need += narrow_bytes(*m);
     if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || need == 0 || (!any_room && need > free_b / 8))
         return SS_OK;
     struct Flags {
@@ -334,21 +334,22 @@ int make_narrow_impl(ss_weights* w, bool any_room)
     // matrices with a value that has no 12-bit form are found first: nothing is allocated for them, not even for a while
     hipStream_t s = w->lane[0].stream;
     for (size_t i = 0; i < mats.size(); ++i)
-        if (const size_t n = narrow_groups(*mats[i])) ss::launch_narrow_weight(mats[i]->p, nullptr, n, flags.b.as<int32_t>() + i, s);
+        if (narrow_bytes(*mats[i]))
+            ss::launch_narrow_weight(mats[i]->p, nullptr, mats[i]->N, mats[i]->Kp, flags.b.as<int32_t>() + i, s);
     HIPCHK(hipStreamSynchronize(s));
     HIPCHK(hipMemcpy(unfit.data(), flags.b.p, mats.size() * 4, hipMemcpyDeviceToHost));
     for (size_t i = 0; i < mats.size(); ++i) {
         PackedMat* m = mats[i];
-        if (narrow_groups(*m) == 0 || unfit[i]) continue;
-        if (hipMalloc(&m->pn, narrow_groups(*m) * 3072) != hipSuccess) {   // no room after all: none of them
+        if (narrow_bytes(*m) == 0 || unfit[i]) continue;
+        if (hipMalloc(&m->pn, narrow_bytes(*m)) != hipSuccess) {   // no room after all: none of them
             (void)hipGetLastError();
             m->pn = nullptr;
             HIPCHK(hipStreamSynchronize(s));
             drop_narrow(w);
             return SS_OK;
         }
-        ss::launch_narrow_weight(m->p, m->pn, narrow_groups(*m), flags.b.as<int32_t>() + i, s);
-        w->copy_bytes += narrow_groups(*m) * 3072;
+        ss::launch_narrow_weight(m->p, m->pn, m->N, m->Kp, flags.b.as<int32_t>() + i, s);
+        w->copy_bytes += narrow_bytes(*m);
     }
     HIPCHK(hipStreamSynchronize(s));
     return SS_OK;
@@ -2107,7 +2108,7 @@ int bench_read_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32_t
     uint32_t* sink = ln.ws.ints.as<uint32_t>();
     // what a small decode batch streams: the 12-bit copy where the matrix has one
     auto mat_bytes = [](const PackedMat& m) {
-        return (m.pn ? narrow_groups(m) * 3072 : (size_t)m.N * m.Kp * 2) & ~(size_t)0xffff;
+        return (m.pn ? (size_t)m.N * m.Kp / 2 * 3 : (size_t)m.N * m.Kp * 2) & ~(size_t)0xffff;
     };
     auto mat_data = [](const PackedMat& m) { return m.pn ? (const f16_t*)m.pn : m.p; };
     EventList evl;

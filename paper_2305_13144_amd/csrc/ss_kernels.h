@@ -66,9 +66,9 @@ struct GemmArgs {
 
 void launch_pack_weight(const void* src, int src_f32, f16_t* dst, int n_src, int k, int kp, int blk_stride,
                         int blk_off, int head_strips, hipStream_t s);
-// Writes the 12-bit form of n_groups groups of 4 packed k-blocks (3 KiB each); sets *unfit if a value has no such form.
-// dst == nullptr: only that.
-void launch_narrow_weight(const f16_t* src, void* dst, size_t n_groups, int32_t* unfit, hipStream_t s);
+// Writes the 12-bit form of a packed [N, Kp] matrix (Kp a multiple of 128; narrow_strip); sets *unfit if a value has no such
+// form.  dst == nullptr: only that.
+void launch_narrow_weight(const f16_t* src, void* dst, int N, int Kp, int32_t* unfit, hipStream_t s);
 void launch_cast_rows(const void* src, int src_f32, bf16_t* dst, size_t count, hipStream_t s);
 void launch_embed(const MbState& st, const bf16_t* embed, float* x, int d, int n_max, hipStream_t s);
 void launch_rmsnorm(const MbState& st, float* x, const float* part, int ksplit, size_t part_stride,

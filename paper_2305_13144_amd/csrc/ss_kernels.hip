@@ -158,18 +158,18 @@ __global__ void k_pack_weight(const void* __restrict__ src, int src_f32, f16_t* 
 // and scale their sums by 1/8, both exactly; sums of products round alike, but for the last bit of some that contain
 // weights which are subnormal as halves.  A matrix with a value of 0.25 or more (or a NaN) has no such copy and is
 // streamed as halves.
-// Layout: [strip][group of 4 k-blocks][3 planes][lane] of 16 bytes: a lane's 4 operand fragments (4 dwords each) take
+// Layout: [strip][group of 4 k-blocks][3 planes][lane] of 16 bytes, strips apart by narrow_strip: a lane's 4 operand fragments (4 dwords each) take
 // 12 dwords, 3 per fragment, read as three fully coalesced 1 KiB loads.  Of a fragment's 4 dwords the first three are
 // stored as they are, and the 8 clear bits of each hold a third of the fourth.
 // Why: a decode step of few rows is a weight stream and its bytes are its time; the 15 vector instructions that open a
-// fragment run beside it.  Measured alone, halves / 12 bits, 16 rows, 7B: q|k|v 18.7 / 14.3 us, gate|up 31.0 / 25.8, down
+// fragment run beside it.  Measured alone and without gaps between strips, halves / 12 bits, 16 rows, 7B: q|k|v 18.7 / 14.3 us, gate|up 31.0 / 25.8, down
 // 16.7 / 14.6, o 8.2 / 7.1, LM head 43.4 / 32.1; 13B gate|up 47.8 / 36.4.  With more row strips LDS reads and matrix work
 // take over (64 rows: gate|up 32.0 / 30.5, 96 rows 37.3 / 36.4), so the copies are read up to kNarrowMaxRows rows.
 constexpr unsigned kNarrowMask = 0xBFF8BFF8u;   // sign, exponent and mantissa bits of two halves
 constexpr float kNarrowScale = 0.125f;
 
 __global__ __launch_bounds__(256) void k_narrow_weight(const u32x4* __restrict__ src, u32x4* __restrict__ dst,
-                                                       size_t n_groups, int32_t* __restrict__ unfit)
+                                                       size_t n_groups, int strip_groups, int32_t* __restrict__ unfit)
 {
     const size_t total = n_groups * 64;   // one thread per group of 4 k-blocks and lane
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (size_t)gridDim.x * blockDim.x) {
@@ -197,9 +197,10 @@ __global__ __launch_bounds__(256) void k_narrow_weight(const u32x4* __restrict__
         }
         if (bad) *unfit = 1;
         if (!dst) continue;
+        const size_t at = (g / strip_groups) * narrow_strip(strip_groups * 4) + (g % strip_groups) * 192 + lane;
 #pragma unroll
         for (int p = 0; p < 3; ++p)
-            dst[(g * 3 + p) * 64 + lane] = (u32x4){o[4 * p], o[4 * p + 1], o[4 * p + 2], o[4 * p + 3]};
+            dst[at + p * 64] = (u32x4){o[4 * p], o[4 * p + 1], o[4 * p + 2], o[4 * p + 3]};
     }
 }
 
@@ -362,7 +363,7 @@ __device__ __forceinline__ void skinny_load(SkinnyFrags<MT, NB, KD, WN>& f, cons
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             const int nb = nb0 + (i < nvalid ? i : 0);
-            const u32x4* g = Wl + ((size_t)nb * (KB >> 2) + (kb >> 2)) * 192;
+            const u32x4* g = Wl + nb * narrow_strip(KB) + (size_t)(kb >> 2) * 192;
 #pragma unroll
             for (int p = 0; p < 3; ++p) f.w[i][p] = __builtin_nontemporal_load(g + p * 64);
         }
@@ -534,7 +535,7 @@ __device__ __forceinline__ void sweep_load_w(SweepSlot<NBW, KQ, WN>& f, const u3
         const int kg = min(kb, kend - 4) >> 2;
 #pragma unroll
         for (int i = 0; i < NBW; ++i) {
-            const uintptr_t wp = (uintptr_t)(Wl + ((size_t)(nb0 + i) * (KB >> 2) + kg) * 192), zp = (uintptr_t)Zl;
+            const uintptr_t wp = (uintptr_t)(Wl + (nb0 + i) * narrow_strip(KB) + (size_t)kg * 192), zp = (uintptr_t)Zl;
             const uintptr_t mask = (kb < kend && i < nvalid) ? ~(uintptr_t)0 : (uintptr_t)0;
             const u32x4* g = (const u32x4*)(zp ^ ((wp ^ zp) & mask));
 #pragma unroll
@@ -2085,10 +2086,11 @@ void launch_pack_weight(const void* src, int src_f32, f16_t* dst, int n_src, int
                        blk_stride, blk_off, head_strips);
 }
 
-void launch_narrow_weight(const f16_t* src, void* dst, size_t n_groups, int32_t* unfit, hipStream_t s)
+void launch_narrow_weight(const f16_t* src, void* dst, int N, int Kp, int32_t* unfit, hipStream_t s)
 {
+    const size_t n_groups = (size_t)(N / 16) * (Kp / 128);
     hipLaunchKernelGGL(k_narrow_weight, dim3(grid_for(n_groups * 64, 256)), dim3(256), 0, s, (const u32x4*)src, (u32x4*)dst,
-                       n_groups, unfit);
+                       n_groups, Kp / 128, unfit);
 }
 
 void launch_cast_rows(const void* src, int src_f32, bf16_t* dst, size_t count, hipStream_t s)

@@ -15,6 +15,19 @@ constexpr int kSweepMaxRows = 192;   // 12 row strips: beyond, the sweep kernel 
 
 constexpr int kNarrowMaxRows = 96;   // most token-rows for which the 12-bit weights are read
 
+// 16-byte units from one strip of a 12-bit matrix to the next: 3 KiB for each group of 4 k-blocks, and a gap.  The units of the
+// chip stream different strips at about the same k, and where strips begin at multiples of 32 KiB, or are long, their requests
+// meet in the same parts of the memory: a gap of 4 KiB, of 12 from 240 KiB on, sends them to different ones.  Whole decode step, without gaps /
+// with them: 7B widths, 12 layers (strips of 96 and 258 KiB) one row 0.955 / 0.888 ms, 16 rows 0.994 / 0.930, 64 rows 1.286 / 1.274, 96 rows
+// 1.539 / 1.542; 8192 wide, 4 layers (192, 516 KiB) 0.954 / 0.883, 0.980 / 0.911, 1.184 / 1.142, 1.436 / 1.424; 13B widths (120, 324 KiB), 2048,
+// 2816, 3072 and 6144 wide within 0.5 % either way.  Other gaps: 6 KiB instead of 12 for the long ones 7B 96 rows 1.550; at strips of 120 and 144
+// KiB one row the same, 16 rows up to 4 % slower with 6.
+constexpr size_t narrow_strip(int k_blocks)
+{
+    const int kib = k_blocks / 4 * 3;
+    return (size_t)(kib + (kib % 32 == 0 ? 4 : kib > 240 ? 12 : 0)) * 64;
+}
+
 // Block kernel: tiles in 16-row strips, workgroups that share a compute unit, and the time of one k-block in
 // nanoseconds while a unit holds one workgroup and while it holds per_cu of them.
 struct BlockTile {

@@ -80,6 +80,26 @@ def test_sliced_projections_agree_with_and_without_the_copies(mode, rows):
             assert np.abs(o[4 * i:4 * i + 4] - ref).max() <= 2e-3 * np.abs(ref).max(), (mode, rows, i)
 
 
+@pytest.mark.parametrize("rows", [1, 17])
+@pytest.mark.parametrize("ffn", [1280, 4096, 5120, 10240, 10368])   # strips of 30, 96, 120, 240 and 243 KiB: with a gap after them or none
+def test_strips_with_gaps_agree_with_and_without_the_copies(ffn, rows):
+    shape = synth.ModelShape("gaps", 1, 512, 4, 128, ffn, 272)
+    rng = np.random.default_rng(rows)
+    W = synth.make_weights(shape, seed=5, threads=8)
+    toks = rng.integers(0, shape.vocab, rows * 3).astype(np.int32)
+    offs = np.arange(rows + 1, dtype=np.int32) * 3
+    gw = ss.Weights(shape, W)
+    out = []
+    for copies in (1, 0):
+        gw.set_option(ss.SS_OPT_WEIGHT_COPIES, copies)
+        out.append(ss.ss_forward_logits(gw, toks, offs, np.full(rows, 1, np.int32)))
+    gw.close()
+    # as above: an input moved to the neighbouring half now and then
+    assert np.abs(out[0] - out[1]).max() <= 1e-3 * np.abs(out[1]).max()
+    ref = OracleModel(shape, W, "f32").teacher_forced(toks[:3], first=0)
+    assert np.abs(out[0][:3] - ref).max() <= 2e-3 * np.abs(ref).max()
+
+
 def test_read_probe_reads_what_small_batches_stream():
     """The probe that the projections are compared with: three quarters of the bytes where a matrix has its copy."""
     shape = synth.ModelShape("probe", 1, 1024, 8, 128, 2048, 4096)      # every matrix whole 64 KiB chunks in both forms
