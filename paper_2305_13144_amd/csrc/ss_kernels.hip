@@ -2207,7 +2207,17 @@ static void launch_block_epi(const GemmArgs& a, const QkvOut& qo, hipStream_t s)
         case 1: return launch_block<16, 12, 4, 2, 4, EPI>(a, qo, s);   // 8 waves of 4 x 6, 112 KiB
         case 2: return launch_block<8, 16, 2, 2, 3, EPI>(a, qo, s);    // 4 waves of 4 x 8, 72 KiB: two per unit
         case 3: return launch_block<8, 12, 2, 2, 4, EPI>(a, qo, s);    // 4 waves of 4 x 6, 80 KiB
-        default: return launch_block<8, 8, 2, 2, 4, EPI>(a, qo, s);    // 4 waves of 4 x 4, 64 KiB
+        case 4: return launch_block<8, 8, 2, 2, 4, EPI>(a, qo, s);     // 4 waves of 4 x 4, 64 KiB
+        case 5: return launch_block<8, 4, 2, 2, 6, EPI>(a, qo, s);     // 4 waves of 4 x 2, 72 KiB
+        case 6: return launch_block<6, 8, 2, 2, 4, EPI>(a, qo, s);     // 4 waves of 3 x 4, 56 KiB
+        case 7: return launch_block<10, 8, 2, 2, 4, EPI>(a, qo, s);    // 4 waves of 5 x 4, 72 KiB
+        case 8: return launch_block<12, 8, 4, 1, 4, EPI>(a, qo, s);    // 4 waves of 3 x 8, 80 KiB
+        case 9: return launch_block<16, 8, 4, 2, 5, EPI>(a, qo, s);    // 8 waves of 4 x 4, 120 KiB: one per unit
+        case 10: return launch_block<10, 12, 2, 2, 3, EPI>(a, qo, s);  // 4 waves of 5 x 6, 66 KiB
+        case 11: return launch_block<12, 12, 2, 2, 3, EPI>(a, qo, s);  // 4 waves of 6 x 6, 72 KiB
+        case 12: return launch_block<14, 16, 2, 4, 4, EPI>(a, qo, s);  // 8 waves of 7 x 4, 120 KiB
+        case 13: return launch_block<20, 12, 4, 2, 4, EPI>(a, qo, s);  // 8 waves of 5 x 6, 128 KiB
+        default: return launch_block<24, 12, 4, 2, 4, EPI>(a, qo, s);  // 8 waves of 6 x 6, 144 KiB
     }
 }
 

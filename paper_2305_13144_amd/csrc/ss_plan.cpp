@@ -3,6 +3,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 
 namespace ss {
 
@@ -15,19 +16,41 @@ constexpr int kSmallMaxKsplit = 8;   // sweep and skinny kernels: at most 8 k-sl
 // Block kernel: rows up to which k may be cut in 4 and in 2 (more rows fill the chip without, and the partial sums of
 // every slice are written and read again)
 constexpr int kBlockRows4 = 512, kBlockRows2 = 2048;
-constexpr double kBlockStart = 3300.0;        // ns: launch, first stage, epilogue
-constexpr double kBlockWrite = 3.84;          // bytes per ns at which results are written
-constexpr double kBlockStream = 3.64;         // bytes per ns at which the weights arrive at best
+// ns for launch, first stage and epilogue; bytes per ns at which results are written and at which the weights arrive at best
+struct BlockRates {
+    double start, write, stream;
+};
+constexpr BlockRates kBlockRates = {4390.0, 6.92, 3.3};
 constexpr double kPartialRead = 4.5;          // bytes per ns at which the consumer adds further slices
+constexpr double kBlockHalfPair = 0.593;      // of trip_full, when next to no unit holds a second workgroup
+// Large matrices, up to so many rows: the weights' way from memory decides more than the products, idle units make nothing faster, and
+// only the first five tiles, with rates of their own (trip_one and trip_full), are chosen from: of those there, smaller ones were
+// faster only where the weights came from the memory-side cache.
+constexpr int kBlockStreamRows = 256, kBlockStreamTiles = 5;
+constexpr BlockRates kBlockStreamRates = {3300.0, 3.84, 3.64};
+constexpr double kBlockStreamTrips[kBlockStreamTiles][2] = {{615.0, 740.0}, {485.0, 613.0}, {412.0, 772.0}, {313.0, 619.0}, {239.0, 475.0}};
+// Weights up to here stay in the L2s of the dies from forward to forward; tiles of fewer than 64 blocks of 16 x 16, which fetch the most
+// bytes per product, are for them (measured up to kBlockRows2 rows).
+constexpr size_t kBlockCached = (size_t)16 << 20;
 
 }
 
-// Trip times fitted to 300 timings of the five tiles at the 7B shapes, 100 to 12311 rows, 1 to 4 slices (8 % off in the
-// root mean square; the plan taken is 0.7 % slower than the best of them on average, 10 % at worst).
-const BlockTile block_tiles[kBlockTiles] = {{16, 16, 1, 615.0, 740.0}, {16, 12, 1, 485.0, 613.0}, {8, 16, 2, 412.0, 772.0},
-                                            {8, 12, 2, 313.0, 619.0}, {8, 8, 2, 239.0, 475.0}};
+// Fitted to 9000 timings of these tiles at widths of 256, 2048, 4096 and 5120, 65 to 12311 rows, 1 to 4 slices.  Of 320 projections the
+// tile taken is 2.5 % slower than the best of them on average; the best of the first five, which were all there was, is 11.8 % slower: with
+// more sizes to choose from, tiles fill whole rounds of the 256 units.  Microseconds, best of the first five / taken:
+// 7B gate|up 304 rows 78 / 67, 608 115 / 99, 752 134 / 115, 1488 246 / 215, 3200 485 / 418, 12311 1672 / 1616; q|k|v 752 rows 73 / 66, 1488 134 / 117;
+// o 752 rows 31 / 28, 3200 100 / 94; down 304 rows 48 / 39, 752 85 / 68, 1488 117 / 122; 13B gate|up 448 rows 118 / 104, down 528 rows 99 / 78, 896 rows
+// 120 / 130; 2048 wide gate|up 304 rows 21 / 19, o 9.9 / 8.0; tiny q|k|v 304 rows 5.7 / 4.5, down 9.0 / 6.3.
+const BlockTile block_tiles[kBlockTiles] = {
+    {16, 16, 1, 707.0, 745.0, 0.65}, {16, 12, 1, 529.0, 579.0, 0.77}, {8, 16, 2, 409.0, 783.0, 0.72}, {8, 12, 2, 306.0, 628.0, 0.68},
+    {8, 8, 2, 217.0, 456.0, 0.65},   {8, 4, 2, 143.0, 366.0, 0.83},   {6, 8, 2, 220.0, 492.0, 0.89},  {10, 8, 2, 265.0, 542.0, 0.65},
+    {12, 8, 2, 305.0, 609.0, 0.63},  {16, 8, 1, 377.0, 425.0, 0.79},  {10, 12, 2, 374.0, 730.0, 0.73}, {12, 12, 2, 438.0, 826.0, 0.68},
+    {14, 16, 1, 627.0, 662.0, 0.61}, {20, 12, 1, 649.0, 693.0, 0.66}, {24, 12, 1, 785.0, 820.0, 0.65}};
 
 namespace {
+bool cached(int N, int Kp) { return (size_t)N * Kp * 2 <= kBlockCached; }
+bool stream_bound(int N, int Kp, int m_rows) { return m_rows <= kBlockStreamRows && !cached(N, Kp); }
+
 // Time of a projection in the block kernel, in nanoseconds: rounds of workgroups over the chip times the k-blocks of a
 // slice, the results, and what adding up the slices costs the consumer.
 double block_ns(const BlockTile& t, int ks, int N, int Kp, int m_rows, int epilogue, int n_cu)
@@ -35,11 +58,23 @@ double block_ns(const BlockTile& t, int ks, int N, int Kp, int m_rows, int epilo
     const long long strips_m = (m_rows + 15) / 16, strips_n = N / 16;
     const long long wgs = ((strips_m + t.ms - 1) / t.ms) * ((strips_n + t.ns - 1) / t.ns) * ks;
     const long long full = wgs / ((long long)n_cu * t.per_cu), rest = wgs % ((long long)n_cu * t.per_cu);
-    const double trip = (double)full * t.trip_full + (rest > n_cu ? t.trip_full : rest > 0 ? t.trip_one : 0.0);
+    const double busy = (double)rest / n_cu;
+    const int trips = (Kp / 32 + ks - 1) / ks;
+    BlockRates r = kBlockRates;
+    double trip;
+    if (stream_bound(N, Kp, m_rows) && &t - block_tiles < kBlockStreamTiles) {
+        const double* ns = kBlockStreamTrips[&t - block_tiles];
+        r = kBlockStreamRates;
+        trip = (double)full * ns[1] + (rest > n_cu ? ns[1] : rest > 0 ? ns[0] : 0.0);
+    } else {
+        const double last = rest > n_cu ? t.trip_full * (kBlockHalfPair + (1.0 - kBlockHalfPair) * busy / t.per_cu)
+                                        : rest > 0 ? t.trip_one * (t.few + (1.0 - t.few) * busy) : 0.0;
+        // long loops run behind their weights more than short ones, small tiles above all
+        trip = ((double)full * t.trip_full + last) * std::pow(trips / 128.0, t.ms * t.ns < 64 ? 0.328 : 0.034);
+    }
     const double cells = (double)m_rows * N;
-    const double work = kBlockStart + trip * ((Kp / 32 + ks - 1) / ks) +
-                        cells * (epilogue == EPI_SWIGLU ? 1.0 : 4.0 * ks) / (kBlockWrite * 1000.0);
-    const double stream = kBlockStart + (double)N * Kp * 2 / (kBlockStream * 1000.0);
+    const double work = r.start + trip * trips + cells * (epilogue == EPI_SWIGLU ? 1.0 : 4.0 * ks) / (r.write * 1000.0);
+    const double stream = r.start + (double)N * Kp * 2 / (r.stream * 1000.0);
     const double ns = work > stream ? work : stream;
     return epilogue == EPI_SWIGLU ? ns : ns + cells * 4.0 * (ks - 1) / (kPartialRead * 1000.0);
 }
@@ -51,8 +86,8 @@ void set_gemm_mode(int mode)
     g_sweep_split.store((mode & 4) ? 0 : 1, std::memory_order_relaxed);
     // bit 3 (value 8): the block kernel never uses its largest tile (A/B measurements)
     g_tall_tiles.store((mode & 8) ? 0 : 1, std::memory_order_relaxed);
-    // bits 4 to 6: 1 + the only tile the block kernel uses
-    g_block_tile.store(((mode >> 4) & 7) - 1, std::memory_order_relaxed);
+    // bits 4 and up: 1 + the only tile the block kernel uses
+    g_block_tile.store((mode >> 4) - 1, std::memory_order_relaxed);
     g_gemm_mode.store(mode & 3, std::memory_order_relaxed);
 }
 int gemm_mode() { return g_gemm_mode.load(std::memory_order_relaxed); }
@@ -143,7 +178,9 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
     const int most = m_rows <= kBlockRows4 ? 4 : m_rows <= kBlockRows2 ? 2 : 1;
     double best = 0.0;
     const int only = g_block_tile.load(std::memory_order_relaxed);
-    for (int t = only >= 0 ? only : tall ? 0 : 1; t < (only >= 0 ? only + 1 : kBlockTiles); ++t)
+    const int tiles = stream_bound(N, Kp, m_rows) ? kBlockStreamTiles : kBlockTiles;
+    for (int t = only >= 0 ? only : tall ? 0 : 1; t < (only >= 0 ? only + 1 : tiles); ++t) {
+        if (only < 0 && (!cached(N, Kp) || m_rows > kBlockRows2) && block_tiles[t].ms * block_tiles[t].ns < 64) continue;
         for (int ks = 1; ks <= std::min(most, max_ksplit) && (ks == 1 || KB / ks >= 16); ks *= 2) {
             const double ns = block_ns(block_tiles[t], ks, N, Kp, m_rows, epilogue, n_cu);
             if (p.block < 0 || ns < best) {
@@ -152,6 +189,7 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
                 p.ksplit = ks;
             }
         }
+    }
     return p;
 }
 

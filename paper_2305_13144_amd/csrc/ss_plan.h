@@ -29,12 +29,13 @@ constexpr size_t narrow_strip(int k_blocks)
 }
 
 // Block kernel: tiles in 16-row strips, workgroups that share a compute unit, and the time of one k-block in
-// nanoseconds while a unit holds one workgroup and while it holds per_cu of them.
+// nanoseconds while a unit holds one workgroup and while it holds per_cu of them; few: the part of trip_one that is left
+// when next to no unit is busy (the others' power is theirs).
 struct BlockTile {
     int ms, ns, per_cu;
-    double trip_one, trip_full;
+    double trip_one, trip_full, few;
 };
-constexpr int kBlockTiles = 5;
+constexpr int kBlockTiles = 15;
 extern const BlockTile block_tiles[kBlockTiles];
 
 struct GemmPlan {

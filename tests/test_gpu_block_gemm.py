@@ -48,3 +48,9 @@ def test_prompt_logits_match_the_oracle(model, rows, mode):
         assert err <= TOL, (rows, mode, i, err)
     # every row is an independent sequence of sums: the same prompts alone give the same logits within rounding
     assert np.isfinite(got).all()
+
+
+@pytest.mark.parametrize("tile", range(5, 15))
+@pytest.mark.parametrize("rows", [65, 161, 193, 385, 641, 769])   # around the tiles' heights, one to eight of them
+def test_prompt_logits_match_the_oracle_in_every_other_tile(model, rows, tile):
+    test_prompt_logits_match_the_oracle(model, rows, 1 + 16 * (tile + 1))
