@@ -586,6 +586,55 @@ ss::RowStepArgs row_step_args(const ss_weights* w, const Lane& ln)
     return a;
 }
 
+// The token choice that ends a forward.
+void choose_tokens(const ss_weights* w, const Lane& ln, const float* logits, const int32_t* d_nsel, int n_sel, hipStream_t s)
+{
+    if (!ln.cur_choose) return;
+    if (ln.cur_inv_temp > 0.f)
+        ss::launch_sample(logits, w->cfg.vocab, d_nsel, ln.st, ln.cur_draws, ln.cur_ids, ln.cur_seed, ln.cur_inv_temp, n_sel, s);
+    else
+        ss::launch_argmax(logits, w->cfg.vocab, d_nsel, ln.st.am, n_sel, s);
+}
+
+// A decode forward of up to kFewRows rows in 5 launches per layer instead of 7 (k_gemm_few); false, and nothing done, if some
+// matrix is not streamed in the 12-bit form.
+bool few_forward(const ss_weights* w, Lane& ln, int n, hipStream_t s)
+{
+    const ss_model_cfg& c = w->cfg;
+    const int d = c.d_model, F = c.d_ffn, V = c.vocab, Fp = ss::padded_k(F), cu = w->n_cu;
+    const ss::FewPlan qkv = ss::few_plan(3 * d, d, n, ss::EPI_PARTIAL, cu), o = ss::few_plan(d, d, n, ss::EPI_RESIDUAL, cu),
+                      gu = ss::few_plan(2 * F, d, n, ss::EPI_SWIGLU, cu), down = ss::few_plan(d, Fp, n, ss::EPI_RESIDUAL, cu),
+                      lm = ss::few_plan(V, d, n, ss::EPI_PARTIAL, cu, 1);
+    if (!qkv.units_wg || !o.units_wg || !gu.units_wg || !down.units_wg || !lm.units_wg || !w->lm_head.pn) return false;
+    for (const Layer& L : w->layers)
+        if (!L.wqkv.pn || !L.wo.pn || !L.wgu.pn || !L.wd.pn) return false;
+    Workspace& ws = ln.ws;
+    const MbState& st = ln.st;
+    float *x = ws.x.as<float>(), *pqkv = ws.pqkv.as<float>();
+    f16_t *ao = ws.ao.as<f16_t>(), *act = ws.act.as<f16_t>();
+    auto run = [&](const PackedMat& W, const ss::FewPlan& p, int epilogue, const ss::bf16_t* gain, const f16_t* X, float* out) {
+        ss::FewArgs a{};
+        a.Wn = W.pn; a.x = x; a.gain = gain; a.X = X; a.out = out; a.out_packed = act; a.plan = p; a.N = W.N; a.Kp = W.Kp;
+        a.n_rows = n; a.kp_out = Fp; a.units = W.N / (epilogue == ss::EPI_SWIGLU ? 32 : 16); a.eps = c.rms_eps;
+        ss::launch_gemm_few(a, epilogue, s);
+    };
+    ss::launch_embed(st, w->embed, x, d, n, s);
+    for (int l = 0; l < c.n_layers; ++l) {
+        const Layer& L = w->layers[l];
+        ss::kv_t* kc = ws.kv.as<ss::kv_t>() + (size_t)l * 2 * ln.kv_layer_stride;
+        run(L.wqkv, qkv, ss::EPI_PARTIAL, L.attn_norm, nullptr, pqkv);
+        ss::launch_attention_decode(st, pqkv, 1, (size_t)n * 3 * d, kc, kc + ln.kv_layer_stride, w->rope_cos, w->rope_sin, ao, d, c.n_heads,
+                                    c.head_dim, n, ln.plan_rows ? ln.plan_rows : n, ln.prompt_rows, ln.max_ctx, ws.qrot.as<float>(), s);
+        run(L.wo, o, ss::EPI_RESIDUAL, nullptr, ao, x);
+        run(L.wgu, gu, ss::EPI_SWIGLU, L.mlp_norm, nullptr, nullptr);
+        run(L.wd, down, ss::EPI_RESIDUAL, nullptr, act, x);
+    }
+    float* logits = ln.cur_logits ? ln.cur_logits : ws.logits.as<float>();
+    run(w->lm_head, lm, ss::EPI_PARTIAL, w->final_norm, nullptr, logits);
+    choose_tokens(w, ln, logits, st.d_n, n, s);
+    return true;
+}
+
 // ---------------------------------------------------------------------------------------- one forward
 // Runs the decoder over the token-rows described by the device state (st.d_n of them, at most n of
 // them: n sizes the grids and picks the kernel variants).  Logits are produced for n_sel rows:
@@ -614,6 +663,9 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
             ss::launch_sample(a.logits, V, st.d_n, st, ln.cur_draws, ln.cur_ids, ln.cur_seed, ln.cur_inv_temp, n_sel, s);
         return;
     }
+
+    // few rows: the norms inside the projections
+    if (decode && !d_sel && !d_nsel && n_sel == n && n <= ss::kFewRows && few_forward(w, ln, n, s)) return;
 
     const int plan_rows = decode && ln.plan_rows ? ln.plan_rows : n;
     const Plans pl = make_plans(w, plan_rows, decode ? plan_rows : n_sel);
@@ -659,12 +711,7 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
     ss::launch_rmsnorm(st, x, add_d, ks_d, st_d, w->final_norm, c.rms_eps, d_sel, d_nsel, hsel, d, n_sel, s);
     float* logits = ln.cur_logits ? ln.cur_logits : ws.logits.as<float>();
     ss::launch_gemm(mk(w->lm_head, hsel, logits, nullptr, n_sel, 0, p_lm), ss::EPI_PARTIAL, s);
-    if (!ln.cur_choose) return;
-    if (ln.cur_inv_temp > 0.f)
-        ss::launch_sample(logits, V, d_nsel ? d_nsel : st.d_n, st, ln.cur_draws, ln.cur_ids, ln.cur_seed,
-                          ln.cur_inv_temp, n_sel, s);
-    else
-        ss::launch_argmax(logits, V, d_nsel ? d_nsel : st.d_n, st.am, n_sel, s);
+    choose_tokens(w, ln, logits, d_nsel ? d_nsel : st.d_n, n_sel, s);
 }
 
 int check_prompts(const ss_weights* w, const int32_t* toks, const int32_t* offs, int B)

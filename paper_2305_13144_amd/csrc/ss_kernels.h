@@ -85,6 +85,20 @@ struct QkvOut {
 
 // EPI_QKV and EPI_RESIDUAL (out += sums) need a plan for the block kernel without k-slices; EPI_QKV needs `qkv`.
 void launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s, const QkvOut* qkv = nullptr);
+// Up to kFewRows rows, 12-bit weights (few_plan).  EPI_PARTIAL and EPI_SWIGLU: of the normalised rows of x [n_rows, Kp]; EPI_PARTIAL: whole
+// sums to out [n_rows, N]; EPI_RESIDUAL: of the packed rows X, added to out [n_rows, N].
+struct FewArgs {
+    const void* Wn;
+    const float* x;
+    const bf16_t* gain;
+    const f16_t* X;
+    float* out;
+    f16_t* out_packed;
+    FewPlan plan;
+    int N, Kp, n_rows, kp_out, units;   // units: strips, or pairs of them with EPI_SWIGLU
+    float eps;
+};
+void launch_gemm_few(const FewArgs& a, int epilogue, hipStream_t s);
 void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride, float* qrot,
                         kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin, int d, int H,
                         int hd, int n_max, hipStream_t s);

@@ -261,6 +261,17 @@ __global__ __launch_bounds__(256) void k_embed(MbState st, const bf16_t* __restr
 constexpr int kNormMaxSplit = 8;
 constexpr int kNormNarrowFrom = 384;   // token-rows from which a row gets 256 threads instead of 1024
 
+// Written out: every kernel that norms rows is to round alike.
+__device__ __forceinline__ float norm_squares(const float4& a) { return fmaf(a.w, a.w, fmaf(a.z, a.z, fmaf(a.x, a.x, a.y * a.y))); }
+
+// Four elements of a row, normalised (r: the row's factor, wr: their gains).
+__device__ __forceinline__ uint2 norm_apply(const float4& v, float r, const uint2& wr)
+{
+    const bf16_t* wv = (const bf16_t*)&wr;
+    const f16_t o[4] = {f2h(v.x * r * bf2f(wv[0])), f2h(v.y * r * bf2f(wv[1])), f2h(v.z * r * bf2f(wv[2])), f2h(v.w * r * bf2f(wv[3]))};
+    return *(const uint2*)o;
+}
+
 template <int T, int ITER>
 __global__ __launch_bounds__(T) void k_rmsnorm(const int32_t* __restrict__ d_count, float* __restrict__ x,
                                                   const float* __restrict__ part, int ksplit, size_t part_stride,
@@ -302,7 +313,7 @@ __global__ __launch_bounds__(T) void k_rmsnorm(const int32_t* __restrict__ d_cou
 #pragma unroll
             for (int s = 0; s < kNormMaxSplit; ++s) { a.x += p[s].x; a.y += p[s].y; a.z += p[s].z; a.w += p[s].w; }
             v[it] = a;
-            ss += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
+            ss += norm_squares(a);
         }
     }
     if (j >= count) return;   // block-uniform
@@ -325,11 +336,8 @@ __global__ __launch_bounds__(T) void k_rmsnorm(const int32_t* __restrict__ d_cou
     for (int it = 0; it < ITER; ++it) {
         const int c = threadIdx.x * 4 + it * T * 4;
         if (c < d) {
-            const bf16_t* wv = (const bf16_t*)&wr[it];
-            const f16_t o[4] = {f2h(v[it].x * r * bf2f(wv[0])), f2h(v[it].y * r * bf2f(wv[1])),
-                                f2h(v[it].z * r * bf2f(wv[2])), f2h(v[it].w * r * bf2f(wv[3]))};
             const size_t at = pk_index(j, c, d);   // d is a multiple of 64: Kp == d
-            *(uint2*)(h + at) = *(const uint2*)o;
+            *(uint2*)(h + at) = norm_apply(v[it], r, wr[it]);
         }
     }
 }
@@ -762,6 +770,196 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
                     *(uint2*)(a.out_packed + at) = *(const uint2*)o;
                 }
         }
+    }
+}
+
+// ------------------------------------------------------------------------------------------ GEMM of few rows
+// Decode forwards of up to kFewRows rows that stream 12-bit weights.  So few rows' activations are small enough for every workgroup
+// to hold all of them: it normalises the residual stream itself (every workgroup the same numbers), or has whole sums and
+// adds them to the stream itself, so that no norm is launched, and reads them from LDS without a barrier in its loop.  The
+// norm's trip to memory runs beside the weights' first ones.
+// The numbers are those of the kernels above, bit for bit, so that a row gets the same whether other rows of its strip are alive
+// or not: a unit's k-blocks are summed in the same chains (FewPlan), the chains added in the same order, and the sums of
+// squares taken in the order of k_rmsnorm<1024, 2>.
+// What bounds it: the weight stream, and per launch the trip to memory for the activations before the first product.  7B, one
+// row, us per launch, before (norm + projection) / now: q|k|v 4.3 + 14.0 / 14.2, o 7.1 / 7.0, gate|up 4.3 + 24.4 / 24.3, down 13.4 / 14.2; a layer with its
+// attention 72.7 / 65; decode of one row, 24 steps 59.3 -> 54.4 ms.  Four rows 74 -> 70: every workgroup reads and norms all of them, which more rows
+// would not pay for.
+template <int R, int NBW, int EPI, bool NORM>
+__global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
+{
+    constexpr int T = 64 * kFewWaves, VT = 1024 / T;   // VT: threads of the norm that a thread stands for
+    extern __shared__ __attribute__((aligned(16))) char few_lds[];
+    const int KB = a.Kp >> 5, xrow = a.Kp + 32;        // 64 bytes between rows: the rows' operand pieces are in different banks
+    f16_t* const xs = (f16_t*)few_lds;                                     // [R][xrow]
+    f32x4* const red = (f32x4*)(few_lds + (size_t)R * xrow * 2);           // [kFewWaves][NBW][64]
+    float* const sq = (float*)(red + kFewWaves * NBW * 64);                // [R][16]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const FewPlan& p = a.plan;
+
+    // activations on their way first, then the weights: what is used first returns first
+    float4 v[NORM ? R : 1][VT][2];
+    uint2 wr[VT][2];
+    constexpr int NP = NORM ? 1 : 4 * R;   // 16-byte pieces per thread (kFewMaxK)
+    u32x4 piece[NP];
+    const int n_pieces = NORM ? 0 : (a.Kp >> 3) * R;
+    if (NORM) {
+#pragma unroll
+        for (int t = 0; t < VT; ++t)
+#pragma unroll
+            for (int it = 0; it < 2; ++it) {
+                const int c = (tid + t * T) * 4 + it * 4096;
+                if (c < a.Kp) {
+                    wr[t][it] = *(const uint2*)(a.gain + c);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) v[NORM ? r : 0][t][it] = *(const float4*)(a.x + (size_t)min(r, a.n_rows - 1) * a.Kp + c);
+                }
+            }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int z = tid + i * T, r = z % R, kg = z / R;   // k-group kg of row r
+            if (z < n_pieces) piece[i] = *(const u32x4*)(a.X + (size_t)(kg >> 2) * 512 + ((kg & 3) * 16 + min(r, a.n_rows - 1)) * 8);
+        }
+    }
+
+    const int slot = wave / p.items, item = wave - slot * p.items;
+    const int unit = blockIdx.x * p.units_wg + slot;
+    const bool active = slot < p.units_wg && unit < a.units;   // wave-uniform
+    // this wave's chain: groups first, first + step, ... of 4 k-blocks, count of them
+    const int slice = item / p.parts, part = item - slice * p.parts;
+    const int s0 = slice * p.kb_slice, s1 = min(KB, s0 + p.kb_slice);
+    const int G = max(s1 - s0, 0) >> 2;
+    int first = s0 >> 2, step = 1, count = G, restart = 0;
+    if (p.wave_kb) {   // contiguous quarters of the slice, whole groups: each a chain
+        const int quarter = (((max(s1 - s0, 0) + 3) >> 2) + 3) >> 2;
+        if (p.parts == 4) {
+            first += min(G, part * quarter);
+            count = min(G, (part + 1) * quarter) - min(G, part * quarter);
+        } else {
+            restart = quarter;
+        }
+    } else if (p.parts == 2) {   // groups in turn
+        first += part;
+        step = 2;
+        count = (G - part + 1) >> 1;
+    }
+    if (!active) count = 0;
+    const size_t strip_bytes = narrow_strip(KB) * 16;
+    const __amdgpu_buffer_rsrc_t wsrc = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)a.Wn + (active ? (size_t)unit * NBW : 0) * strip_bytes),
+                                                                          (short)0, (int)(NBW * strip_bytes), 0x00020000);
+    struct Slot {
+        u32x4 w[NBW][3];
+    } fa, fb;
+    auto load = [&](Slot& f, int i) {   // past the chain's end: beyond the buffer, nothing is fetched
+        const unsigned at = i < count ? (unsigned)((first + i * step) * 3072 + lane * 16) : 0xF0000000u;
+#pragma unroll
+        for (int n = 0; n < NBW; ++n)
+#pragma unroll
+            for (int z = 0; z < 3; ++z)
+                f.w[n][z] = __builtin_amdgcn_raw_buffer_load_b128(wsrc, at + (unsigned)(z * 1024 + n * (int)strip_bytes), 0, 2);
+    };
+    load(fa, 0);
+    load(fb, 1);
+    __builtin_amdgcn_sched_barrier(0);
+
+    float4 old = make_float4(0.f, 0.f, 0.f, 0.f);   // the residual stream at this lane's place
+    const int col4 = (lane >> 4) * 4, row = lane & 15;
+    if (NORM) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int t = 0; t < VT; ++t) {
+                float ss = 0.f;
+#pragma unroll
+                for (int it = 0; it < 2; ++it)
+                    if ((tid + t * T) * 4 + it * 4096 < a.Kp) ss += norm_squares(v[NORM ? r : 0][t][it]);
+                ss = wave_sum(ss);
+                if (lane == 0) sq[r * 16 + t * kFewWaves + wave] = ss;
+            }
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            float tot = 0.f;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) tot += sq[r * 16 + i];
+            const float f = rsqrtf(tot / (float)a.Kp + a.eps);
+#pragma unroll
+            for (int t = 0; t < VT; ++t)
+#pragma unroll
+                for (int it = 0; it < 2; ++it) {
+                    const int c = (tid + t * T) * 4 + it * 4096;
+                    if (c < a.Kp) *(uint2*)(xs + r * xrow + c) = norm_apply(v[NORM ? r : 0][t][it], f, wr[t][it]);
+                }
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int z = tid + i * T, r = z % R, kg = z / R;
+            if (z < n_pieces) *(u32x4*)(xs + r * xrow + kg * 8) = piece[i];
+        }
+    }
+    __syncthreads();
+
+    f32x4 acc[NBW], tot[NBW];
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) acc[n] = tot[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const f16_t* const xl = xs + min(row, R - 1) * xrow + (lane >> 4) * 8;
+    int left = restart;
+    auto use = [&](const Slot& f, int i) {
+        const f16_t* xg = xl + (first + i * step) * 128;
+        u32x4 xv[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) xv[q] = *(const u32x4*)(xg + q * 32);
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) {
+            const u32x4 w[4] = {narrow_group_frag<0>(f.w[n]), narrow_group_frag<1>(f.w[n]), narrow_group_frag<2>(f.w[n]),
+                                narrow_group_frag<3>(f.w[n])};
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                acc[n] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w[q]), __builtin_bit_cast(f16x8, xv[q]),
+                                                                acc[n], 0, 0, 0);
+        }
+        if (restart > 0 && --left == 0) {   // the chain ends: the next one begins at zero
+            left = restart;
+#pragma unroll
+            for (int n = 0; n < NBW; ++n) {
+                tot[n] = tot[n] + acc[n];
+                acc[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+        }
+    };
+    for (int i = 0; i < count; i += 2) {
+        use(fa, i);
+        load(fa, i + 2);
+        if (i + 1 < count) use(fb, i + 1);
+        load(fb, i + 3);
+    }
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) red[(wave * NBW + n) * 64 + lane] = restart > 0 ? tot[n] + acc[n] : acc[n];
+    const bool stores = active && item == 0 && row < a.n_rows;
+    if (EPI == EPI_RESIDUAL && stores) old = *(const float4*)(a.out + (size_t)row * a.N + unit * 16 + col4);
+    __syncthreads();
+    if (!stores) return;
+    f32x4 sum[NBW];
+#pragma unroll
+    for (int n = 0; n < NBW; ++n) sum[n] = EPI == EPI_RESIDUAL ? (f32x4){old.x, old.y, old.z, old.w} : (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < p.items; i += p.parts)
+#pragma unroll
+        for (int n = 0; n < NBW; ++n) {
+            f32x4 z = red[((wave + i) * NBW + n) * 64 + lane];
+            for (int j = 1; j < p.parts; ++j) z += red[((wave + i + j) * NBW + n) * 64 + lane];
+            z *= kNarrowScale;
+            sum[n] = EPI == EPI_SWIGLU ? z : sum[n] + z;
+        }
+    if (EPI == EPI_SWIGLU) {
+        const int f = unit * 16 + col4;
+        f16_t o[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = f2h(silu_f(sum[0][e]) * sum[NBW - 1][e]);
+        *(uint2*)(a.out_packed + pk_index(row, f, a.kp_out)) = *(const uint2*)o;
+    } else {
+        *(float4*)(a.out + (size_t)row * a.N + unit * 16 + col4) = make_float4(sum[0][0], sum[0][1], sum[0][2], sum[0][3]);
     }
 }
 
@@ -2257,6 +2455,24 @@ void launch_gemm(const GemmArgs& a, int epilogue, hipStream_t s, const QkvOut* q
         case EPI_RESIDUAL: return launch_block_epi<EPI_RESIDUAL>(a, QkvOut{}, s);
         default: return launch_gemm_epi<EPI_PARTIAL>(a, s);
     }
+}
+
+template <int R>
+static void launch_few_r(const FewArgs& a, int epilogue, hipStream_t s)
+{
+    const dim3 grid((a.units + a.plan.units_wg - 1) / a.plan.units_wg), block(64 * kFewWaves);
+    const size_t lds = few_lds_bytes(R, a.Kp, epilogue);
+    if (epilogue == EPI_SWIGLU) hipLaunchKernelGGL((k_gemm_few<R, 2, EPI_SWIGLU, true>), grid, block, lds, s, a);
+    else if (epilogue == EPI_RESIDUAL) hipLaunchKernelGGL((k_gemm_few<R, 1, EPI_RESIDUAL, false>), grid, block, lds, s, a);
+    else hipLaunchKernelGGL((k_gemm_few<R, 1, EPI_PARTIAL, true>), grid, block, lds, s, a);
+}
+
+void launch_gemm_few(const FewArgs& a, int epilogue, hipStream_t s)
+{
+    if (a.n_rows == 1) launch_few_r<1>(a, epilogue, s);
+    else if (a.n_rows == 2) launch_few_r<2>(a, epilogue, s);
+    else if (a.n_rows == 3) launch_few_r<3>(a, epilogue, s);
+    else launch_few_r<4>(a, epilogue, s);
 }
 
 void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride, float* qrot,

@@ -193,6 +193,28 @@ GemmPlan gemm_plan(int N, int Kp, int m_rows, int epilogue, int n_cu, int max_ks
     return p;
 }
 
+FewPlan few_plan(int N, int Kp, int n_rows, int epilogue, int n_cu, int max_ksplit)
+{
+    FewPlan f{0, 1, 1, 0, 0};
+    if (gemm_mode() != 0 || !g_sweep_split.load(std::memory_order_relaxed) || n_rows > kFewRows || Kp > kFewMaxK || Kp % 128) return f;
+    if (few_lds_bytes(n_rows, Kp, epilogue) > (size_t)160 << 10) return f;
+    const GemmPlan p = gemm_plan(N, Kp, n_rows, epilogue == EPI_RESIDUAL ? (int)EPI_PARTIAL : epilogue, n_cu, max_ksplit);
+    if (!p.narrow || p.block >= 0) return f;
+    const int nbw = epilogue == EPI_SWIGLU ? 2 : 1, units = N / 16 / nbw;
+    f.kb_slice = ((Kp / 32 + p.ksplit - 1) / p.ksplit + 3) & ~3;   // whole groups, as the launchers cut them
+    if (p.sweep_gn > 0) {
+        const int per = (units + p.sweep_gn - 1) / p.sweep_gn;
+        f.parts = p.sweep_p == 4 && per <= 4 && p.narrow == 2 ? 2 : 1;
+    } else {
+        f.wave_kb = 1;
+        f.parts = p.ksplit * 4 <= kFewWaves ? 4 : 1;
+    }
+    f.items = p.ksplit * f.parts;
+    if (f.items > kFewWaves) return f;
+    f.units_wg = std::min(kFewWaves / f.items, std::max(1, (units + n_cu - 1) / n_cu));
+    return f;
+}
+
 // Both ways to take a decode step of a small model, in microseconds, fitted to 1510 timings of either on 200 models of 1 to 16
 // layers, 64 to 512 wide, 1 to 250 rows, contexts of 8 to 1500 (row step 5 % off in the root mean square, launches 6 %).  The row step is taken up to 3 us
 // behind: all steps of a row in one launch save it another 7 us each, and micro-batches in flight beside each other hold each

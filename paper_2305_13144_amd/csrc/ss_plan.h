@@ -47,6 +47,21 @@ struct GemmPlan {
     int block;      // block kernel: index into block_tiles; -1: one of the others
 };
 
+// Few rows (k_gemm_few): how a workgroup of kFewWaves waves computes the sums that the sweep or skinny kernel would, in the same chains.
+// A wave takes an item of a unit: the k-blocks of a slice (kb_slice), or one of `parts` parts of it: 2 parts take its groups of 4
+// k-blocks in turn (sweep kernel, two waves per unit), 4 parts a quarter each (skinny kernel).  wave_kb: the slice's quarters are chains of
+// their own also where one wave takes them all.  items: those of a unit; units_wg: units of a workgroup (0: no such plan).
+constexpr int kFewRows = 4, kFewWaves = 8, kFewMaxK = 16384;
+struct FewPlan {
+    int units_wg, items, parts, kb_slice, wave_kb;
+};
+FewPlan few_plan(int N, int Kp, int n_rows, int epilogue, int n_cu, int max_ksplit = 8);
+// Its LDS: the rows, 64 bytes apart, the waves' sums, the rows' sums of squares.
+constexpr size_t few_lds_bytes(int rows, int Kp, int epilogue)
+{
+    return (size_t)rows * (Kp + 32) * 2 + (size_t)kFewWaves * (epilogue == EPI_SWIGLU ? 2 : 1) * 1024 + (size_t)rows * 64;
+}
+
 constexpr int kBlockTallFrom = 896;   // token-rows (in whole strips) from which the block kernel may use its largest tile
 
 // n_cu: compute units of the device (the sweep kernel runs one workgroup per unit).
