@@ -566,7 +566,7 @@ ss::RowStepArgs row_step_args(const ss_weights* w, const Lane& ln)
     ss::RowStepArgs a{};
     for (int l = 0; l < c.n_layers; ++l) {
         const Layer& L = w->layers[l];
-        a.layer[l] = {L.wqkv.p, L.wo.p, L.wgu.p, L.wd.p, L.attn_norm, L.mlp_norm};
+        a.layer[l] = {{L.wqkv.p, L.wo.p, L.wgu.p, L.wd.p}, L.attn_norm, L.mlp_norm};
     }
     a.embed = w->embed;
     a.final_norm = w->final_norm;

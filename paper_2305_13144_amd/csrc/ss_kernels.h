@@ -118,7 +118,7 @@ void launch_attention_decode(const MbState& st, const float* qkv_part, int kspli
 // tokens, or with `compact` those that it owes, and writes them out itself (the tables of live rows stay as they are).
 struct RowStepArgs {
     struct Layer {
-        const f16_t *wqkv, *wo, *wgu, *wd;
+        const f16_t* w[4];   // q|k|v, o, gate|up, down
         const bf16_t *attn_norm, *mlp_norm;
     } layer[kRowMaxLayers];
     const bf16_t *embed, *final_norm;
