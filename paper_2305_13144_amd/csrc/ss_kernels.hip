@@ -785,7 +785,7 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
 // row, us per launch, before (norm + projection) / now: q|k|v 4.3 + 14.0 / 14.2, o 7.1 / 7.0, gate|up 4.3 + 24.4 / 24.3, down 13.4 / 14.2; a layer with its
 // attention 72.7 / 65; decode of one row, 24 steps 59.3 -> 54.4 ms.  Four rows 74 -> 70: every workgroup reads and norms all of them, which more rows
 // would not pay for.
-template <int R, int NBW, int EPI, bool NORM>
+template <int R, int NBW, int EPI, bool NORM, int PR = 1>
 __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
 {
     constexpr int T = 64 * kFewWaves, VT = 1024 / T;   // VT: threads of the norm that a thread stands for
@@ -800,7 +800,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
     // activations on their way first, then the weights: what is used first returns first
     float4 v[NORM ? R : 1][VT][2];
     uint2 wr[VT][2];
-    constexpr int NP = NORM ? 1 : 4 * R;   // 16-byte pieces per thread (kFewMaxK)
+    constexpr int NP = NORM ? 1 : PR * R;   // 16-byte pieces per thread: rows of up to PR * 4096 columns
     u32x4 piece[NP];
     const int n_pieces = NORM ? 0 : (a.Kp >> 3) * R;
     if (NORM) {
@@ -816,10 +816,11 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
                 }
             }
     } else {
+        const __amdgpu_buffer_rsrc_t xsrc = __builtin_amdgcn_make_buffer_rsrc((void*)a.X, (short)0, KB * 1024, 0x00020000);
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
+        for (int i = 0; i < NP; ++i) {   // beyond the last piece: beyond the buffer
             const int z = tid + i * T, r = z % R, kg = z / R;   // k-group kg of row r
-            if (z < n_pieces) piece[i] = *(const u32x4*)(a.X + (size_t)(kg >> 2) * 512 + ((kg & 3) * 16 + min(r, a.n_rows - 1)) * 8);
+            piece[i] = __builtin_amdgcn_raw_buffer_load_b128(xsrc, (kg >> 2) * 1024 + ((kg & 3) * 16 + min(r, a.n_rows - 1)) * 16, 0, 0);
         }
     }
 
@@ -929,6 +930,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
             }
         }
     };
+#pragma unroll 1
     for (int i = 0; i < count; i += 2) {
         use(fa, i);
         load(fa, i + 2);
@@ -2470,7 +2472,9 @@ static void launch_few_r(const FewArgs& a, int epilogue, hipStream_t s)
     const dim3 grid((a.units + a.plan.units_wg - 1) / a.plan.units_wg), block(64 * kFewWaves);
     const size_t lds = few_lds_bytes(R, a.Kp, epilogue);
     if (epilogue == EPI_SWIGLU) hipLaunchKernelGGL((k_gemm_few<R, 2, EPI_SWIGLU, true>), grid, block, lds, s, a);
-    else if (epilogue == EPI_RESIDUAL) hipLaunchKernelGGL((k_gemm_few<R, 1, EPI_RESIDUAL, false>), grid, block, lds, s, a);
+    else if (epilogue == EPI_RESIDUAL && a.Kp <= 4096) hipLaunchKernelGGL((k_gemm_few<R, 1, EPI_RESIDUAL, false, 1>), grid, block, lds, s, a);
+    else if (epilogue == EPI_RESIDUAL && a.Kp <= 12288) hipLaunchKernelGGL((k_gemm_few<R, 1, EPI_RESIDUAL, false, 3>), grid, block, lds, s, a);
+    else if (epilogue == EPI_RESIDUAL) hipLaunchKernelGGL((k_gemm_few<R, 1, EPI_RESIDUAL, false, 4>), grid, block, lds, s, a);
     else hipLaunchKernelGGL((k_gemm_few<R, 1, EPI_PARTIAL, true>), grid, block, lds, s, a);
 }
 
