@@ -1236,13 +1236,13 @@ __global__ __launch_bounds__(256) void k_rope_append(MbState st, const float* __
 // Short contexts are bound by vector instructions (a load's share of the dot products and of the sums is some 60), so the
 // loads of a group that lie beyond the context are left out of both passes.  Per layer, 7B: 163 rows
 // 31.4 -> 27.1 us, 51 rows 15.7 -> 14.1, one row 8.1 -> 6.8 (contexts of 16 to 70).
-constexpr int kAttnUnroll = 8;
+constexpr int kAttnUnroll = 8, kAttnShort = 4;   // loads of a wave before it consumes them; where that many hold the whole context
 
 // The slots are dealt to NW slices, one per wave, or NW / PW for each of PW waves: the sums are the same sums in the same order.
 // A wave's loads then go to its slices in turn, so that the workgroup walks over the slots as with NW = PW (one slice after the
 // other it asks for every second 4 KB at a time: 16 rows of 40 heads, context 1500, 174 us a layer instead of 165).
 // SPLIT: the slots are a share of the row's; their sums, maximum and total go to `share` (see k_attention_join).
-template <int HD, int NW, int PW, bool SPLIT>
+template <int HD, int NW, int PW, bool SPLIT, int AU>
 __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __restrict__ sc, float* __restrict__ red,
                                        float (*__restrict__ oacc)[HD], const kv_t* __restrict__ kbase,
                                        const kv_t* __restrict__ vbase, int ctx, f16_t* __restrict__ out, int out_r,
@@ -1250,12 +1250,26 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
 {
     constexpr int LPK = HD / 8;       // lanes per key
     constexpr int KPW = 64 / LPK;     // keys per wave load
-    constexpr int AU = kAttnUnroll;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int sub = lane % LPK, kin = lane / LPK;
     constexpr int R = NW / PW;        // slices per wave
     static_assert(NW % PW == 0 && AU % R == 0, "every load of a trip belongs to one slice");
     const float scale = rsqrtf((float)HD);
+    // Slots beyond the context are beyond the buffer: they read as zeros, and nothing is fetched for them.  A fifth of the
+    // instructions of loads that test each lane (and 12 registers less); where they issue, 8 loads for the few slots of a short context
+    // would take that back, hence the form with kAttnShort.  Decode step of 7B per layer: 64 rows at context 1000 296 -> 291 us, 16 rows 127.2 -> 126.5, 3000
+    // slots 209 -> 207, one row 1000 77.0 -> 75.6; 51 rows at 40 slots 105.1 -> 104.3.
+    auto slots = [&](const kv_t* base) {
+        const uint64_t at = (uint64_t)base;
+        const uint64_t u = (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)at) |
+                           (uint64_t)(unsigned)__builtin_amdgcn_readfirstlane((int)(at >> 32)) << 32;
+        return __builtin_amdgcn_make_buffer_rsrc((void*)u, (short)0, __builtin_amdgcn_readfirstlane(ctx) * HD * 2, 0x00020000);
+    };
+    const __amdgpu_buffer_rsrc_t ksrc = slots(kbase), vsrc = slots(vbase);
+    const unsigned lane_at = (unsigned)(kin * HD + sub * 8) * 2;
+    auto load = [&](__amdgpu_buffer_rsrc_t src, int first) {   // this lane's piece of the wave's keys from `first` on
+        return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(src, lane_at + (unsigned)(first * HD * 2), 0, 0));
+    };
     float q[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) q[e] = qs[sub * 8 + e];
@@ -1265,8 +1279,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
         uint4 raw[AU];
 #pragma unroll
         for (int u = 0; u < AU; ++u) {
-            const int s = c0 + u * PW * KPW + kin;
-            raw[u] = s < ctx ? *(const uint4*)(kbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
+            raw[u] = load(ksrc, c0 + u * PW * KPW);
         }
 #pragma unroll
         for (int u = 0; u < AU; ++u) {
@@ -1287,8 +1300,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     uint4 vraw[AU];
 #pragma unroll
     for (int u = 0; u < AU; ++u) {
-        const int s = wave * KPW + u * PW * KPW + kin;
-        vraw[u] = s < ctx ? *(const uint4*)(vbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
+        vraw[u] = load(vsrc, wave * KPW + u * PW * KPW);
     }
     mx = wave_max(mx);
     if (lane == 0) red[wave] = mx;
@@ -1322,11 +1334,10 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
         uint4 raw[AU];
 #pragma unroll
         for (int u = 0; u < AU; ++u) {
-            const int s = c0 + u * PW * KPW + kin;
             if (c0 == wave * KPW)
                 raw[u] = vraw[u];
             else
-                raw[u] = s < ctx ? *(const uint4*)(vbase + (size_t)s * HD + sub * 8) : make_uint4(0, 0, 0, 0);
+                raw[u] = load(vsrc, c0 + u * PW * KPW);
         }
 #pragma unroll
         for (int u = 0; u < AU; ++u) {
@@ -1669,8 +1680,11 @@ __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const 
     finish(threadIdx.x);
     if (64 * PW < 3 * HALF) finish(threadIdx.x + 64 * PW);
     __syncthreads();   // the new key/value slot and q are visible to the whole workgroup
-    attend<HD, NW, PW, SPLIT>(qs, sc, red, oacc, kc + base + (size_t)begin * HD, vc + base + (size_t)begin * HD, slots, out, j, h * HD, d,
-                              share);
+    const kv_t *kb = kc + base + (size_t)begin * HD, *vb = vc + base + (size_t)begin * HD;
+    if (!SPLIT && slots <= kAttnShort * PW * (512 / HD))
+        attend<HD, NW, PW, SPLIT, kAttnShort>(qs, sc, red, oacc, kb, vb, slots, out, j, h * HD, d, share);
+    else
+        attend<HD, NW, PW, SPLIT, kAttnUnroll>(qs, sc, red, oacc, kb, vb, slots, out, j, h * HD, d, share);
 }
 
 // The shares of a pair's slots put together: one wave per pair, two elements a lane (HD 64: half the lanes).
