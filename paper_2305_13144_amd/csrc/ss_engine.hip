@@ -531,20 +531,20 @@ int ensure_workspace(const ss_weights* w, Lane& ln, int n_max, int B, int n_sel,
     return SS_OK;
 }
 
-// Launch plans of the five projections of a forward over n token-rows with n_sel logit rows.
+// Launch plans of the five projections of a forward over n token-rows with n_sel logit rows; rotate: q|k|v of whole launches are finished there.
 struct Plans {
     ss::GemmPlan qkv, o, gu, down, lm;
 };
 
-Plans make_plans(const ss_weights* w, int n, int n_sel)
+Plans make_plans(const ss_weights* w, int n, int n_sel, bool rotate)
 {
     const ss_model_cfg& c = w->cfg;
     const int d = c.d_model, F = c.d_ffn, V = c.vocab, Fp = ss::padded_k(F), cu = w->n_cu;
     Plans p;
-    p.qkv = ss::gemm_plan(3 * d, d, n, ss::EPI_PARTIAL, cu);
-    p.o = ss::gemm_plan(d, d, n, ss::EPI_PARTIAL, cu);
+    p.qkv = ss::gemm_plan(3 * d, d, n, rotate ? ss::EPI_QKV : ss::EPI_PARTIAL, cu);
+    p.o = ss::gemm_plan(d, d, n, ss::EPI_RESIDUAL, cu);
     p.gu = ss::gemm_plan(2 * F, d, n, ss::EPI_SWIGLU, cu);
-    p.down = ss::gemm_plan(d, Fp, n, ss::EPI_PARTIAL, cu);
+    p.down = ss::gemm_plan(d, Fp, n, ss::EPI_RESIDUAL, cu);
     p.lm = ss::gemm_plan(V, d, n_sel, ss::EPI_PARTIAL, cu, 1);   // logits are read directly: no k-slices
     return p;
 }
@@ -668,7 +668,7 @@ void forward(const ss_weights* w, Lane& ln, int n, int n_sel, const int32_t* d_s
     if (decode && !d_sel && !d_nsel && n_sel == n && n <= ss::kFewRows && few_forward(w, ln, n, s)) return;
 
     const int plan_rows = decode && ln.plan_rows ? ln.plan_rows : n;
-    const Plans pl = make_plans(w, plan_rows, decode ? plan_rows : n_sel);
+    const Plans pl = make_plans(w, plan_rows, decode ? plan_rows : n_sel, !decode);
     const ss::GemmPlan &p_qkv = pl.qkv, &p_o = pl.o, &p_gu = pl.gu, &p_d = pl.down, &p_lm = pl.lm;
     const int ks_qkv = p_qkv.ksplit, ks_o = p_o.ksplit, ks_d = p_d.ksplit;
     const size_t st_qkv = (size_t)n * 3 * d, st_d = (size_t)n * d;
@@ -2108,7 +2108,7 @@ int bench_weight_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32
     const ss_model_cfg& c = w->cfg;
     const int Fp = ss::padded_k(c.d_ffn), n = B;
     Workspace& ws = ln.ws;
-    const Plans pl = make_plans(w, n, n);
+    const Plans pl = make_plans(w, n, n, false);
     const ss::GemmPlan &p_qkv = pl.qkv, &p_o = pl.o, &p_gu = pl.gu, &p_d = pl.down, &p_lm = pl.lm;
     auto mk = [w](const PackedMat& W, const f16_t* X, float* out, f16_t* outp, int rows, int kp_out, const ss::GemmPlan& p) {
         return gemm_args(w, W, X, out, outp, rows, kp_out, p);

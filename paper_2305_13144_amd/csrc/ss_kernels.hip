@@ -783,8 +783,8 @@ __global__ __launch_bounds__(64 * P) void k_gemm_sweep(GemmArgs a, int n_units, 
 // squares taken in the order of k_rmsnorm<1024, 2>.
 // What bounds it: the weight stream, and per launch the trip to memory for the activations before the first product.  7B, one
 // row, us per launch, before (norm + projection) / now: q|k|v 4.3 + 14.0 / 14.2, o 7.1 / 7.0, gate|up 4.3 + 24.4 / 24.3, down 13.4 / 14.2; a layer with its
-// attention 72.7 / 65; decode of one row, 24 steps 59.3 -> 54.4 ms.  Four rows 74 -> 70: every workgroup reads and norms all of them, which more rows
-// would not pay for.
+// attention 72.7 / 65; decode of one row, 24 steps 59.3 -> 54.4 ms.  Four rows 74.8 -> 72.6: every workgroup reads and norms all of them, which more
+// rows would not pay for (kFewRows).
 template <int R, int NBW, int EPI, bool NORM, int PR = 1>
 __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
 {

@@ -20,8 +20,14 @@ constexpr int kBlockRows4 = 512, kBlockRows2 = 2048;
 struct BlockRates {
     double start, write, stream;
 };
-constexpr BlockRates kBlockRates = {4390.0, 6.92, 3.3};
+constexpr BlockRates kBlockRates = {4390.0, 9.59, 3.3};
 constexpr double kPartialRead = 4.5;          // bytes per ns at which the consumer adds further slices
+constexpr double kRotateStart = 3000.0;       // ns of the launch that rotates slices of q|k|v
+// Tiles of which a unit holds two, from so many full rounds and up to so many k-blocks on: the workgroups of a unit have drifted apart, and one
+// multiplies while the other starts or finishes (gate|up, 12311 rows, tiles of 192 x 192 / 384 x 192: 1560 / 1607 us; down, 344 k-blocks: 937 / 871).
+constexpr int kBlockManyRounds = 4, kBlockManyTrips = 192;
+constexpr double kBlockManyGain = 0.987;
+constexpr double kBlockPad = 0.08;             // share of the products beyond the matrix that is paid for again, in power
 constexpr double kBlockHalfPair = 0.593;      // of trip_full, when next to no unit holds a second workgroup
 // Large matrices, up to so many rows: the weights' way from memory decides more than the products, idle units make nothing faster, and
 // only the first five tiles, with rates of their own (trip_one and trip_full), are chosen from: of those there, smaller ones were
@@ -35,21 +41,26 @@ constexpr size_t kBlockCached = (size_t)16 << 20;
 
 }
 
-// Fitted to 9000 timings of these tiles at widths of 256, 2048, 4096 and 5120, 65 to 12311 rows, 1 to 4 slices.  Of 320 projections the
-// tile taken is 2.5 % slower than the best of them on average; the best of the first five, which were all there was, is 11.8 % slower: with
-// more sizes to choose from, tiles fill whole rounds of the 256 units.  Microseconds, best of the first five / taken:
-// 7B gate|up 304 rows 78 / 67, 608 115 / 99, 752 134 / 115, 1488 246 / 215, 3200 485 / 418, 12311 1672 / 1616; q|k|v 752 rows 73 / 66, 1488 134 / 117;
-// o 752 rows 31 / 28, 3200 100 / 94; down 304 rows 48 / 39, 752 85 / 68, 1488 117 / 122; 13B gate|up 448 rows 118 / 104, down 528 rows 99 / 78, 896 rows
-// 120 / 130; 2048 wide gate|up 304 rows 21 / 19, o 9.9 / 8.0; tiny q|k|v 304 rows 5.7 / 4.5, down 9.0 / 6.3.
+// Fitted to 3000 timings inside prompt forwards of the 7B and 13B shapes, 304 to 12311 rows, every tile in turn (a projection that is launched
+// over and over finds its weights and its clock otherwise than one between others: up to 18 % apart, and not the same for all tiles), and to 1500
+// of launches alone at widths of 256 and 2048.  Of 248 projections in their forwards the tile taken is 0.4 % slower than the best of them on
+// average, 1.0 % at the smaller widths; the best of the first five, which were all there was, was 11.8 % slower: with more sizes to choose from,
+// tiles fill whole rounds of the 256 units.  The last digits are those with which the choice is best.  Fitted to launches alone, without what a launch's last step costs (finish_bytes), the tile taken was
+// 3.1 % slower.  Microseconds in a forward, with the consumer's reads, that fit / this one: 7B o 995 rows 44 / 39, 2033 rows 75 / 69, down 995 rows
+// 89 / 86, gate|up 7200 rows 976 / 936, 12311 rows 1607 / 1560; 13B o 608 rows 53 / 43, 995 rows 70 / 57, down 12311 rows 1350 / 1304.
 const BlockTile block_tiles[kBlockTiles] = {
-    {16, 16, 1, 707.0, 745.0, 0.65}, {16, 12, 1, 529.0, 579.0, 0.77}, {8, 16, 2, 409.0, 783.0, 0.72}, {8, 12, 2, 306.0, 628.0, 0.68},
-    {8, 8, 2, 217.0, 456.0, 0.65},   {8, 4, 2, 143.0, 366.0, 0.83},   {6, 8, 2, 220.0, 492.0, 0.89},  {10, 8, 2, 265.0, 542.0, 0.65},
-    {12, 8, 2, 305.0, 609.0, 0.63},  {16, 8, 1, 377.0, 425.0, 0.79},  {10, 12, 2, 374.0, 730.0, 0.73}, {12, 12, 2, 438.0, 826.0, 0.68},
-    {14, 16, 1, 627.0, 662.0, 0.61}, {20, 12, 1, 649.0, 693.0, 0.66}, {24, 12, 1, 785.0, 820.0, 0.65}};
+    {16, 16, 1, 704.0, 736.0, 1.0}, {16, 12, 1, 554.0, 590.0, 0.91}, {8, 16, 2, 449.0, 773.0, 0.79}, {8, 12, 2, 346.0, 638.0, 0.71},
+    {8, 8, 2, 261.0, 493.0, 0.55}, {8, 4, 2, 155.0, 404.0, 0.89}, {6, 8, 2, 223.0, 549.0, 0.98}, {10, 8, 2, 296.0, 576.0, 0.66},
+    {12, 8, 2, 321.0, 635.0, 0.74}, {16, 8, 1, 389.0, 425.0, 0.86}, {10, 12, 2, 424.0, 756.0, 0.75}, {12, 12, 2, 446.0, 824.0, 0.89},
+    {14, 16, 1, 594.0, 670.0, 1.0}, {20, 12, 1, 624.0, 700.0, 1.0}, {24, 12, 1, 743.0, 823.0, 1.0}};
 
 namespace {
 bool cached(int N, int Kp) { return (size_t)N * Kp * 2 <= kBlockCached; }
 bool stream_bound(int N, int Kp, int m_rows) { return m_rows <= kBlockStreamRows && !cached(N, Kp); }
+
+// What an unsliced launch's results cost, as bytes written per element: the rows of the residual stream are read first, and every
+// workgroup waits for its own at the end; rotated elements go to three places.
+double finish_bytes(int epilogue) { return epilogue == EPI_RESIDUAL ? 16.4 : epilogue == EPI_QKV ? 6.0 : 4.0; }
 
 // Time of a projection in the block kernel, in nanoseconds: rounds of workgroups over the chip times the k-blocks of a
 // slice, the results, and what adding up the slices costs the consumer.
@@ -61,7 +72,8 @@ double block_ns(const BlockTile& t, int ks, int N, int Kp, int m_rows, int epilo
     const double busy = (double)rest / n_cu;
     const int trips = (Kp / 32 + ks - 1) / ks;
     BlockRates r = kBlockRates;
-    double trip;
+    double trip, bytes = epilogue == EPI_SWIGLU ? 1.0 : 4.0 * ks;
+    const bool large = !cached(N, Kp) && m_rows > kBlockStreamRows;
     if (stream_bound(N, Kp, m_rows) && &t - block_tiles < kBlockStreamTiles) {
         const double* ns = kBlockStreamTrips[&t - block_tiles];
         r = kBlockStreamRates;
@@ -69,14 +81,21 @@ double block_ns(const BlockTile& t, int ks, int N, int Kp, int m_rows, int epilo
     } else {
         const double last = rest > n_cu ? t.trip_full * (kBlockHalfPair + (1.0 - kBlockHalfPair) * busy / t.per_cu)
                                         : rest > 0 ? t.trip_one * (t.few + (1.0 - t.few) * busy) : 0.0;
-        // long loops run behind their weights more than short ones, small tiles above all
-        trip = ((double)full * t.trip_full + last) * std::pow(trips / 128.0, t.ms * t.ns < 64 ? 0.328 : 0.034);
+        // small tiles run behind their weights in long loops
+        trip = ((double)full * t.trip_full + last) * std::pow(trips / 128.0, t.ms * t.ns < 64 ? 0.35 : -0.108);
+        if (t.per_cu == 2 && full >= kBlockManyRounds && trips <= kBlockManyTrips) trip *= kBlockManyGain;
+        // tiles that reach past the matrix multiply there as well: units that would idle cost less of the chip's power
+        if (large) trip *= 1.0 + kBlockPad * ((double)(wgs / ks) * t.ms * t.ns / ((double)strips_m * strips_n) - 1.0);
+        if (large && ks == 1 && epilogue != EPI_SWIGLU) bytes = finish_bytes(epilogue);
     }
     const double cells = (double)m_rows * N;
-    const double work = r.start + trip * trips + cells * (epilogue == EPI_SWIGLU ? 1.0 : 4.0 * ks) / (r.write * 1000.0);
+    const double work = r.start + trip * trips + cells * bytes / (r.write * 1000.0);
     const double stream = r.start + (double)N * Kp * 2 / (r.stream * 1000.0);
     const double ns = work > stream ? work : stream;
-    return epilogue == EPI_SWIGLU ? ns : ns + cells * 4.0 * (ks - 1) / (kPartialRead * 1000.0);
+    if (epilogue == EPI_SWIGLU || ks == 1) return ns;
+    // sliced q|k|v of a prompt forward: a launch that rotates reads all slices
+    if (large && epilogue == EPI_QKV) return ns + kRotateStart + cells * 4.0 * ks / (kPartialRead * 1000.0);
+    return ns + cells * 4.0 * (ks - 1) / (kPartialRead * 1000.0);
 }
 }
 

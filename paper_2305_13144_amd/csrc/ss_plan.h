@@ -8,7 +8,8 @@
 
 namespace ss {
 
-// EPI_RESIDUAL and EPI_QKV: block kernel without k-slices only; planned as EPI_PARTIAL.
+// EPI_RESIDUAL and EPI_QKV: block kernel without k-slices only.  A plan for them is one for EPI_PARTIAL that, in the block kernel, counts what
+// finishing costs with and without k-slices.
 enum Epilogue { EPI_PARTIAL = 0, EPI_SWIGLU = 1, EPI_RESIDUAL = 2, EPI_QKV = 3 };
 
 constexpr int kSweepMaxRows = 192;   // 12 row strips: beyond, the sweep kernel is never the faster one (see sweep_rows)
@@ -51,6 +52,8 @@ struct GemmPlan {
 // A wave takes an item of a unit: the k-blocks of a slice (kb_slice), or one of `parts` parts of it: 2 parts take its groups of 4
 // k-blocks in turn (sweep kernel, two waves per unit), 4 parts a quarter each (skinny kernel).  wave_kb: the slice's quarters are chains of
 // their own also where one wave takes them all.  items: those of a unit; units_wg: units of a workgroup (0: no such plan).
+// kFewRows: where the two meet on the wider matrices; ms per step of 12 layers of the 7B widths, others / these kernels: 4 rows 0.897 / 0.871,
+// 5 rows 0.898 / 0.900, 6 rows 0.901 / 0.920; 13B widths, 8 layers, 5 rows 0.856 / 0.840; 2048 wide, 5 rows 0.517 / 0.483, 6 rows 0.516 / 0.497.
 constexpr int kFewRows = 4, kFewWaves = 8, kFewMaxK = 16384;
 struct FewPlan {
     int units_wg, items, parts, kb_slice, wave_kb;
