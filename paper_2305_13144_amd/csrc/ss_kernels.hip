@@ -43,6 +43,14 @@ __device__ __forceinline__ f16_t f2h(float f)
     return __builtin_bit_cast(f16_t, (_Float16)(f != f ? f : c));
 }
 
+// Rotation of a pair of elements.  Which product of the sum is rounded first is written out: the compiler would choose by what is around
+// it, and every kernel that rotates is to round alike (a prompt's keys and queries do not depend on whether q|k|v was cut in k-slices).
+// In the difference it rounds the second product in all of them.
+__device__ __forceinline__ float2 rotated(float a, float b, float cs, float sn)
+{
+    return make_float2(a * cs - b * sn, fmaf(b, cs, a * sn));
+}
+
 // Key/value slots are stored as IEEE half: the same 2 bytes per element as bf16 with three more
 // significand bits; keys and values are projections of RMS-normalised activations, far inside its range.
 __device__ __forceinline__ float kv2f(kv_t b) { return (float)__builtin_bit_cast(_Float16, b); }
@@ -1157,9 +1165,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_block(GemmArgs a, QkvO
                         const float cs[4] = {c4.x, c4.y, c4.z, c4.w}, sn[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
                         for (int q = 0; q < 4; ++q) {
-                            const float a1 = x[q], a2 = y[q];
-                            x[q] = a1 * cs[q] - a2 * sn[q];
-                            y[q] = a1 * sn[q] + a2 * cs[q];
+                            const float2 r = rotated(x[q], y[q], cs[q], sn[q]);
+                            x[q] = r.x;
+                            y[q] = r.y;
                         }
                     }
                     if (part == 0) {
@@ -1224,11 +1232,12 @@ __global__ __launch_bounds__(256) void k_rope_append(MbState st, const float* __
 #pragma unroll
         for (int s = 0; s < kNormMaxSplit; ++s) t[i] += v[s][i];
     }
-    qrot[(size_t)j * d + c] = t[0] * cs - t[1] * sn;
-    qrot[(size_t)j * d + c + half] = t[0] * sn + t[1] * cs;
+    const float2 q = rotated(t[0], t[1], cs, sn), k = rotated(t[2], t[3], cs, sn);
+    qrot[(size_t)j * d + c] = q.x;
+    qrot[(size_t)j * d + c + half] = q.y;
     const size_t o = slab + ((size_t)h * cap + pos) * hd + e;
-    kc[o] = f2kv(t[2] * cs - t[3] * sn);
-    kc[o + half] = f2kv(t[2] * sn + t[3] * cs);
+    kc[o] = f2kv(k.x);
+    kc[o + half] = f2kv(k.y);
     vc[o] = f2kv(t[4]);
     vc[o + half] = f2kv(t[5]);
 }
@@ -1670,9 +1679,9 @@ __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const 
         }
         if (which < 2) {
             const float cs = rcos[(size_t)pos * HALF + e], sn = rsin[(size_t)pos * HALF + e];
-            const float ra = a * cs - b * sn, rb = a * sn + b * cs;
-            a = ra;
-            b = rb;
+            const float2 r = rotated(a, b, cs, sn);
+            a = r.x;
+            b = r.y;
         }
         if (which == 0) {
             qs[e] = a;
@@ -1931,9 +1940,9 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
                         } else {   // elements e and e + HD/2 of a head (see qkv_strip)
                             const int which = now / (d >> 5), r = now - which * (d >> 5), e = r / PH * HD + r % PH * 16 + col;
                             if (which < 2) {
-                                const float c = cs[e % HD], s = cs[HALF + e % HD], r0 = s0 * c - s1 * s, r1 = s0 * s + s1 * c;
-                                s0 = r0;
-                                s1 = r1;
+                                const float2 r = rotated(s0, s1, cs[e % HD], cs[HALF + e % HD]);
+                                s0 = r.x;
+                                s1 = r.y;
                             }
                             if (which == 0) {
                                 q[e] = s0;
