@@ -272,12 +272,12 @@ constexpr int kNormNarrowFrom = 384;   // token-rows from which a row gets 256 t
 // Written out: every kernel that norms rows is to round alike.
 __device__ __forceinline__ float norm_squares(const float4& a) { return fmaf(a.w, a.w, fmaf(a.z, a.z, fmaf(a.x, a.x, a.y * a.y))); }
 
-// Four elements of a row, normalised (r: the row's factor, wr: their gains).
-__device__ __forceinline__ uint2 norm_apply(const float4& v, float r, const uint2& wr)
+// Four elements of a row, normalised (r: the row's factor, wr: their gains), to `out`.
+__device__ __forceinline__ void norm_store(f16_t* out, const float4& v, float r, const uint2& wr)
 {
     const bf16_t* wv = (const bf16_t*)&wr;
     const f16_t o[4] = {f2h(v.x * r * bf2f(wv[0])), f2h(v.y * r * bf2f(wv[1])), f2h(v.z * r * bf2f(wv[2])), f2h(v.w * r * bf2f(wv[3]))};
-    return *(const uint2*)o;
+    *(uint2*)out = *(const uint2*)o;
 }
 
 template <int T, int ITER>
@@ -345,7 +345,7 @@ __global__ __launch_bounds__(T) void k_rmsnorm(const int32_t* __restrict__ d_cou
         const int c = threadIdx.x * 4 + it * T * 4;
         if (c < d) {
             const size_t at = pk_index(j, c, d);   // d is a multiple of 64: Kp == d
-            *(uint2*)(h + at) = norm_apply(v[it], r, wr[it]);
+            norm_store(h + at, v[it], r, wr[it]);
         }
     }
 }
@@ -898,7 +898,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
 #pragma unroll
                 for (int it = 0; it < 2; ++it) {
                     const int c = (tid + t * T) * 4 + it * 4096;
-                    if (c < a.Kp) *(uint2*)(xs + r * xrow + c) = norm_apply(v[NORM ? r : 0][t][it], f, wr[t][it]);
+                    if (c < a.Kp) norm_store(xs + r * xrow + c, v[NORM ? r : 0][t][it], f, wr[t][it]);
                 }
         }
     } else {
