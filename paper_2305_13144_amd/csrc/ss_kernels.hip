@@ -1252,12 +1252,19 @@ __global__ __launch_bounds__(256) void k_rope_append(MbState st, const float* __
 // loads of a group that lie beyond the context are left out of both passes.  Per layer, 7B: 163 rows
 // 31.4 -> 27.1 us, 51 rows 15.7 -> 14.1, one row 8.1 -> 6.8 (contexts of 16 to 70).
 constexpr int kAttnUnroll = 8, kAttnShort = 4;   // loads of a wave before it consumes them; where that many hold the whole context
+// (row, head) pairs, and trips of all waves over the context, for which a load that lies wholly beyond the context is skipped by a branch
+// instead of issued for nothing: some units have a pair more than others there, and what those issue is on the longest path; with more
+// trips, or next to no or many pairs a unit, the branches cost more.  Microseconds a launch, lanes tested (the form before buffers) / all loads
+// issued / skipped: 288 pairs (7B, 9 rows) at 140 slots 8.0 / 8.7 / 7.8, 250 slots 10.8 / 11.3 / 10.5, 520 slots 17.0 / 18.1 / 16.9, 700 slots (6
+// trips) 21.4 / 19.6 / 20.8; 640 pairs (13B, 16 rows) at 110 slots 10.2 / 10.7 / 10.3; 32 pairs at 200 slots 6.1 / 5.9 / 6.3; 1536 at 330 51.9 / 51.6 / 52.6.
+constexpr int kAttnTailFrom = 256, kAttnTailTo = 1024, kAttnTailTrips = 3;
 
 // The slots are dealt to NW slices, one per wave, or NW / PW for each of PW waves: the sums are the same sums in the same order.
 // A wave's loads then go to its slices in turn, so that the workgroup walks over the slots as with NW = PW (one slice after the
 // other it asks for every second 4 KB at a time: 16 rows of 40 heads, context 1500, 174 us a layer instead of 165).
 // SPLIT: the slots are a share of the row's; their sums, maximum and total go to `share` (see k_attention_join).
-template <int HD, int NW, int PW, bool SPLIT, int AU>
+// TAIL: loads that lie wholly beyond the context are not issued.
+template <int HD, int NW, int PW, bool SPLIT, int AU, bool TAIL>
 __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __restrict__ sc, float* __restrict__ red,
                                        float (*__restrict__ oacc)[HD], const kv_t* __restrict__ kbase,
                                        const kv_t* __restrict__ vbase, int ctx, f16_t* __restrict__ out, int out_r,
@@ -1283,6 +1290,7 @@ __device__ __forceinline__ void attend(const float* __restrict__ qs, float* __re
     const __amdgpu_buffer_rsrc_t ksrc = slots(kbase), vsrc = slots(vbase);
     const unsigned lane_at = (unsigned)(kin * HD + sub * 8) * 2;
     auto load = [&](__amdgpu_buffer_rsrc_t src, int first) {   // this lane's piece of the wave's keys from `first` on
+        if (TAIL && first >= ctx) return make_uint4(0, 0, 0, 0);   // wave-uniform
         return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(src, lane_at + (unsigned)(first * HD * 2), 0, 0));
     };
     float q[8];
@@ -1696,10 +1704,13 @@ __global__ __launch_bounds__(64 * PW) void k_attention_decode(MbState st, const 
     if (64 * PW < 3 * HALF) finish(threadIdx.x + 64 * PW);
     __syncthreads();   // the new key/value slot and q are visible to the whole workgroup
     const kv_t *kb = kc + base + (size_t)begin * HD, *vb = vc + base + (size_t)begin * HD;
-    if (!SPLIT && slots <= kAttnShort * PW * (512 / HD))
-        attend<HD, NW, PW, SPLIT, kAttnShort>(qs, sc, red, oacc, kb, vb, slots, out, j, h * HD, d, share);
+    const int pairs = gridDim.x * gridDim.y, load_slots = PW * (512 / HD);   // slots of one load of every wave
+    if (!SPLIT && slots <= kAttnShort * load_slots)
+        attend<HD, NW, PW, SPLIT, kAttnShort, false>(qs, sc, red, oacc, kb, vb, slots, out, j, h * HD, d, share);
+    else if (!SPLIT && NW <= 8 && pairs > kAttnTailFrom && pairs <= kAttnTailTo && slots <= kAttnTailTrips * kAttnUnroll * load_slots)
+        attend<HD, NW, PW, SPLIT, kAttnUnroll, true>(qs, sc, red, oacc, kb, vb, slots, out, j, h * HD, d, share);
     else
-        attend<HD, NW, PW, SPLIT, kAttnUnroll>(qs, sc, red, oacc, kb, vb, slots, out, j, h * HD, d, share);
+        attend<HD, NW, PW, SPLIT, kAttnUnroll, false>(qs, sc, red, oacc, kb, vb, slots, out, j, h * HD, d, share);
 }
 
 // The shares of a pair's slots put together: one wave per pair, two elements a lane (HD 64: half the lanes).
