@@ -365,7 +365,8 @@ int ss_bench_decode_steps_in_flight(ss_weights* w, const int32_t* prompt_tokens,
  * Measurement entry point: the projection kernels of one decode step alone.  Launches, back to back on
  * one stream, exactly the matrix kernels a B-row decode forward launches where its rows do not take their steps in
  * one workgroup each, as those of small models do (per layer q|k|v, o, gate|up
- * with the SwiGLU epilogue, down; then the LM head) with the same launch configuration, on whatever the
+ * with the SwiGLU epilogue, down; then the LM head) with the same launch configuration (up to 4 rows, where every matrix has
+ * its 12-bit copy, those that have the norms inside them), on whatever the
  * activation buffers currently hold, `iters` times.  Every matrix is streamed once per iteration, in the form that
  * B rows read: the 12-bit copies up to 96 rows where there are any (ss_bench_read_stream gives their bytes), else 2
  * bytes per weight.  ms_out: host, double[iters], device time of

@@ -596,41 +596,66 @@ void choose_tokens(const ss_weights* w, const Lane& ln, const float* logits, con
         ss::launch_argmax(logits, w->cfg.vocab, d_nsel, ln.st.am, n_sel, s);
 }
 
-// A decode forward of up to kFewRows rows in 5 launches per layer instead of 7 (k_gemm_few); false, and nothing done, if some
-// matrix is not streamed in the 12-bit form.
+// The projections of a decode forward of up to kFewRows rows, the norms inside them (k_gemm_few); not ok if some matrix is not
+// streamed in the 12-bit form.
+struct FewRows {
+    const ss_weights* w;
+    Workspace& ws;
+    int n;
+    ss::FewPlan plan_qkv, plan_o, plan_gu, plan_down, plan_lm;
+    bool ok;
+
+    FewRows(const ss_weights* w_, Workspace& ws_, int n_) : w(w_), ws(ws_), n(n_)
+    {
+        const int d = w->cfg.d_model, F = w->cfg.d_ffn, cu = w->n_cu;
+        plan_qkv = ss::few_plan(3 * d, d, n, ss::EPI_PARTIAL, cu);
+        plan_o = ss::few_plan(d, d, n, ss::EPI_RESIDUAL, cu);
+        plan_gu = ss::few_plan(2 * F, d, n, ss::EPI_SWIGLU, cu);
+        plan_down = ss::few_plan(d, ss::padded_k(F), n, ss::EPI_RESIDUAL, cu);
+        plan_lm = ss::few_plan(w->cfg.vocab, d, n, ss::EPI_PARTIAL, cu, 1);
+        ok = plan_qkv.units_wg && plan_o.units_wg && plan_gu.units_wg && plan_down.units_wg && plan_lm.units_wg && w->lm_head.pn;
+        for (const Layer& L : w->layers) ok = ok && L.wqkv.pn && L.wo.pn && L.wgu.pn && L.wd.pn;
+    }
+
+    void run(const PackedMat& W, const ss::FewPlan& p, int epilogue, const ss::bf16_t* gain, const f16_t* X, float* out, hipStream_t s) const
+    {
+        ss::FewArgs a{};
+        a.Wn = W.pn; a.x = ws.x.as<float>(); a.gain = gain; a.X = X; a.out = out; a.out_packed = ws.act.as<f16_t>(); a.plan = p; a.N = W.N; a.Kp = W.Kp;
+        a.n_rows = n; a.kp_out = ss::padded_k(w->cfg.d_ffn); a.units = W.N / (epilogue == ss::EPI_SWIGLU ? 32 : 16); a.eps = w->cfg.rms_eps;
+        ss::launch_gemm_few(a, epilogue, s);
+    }
+    void qkv(const Layer& L, hipStream_t s) const { run(L.wqkv, plan_qkv, ss::EPI_PARTIAL, L.attn_norm, nullptr, ws.pqkv.as<float>(), s); }
+    void rest(const Layer& L, hipStream_t s) const   // what follows the attention
+    {
+        run(L.wo, plan_o, ss::EPI_RESIDUAL, nullptr, ws.ao.as<f16_t>(), ws.x.as<float>(), s);
+        run(L.wgu, plan_gu, ss::EPI_SWIGLU, L.mlp_norm, nullptr, nullptr, s);
+        run(L.wd, plan_down, ss::EPI_RESIDUAL, nullptr, ws.act.as<f16_t>(), ws.x.as<float>(), s);
+    }
+    void head(float* logits, hipStream_t s) const { run(w->lm_head, plan_lm, ss::EPI_PARTIAL, w->final_norm, nullptr, logits, s); }
+};
+
+// A decode forward of up to kFewRows rows in 5 launches per layer instead of 7; false, and nothing done, if its projections cannot be.
 bool few_forward(const ss_weights* w, Lane& ln, int n, hipStream_t s)
 {
     const ss_model_cfg& c = w->cfg;
-    const int d = c.d_model, F = c.d_ffn, V = c.vocab, Fp = ss::padded_k(F), cu = w->n_cu;
-    const ss::FewPlan qkv = ss::few_plan(3 * d, d, n, ss::EPI_PARTIAL, cu), o = ss::few_plan(d, d, n, ss::EPI_RESIDUAL, cu),
-                      gu = ss::few_plan(2 * F, d, n, ss::EPI_SWIGLU, cu), down = ss::few_plan(d, Fp, n, ss::EPI_RESIDUAL, cu),
-                      lm = ss::few_plan(V, d, n, ss::EPI_PARTIAL, cu, 1);
-    if (!qkv.units_wg || !o.units_wg || !gu.units_wg || !down.units_wg || !lm.units_wg || !w->lm_head.pn) return false;
-    for (const Layer& L : w->layers)
-        if (!L.wqkv.pn || !L.wo.pn || !L.wgu.pn || !L.wd.pn) return false;
+    const int d = c.d_model;
     Workspace& ws = ln.ws;
+    const FewRows few(w, ws, n);
+    if (!few.ok) return false;
     const MbState& st = ln.st;
-    float *x = ws.x.as<float>(), *pqkv = ws.pqkv.as<float>();
-    f16_t *ao = ws.ao.as<f16_t>(), *act = ws.act.as<f16_t>();
-    auto run = [&](const PackedMat& W, const ss::FewPlan& p, int epilogue, const ss::bf16_t* gain, const f16_t* X, float* out) {
-        ss::FewArgs a{};
-        a.Wn = W.pn; a.x = x; a.gain = gain; a.X = X; a.out = out; a.out_packed = act; a.plan = p; a.N = W.N; a.Kp = W.Kp;
-        a.n_rows = n; a.kp_out = Fp; a.units = W.N / (epilogue == ss::EPI_SWIGLU ? 32 : 16); a.eps = c.rms_eps;
-        ss::launch_gemm_few(a, epilogue, s);
-    };
-    ss::launch_embed(st, w->embed, x, d, n, s);
+    float* pqkv = ws.pqkv.as<float>();
+    f16_t* ao = ws.ao.as<f16_t>();
+    ss::launch_embed(st, w->embed, ws.x.as<float>(), d, n, s);
     for (int l = 0; l < c.n_layers; ++l) {
         const Layer& L = w->layers[l];
         ss::kv_t* kc = ws.kv.as<ss::kv_t>() + (size_t)l * 2 * ln.kv_layer_stride;
-        run(L.wqkv, qkv, ss::EPI_PARTIAL, L.attn_norm, nullptr, pqkv);
+        few.qkv(L, s);
         ss::launch_attention_decode(st, pqkv, 1, (size_t)n * 3 * d, kc, kc + ln.kv_layer_stride, w->rope_cos, w->rope_sin, ao, d, c.n_heads,
                                     c.head_dim, n, ln.plan_rows ? ln.plan_rows : n, ln.prompt_rows, ln.max_ctx, ws.qrot.as<float>(), s);
-        run(L.wo, o, ss::EPI_RESIDUAL, nullptr, ao, x);
-        run(L.wgu, gu, ss::EPI_SWIGLU, L.mlp_norm, nullptr, nullptr);
-        run(L.wd, down, ss::EPI_RESIDUAL, nullptr, act, x);
+        few.rest(L, s);
     }
     float* logits = ln.cur_logits ? ln.cur_logits : ws.logits.as<float>();
-    run(w->lm_head, lm, ss::EPI_PARTIAL, w->final_norm, nullptr, logits);
+    few.head(logits, s);
     choose_tokens(w, ln, logits, st.d_n, n, s);
     return true;
 }
@@ -2116,6 +2141,7 @@ int bench_weight_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32
     f16_t *h = ws.h.as<f16_t>(), *ao = ws.ao.as<f16_t>(), *act = ws.act.as<f16_t>();
     float *pqkv = ws.pqkv.as<float>(), *pd = ws.pd.as<float>(), *x = ws.x.as<float>();
     const bool whole_o = p_o.block >= 0 && p_o.ksplit == 1, whole_d = p_d.block >= 0 && p_d.ksplit == 1;   // as in forward()
+    const FewRows few(w, ws, n);
     EventList evl;
     if (int rc = evl.create(iters + 1)) return rc;
     const std::vector<hipEvent_t>& ev = evl.e;
@@ -2125,15 +2151,22 @@ int bench_weight_stream_impl(const ss_weights* w, Lane& ln, hipStream_t s, int32
         launches = 0;
         for (int l = 0; l < c.n_layers; ++l) {
             const Layer& L = w->layers[l];
+            launches += 4;
+            if (few.ok) {
+                few.qkv(L, s);
+                few.rest(L, s);
+                continue;
+            }
             ss::launch_gemm(mk(L.wqkv, h, pqkv, nullptr, n, 0, p_qkv), ss::EPI_PARTIAL, s);
             ss::launch_gemm(mk(L.wo, ao, whole_o ? x : pd, nullptr, n, 0, p_o), whole_o ? ss::EPI_RESIDUAL : ss::EPI_PARTIAL, s);
             ss::launch_gemm(mk(L.wgu, h, nullptr, act, n, Fp, p_gu), ss::EPI_SWIGLU, s);
             ss::launch_gemm(mk(L.wd, act, whole_d ? x : pd, nullptr, n, 0, p_d), whole_d ? ss::EPI_RESIDUAL : ss::EPI_PARTIAL, s);
-            launches += 4;
         }
-        ss::launch_gemm(mk(w->lm_head, ws.hsel.as<f16_t>(), ws.logits.as<float>(), nullptr, n, 0, p_lm),
-                        ss::EPI_PARTIAL, s);
         launches += 1;
+        if (few.ok)
+            few.head(ws.logits.as<float>(), s);
+        else
+            ss::launch_gemm(mk(w->lm_head, ws.hsel.as<f16_t>(), ws.logits.as<float>(), nullptr, n, 0, p_lm), ss::EPI_PARTIAL, s);
         HIPCHK(hipEventRecord(ev[it + 1], s));
     }
     HIPCHK(hipStreamSynchronize(s));
