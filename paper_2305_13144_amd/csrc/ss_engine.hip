@@ -621,8 +621,8 @@ struct FewRows {
     {
         ss::FewArgs a{};
         a.Wn = W.pn; a.x = ws.x.as<float>(); a.gain = gain; a.X = X; a.out = out; a.out_packed = ws.act.as<f16_t>(); a.plan = p; a.N = W.N; a.Kp = W.Kp;
-        a.n_rows = n; a.kp_out = ss::padded_k(w->cfg.d_ffn); a.units = W.N / (epilogue == ss::EPI_SWIGLU ? 32 : 16); a.eps = w->cfg.rms_eps;
-        ss::launch_gemm_few(a, epilogue, s);
+        a.kp_out = ss::padded_k(w->cfg.d_ffn); a.units = W.N / (epilogue == ss::EPI_SWIGLU ? 32 : 16); a.eps = w->cfg.rms_eps;
+        ss::launch_gemm_few(a, n, epilogue, s);
     }
     void qkv(const Layer& L, hipStream_t s) const { run(L.wqkv, plan_qkv, ss::EPI_PARTIAL, L.attn_norm, nullptr, ws.pqkv.as<float>(), s); }
     void rest(const Layer& L, hipStream_t s) const   // what follows the attention

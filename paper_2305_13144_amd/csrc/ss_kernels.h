@@ -95,10 +95,10 @@ struct FewArgs {
     float* out;
     f16_t* out_packed;
     FewPlan plan;
-    int N, Kp, n_rows, kp_out, units;   // units: strips, or pairs of them with EPI_SWIGLU
+    int N, Kp, kp_out, units;   // units: strips, or pairs of them with EPI_SWIGLU
     float eps;
 };
-void launch_gemm_few(const FewArgs& a, int epilogue, hipStream_t s);
+void launch_gemm_few(const FewArgs& a, int n_rows, int epilogue, hipStream_t s);
 void launch_rope_append(const MbState& st, const float* qkv_part, int ksplit, size_t part_stride, float* qrot,
                         kv_t* kcache, kv_t* vcache, const float* rope_cos, const float* rope_sin, int d, int H,
                         int hd, int n_max, hipStream_t s);

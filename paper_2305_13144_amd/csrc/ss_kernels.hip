@@ -820,7 +820,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
                 if (c < a.Kp) {
                     wr[t][it] = *(const uint2*)(a.gain + c);
 #pragma unroll
-                    for (int r = 0; r < R; ++r) v[NORM ? r : 0][t][it] = *(const float4*)(a.x + (size_t)min(r, a.n_rows - 1) * a.Kp + c);
+                    for (int r = 0; r < R; ++r) v[NORM ? r : 0][t][it] = *(const float4*)(a.x + (size_t)r * a.Kp + c);
                 }
             }
     } else {
@@ -828,7 +828,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
 #pragma unroll
         for (int i = 0; i < NP; ++i) {   // beyond the last piece: beyond the buffer
             const int z = tid + i * T, r = z % R, kg = z / R;   // k-group kg of row r
-            piece[i] = __builtin_amdgcn_raw_buffer_load_b128(xsrc, (kg >> 2) * 1024 + ((kg & 3) * 16 + min(r, a.n_rows - 1)) * 16, 0, 0);
+            piece[i] = __builtin_amdgcn_raw_buffer_load_b128(xsrc, (kg >> 2) * 1024 + ((kg & 3) * 16 + r) * 16, 0, 0);
         }
     }
 
@@ -947,7 +947,7 @@ __global__ __launch_bounds__(64 * kFewWaves) void k_gemm_few(FewArgs a)
     }
 #pragma unroll
     for (int n = 0; n < NBW; ++n) red[(wave * NBW + n) * 64 + lane] = restart > 0 ? tot[n] + acc[n] : acc[n];
-    const bool stores = active && item == 0 && row < a.n_rows;
+    const bool stores = active && item == 0 && row < R;
     if (EPI == EPI_RESIDUAL && stores) old = *(const float4*)(a.out + (size_t)row * a.N + unit * 16 + col4);
     __syncthreads();
     if (!stores) return;
@@ -2518,11 +2518,11 @@ static void launch_few_r(const FewArgs& a, int epilogue, hipStream_t s)
     else hipLaunchKernelGGL((k_gemm_few<R, 1, EPI_PARTIAL, true>), grid, block, lds, s, a);
 }
 
-void launch_gemm_few(const FewArgs& a, int epilogue, hipStream_t s)
+void launch_gemm_few(const FewArgs& a, int n_rows, int epilogue, hipStream_t s)
 {
-    if (a.n_rows == 1) launch_few_r<1>(a, epilogue, s);
-    else if (a.n_rows == 2) launch_few_r<2>(a, epilogue, s);
-    else if (a.n_rows == 3) launch_few_r<3>(a, epilogue, s);
+    if (n_rows == 1) launch_few_r<1>(a, epilogue, s);
+    else if (n_rows == 2) launch_few_r<2>(a, epilogue, s);
+    else if (n_rows == 3) launch_few_r<3>(a, epilogue, s);
     else launch_few_r<4>(a, epilogue, s);
 }
 
