@@ -1013,8 +1013,6 @@ __device__ __forceinline__ void wait_copies_and_meet()
     asm volatile("" ::: "memory");
 }
 
-constexpr int kBlockOwnFrom = 4;   // row tiles per die from which a die keeps its own
-
 // Unsliced launches finish their results themselves.  EPI_RESIDUAL adds the sums to the residual stream in place, EPI_QKV
 // rotates q and k and puts q, k and v where the attention reads them, instead of writing fp32 sums for the next launch to
 // read.  12311 token-rows, 7B, per layer: the rotation launch (184 us) is gone, the norms take 108 us instead of 167, o
@@ -1033,26 +1031,9 @@ __global__ __launch_bounds__(64 * WM * WN, 2) void k_gemm_block(GemmArgs a, QkvO
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % WM, wn = wave / WM;
     const int KB = a.Kp >> 5, NBT = a.N >> 4, MBT = (a.m_rows + 15) >> 4;
-    // Workgroup ids are dealt to the 8 dies round-robin; the tiles a die works on at one time share their operands through
-    // its L2.  Few row tiles: panels of 8 of them, column tile by column tile inside a panel, a contiguous share for each
-    // die.  Many (4 or more for each die): a die keeps its own row tiles and takes them through all columns, so that the dies
-    // read the same weights at about the same time, once from HBM (fetching a line from afar is also power, which the matrix
-    // cores then lack: gate|up, 12311 rows, 1628 -> 1603 us); what is left over goes in panels as above.
-    const int tiles = n_ntiles * n_mtiles;
-    const int ks = blockIdx.x / tiles, b = blockIdx.x % tiles;
-    const int x = b & 7, own = MS >= 16 && n_mtiles >= 8 * kBlockOwnFrom ? n_mtiles >> 3 : 0, i = (b >> 3) - own * n_ntiles;
-    int n_tile, m_tile;
-    if (i < 0) {
-        n_tile = (b >> 3) / max(own, 1);
-        m_tile = x * own + (b >> 3) % max(own, 1);
-    } else {
-        const int rest = tiles - 8 * own * n_ntiles, per = rest >> 3, extra = rest & 7;
-        const int t = x * per + min(x, extra) + i;
-        const int panel = t / (8 * n_ntiles), in_panel = t % (8 * n_ntiles), ph = min(8, n_mtiles - 8 * own - panel * 8);
-        n_tile = in_panel / ph;
-        m_tile = 8 * own + panel * 8 + in_panel % ph;
-    }
-    const int nb0 = n_tile * NS, mb0 = m_tile * MS;
+    const int tiles = n_ntiles * n_mtiles, ks = blockIdx.x / tiles;
+    const BlockPlace place_of = block_place(blockIdx.x % tiles, n_ntiles, n_mtiles, MS);
+    const int nb0 = place_of.n_tile * NS, mb0 = place_of.m_tile * MS;
     const int s0 = ks * kb_per_slice, s1 = min(KB, s0 + kb_per_slice);
     const int trips = s1 - s0;
 
