@@ -97,7 +97,7 @@ PLAN_DRIVER = textwrap.dedent(r"""
                                 32704, 32705, 100000, 1048576};
         const int cus[] = {64, 256, 304};
         long checked = 0;
-        const int modes[] = {0, 1, 2, 4, 5, 6, 8, 9, 10, 12, 13, 14, 17, 33, 49, 65, 81};
+        const int modes[] = {0, 1, 2, 4, 5, 6, 8, 9, 10, 12, 13, 14, 17, 33, 49, 65, 81, 97, 113, 129, 145, 161, 177, 193, 209, 225, 241};
         for (int mode : modes) {
             ss::set_gemm_mode(mode);
             for (int cu : cus)
@@ -105,8 +105,8 @@ PLAN_DRIVER = textwrap.dedent(r"""
                     for (int F : ffns) {
                         const int Fp = (F + 63) / 64 * 64;
                         struct { int N, Kp, epi; } mats[] = {
-                            {3 * d, d, ss::EPI_PARTIAL}, {d, d, ss::EPI_PARTIAL},
-                            {2 * F, d, ss::EPI_SWIGLU}, {d, Fp, ss::EPI_PARTIAL}};
+                            {3 * d, d, ss::EPI_PARTIAL}, {3 * d, d, ss::EPI_QKV}, {d, d, ss::EPI_PARTIAL}, {d, d, ss::EPI_RESIDUAL},
+                            {2 * F, d, ss::EPI_SWIGLU}, {d, Fp, ss::EPI_PARTIAL}, {d, Fp, ss::EPI_RESIDUAL}};
                         for (auto& m : mats)
                             for (int n_max : row_grid) {
                                 const size_t cap = ss::gemm_partial_rows_bound(n_max);
@@ -161,6 +161,8 @@ PLAN_DRIVER = textwrap.dedent(r"""
             for (int n = 1; n <= n_max; n += 13) {
                 if ((size_t)ss::gemm_plan(1024, 4096, n, ss::EPI_PARTIAL, 256).ksplit * n > c1) return 4;
                 if ((size_t)ss::gemm_plan(1024, 1024, n, ss::EPI_PARTIAL, 256).ksplit * n > c1) return 5;
+                if ((size_t)ss::gemm_plan(1024, 4096, n, ss::EPI_RESIDUAL, 256).ksplit * n > c1) return 8;
+                if ((size_t)ss::gemm_plan(3072, 1024, n, ss::EPI_QKV, 256).ksplit * n > c1) return 9;
                 if (ss::gemm_plan(2 * 512, 4096, n, ss::EPI_SWIGLU, 256).ksplit > 1) return 6;
             }
         }

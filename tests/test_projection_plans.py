@@ -18,15 +18,16 @@ HEAD = textwrap.dedent(r"""
     #include "ss_plan.h"
     static inline bool same(const ss::GemmPlan& a, const ss::GemmPlan& b) { return std::memcmp(&a, &b, sizeof a) == 0; }   // ints only
     struct Mat { int N, Kp, epi, max_ksplit; };
-    // q|k|v, o, gate|up, down and the head of models of every width the library takes
+    // q|k|v, o, gate|up, down and the head of models of every width the library takes, q|k|v, o and down with every
+    // epilogue that they are planned with
     template <class F> static int every_matrix(F f) {
         const int dims[] = {64, 256, 512, 1024, 2048, 3072, 4096, 5120, 8192};
         const int ffns[] = {16, 688, 2752, 11008, 13824, 28672};
         for (int d : dims)
             for (int F_ : ffns) {
                 const int Fp = (F_ + 63) / 64 * 64;
-                const Mat mats[] = {{3 * d, d, ss::EPI_PARTIAL, 8}, {d, d, ss::EPI_PARTIAL, 8}, {2 * F_, d, ss::EPI_SWIGLU, 8},
-                                    {d, Fp, ss::EPI_PARTIAL, 8}, {32000, d, ss::EPI_PARTIAL, 1}, {1040, d, ss::EPI_PARTIAL, 1}};
+                const Mat mats[] = {{3 * d, d, ss::EPI_PARTIAL, 8}, {3 * d, d, ss::EPI_QKV, 8}, {d, d, ss::EPI_PARTIAL, 8}, {d, d, ss::EPI_RESIDUAL, 8},
+                                    {2 * F_, d, ss::EPI_SWIGLU, 8}, {d, Fp, ss::EPI_PARTIAL, 8}, {d, Fp, ss::EPI_RESIDUAL, 8}, {32000, d, ss::EPI_PARTIAL, 1}, {1040, d, ss::EPI_PARTIAL, 1}};
                 for (const Mat& m : mats)
                     if (int rc = f(m)) return rc;
             }
@@ -52,7 +53,7 @@ def test_row_counts_of_one_strip_share_a_plan(tmp_path):
         int main() {
             return every_matrix([](const Mat& m) {
                 for (int cu : {64, 256, 304})
-                    for (int n = 1; n <= 1040; ++n) {
+                    for (int n = 1; n <= 12320; n += n <= 1040 ? 1 : 7) {
                         const int full = (n + 15) / 16 * 16;
                         if (same(ss::gemm_plan(m.N, m.Kp, n, m.epi, cu, m.max_ksplit), ss::gemm_plan(m.N, m.Kp, full, m.epi, cu, m.max_ksplit)))
                             continue;
