@@ -38,9 +38,8 @@ void ss_set_verbose(int32_t level);
  * token-rows, the block kernel, which stages both operands, above); 2: that kernel for every projection of at most 192
  * token-rows.
  * Adding 4 to a mode (4, 5, 6) keeps that kernel from sharing a strip's k-blocks between two wavefronts; adding 8 keeps
- * the block kernel from its largest tile (256 x 256, prompt forwards of more than 880 token-rows); both for A/B
- * measurements.  Adding 16 to 240 makes the block kernel use one of its fifteen tiles throughout (16: 256 x 256 token-rows x
- * columns, 32: 256 x 192, 48: 128 x 256, 64: 128 x 192, 80: 128 x 128, 96: 128 x 64, 112: 96 x 128, 128: 160 x 128,
+ * the block kernel from its tile of 256 x 256 (forwards of more than 256 token-rows); both for A/B measurements.
+ * Adding 16 to 240 makes the block kernel use one of its fifteen tiles throughout (16: 256 x 256 token-rows x columns, 32: 256 x 192, 48: 128 x 256, 64: 128 x 192, 80: 128 x 128, 96: 128 x 64, 112: 96 x 128, 128: 160 x 128,
  * 144: 192 x 128, 160: 256 x 128, 176: 160 x 192, 192: 192 x 192, 208: 224 x 256, 224: 320 x 192, 240: 384 x 192).
  * Any mode but 0 also keeps small models from taking a row's whole decode step in one workgroup.
  * Results agree to the rounding differences between launch shapes (about 1e-3 of the largest logit).  Process-wide (atomic

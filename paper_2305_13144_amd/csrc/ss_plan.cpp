@@ -25,6 +25,7 @@ constexpr double kPartialRead = 4.5;          // bytes per ns at which the consu
 constexpr double kRotateStart = 3000.0;       // ns of the launch that rotates slices of q|k|v
 // Tiles of which a unit holds two, from so many full rounds and up to so many k-blocks on: the workgroups of a unit have drifted apart, and one
 // multiplies while the other starts or finishes (gate|up, 12311 rows, tiles of 192 x 192 / 384 x 192: 1560 / 1607 us; down, 344 k-blocks: 937 / 871).
+// Where between 192 and 344 k-blocks the line lies made no difference (8192 wide; MLPs of 6912 and 8192).
 constexpr int kBlockManyRounds = 4, kBlockManyTrips = 192;
 constexpr double kBlockManyGain = 0.987;
 constexpr double kBlockPad = 0.08;             // share of the products beyond the matrix that is paid for again, in power
@@ -43,10 +44,12 @@ constexpr size_t kBlockCached = (size_t)16 << 20;
 
 // Fitted to 3000 timings inside prompt forwards of the 7B and 13B shapes, 304 to 12311 rows, every tile in turn (a projection that is launched
 // over and over finds its weights and its clock otherwise than one between others: up to 18 % apart, and not the same for all tiles), and to 1500
-// of launches alone at widths of 256 and 2048.  Of 248 projections in their forwards the tile taken is 0.4 % slower than the best of them on
-// average, 1.0 % at the smaller widths; the best of the first five, which were all there was, was 11.8 % slower: with more sizes to choose from,
-// tiles fill whole rounds of the 256 units.  The last digits are those with which the choice is best.  Fitted to launches alone, without what a launch's last step costs (finish_bytes), the tile taken was
-// 3.1 % slower.  Microseconds in a forward, with the consumer's reads, that fit / this one: 7B o 995 rows 44 / 39, 2033 rows 75 / 69, down 995 rows
+// of launches alone at widths of 256 and 2048.  With more sizes to choose from tiles fill whole rounds of the 256 units.  Timed anew inside forwards, every
+// tile in turn, how much slower than the best one are the tile taken / the best of the first five, which were all there was: 88 projections of the
+// 7B and 13B shapes 0.8 / 4.1 %; 336 of widths from 1280 to 8192 that the fit has not seen 1.2 / 4.5 % (27 % at worst); 240 of matrices up to 16 MB,
+// 640 to 2048 wide, 1.1 / 12.5 %.  Against the choice among five, 32 of the 664 are 2 to 12 % slower, none of 7B and 13B, and all together 8 % faster.
+// The last digits are those with which the choice is best.  Fitted to launches alone, without what a launch's last step costs (finish_bytes), the tile
+// taken was 3.1 % slower at 7B and 13B.  Microseconds in a forward, with the consumer's reads, that fit / this one: 7B o 995 rows 44 / 39, 2033 rows 75 / 69, down 995 rows
 // 89 / 86, gate|up 7200 rows 976 / 936, 12311 rows 1607 / 1560; 13B o 608 rows 53 / 43, 995 rows 70 / 57, down 12311 rows 1350 / 1304.
 const BlockTile block_tiles[kBlockTiles] = {
     {16, 16, 1, 704.0, 736.0, 1.0}, {16, 12, 1, 554.0, 590.0, 0.91}, {8, 16, 2, 449.0, 773.0, 0.79}, {8, 12, 2, 346.0, 638.0, 0.71},
@@ -81,8 +84,9 @@ double block_ns(const BlockTile& t, int ks, int N, int Kp, int m_rows, int epilo
     } else {
         const double last = rest > n_cu ? t.trip_full * (kBlockHalfPair + (1.0 - kBlockHalfPair) * busy / t.per_cu)
                                         : rest > 0 ? t.trip_one * (t.few + (1.0 - t.few) * busy) : 0.0;
-        // small tiles run behind their weights in long loops
-        trip = ((double)full * t.trip_full + last) * std::pow(trips / 128.0, t.ms * t.ns < 64 ? 0.35 : -0.108);
+        // small tiles run behind their weights in long loops (an exponent of 0.35, fitted to launches alone at widths of 256 and 2048, made short
+        // loops too cheap: 1536 wide, 2033 rows, o 32 us with what follows instead of 26; 768 wide, 2033 rows, gate|up 27 instead of 21)
+        trip = ((double)full * t.trip_full + last) * std::pow(trips / 128.0, t.ms * t.ns < 64 ? 0.1 : -0.108);
         if (t.per_cu == 2 && full >= kBlockManyRounds && trips <= kBlockManyTrips) trip *= kBlockManyGain;
         // tiles that reach past the matrix multiply there as well: units that would idle cost less of the chip's power
         if (large) trip *= 1.0 + kBlockPad * ((double)(wgs / ks) * t.ms * t.ns / ((double)strips_m * strips_n) - 1.0);
@@ -94,7 +98,7 @@ double block_ns(const BlockTile& t, int ks, int N, int Kp, int m_rows, int epilo
     const double ns = work > stream ? work : stream;
     if (epilogue == EPI_SWIGLU || ks == 1) return ns;
     // sliced q|k|v of a prompt forward: a launch that rotates reads all slices
-    if (large && epilogue == EPI_QKV) return ns + kRotateStart + cells * 4.0 * ks / (kPartialRead * 1000.0);
+    if (epilogue == EPI_QKV && !stream_bound(N, Kp, m_rows)) return ns + kRotateStart + cells * 4.0 * ks / (kPartialRead * 1000.0);
     return ns + cells * 4.0 * (ks - 1) / (kPartialRead * 1000.0);
 }
 }
@@ -103,7 +107,7 @@ void set_gemm_mode(int mode)
 {
     // bit 2 (value 4) added to a mode: the sweep kernel never splits a unit between two waves (A/B measurements)
     g_sweep_split.store((mode & 4) ? 0 : 1, std::memory_order_relaxed);
-    // bit 3 (value 8): the block kernel never uses its largest tile (A/B measurements)
+    // bit 3 (value 8): the block kernel never uses its tile of 256 x 256 (A/B measurements)
     g_tall_tiles.store((mode & 8) ? 0 : 1, std::memory_order_relaxed);
     // bits 4 and up: 1 + the only tile the block kernel uses
     g_block_tile.store((mode >> 4) - 1, std::memory_order_relaxed);

@@ -18,7 +18,7 @@ constexpr int kNarrowMaxRows = 96;   // most token-rows for which the 12-bit wei
 
 // 16-byte units from one strip of a 12-bit matrix to the next: 3 KiB for each group of 4 k-blocks, and a gap.  The units of the
 // chip stream different strips at about the same k, and where strips begin at multiples of 32 KiB, or are long, their requests
-// meet in the same parts of the memory: a gap of 4 KiB, of 12 from 240 KiB on, sends them to different ones.  Whole decode step, without gaps /
+// meet in the same parts of the memory: a gap of 4 KiB, of 12 above 240 KiB where it is no multiple of 32, sends them to different ones.  Whole decode step, without gaps /
 // with them: 7B widths, 12 layers (strips of 96 and 258 KiB) one row 0.955 / 0.888 ms, 16 rows 0.994 / 0.930, 64 rows 1.286 / 1.274, 96 rows
 // 1.539 / 1.542; 8192 wide, 4 layers (192, 516 KiB) 0.954 / 0.883, 0.980 / 0.911, 1.184 / 1.142, 1.436 / 1.424; 13B widths (120, 324 KiB), 2048,
 // 2816, 3072 and 6144 wide within 0.5 % either way.  Other gaps: 6 KiB instead of 12 for the long ones 7B 96 rows 1.550; at strips of 120 and 144
@@ -84,7 +84,10 @@ constexpr size_t few_lds_bytes(int rows, int Kp, int epilogue)
     return (size_t)rows * (Kp + 32) * 2 + (size_t)kFewWaves * (epilogue == EPI_SWIGLU ? 2 : 1) * 1024 + (size_t)rows * 64;
 }
 
-constexpr int kBlockTallFrom = 896;   // token-rows (in whole strips) from which the block kernel may use its largest tile
+// Token-rows (in whole strips) from which the block kernel may use its tile of 256 x 256: from the first that is priced by its products.  Below,
+// two of them at most share a column of weights, and smaller tiles spread those over more units.  Barred up to 880 rows, as it was when there were five
+// tiles: 494 rows, gate|up of 13B 137.8 us instead of 115.0, 6144 wide 170.7 / 150.8, 4096 wide with an MLP of 14336 110.4 / 96.0.
+constexpr int kBlockTallFrom = 272;
 
 // n_cu: compute units of the device (the sweep kernel runs one workgroup per unit).
 // max_ksplit: 1 when the consumer reads the output directly (logits).
