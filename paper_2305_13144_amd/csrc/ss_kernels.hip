@@ -1818,7 +1818,7 @@ __global__ __launch_bounds__(kRowThreads) void k_row_step(MbState st, RowStepArg
         return ph == phases - 1 ? a.V >> 4 : t == 0 ? 3 * d >> 4 : t == 2 ? a.F >> 3 : d >> 4;
     };
     // of the phase to come; each phase looks the next one's up while it waits for its own operands
-    // (looked up when it began, they kept every phase waiting 350 clocks: 16 rows 49.9 -> 49.0 us a step, the group of 16 2.26 -> 2.24 ms)
+    // (looked up when it began, they kept every phase waiting 350 clocks: 16 rows 49.5 -> 49.1 us a step, their 48 tokens 2.25 -> 2.22 ms)
     const f16_t* W2 = weights(0);
     int KB2 = kblocks(0), strips2 = strips_of(0);
     u32x4 v[2][kRowGroup];

@@ -46,7 +46,7 @@ constexpr size_t kBlockCached = (size_t)16 << 20;
 // over and over finds its weights and its clock otherwise than one between others: up to 18 % apart, and not the same for all tiles), and to 1500
 // of launches alone at widths of 256 and 2048.  With more sizes to choose from tiles fill whole rounds of the 256 units.  Timed anew inside forwards, every
 // tile in turn, how much slower than the best one are the tile taken / the best of the first five, which were all there was: 88 projections of the
-// 7B and 13B shapes 0.8 / 4.1 %; 336 of widths from 1280 to 8192 that the fit has not seen 1.2 / 4.5 % (27 % at worst); 240 of matrices up to 16 MB,
+// 7B and 13B shapes 0.8 / 4.1 %; 336 of nine shapes from 1280 to 8192 wide that those forwards did not hold 1.2 / 4.5 % (27 % at worst); 240 of matrices up to 16 MB,
 // 640 to 2048 wide, 1.1 / 12.5 %.  Against the choice among five, 32 of the 664 are 2 to 12 % slower, none of 7B and 13B, and all together 8 % faster.
 // The last digits are those with which the choice is best.  Fitted to launches alone, without what a launch's last step costs (finish_bytes), the tile
 // taken was 3.1 % slower at 7B and 13B.  Microseconds in a forward, with the consumer's reads, that fit / this one: 7B o 995 rows 44 / 39, 2033 rows 75 / 69, down 995 rows
